@@ -1,6 +1,6 @@
 """Measured workloads of the Tucker-attention library: what a program that uses it runs, over the sizes it runs it at.
 
-Five kinds of pass, each through the public binding (`paper_2603_30033_amd.binding`, `device.from_mha_hosvd`):
+Four kinds of pass, each through the public binding (`paper_2603_30033_amd.binding`, `device.from_mha_hosvd`):
 
   prefill    forward of B sequences of N tokens, with or without writing the latent caches
   decode     one new token per sequence against the latent cache(s), sequences of different lengths
