@@ -294,15 +294,6 @@ PrepArgs make_prep(const tucker_attn_ctx* c, const tucker_attn_weights* w, void*
   return pa;
 }
 
-// Token-tile width of a GEMM launch.  A 128-wide tile pays only where the contraction is long
-// (operand re-reads dominate) and the grid still gives every compute unit two workgroups; short
-// contractions are bound by their output stores and run best with more, smaller workgroups.
-int pick_tile_n(int m_tiles, long TP, int K) {
-  if (K >= 1024 && (long)m_tiles * ((TP + 127) / 128) >= 512) return 128;
-  if ((long)m_tiles * ((TP + 63) / 64) >= 256) return 64;
-  return 32;
-}
-
 struct Recorder {
   tucker_attn_ctx* c;
   hipStream_t s;
@@ -333,7 +324,6 @@ int forward_core(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X
                  hipStream_t s, Recorder& rec, const void** ut2_out, long* ut2_ld_out) {
   const tucker_attn_config& f = c->cfg;
   const int Npad = pad64(N);
-  const long TP = (long)B * Npad;
   const void* ut2;
   long ut2_ld;
   PrepArgs pa = make_prep(c, w, ws.Gt, ws.Gtil2, ws.Wcat, ws.Ut2p, &ut2, &ut2_ld);
@@ -351,7 +341,7 @@ int forward_core(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X
   g.Qlat = ws.Qlat; g.R2 = c->R2; g.Kr = ws.Kr; g.D = c->D; g.Vt = ws.Vt; g.Vr = Vr; g.Krt = Krt;
   g.Kcache = Kcache_out; g.Vcache = Vcache_out; g.Lmax = Lmax; g.r3 = f.r3; g.rt3 = f.rt3;
   g.rope = c->rope; g.rope_ld = f.max_positions; g.pos0 = pos0; g.decode = 0; g.ksplit = 1;
-  if (launch_gemm(f.dtype, g, pick_tile_n((g.M + 127) / 128, TP, g.K), s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+  if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("factor_projection");
 
   AttnArgs a;
@@ -371,7 +361,7 @@ int forward_core(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X
   z.Bsrc = ws.O; z.ldb = (long)f.n_heads * c->D; z.K = f.n_heads * c->D;
   z.Bsz = B; z.N = N; z.Npad = Npad; z.src_padded = 1;
   z.epi = 1; z.Out = ws.Z; z.ldo = c->RT2; z.ksplit = 1; z.R2 = 0; z.D = 0;
-  if (launch_gemm(f.dtype, z, pick_tile_n((z.M + 127) / 128, TP, z.K), s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+  if (launch_gemm(f.dtype, z, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("latent_merge");
   *ut2_out = ut2;
   *ut2_ld_out = ut2_ld;
@@ -454,7 +444,7 @@ int decode_impl(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* x,
       std::memset(&none, 0, sizeof(none));
       if (launch_decode_proj(f.dtype, dp, prepare_now ? pa : none, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     } else {
-      if (launch_gemm(f.dtype, g, 32, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+      if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     }
     rec.after("factor_projection");
 
@@ -624,7 +614,6 @@ int tucker_attn_forward(tucker_attn_ctx* c, const tucker_attn_weights* w, const 
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int Npad = pad64(N);
-  const long TP = (long)B * Npad;
   Recorder rec{c, s, c->profile != 0};
   if (rec.begin() != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   const void* ut2;
@@ -641,7 +630,7 @@ int tucker_attn_forward(tucker_attn_ctx* c, const tucker_attn_weights* w, const 
   y.Bsz = B; y.N = N; y.Npad = Npad; y.src_padded = 1;
   y.epi = 2; y.Out = Y; y.ldo = f.d_model; y.ksplit = 1;
   const hipError_t ye = out_proj_supported(f.dtype, y) ? launch_out_proj(f.dtype, y, s)
-                                                       : launch_gemm(f.dtype, y, pick_tile_n((y.M + 127) / 128, TP, y.K), s);
+                                                       : launch_gemm(f.dtype, y, s);
   if (ye != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("output_projection");
   return TUCKER_ATTN_OK;
@@ -672,7 +661,6 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int Npad = pad64(N);
-  const long TP = (long)B * Npad;
   const int nHD = f.n_heads * c->D, LW = ws.LW, es = c->es;
   Recorder rec{c, s, c->profile != 0};
   if (rec.begin() != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
@@ -716,7 +704,7 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
     g.Bsrc = dY; g.ldb = f.d_model; g.K = f.d_model;
     g.Bsz = B; g.N = N; g.Npad = Npad; g.src_padded = 0;
     g.epi = 1; g.Out = ws.dZ; g.ldo = c->RT2; g.ksplit = 1;
-    if (launch_gemm(f.dtype, g, pick_tile_n((g.M + 127) / 128, TP, g.K), s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+    if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     rec.after("grad_z");
   }
 
@@ -750,7 +738,7 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
     g.Bsrc = ws.dQ; g.ldb = nHD; g.K = nHD;
     g.Bsz = B; g.N = N; g.Npad = Npad; g.src_padded = 1;
     g.epi = 1; g.Out = ws.dLat; g.ldo = LW; g.ksplit = 1;
-    if (launch_gemm(f.dtype, g, pick_tile_n((g.M + 127) / 128, TP, g.K), s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+    if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     rec.after("grad_q_latent");
   }
 
@@ -762,7 +750,7 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
     g.Bsrc = ws.dLat; g.ldb = LW; g.K = LW;
     g.Bsz = B; g.N = N; g.Npad = Npad; g.src_padded = 1;
     g.epi = 2; g.Out = dX; g.ldo = f.d_model; g.ksplit = 1;
-    if (launch_gemm(f.dtype, g, pick_tile_n((g.M + 127) / 128, TP, g.K), s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+    if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     rec.after("grad_x");
   }
 

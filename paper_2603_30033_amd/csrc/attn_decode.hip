@@ -438,20 +438,6 @@ template <int D, bool ROT> struct DecWaveLds {
   static constexpr size_t bytes(int HB) { return pipeline_bytes() > merge_bytes(HB) ? pipeline_bytes() : merge_bytes(HB); }
 };
 
-// at most N vector-memory operations of this wave (loads, direct-to-LDS loads) still in flight
-template <int N> __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "six-bit counter");
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-  asm volatile("" ::: "memory");
-}
-// every LDS read of this wave has returned
-__device__ __forceinline__ void wait_lds() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  asm volatile("" ::: "memory");
-}
-
 // Up to 32 heads the kernel is held to 256 registers: with more, the compiler parks values in accumulation
 // registers and pays a copy for every use by the vector unit.
 template <int D, int HB, bool ROT>

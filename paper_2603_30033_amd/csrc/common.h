@@ -298,6 +298,26 @@ __device__ __forceinline__ void dma_piece(T* tile, int q, int lane, RowPtr row_p
                                    (__attribute__((address_space(3))) void*)(tile + q * 64 * CE), 16, 0, 0);
 }
 
+// one range-checked load of this wave straight into LDS: lane l's 16 bytes at byte offset `off` of the buffer land at
+// chunk l of `lds` (wave-uniform); zeros where the offset lies outside the buffer
+template <typename T> __device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t buf, T* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+}
+
+// at most N vector-memory operations of this wave (loads, direct-to-LDS loads) still in flight
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "six-bit counter");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+  asm volatile("" ::: "memory");
+}
+// every LDS read of this wave has returned
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  asm volatile("" ::: "memory");
+}
+
 // four consecutive accumulator registers (rows 8q+4h .. +3) -> 4 elements of T at p (natural order)
 __device__ __forceinline__ void store4(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<f32x4*>(p) = f32x4{a, b, c, d};

@@ -12,11 +12,13 @@
 // and tokens as MFMA columns, so that an accumulator lane owns one token and four
 // consecutive output channels per register quad.
 //
-// Tiling: workgroup = 4 waves, tile TM x TN (weights x tokens), contraction staged through
-// LDS in slices of 64 elements, double buffered, fed from a ring of register slots that keeps
-// three slices in flight; LDS rows are padded by 16 bytes so that the 16-byte fragment reads of
-// 8 consecutive rows fall into distinct bank groups.  Token counts of a decode step run the same
-// kernel with the contraction split over workgroups and a second kernel that sums the parts.
+// Tiling: workgroup = 4 or 8 waves on a TM x TN tile (weights x tokens).  A stage is RB bytes of every tile row,
+// moved from global memory straight into LDS (range-checked buffer loads, no register stage; chunks of a
+// row XOR-swizzled against bank conflicts), ST stages in a ring, one barrier per stage.  The waves are dealt
+// over the tile AND over the contraction: WGK groups of waves each multiply their own part of every stage, so
+// that a wave's piece of the tile stays large (few LDS bytes per matrix instruction) even where the tile is
+// small, and the groups' accumulators are added through LDS at the end, in a fixed order.  Split-K over
+// workgroups (ksplit > 1) leaves partial tiles for a second kernel, or for the caller's next one, to sum.
 #include <type_traits>
 
 #include "common.h"
@@ -25,63 +27,44 @@
 
 namespace ta {
 
-constexpr int kKS = 64;   // contraction elements per LDS stage
-
-template <typename T> struct Lds {
-  static constexpr int kRowBytes = kKS * sizeof(T) + 16;
-  static constexpr int kRowElems = kRowBytes / sizeof(T);
-  static constexpr int kChunksPerRow = kKS * sizeof(T) / 16;
-  static constexpr int kChunkElems = 16 / sizeof(T);
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST> struct GemmCfg {
+  static constexpr int kWaves = WGM * WGN * WGK;
+  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int CE = 16 / (int)sizeof(T);                // elements per 16-byte chunk
+  static constexpr int CPR = RB / 16;                           // chunks per row of a stage
+  static constexpr int KS = RB / (int)sizeof(T);                // contraction elements of a stage
+  static constexpr int RPP = 1024 / RB;                         // tile rows per 1 KB piece
+  // pieces of the two operands of a stage, rounded up so that every wave moves the same number
+  static constexpr int PA = (TM / RPP + kWaves - 1) / kWaves, PB = (TN / RPP + kWaves - 1) / kWaves;   // per wave
+  static constexpr int kOps = PA + PB;
+  static constexpr int kAElems = PA * kWaves * 1024 / (int)sizeof(T);
+  static constexpr int kStageElems = kOps * kWaves * 1024 / (int)sizeof(T);
+  static constexpr int MB = TM / WGM / 32, NB = TN / WGN / 32;
+  static constexpr int CS = CPR / WGK / 2;                      // chunks of a stage per wave and half
+  static_assert(CS >= 1 && CS * WGK * 2 == CPR, "every group of waves gets whole chunks");
+  static_assert((ST - 2) * kOps < 64, "six-bit counter");
+  // reduction over the WGK groups: blocks per round
+  static constexpr int kMost = ST < 3 ? 1 : (sizeof(T) == 2 ? 4 : 2);   // what fits beside the rows' patches
+  static constexpr int kLess = MB * NB < WGK ? MB * NB : WGK;
+  static constexpr int RS = WGK == 1 ? 1 : (kLess < kMost ? kLess : kMost);
+  static constexpr size_t kReduceBytes = WGK > 1 ? (size_t)kWaves * RS * 4096 : 0;
+  static constexpr int kPatchElems = WGK > 1 ? 32 * (32 + CE) : NB * 32 * (MB * 32 + CE);   // one wave's output rows
+  static constexpr size_t kPatchBytes = (size_t)kWaves * kPatchElems * sizeof(T);
+  static constexpr size_t kRing = (size_t)ST * kStageElems * sizeof(T);
+  static constexpr size_t kTail = kReduceBytes + (WGK > 1 ? kPatchBytes : 0) > kPatchBytes
+                                      ? kReduceBytes + (WGK > 1 ? kPatchBytes : 0) : kPatchBytes;
+  static constexpr size_t kBytes = kRing > kTail ? kRing : kTail;
+  static_assert(kBytes <= 160 * 1024, "fits the LDS of a compute unit");
 };
 
-// Copy a [ROWS x kKS] slice of a row-major matrix into registers / from registers into LDS.
-// Each thread moves ROWS*chunks/256 16-byte chunks.  Loads are buffer loads whose range check
-// supplies the zeros: a chunk of a row that does not exist, or past the end of the contraction,
-// gets an offset beyond the descriptor's size.  No load sits behind a branch, so the compiler
-// can keep several slices in flight and wait for exactly the one it stores next.
-template <typename T, int ROWS> struct Stager {
-  static constexpr int kChunks = ROWS * Lds<T>::kChunksPerRow;
-  static constexpr int kPerThread = (kChunks + 255) / 256;
-  static_assert(kChunks % 256 == 0, "tile rows must fill all threads");
-  static constexpr uint32_t kNone = 0x80000000u;              // offset no descriptor here reaches
-  struct Regs { u32x4 r[kPerThread]; };                        // one slice in flight
-  __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t roff[kPerThread];                                   // byte offset of the chunk at k = 0, or kNone
-  int koff[kPerThread];
-
-  // base: first row of the tile; bytes: extent of the matrix from there on; rowoff(row) gives the
-  // element offset of tile row `row` from base, or -1 for a row of zeros
-  template <class RowOff>
-  __device__ __forceinline__ void init(const T* base, long bytes, RowOff rowoff) {
-    const long lim = 0x7fffffffl;
-    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)(bytes < 0 ? 0 : (bytes > lim ? lim : bytes)),
-                                             0x00020000);
+// acc += (16-byte chunk of a row of A) x (chunk of a row of B), both halves of the wave holding different chunks
+__device__ __forceinline__ void mma_chunk(f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma_chunk(f32x16& acc, const f32x4& a, const f32x4& b) {
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      int ci = threadIdx.x + i * 256;
-      int row = ci / Lds<T>::kChunksPerRow, cc = ci % Lds<T>::kChunksPerRow;
-      koff[i] = cc * Lds<T>::kChunkElems;
-      long ro = rowoff(row);
-      roff[i] = ro < 0 ? kNone : (uint32_t)((ro + koff[i]) * (long)sizeof(T));
-    }
-  }
-  __device__ __forceinline__ void load(Regs& R, int k0, int K) const {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const bool ok = roff[i] != kNone && k0 + koff[i] < K;
-      const uint32_t off = ok ? roff[i] + (uint32_t)k0 * (uint32_t)sizeof(T) : kNone;
-      R.r[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
-    }
-  }
-  __device__ __forceinline__ void store(const Regs& R, T* lds) const {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      int ci = threadIdx.x + i * 256;
-      int row = ci / Lds<T>::kChunksPerRow, cc = ci % Lds<T>::kChunksPerRow;
-      *reinterpret_cast<u32x4*>(lds + row * Lds<T>::kRowElems + cc * Lds<T>::kChunkElems) = R.r[i];
-    }
-  }
-};
+  for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+}
 
 // Output tile of one wave written as whole rows: accumulators go to a wave-private LDS patch as
 // [token][channel], then 16-byte chunks of consecutive channels are stored, eight rows per
@@ -117,17 +100,13 @@ __device__ __forceinline__ void store_rows_y(const GemmArgs& g, const f32x16 (&a
   }
 }
 
-// TM x TN tile, WGM x WGN waves
-template <typename T, int TM, int TN, int WGM, int WGN>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
-  static_assert(WGM * WGN == 4, "four waves");
-  constexpr int MB = TM / WGM / 32, NB = TN / WGN / 32;
-  constexpr int RE = Lds<T>::kRowElems;
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_kernel(GemmArgs g) {
+  using Cfg = GemmCfg<T, TM, TN, WGM, WGN, WGK, RB, ST>;
+  constexpr int MB = Cfg::MB, NB = Cfg::NB, CE = Cfg::CE, CPR = Cfg::CPR, NW = Cfg::kWaves;
+  using Vec = std::conditional_t<sizeof(T) == 2, bf16x8, f32x4>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* smem = reinterpret_cast<T*>(smem_raw);
-  // stage s: A rows [TM], then B rows [TN]
-  auto stageA = [&](int s) { return smem + (long)s * (TM + TN) * RE; };
-  auto stageB = [&](int s) { return smem + (long)s * (TM + TN) * RE + TM * RE; };
 
   // Workgroups go to the eight XCDs round-robin in dispatch order (x fastest).  Remap the index
   // so that each XCD works through one contiguous range of (token tile, weight tile) pairs: the
@@ -144,23 +123,25 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     }
   }
   const int m_tile = bx * TM, t_tile = by * TN;
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int wm = wave % WGM, wn = wave / WGM;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wm = wave % WGM, wn = (wave / WGM) % WGN, kg = wave / (WGM * WGN);
   const int h = lane / 32, lr = lane % 32;
   const int TP = g.Bsz * g.Npad;
 
-  const T* A = static_cast<const T*>(g.A);
-  const T* Bs = static_cast<const T*>(g.Bsrc);
-  // tile rows as offsets from the tile's first row; rows that do not exist read as zeros
-  const T* baseA = A + (long)m_tile * g.lda;
-  const long bytesA = (long)(g.M - m_tile) * g.lda * (long)sizeof(T);
-  auto rowA = [&](int r) -> long { return m_tile + r < g.M ? (long)r * g.lda : -1l; };
-  // token rows: the workspace copies are padded per sequence, the caller's X is not
-  const long TR = g.src_padded ? (long)TP : (long)g.Bsz * g.N;  // rows the source holds
+  // Operands as buffers that start at the tile's first row; a row that does not exist (past the weights, a
+  // padding token of the caller's unpadded X) and elements past the contraction get an offset beyond the
+  // descriptor's size, and the range check of the load supplies zeros for them.
+  constexpr uint32_t kNone = 0x80000000u;
+  auto buffer = [](const T* base, long bytes) {
+    const long lim = 0x7fffffffl;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)(bytes < 0 ? 0 : (bytes > lim ? lim : bytes)),
+                                             0x00020000);
+  };
+  const long TR = g.src_padded ? (long)TP : (long)g.Bsz * g.N;  // rows the token source holds
   auto src_row = [&](int tp) -> long {                          // source row of padded token tp, -1 if none
     if (tp >= TP) return -1l;
     if (g.src_padded) return tp;
-    int b = tp / g.Npad, n = tp % g.Npad;
+    const int b = tp / g.Npad, n = tp % g.Npad;
     return n < g.N ? (long)b * g.N + n : -1l;
   };
   long row0 = TR;                                               // first source row the tile touches
@@ -169,11 +150,43 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     if (g.src_padded) row0 = tp;
     else if (tp < TP) row0 = (long)(tp / g.Npad) * g.N + min(tp % g.Npad, g.N);
   }
-  const T* baseB = Bs + row0 * g.ldb;
-  const long bytesB = (TR - row0) * g.ldb * (long)sizeof(T);
-  auto rowB = [&](int r) -> long {
-    long sr = src_row(t_tile + r);
-    return sr < 0 ? -1l : (sr - row0) * g.ldb;
+  const __amdgpu_buffer_rsrc_t ra = buffer(static_cast<const T*>(g.A) + (long)m_tile * g.lda,
+                                           (long)(g.M - m_tile) * g.lda * (long)sizeof(T));
+  const __amdgpu_buffer_rsrc_t rb = buffer(static_cast<const T*>(g.Bsrc) + row0 * g.ldb, (TR - row0) * g.ldb * (long)sizeof(T));
+  // piece i of this wave holds tile rows (wave + NW i) RPP ..; the chunk a lane moves is the same in all pieces
+  const int prow = lane / CPR;
+  const int koff = ((lane % CPR) ^ swz_x<CPR>(wave * Cfg::RPP + prow)) * CE;
+  static_assert((NW * Cfg::RPP) % 16 == 0, "the swizzle repeats from piece to piece");
+  uint32_t aoff[Cfg::PA], boff[Cfg::PB];
+#pragma unroll
+  for (int i = 0; i < Cfg::PA; ++i) {
+    const int r = (wave + NW * i) * Cfg::RPP + prow;
+    aoff[i] = r < TM && m_tile + r < g.M ? (uint32_t)(((long)r * g.lda + koff) * (long)sizeof(T)) : kNone;
+  }
+#pragma unroll
+  for (int i = 0; i < Cfg::PB; ++i) {
+    const int r = (wave + NW * i) * Cfg::RPP + prow;
+    const long sr = r < TN ? src_row(t_tile + r) : -1l;
+    boff[i] = sr < 0 ? kNone : (uint32_t)(((sr - row0) * g.ldb + koff) * (long)sizeof(T));
+  }
+
+  // stages of this workgroup's part of the contraction
+  const int nk_all = (g.K + Cfg::KS - 1) / Cfg::KS;
+  const int per = (nk_all + g.ksplit - 1) / g.ksplit;
+  const int s0 = blockIdx.z * per;
+  const int cnt = max(min(nk_all, s0 + per) - s0, 0);
+  auto issue = [&](int i) {                                     // fetch stage i (past the end: zeros, no memory traffic)
+    constexpr int kPiece = 1024 / (int)sizeof(T);
+    T* st = smem + (long)(i % ST) * Cfg::kStageElems;
+    const int k0 = (s0 + i) * Cfg::KS;
+    const bool ok = i < cnt && k0 + koff < g.K;
+    const uint32_t kb = (uint32_t)k0 * (uint32_t)sizeof(T);
+#pragma unroll
+    for (int p = 0; p < Cfg::PA; ++p)
+      buffer_to_lds(ra, st + (wave + NW * p) * kPiece, ok && aoff[p] != kNone ? aoff[p] + kb : kNone);
+#pragma unroll
+    for (int p = 0; p < Cfg::PB; ++p)
+      buffer_to_lds(rb, st + Cfg::kAElems + (wave + NW * p) * kPiece, ok && boff[p] != kNone ? boff[p] + kb : kNone);
   };
 
   f32x16 acc[MB][NB];
@@ -184,96 +197,107 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // Slices of the contraction travel global -> registers -> LDS.  PF slices are in flight in
-  // registers so that a round trip to memory is hidden behind PF-1 slices of MFMA work.
-  constexpr int PF = sizeof(T) == 2 ? 3 : 2;
-  Stager<T, TM> sa;
-  Stager<T, TN> sb;
-  typename Stager<T, TM>::Regs ra[PF];
-  typename Stager<T, TN>::Regs rb[PF];
-  const int nk_all = (g.K + kKS - 1) / kKS;
-  const int per = (nk_all + g.ksplit - 1) / g.ksplit;
-  const int ks0 = blockIdx.z * per;
-  const int nk = min(nk_all, ks0 + per);
-  const int klim = min(g.K, nk * kKS);                          // nothing is fetched past this split
-  const int cnt = nk - ks0;
-  auto kof = [&](int i) { return i < cnt ? (ks0 + i) * kKS : klim; };
-  sa.init(baseA, bytesA, rowA);
-  sb.init(baseB, bytesB, rowB);
 #pragma unroll
-  for (int u = 0; u < PF; ++u) {
-    sa.load(ra[u], kof(u), klim);
-    sb.load(rb[u], kof(u), klim);
+  for (int i = 0; i < ST - 1; ++i) issue(i);
+  const int x = swz_x<CPR>(lr);                                 // swizzle of this lane's fragment rows
+  for (int i = 0; i < cnt; ++i) {
+    // this wave's share of stage i has landed, and its reads of stage i - 1 have returned; behind the barrier
+    // both hold for every wave: stage i is whole, and the slot of stage i - 1 may be filled again
+    wait_vm<(ST - 2) * Cfg::kOps>();
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    issue(i + ST - 1);
+    const T* st = smem + (long)(i % ST) * Cfg::kStageElems;
+    const T* la = st + (wm * MB * 32 + lr) * Cfg::KS;
+    const T* lb = st + Cfg::kAElems + (wn * NB * 32 + lr) * Cfg::KS;
+#pragma unroll
+    for (int c = 0; c < Cfg::CS; ++c) {
+      const int ch = (((kg * Cfg::CS + c) * 2 + h) ^ x) * CE;
+      Vec fa[MB], fb[NB];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) fa[m] = *reinterpret_cast<const Vec*>(la + m * 32 * Cfg::KS + ch);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) fb[n] = *reinterpret_cast<const Vec*>(lb + n * 32 * Cfg::KS + ch);
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) mma_chunk(acc[m][n], fa[m], fb[n]);
+    }
   }
-  sa.store(ra[0], stageA(0));
-  sb.store(rb[0], stageB(0));
-  sa.load(ra[0], kof(PF), klim);
-  sb.load(rb[0], kof(PF), klim);
+  wait_vm<0>();                                                 // nothing may land in LDS from here on
   __syncthreads();
 
-  // One slice: multiply from LDS, then move the next slice from its register slot to the other
-  // LDS stage and refill that slot at once with the slice PF further on.  A slot is never idle,
-  // so its registers are not handed to anything else while a load into them is in flight.
-  auto slice = [&](auto slot_c, int ks) {
-    constexpr int S1 = (decltype(slot_c)::value + 1) % PF;      // slot of slice ks + 1
-    const int cur = (ks - ks0) & 1;
-    const T* la = stageA(cur) + (wm * MB * 32 + lr) * RE + 16 * h;
-    const T* lb = stageB(cur) + (wn * NB * 32 + lr) * RE + 16 * h;
+  const int Mp = g.epi == 0 ? g.R2 + (g.shared_kv ? 1 : 2) * g.D : pad32(g.M);
+  auto finish = [&](const f32x16& v, int m0, int t0, T* patch) {  // one 32x32 block of finished sums
+    const int tp = t0 + lr;
+    if (m0 >= Mp) return;
+    if (g.ksplit > 1) {
+      if (tp < TP) {
+        float* dst = g.part + ((long)blockIdx.z * TP + tp) * Mp + m0 + 4 * h;
 #pragma unroll
-    for (int kb = 0; kb < kKS / 32; ++kb) {
-      Frag<T> fa[MB], fb[NB];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) fa[i] = load_frag<T>(la + i * 32 * RE + kb * 32);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) fb[j] = load_frag<T>(lb + j * 32 * RE + kb * 32);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) mma32(acc[i][j], fa[i], fb[j]);
+        for (int q = 0; q < 4; ++q) store4(dst + 8 * q, v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+      }
+    } else if (g.epi == 2) {
+      const f32x16 one[1][1] = {{v}};
+      store_rows_y<T, 1, 1>(g, one, patch, m0, t0);
+    } else {
+      epilogue_block<T>(g, v, m0, tp);
     }
-    // (after the last slice this stages and fetches zeros: cheaper than a branch, behind which
-    // the compiler would have to wait for every load in flight)
-    sa.store(ra[S1], stageA(cur ^ 1));
-    sb.store(rb[S1], stageB(cur ^ 1));
-    sa.load(ra[S1], kof(ks - ks0 + 1 + PF), klim);
-    sb.load(rb[S1], kof(ks - ks0 + 1 + PF), klim);
-    __syncthreads();
   };
-  // whole groups of PF slices run as one straight-line loop body; the remainder follows
-  int ks = ks0;
-  for (; ks + PF <= nk; ks += PF) {
-    slice(std::integral_constant<int, 0>{}, ks);
-    if (PF > 1) slice(std::integral_constant<int, 1 % PF>{}, ks + 1);
-    if (PF > 2) slice(std::integral_constant<int, 2 % PF>{}, ks + 2);
-  }
-  if (ks < nk) slice(std::integral_constant<int, 0>{}, ks);
-  if (PF > 2 && ks + 1 < nk) slice(std::integral_constant<int, 1 % PF>{}, ks + 1);
-
-  if (g.epi == 2 && g.ksplit <= 1) {                            // Y: whole rows through LDS
-    constexpr int PatchElems = NB * 32 * (MB * 32 + 16 / sizeof(T));
-    store_rows_y<T, MB, NB>(g, acc, smem + wave * PatchElems, m_tile + wm * MB * 32, t_tile + wn * NB * 32);
-    return;
-  }
-
+  constexpr int NBLK = MB * NB;
+  // (the block loops are not unrolled: one copy of the epilogue's code)
+  if constexpr (WGK == 1) {
+    T* patch = smem + (long)wave * Cfg::kPatchElems;
+    if (g.epi == 2 && g.ksplit <= 1) {                          // Y: whole rows through LDS
+      store_rows_y<T, MB, NB>(g, acc, patch, m_tile + wm * MB * 32, t_tile + wn * NB * 32);
+      return;
+    }
+#pragma clang loop unroll(disable)
+    for (int k = 0; k < NBLK; ++k) {
+      f32x16 v;
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+      for (int u = 0; u < NBLK; ++u)
+        if (u == k) v = acc[u / NB][u % NB];
+      finish(v, m_tile + (wm * MB + k / NB) * 32, t_tile + (wn * NB + k % NB) * 32, patch);
+    }
+  } else {
+    // RS blocks of every wave per round: all groups leave them in LDS, then one wave per block adds the WGK
+    // parts in group order and finishes it
+    constexpr int RS = Cfg::RS, WMN = WGM * WGN;
+    f32x4* red = reinterpret_cast<f32x4*>(smem_raw);
+    T* patch = reinterpret_cast<T*>(smem_raw + Cfg::kReduceBytes) + (long)wave * Cfg::kPatchElems;
+    static_assert(RS * WMN <= NW, "one wave per block of a round");
+#pragma clang loop unroll(disable)
+    for (int r0 = 0; r0 < NBLK; r0 += RS) {
+      if (r0 > 0) __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      int m0 = m_tile + (wm * MB + i) * 32;
-      int tp = t_tile + (wn * NB + j) * 32 + lr;
-      const int Mp = (g.epi == 0) ? g.R2 + (g.shared_kv ? 1 : 2) * g.D : pad32(g.M);
-      if (m0 >= Mp) continue;
-      if (g.ksplit > 1) {
-        if (tp < TP) {
-          float* dst = g.part + ((long)blockIdx.z * TP + tp) * Mp + m0 + 4 * h;
+      for (int u = 0; u < NBLK; ++u) {
+        if (u < r0 || u >= r0 + RS) continue;
+        f32x4* slot = red + (((long)kg * WMN + wn * WGM + wm) * RS + (u - r0)) * 256 + lane;
+        const f32x16 v = acc[u / NB][u % NB];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            store4(dst + 8 * q, acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        for (int q = 0; q < 4; ++q) slot[q * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      }
+      __syncthreads();
+      const int xs = wave % RS, wmn = wave / RS, u = r0 + xs;
+      if (wmn < WMN && u < NBLK) {
+        f32x16 v;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = 0.f;
+#pragma unroll
+        for (int o = 0; o < WGK; ++o) {
+          const f32x4* slot = red + (((long)o * WMN + wmn) * RS + xs) * 256 + lane;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 y = slot[q * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * q + e] += y[e];
+          }
         }
-      } else {
-        epilogue_block<T>(g, acc[i][j], m0, tp);
+        finish(v, m_tile + ((wmn % WGM) * MB + u / NB) * 32, t_tile + ((wmn / WGM) * NB + u % NB) * 32, patch);
       }
     }
+  }
 }
 
 // sum of split-K partial tiles, then the ordinary epilogue; one wave per 32x32 block
@@ -311,15 +335,15 @@ __global__ __launch_bounds__(64) void splitk_reduce_kernel(GemmArgs g) {
   epilogue_block<T>(g, acc, m0, tp);
 }
 
-template <typename T, int TM, int TN, int WGM, int WGN>
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST>
 static hipError_t launch_one(const GemmArgs& a, int m_rows, hipStream_t s) {
+  using Cfg = GemmCfg<T, TM, TN, WGM, WGN, WGK, RB, ST>;
   const int TP = a.Bsz * a.Npad;
   dim3 grid((m_rows + TM - 1) / TM, (TP + TN - 1) / TN, a.ksplit > 1 ? a.ksplit : 1);
-  size_t smem = 2ul * (TM + TN) * Lds<T>::kRowBytes;
-  auto kern = gemm_kernel<T, TM, TN, WGM, WGN>;
+  auto kern = gemm_kernel<T, TM, TN, WGM, WGN, WGK, RB, ST>;
   static LdsOnce lds_once;                                       // one per kernel instantiation
-  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, a);
+  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, Cfg::kBytes); ae != hipSuccess) return ae;
+  hipLaunchKernelGGL(kern, grid, dim3(Cfg::kThreads), Cfg::kBytes, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.ksplit <= 1 || a.defer_reduce) return e;
   dim3 rgrid((m_rows + 31) / 32, (TP + 31) / 32);
@@ -340,31 +364,45 @@ hipError_t launch_splitk_reduce(int dtype, const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemm(int dtype, const GemmArgs& a, int tile_n, hipStream_t s) {
+// Which tile a product runs with.  Times in us of one launch, operands partly cached (M x K x tokens, bf16):
+//                                    32x32/8  64x64/4  96x128/8  128x128/8  96x128/4     (tile / waves)
+//   384 x 4096 x  8192 (projection)     81       41       35         41        42
+//   256 x 4096 x 16384                 105       54       63         43        49
+//   192 x  768 x 65536                 101       46       46         51        33
+//   192 x  768 x  8192                15.7      8.9     12.1       13.8      12.5
+//   128 x 4096 x  8192 (head merge)     30       18       33         36        39
+//   128 x 4096 x 16384                  58       29       35         38        41
+//    64 x  768 x  8192                 6.4      7.0     10.5       11.8      11.4
+//   384 x 4096 x   384                 9.1       17       29         35        36
+//  4096 x  384 x  8192                 211       74       82         71        53
+// (before, four waves that split the tile only: 48, 63, 39, 14, 25, 36, 7.7, 22.6, 59).  Few tiles: as many
+// workgroups as possible, the eight waves of each dealt over the contraction.  A long contraction with enough
+// tiles for every compute unit is bound by the bytes that the caches deliver, hence the largest tile that still
+// gives 256 workgroups; a short one by the start and the end of a workgroup, hence four waves and 64 KB of LDS,
+// so that two workgroups share a compute unit.  fp32 is bound by its matrix instructions (64 cycles each): only
+// the number of workgroups matters (192 x 768 x 1018 tokens 8.9 us with 32x32 and four waves, 8.0 with eight, 19
+// with 64x64, 21 before; 768 x 192 x 1018 tokens 7.5, 10.0, 8.2, 8.9 before).
+template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
   const int m_rows = (a.epi == 0) ? a.R2 + (a.shared_kv ? 1 : 2) * a.D : a.M;
-  if (dtype == 0) {
-    if (tile_n >= 128) return launch_one<float, 128, 128, 2, 2>(a, m_rows, s);
-    if (tile_n >= 64) return launch_one<float, 128, 64, 2, 2>(a, m_rows, s);
-    return launch_one<float, 128, 32, 4, 1>(a, m_rows, s);
+  const long tokens = (long)a.Bsz * a.Npad;
+  auto tiles = [&](int tm, int tn) { return (long)((m_rows + tm - 1) / tm) * ((tokens + tn - 1) / tn); };
+  const bool few = tiles(64, 64) < 192 || a.ksplit > 1;
+  if constexpr (sizeof(T) == 4) {
+    if (few) return launch_one<T, 32, 32, 1, 1, 4, 128, 4>(a, m_rows, s);
+    return launch_one<T, 64, 64, 2, 2, 1, 128, 4>(a, m_rows, s);
+  } else {
+    if (few) return launch_one<T, 32, 32, 1, 1, 8, 256, 4>(a, m_rows, s);
+    if (a.K >= 1024) {
+      if (m_rows % 96 == 0 && tiles(96, 128) >= 256) return launch_one<T, 96, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
+      if (m_rows > 64 && tiles(128, 128) >= 256) return launch_one<T, 128, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
+    } else if (tiles(96, 128) >= 256) {
+      return launch_one<T, 96, 128, 1, 4, 1, 128, 2>(a, m_rows, s);
+    }
+    return launch_one<T, 64, 64, 1, 1, 4, 128, 4>(a, m_rows, s);
   }
-  // 129..192 weight rows (three 64-wide factor blocks): one 192-row tile instead of one full and one
-  // half-empty 128-row tile, and the token rows are read once (only when the token tiles alone give
-  // every compute unit two workgroups)
-  if (tile_n == 64 && m_rows > 128 && m_rows <= 192 && ((long)a.Bsz * a.Npad + 63) / 64 >= 512)
-    return launch_one<bf16, 192, 64, 2, 2>(a, m_rows, s);
-  // An odd number of 128-row tiles that is a whole number of 96-row tiles (384 rows: query, key and value
-  // factors of 128 each) leaves the compute units one and a half workgroups each.  96 x 128 tiles (every wave
-  // 96 rows x 32 tokens) give 256 equal workgroups at 8192 tokens and move 224 instead of 256 (192 x 64 tiles)
-  // or 288 (128 x 64) rows through LDS per 12288 outputs: 50.0 us against 53.9 (192 x 64) and 56 (128 x 64),
-  // event-bracketed.  With fewer tokens than fill the chip that way, 192-row tiles still even out the count.
-  if (tile_n == 64 && m_rows % 96 == 0 && (m_rows / 128) % 2 == 1) {
-    const long tokens = (long)a.Bsz * a.Npad;
-    if ((m_rows / 96) * ((tokens + 127) / 128) >= 256) return launch_one<bf16, 96, 128, 1, 4>(a, m_rows, s);
-    if (m_rows % 192 == 0) return launch_one<bf16, 192, 64, 2, 2>(a, m_rows, s);
-  }
-  if (tile_n >= 128) return launch_one<bf16, 128, 128, 2, 2>(a, m_rows, s);
-  if (tile_n >= 64) return launch_one<bf16, 128, 64, 2, 2>(a, m_rows, s);
-  return launch_one<bf16, 128, 32, 4, 1>(a, m_rows, s);
+}
+hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
+  return dtype == 0 ? launch_tiles<float>(a, s) : launch_tiles<bf16>(a, s);
 }
 
 }  // namespace ta

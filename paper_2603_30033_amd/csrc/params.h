@@ -201,7 +201,7 @@ int prep_job_blocks(const PrepJob& j);     // workgroups (output tiles) of one j
 hipError_t launch_prep(int dtype, const PrepArgs& a, hipStream_t s);
 bool out_proj_supported(int dtype, const GemmArgs& a);
 hipError_t launch_out_proj(int dtype, const GemmArgs& a, hipStream_t s);
-hipError_t launch_gemm(int dtype, const GemmArgs& a, int tile_n, hipStream_t s);
+hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 hipError_t launch_splitk_reduce(int dtype, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn(int dtype, const TnArgs& a, hipStream_t s);
 // k0, k1 (both or neither): events that take the start and the end of the kernel itself (profiling)

@@ -1,0 +1,26 @@
+"""Sizes at which the kernels' tilings change: every tile of a dispatch rule, with remainders in the tokens, the
+contraction and the heads, against the CPU oracle.  Bars as in test_gpu_parity.py (relative L2 at most 1e-5 in fp32 and
+2e-2 in bf16 storage, every row within four times that)."""
+import pytest
+
+from paper_2603_30033_amd import workloads as wl
+from tests.test_gpu_parity import check, oracle_forward, run_forward
+
+pytestmark = pytest.mark.gpu
+
+
+# (dtype, sequences, tokens, model width, r2, r3, shared): the factor projection's tile at each is named in the comment
+@pytest.mark.parametrize("dtype,B,N,d,r2,r3,shared", [
+    ("bf16", 1, 70, 1032, 128, 96, False),      # 32 x 32, eight waves over the contraction
+    ("bf16", 5, 1000, 776, 64, 64, False),      # 64 x 64
+    ("bf16", 127, 130, 776, 64, 64, False),     # 96 x 128, four waves
+    ("bf16", 33, 250, 1032, 128, 128, False),   # 96 x 128, eight waves
+    ("bf16", 65, 250, 1032, 128, 128, True),    # 128 x 128
+    ("f32", 1, 70, 264, 64, 40, False),         # 32 x 32
+    ("f32", 9, 500, 264, 64, 64, False),        # 64 x 64
+])
+def test_projection_tiles(dtype, B, N, d, r2, r3, shared):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=d, n_heads=3, d_head=32, r1=2, r2=r2, r3=r3, dtype=dtype,
+                  shared_kv=shared, seed=51)
+    inp = wl.make_inputs(w)
+    check(run_forward(w, inp), oracle_forward(w, inp), dtype, repr(w))
