@@ -142,17 +142,20 @@ struct BackwardWs {
   void *Vr, *Krt, *Ut2T, *Gtil_t, *G2, *Wb, *dZ, *Qr, *dO, *dQ, *dLat;
   int LW;            // width of the latent-gradient rows: R2 + D (shared latent) or R2 + 2 D
   int hpg, n_hg;     // heads per group / number of groups of the key-value gradient kernel
-  int ks_w, ks_u, ks_g;   // contraction splits of the weight-gradient products
   size_t bytes;
 };
 
-// contraction split of a token-contracted product with `tiles` output tiles and K tokens
-int grad_ksplit(long tiles, long K) {
-  long want = (512 + tiles - 1) / tiles;
-  const long nk = (K + 63) / 64;
-  if (want > 16) want = 16;
-  if (want > nk) want = nk;
-  return want < 1 ? 1 : (int)want;
+// sizes of the weight-gradient products (all that tn_part_bytes and the launcher's tiling need)
+TnArgs grad_products(const tucker_attn_ctx* c, int LW, int B, int N) {
+  const tucker_attn_config& f = c->cfg;
+  TnArgs t;
+  std::memset(&t, 0, sizeof(t));
+  t.n = 4; t.Bsz = B; t.N = N; t.Npad = pad64(N);
+  t.p[0].M = f.d_model; t.p[0].cols = LW;
+  t.p[1].M = f.d_model; t.p[1].cols = c->RT2;
+  t.p[2].M = c->R2; t.p[2].cols = f.n_heads * c->D;
+  t.p[3].M = c->RT2; t.p[3].cols = f.n_heads * c->D;
+  return t;
 }
 
 BackwardWs carve_backward(const tucker_attn_ctx* c, void* ws, int B, int N) {
@@ -186,17 +189,7 @@ BackwardWs carve_backward(const tucker_attn_ctx* c, void* ws, int B, int N) {
   w.dLat = cv.take<char>(TP * w.LW * es);
   w.dG = cv.take<float>((size_t)c->R2 * nHD * 4);
   w.dGt = cv.take<float>((size_t)c->RT2 * nHD * 4);
-  const long mt = (f.d_model + 127) / 128;
-  auto col_tiles = [&](long cols) { return f.dtype == TUCKER_ATTN_BF16 && cols % 128 == 0 ? cols / 128 : (cols + 63) / 64; };
-  w.ks_w = grad_ksplit(mt * col_tiles(w.LW), (long)TP);
-  w.ks_u = grad_ksplit(mt * col_tiles(c->RT2), (long)TP);
-  const int rmax = c->R2 > c->RT2 ? c->R2 : c->RT2;
-  w.ks_g = grad_ksplit(((rmax + 127) / 128) * col_tiles((long)nHD), (long)TP);
-  size_t part = (size_t)w.ks_w * w.LW * pad32(f.d_model);
-  const size_t p2 = (size_t)w.ks_u * c->RT2 * pad32(f.d_model), p3 = (size_t)w.ks_g * nHD * rmax;
-  if (p2 > part) part = p2;
-  if (p3 > part) part = p3;
-  w.part = cv.take<float>(part * 4);
+  w.part = cv.take<float>(tn_part_bytes(f.dtype, grad_products(c, w.LW, B, N)));
   w.bytes = cv.off;
   return w;
 }
@@ -431,8 +424,7 @@ int decode_impl(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* x,
     g.Kcache = Kb; g.Vcache = Vb; g.Lmax = Lmax; g.r3 = f.r3; g.rt3 = f.rt3;
     g.rope = c->rope; g.rope_ld = f.max_positions; g.pos0 = 0; g.decode = 1;
     for (int b = 0; b < Bc; ++b) g.kv_pos[b] = len[b] - 1;
-    g.ksplit = decode_ksplit(g.K); g.part = ws.part;
-    g.defer_reduce = 1;                                           // the query launch sums the partial tiles
+    g.ksplit = decode_ksplit(g.K); g.part = ws.part;              // the query launch sums the partial tiles
     if (direct) {
       if (g.ksplit < 2) g.ksplit = 2;                             // always partial tiles on this path
       DecodeProjArgs dp;
@@ -754,45 +746,27 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
     rec.after("grad_x");
   }
 
-  // ---- products over tokens: out[m][n] = sum_t A[t][m] B[t][n], operands token-major as they are -----------------
-  auto over_tokens = [&](const void* At, long lda, int a_padded, int M, int perm_m, const void* Bt, long ldb, int cols,
-                         int perm_n, int ksplit, const GemmArgs::Out3 (&outs)[3]) {
-    TnArgs t;
-    std::memset(&t, 0, sizeof(t));
-    t.At = At; t.lda = lda; t.a_padded = a_padded; t.Bt = Bt; t.ldb = ldb; t.b_padded = 1;
-    t.Bsz = B; t.N = N; t.Npad = Npad;
-    t.g.M = M; t.g.Bsz = 1; t.g.N = cols; t.g.Npad = cols;
-    t.g.epi = 3; t.g.ksplit = ksplit; t.g.part = ws.part; t.g.out_scale = 1.f;
-    t.g.perm_m = perm_m; t.g.perm_n = perm_n;
-    for (int u = 0; u < 3; ++u) t.g.out3[u] = outs[u];
-    return launch_gemm_tn(f.dtype, t, s);
-  };
+  // ---- products over tokens, operands token-major as they are -----------------------------------------------------
   {
-    const GemmArgs::Out3 o[3] = {{gr->dU2, 0, f.r2, f.r2},
-                                 {gr->dU3, c->R2, c->R2 + f.r3, f.r3},
-                                 {f.shared_kv ? nullptr : gr->dUt3, c->R2 + c->D, c->R2 + c->D + f.rt3, f.rt3}};
-    if (over_tokens(X, f.d_model, 0, f.d_model, 0, ws.dLat, LW, LW, 0, ws.ks_w, o) != hipSuccess)
-      return TUCKER_ATTN_HIP_ERROR;
-    rec.after("grad_u2_u3_ut3");
-  }
-  {
-    const GemmArgs::Out3 o[3] = {{gr->dUt2, 0, f.rt2, f.rt2}, {nullptr, 0, 0, 0}, {nullptr, 0, 0, 0}};
-    if (over_tokens(dY, f.d_model, 0, f.d_model, 0, ws.f.Z, c->RT2, c->RT2, 0, ws.ks_u, o) != hipSuccess)
-      return TUCKER_ATTN_HIP_ERROR;
-    rec.after("grad_ut2");
-  }
-  {
+    TnArgs t = grad_products(c, LW, B, N);
+    t.part = ws.part;
+    auto set = [&](TnProduct& p, const void* At, long lda, int a_padded, int M_ld, int perm_m, const void* Bt, long ldb, int perm_n) {
+      p.At = At; p.lda = lda; p.a_padded = a_padded; p.M_ld = M_ld; p.perm_m = perm_m;
+      p.Bt = Bt; p.ldb = ldb; p.b_padded = 1; p.perm_n = perm_n;
+    };
+    set(t.p[0], X, f.d_model, 0, f.d_model, 0, ws.dLat, LW, 0);             // dU2 | dU3 | dU~3
+    t.p[0].out[0] = {gr->dU2, 0, f.r2, f.r2};
+    t.p[0].out[1] = {gr->dU3, c->R2, c->R2 + f.r3, f.r3};
+    t.p[0].out[2] = {f.shared_kv ? nullptr : gr->dUt3, c->R2 + c->D, c->R2 + c->D + f.rt3, f.rt3};
+    set(t.p[1], dY, f.d_model, 0, f.d_model, 0, ws.f.Z, c->RT2, 0);         // dU~2
+    t.p[1].out[0] = {gr->dUt2, 0, f.rt2, f.rt2};
     // Qlat holds its columns, and dQ / O their channels, in acc order: undone when the result is stored
-    const GemmArgs::Out3 o[3] = {{ws.dG, 0, nHD, nHD}, {nullptr, 0, 0, 0}, {nullptr, 0, 0, 0}};
-    if (over_tokens(ws.f.Qlat, c->R2, 1, c->R2, 1, ws.dQ, nHD, nHD, 1, ws.ks_g, o) != hipSuccess)
-      return TUCKER_ATTN_HIP_ERROR;
-    rec.after("grad_core_mixed");
-  }
-  {
-    const GemmArgs::Out3 o[3] = {{ws.dGt, 0, nHD, nHD}, {nullptr, 0, 0, 0}, {nullptr, 0, 0, 0}};
-    if (over_tokens(ws.dZ, c->RT2, 1, c->RT2, 0, ws.f.O, nHD, nHD, 1, ws.ks_g, o) != hipSuccess)
-      return TUCKER_ATTN_HIP_ERROR;
-    rec.after("grad_core_mixed_post");
+    set(t.p[2], ws.f.Qlat, c->R2, 1, c->R2, 1, ws.dQ, nHD, 1);              // dG
+    t.p[2].out[0] = {ws.dG, 0, nHD, nHD};
+    set(t.p[3], ws.dZ, c->RT2, 1, c->RT2, 0, ws.f.O, nHD, 1);               // dG~
+    t.p[3].out[0] = {ws.dGt, 0, nHD, nHD};
+    if (launch_gemm_tn(f.dtype, t, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+    rec.after("grad_weights");
   }
 
   // ---- G_i = sum_a U1[i,a] C[a]: gradients of the core and of the head factor ----------------------------------

@@ -1,5 +1,5 @@
 // Epilogues of the token-side products: what becomes of one 32x32 accumulator block.  Shared by the
-// product kernel, the split-K reduction and the decode kernel that sums the projection's partial tiles itself.
+// product kernel and the decode kernel that sums the projection's partial tiles itself.
 #pragma once
 #include "common.h"
 #include "params.h"
@@ -121,22 +121,6 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, in
     for (int q = 0; q < 4; ++q) {
       int c = m0 + 8 * q + 4 * h;
       if (c < g.M) store4(row + c, acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-    }
-  } else if (g.epi == 3) {                                      // ---- fp32 matrix, column ranges routed
-    // a row or column that sits at an acc-order position of its 32-block is stored at its natural index
-    const int nn = g.perm_n ? (tp & ~31) + acc_index(tp & 31) : tp;
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      const GemmArgs::Out3& o = g.out3[u];
-      if (o.ptr == nullptr || nn < o.n0 || nn >= o.n1) continue;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int mp = 8 * q + 4 * h + e;
-          const int m = m0 + (g.perm_m ? acc_index(mp) : mp);
-          if (m < g.M) o.ptr[(long)m * o.ld + (nn - o.n0)] = g.out_scale * acc[4 * q + e];
-        }
     }
   } else {                                                      // ---- Y, caller's [B][N][d]
     if (!valid) return;

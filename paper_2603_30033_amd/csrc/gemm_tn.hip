@@ -2,12 +2,17 @@
 // of the backward pass (dU = X^T dLatent, dU~2 = dY^T Z, dG = Qlat^T dQ, dG~ = dZ^T O: the
 // derivatives of the factor projections and of the head-mixed cores of Definition "Tucker
 // Attention").  Both operands are token-major, as the forward and backward kernels leave them, so
-// the contraction index is the slow index in memory.  A slice of 64 tokens of each operand is staged
-// row-major in LDS and the MFMA operand fragments, which want the contraction index inside a lane,
-// are read with transposing LDS loads (see load_frag_tr in common.h): no token-minor copy of any
-// operand is made.  Slices never straddle two sequences; rows of padding tokens read as zeros.
-// The contraction is split over workgroups (blockIdx.z); partial tiles are summed, scaled and
-// routed to their destinations by splitk_reduce_kernel through epilogue 3 of gemm.hip.
+// the contraction index is the slow index in memory.  A stage of 64 tokens of each operand goes straight
+// into LDS as it lies in memory (range-checked loads, chunks of a row XOR-swizzled) and the MFMA operand
+// fragments, which want the contraction index inside a lane, are read with transposing LDS loads: no
+// token-minor copy of any operand is made.  Stages never straddle two sequences; rows of padding tokens
+// read as zeros.
+//
+// All products of a backward call run in ONE launch (they are independent; each alone leaves part of the chip
+// idle), every workgroup one TM x TN tile of one product over one part of the tokens.  The waves of a workgroup
+// are dealt over the tile and over the tokens of a stage, and their sums are added through LDS, as in gemm.hip.
+// With the tokens split over workgroups a second launch adds the partial tiles, which are kept in the order in
+// which the lanes hold them (whole kilobytes per access).
 #include <type_traits>
 
 #include "common.h"
@@ -15,72 +20,151 @@
 
 namespace ta {
 
-constexpr int kTS = 64;   // tokens per LDS stage
+constexpr int kTS = 64;   // tokens per stage
 
-// [kTS tokens][COLS columns] slice of a token-major matrix: registers <- global, LDS <- registers
-template <typename T, int COLS> struct TnStager {
-  static constexpr int CE = 16 / sizeof(T);
-  static constexpr int kCPR = COLS / CE;                         // chunks per row
-  static constexpr int kChunks = kTS * kCPR;
-  static constexpr int kPerThread = kChunks / 256;
-  static_assert(kChunks % 256 == 0, "slice must fill all threads");
-  // LDS row padded by 64 bytes: the four rows that one transposing read of 16 lanes touches (32
-  // bytes each, and the 32 bytes next to them for the neighbouring 16 lanes) then fall into
-  // disjoint banks
-  static constexpr int kRow = COLS + 64 / (int)sizeof(T);
-  static constexpr uint32_t kNone = 0x80000000u;
-  struct Regs { u32x4 r[kPerThread]; };
-  uint32_t off[kPerThread];                                      // byte offset inside a slice, or kNone
-  const T* base; long ld; int padded, N, Npad, spp;              // spp: slices per sequence
-
-  __device__ __forceinline__ void init(const T* mat, long ld_, int col0, int cols, int padded_, int N_, int Npad_) {
-    base = mat + col0; ld = ld_; padded = padded_; N = N_; Npad = Npad_; spp = Npad_ / kTS;
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int ci = threadIdx.x + i * 256;
-      const int row = ci / kCPR, cc = ci % kCPR;
-      off[i] = col0 + cc * CE < cols ? (uint32_t)((row * ld_ + cc * CE) * (long)sizeof(T)) : kNone;
-    }
-  }
-  // slice s of the padded token axis: sequence s / spp, tokens (s % spp) * kTS .. + kTS - 1
-  __device__ __forceinline__ void load(Regs& R, int s, int s_end) const {
-    const int sc = min(s, s_end - 1);
-    const int b = sc / spp, n0 = (sc % spp) * kTS;
-    const long row0 = padded ? (long)b * Npad + n0 : (long)b * N + n0;
-    // rows that exist from row0 on: the descriptor's size makes the others (and a slice past the
-    // end of this workgroup's range) read as zeros
-    int rows = padded ? kTS : max(0, min(kTS, N - n0));
-    if (s >= s_end) rows = 0;
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(base + row0 * ld), 0, (int)(rows * ld * (long)sizeof(T)), 0x00020000);
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) R.r[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], 0, 0);
-  }
-  __device__ __forceinline__ void store(const Regs& R, T* lds) const {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int ci = threadIdx.x + i * 256;
-      const int row = ci / kCPR, cc = ci % kCPR;
-      *reinterpret_cast<u32x4*>(lds + row * kRow + cc * CE) = R.r[i];
-    }
-  }
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST> struct TnCfg {
+  static constexpr int kWaves = WGM * WGN * WGK, kThreads = 64 * kWaves;
+  static constexpr int CE = 16 / (int)sizeof(T);
+  static constexpr int CPA = TM / CE, CPB = TN / CE;             // chunks per token row
+  static constexpr int PA = kTS * CPA / 64 / kWaves, PB = kTS * CPB / 64 / kWaves;   // 1 KB pieces per wave
+  static_assert(PA * kWaves * 64 == kTS * CPA && PB * kWaves * 64 == kTS * CPB, "whole pieces per wave");
+  static constexpr int kOps = PA + PB;
+  static_assert((ST - 2) * kOps < 64, "six-bit counter");
+  static constexpr int kAElems = kTS * TM, kStageElems = kTS * (TM + TN);
+  static constexpr int MB = TM / WGM / 32, NB = TN / WGN / 32;
+  static constexpr int kTokens = kTS / WGK;                      // tokens of a stage per group of waves
+  static_assert(kTokens % (sizeof(T) == 2 ? 16 : 8) == 0, "whole matrix instructions");
+  static constexpr int NBLK = MB * NB;
+  static constexpr int RS = WGK == 1 ? 1 : (NBLK < WGK ? NBLK : (WGK < 4 ? WGK : 4));   // blocks per reduction round
+  static constexpr size_t kRing = (size_t)ST * kStageElems * sizeof(T);
+  static constexpr size_t kReduce = (size_t)kWaves * RS * 4096;
+  static constexpr size_t kBytes = kRing > kReduce ? kRing : kReduce;
+  static_assert(kBytes <= 160 * 1024, "fits the LDS of a compute unit");
 };
 
-template <typename T, int TM, int TN>
-__global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs a) {
-  constexpr int MB = TM / 2 / 32, NB = TN / 2 / 32;
-  using SA = TnStager<T, TM>;
-  using SB = TnStager<T, TN>;
-  constexpr int StageElems = kTS * (SA::kRow + SB::kRow);
+// operand pieces of one 32-column block for the tokens row0 .. of a swizzled [token][column] tile: bf16 16 tokens
+// (two transposing reads, which hand a lane tokens 4h + r and 8 + 4h + r of its column), fp32 8 tokens
+struct TnFrag16 { u32x2 q[2]; };
+template <int CPR> __device__ __forceinline__ void tn_read(TnFrag16& f, const bf16* tile, int row0, int col0, int lane) {
+  const int h = lane / 32, i = lane % 16;
+  const int col = col0 + (lane & 16) + 4 * (i % 4);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int row = row0 + 8 * q + 4 * h + i / 4;
+    const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
+    const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16*)src;
+    // (assembly, not the builtin: in front of that the compiler waits for every direct-to-LDS load in flight)
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.q[q]) : "v"(addr) : "memory");
+  }
+}
+__device__ __forceinline__ void tn_wait(TnFrag16& f) { asm volatile("" : "+v"(f.q[0]), "+v"(f.q[1])); }
+__device__ __forceinline__ void tn_mma(f32x16& acc, const TnFrag16& a, const TnFrag16& b) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+      __builtin_bit_cast(bf16x8, u32x4{a.q[0][0], a.q[0][1], a.q[1][0], a.q[1][1]}),
+      __builtin_bit_cast(bf16x8, u32x4{b.q[0][0], b.q[0][1], b.q[1][0], b.q[1][1]}), acc, 0, 0, 0);
+}
+struct TnFrag32 { float v[4]; };
+template <int CPR> __device__ __forceinline__ void tn_read(TnFrag32& f, const float* tile, int row0, int col0, int lane) {
+  const int h = lane / 32, col = col0 + lane % 32;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = row0 + 4 * h + r;
+    f.v[r] = tile[row * (CPR * 4) + (((col / 4) ^ swz_x<CPR>(row)) * 4) + col % 4];
+  }
+}
+__device__ __forceinline__ void tn_wait(TnFrag32&) {}
+__device__ __forceinline__ void tn_mma(f32x16& acc, const TnFrag32& a, const TnFrag32& b) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[r], b.v[r], acc, 0, 0, 0);
+}
+
+// one finished 32x32 block: column ranges routed to their destinations as fp32, a row or column that sits at an
+// acc-order position of its 32-block stored at its natural index
+__device__ __forceinline__ void tn_store(const TnProduct& p, const f32x16& v, int m0, int n0, int lane) {
+  const int h = lane / 32, np = n0 + lane % 32;
+  const int nn = p.perm_n ? (np & ~31) + acc_index(np & 31) : np;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const TnProduct::Out& o = p.out[u];
+    if (o.ptr == nullptr || nn < o.n0 || nn >= o.n1) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int mp = 8 * q + 4 * h + e;
+        const int m = m0 + (p.perm_m ? acc_index(mp) : mp);
+        if (m < p.M) o.ptr[(long)m * o.ld + (nn - o.n0)] = v[4 * q + e];
+      }
+  }
+}
+
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_tn_kernel(TnArgs a) {
+  using Cfg = TnCfg<T, TM, TN, WGM, WGN, WGK, ST>;
+  using F = std::conditional_t<sizeof(T) == 2, TnFrag16, TnFrag32>;
+  constexpr int MB = Cfg::MB, NB = Cfg::NB, CE = Cfg::CE, NW = Cfg::kWaves;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* smem = reinterpret_cast<T*>(smem_raw);
-  auto stageA = [&](int s) { return smem + (long)s * StageElems; };
-  auto stageB = [&](int s) { return smem + (long)s * StageElems + kTS * SA::kRow; };
 
-  const int m_tile = blockIdx.x * TM, n_tile = blockIdx.y * TN;
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int wm = wave % 2, wn = wave / 2;
-  const int h = lane / 32, lr = lane % 32;
+  // Work items in the order (token split, product, row tile, column tile), dealt to the eight XCDs in contiguous
+  // ranges: items that run together on an XCD read the same tokens, and neighbours the same columns of A.
+  int lin = blockIdx.x;
+  if (const int per = gridDim.x / 8; lin < per * 8) lin = (lin % 8) * per + lin / 8;
+  // (readfirstlane: what the buffer descriptors are made of must be known to be uniform)
+  const int z = __builtin_amdgcn_readfirstlane(lin / a.tiles);
+  int t = lin - z * a.tiles, pi = 0;
+  while (pi + 1 < a.n && t >= a.p[pi + 1].first_tile) ++pi;
+  const TnProduct& p = a.p[__builtin_amdgcn_readfirstlane(pi)];
+  t -= p.first_tile;
+  const int n_ntiles = (p.cols + TN - 1) / TN;
+  const int mt = __builtin_amdgcn_readfirstlane(t / n_ntiles);
+  const int m_tile = mt * TM, n_tile = (t - mt * n_ntiles) * TN;
+
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wm = wave % WGM, wn = (wave / WGM) % WGN, kg = wave / (WGM * WGN);
+
+  constexpr uint32_t kNone = 0x80000000u;
+  uint32_t aoff[Cfg::PA], boff[Cfg::PB];
+#pragma unroll
+  for (int i = 0; i < Cfg::PA; ++i) {
+    const int ci = (wave + NW * i) * 64 + lane, row = ci / Cfg::CPA;
+    const int col = ((ci % Cfg::CPA) ^ swz_x<Cfg::CPA>(row)) * CE;
+    aoff[i] = m_tile + col < p.M_ld ? (uint32_t)(((long)row * p.lda + col) * (long)sizeof(T)) : kNone;
+  }
+#pragma unroll
+  for (int i = 0; i < Cfg::PB; ++i) {
+    const int ci = (wave + NW * i) * 64 + lane, row = ci / Cfg::CPB;
+    const int col = ((ci % Cfg::CPB) ^ swz_x<Cfg::CPB>(row)) * CE;
+    boff[i] = n_tile + col < p.cols ? (uint32_t)(((long)row * p.ldb + col) * (long)sizeof(T)) : kNone;
+  }
+  const int spp = a.Npad / kTS, n_slices = a.Bsz * spp;
+  const int per = __builtin_amdgcn_readfirstlane((n_slices + a.ksplit - 1) / a.ksplit);
+  const int s0 = __builtin_amdgcn_readfirstlane(min(z * per, n_slices));
+  const int cnt = __builtin_amdgcn_readfirstlane(min(n_slices, s0 + per) - s0);   // this workgroup's stages
+  // Stages are fetched in order: sequence sb, its tokens sn .. sn + 63 next.  The size of the descriptor makes rows
+  // that do not exist (padding tokens of an unpadded operand, stages past the end of this workgroup's range) read
+  // as zeros.
+  int sb = __builtin_amdgcn_readfirstlane(s0 / spp), sn = (s0 - sb * spp) * kTS, left = cnt;
+  auto buffer = [&](const void* mat, long ld, int padded, int tile0) {
+    const long row0 = padded ? (long)sb * a.Npad + sn : (long)sb * a.N + sn;
+    int rows = padded ? kTS : max(0, min(kTS, a.N - sn));
+    if (left <= 0) rows = 0;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(static_cast<const T*>(mat) + (left > 0 ? row0 * ld : 0l) + tile0), 0,
+                                             (int)(rows * ld * (long)sizeof(T)), 0x00020000);
+  };
+  auto issue = [&](int slot) {
+    constexpr int kPiece = 1024 / (int)sizeof(T);
+    T* st = smem + (long)slot * Cfg::kStageElems;
+    const __amdgpu_buffer_rsrc_t ra = buffer(p.At, p.lda, p.a_padded, m_tile);
+    const __amdgpu_buffer_rsrc_t rb = buffer(p.Bt, p.ldb, p.b_padded, n_tile);
+#pragma unroll
+    for (int k = 0; k < Cfg::PA; ++k) buffer_to_lds(ra, st + (wave + NW * k) * kPiece, aoff[k]);
+#pragma unroll
+    for (int k = 0; k < Cfg::PB; ++k) buffer_to_lds(rb, st + Cfg::kAElems + (wave + NW * k) * kPiece, boff[k]);
+    --left;
+    sn += kTS;
+    if (sn == a.Npad) { sn = 0; ++sb; }
+  };
 
   f32x16 acc[MB][NB];
 #pragma unroll
@@ -90,98 +174,186 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // this workgroup's range of token slices
-  const int n_slices = a.Bsz * (a.Npad / kTS);
-  const int per = (n_slices + a.g.ksplit - 1) / a.g.ksplit;
-  const int s0 = min((int)blockIdx.z * per, n_slices), s_end = min(n_slices, s0 + per);
-
-  constexpr int PF = sizeof(T) == 2 ? 3 : 2;
-  SA sa;
-  SB sb;
-  typename SA::Regs ra[PF];
-  typename SB::Regs rb[PF];
-  sa.init(static_cast<const T*>(a.At), a.lda, m_tile, a.g.M, a.a_padded, a.N, a.Npad);
-  sb.init(static_cast<const T*>(a.Bt), a.ldb, n_tile, a.g.Npad, a.b_padded, a.N, a.Npad);
-  if (s0 < s_end) {
+  if (cnt > 0) {                                                // (the same for the whole workgroup)
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      sa.load(ra[u], s0 + u, s_end);
-      sb.load(rb[u], s0 + u, s_end);
-    }
-    sa.store(ra[0], stageA(0));
-    sb.store(rb[0], stageB(0));
-    sa.load(ra[0], s0 + PF, s_end);
-    sb.load(rb[0], s0 + PF, s_end);
-    __syncthreads();
-    // one slice: multiply from LDS, then move the next slice from its register slot to the other LDS
-    // stage and refill that slot at once (a slot is never idle; past the end zeros are fetched)
-    auto slice = [&](auto slot_c, int s) {
-      constexpr int S1 = (decltype(slot_c)::value + 1) % PF;
-      const int cur = (s - s0) & 1;
-      const T* la = stageA(cur);
-      const T* lb = stageB(cur);
+    for (int i = 0; i < ST - 1; ++i) issue(i);
+    for (int i = 0; i < cnt; ++i) {
+      wait_vm<(ST - 2) * Cfg::kOps>();                          // as in gemm.hip: stage i whole, the slot of i - 1 free
+      wait_lds();
+      __builtin_amdgcn_s_barrier();
+      const T* la = smem + (long)(i % ST) * Cfg::kStageElems;
+      const T* lb = la + Cfg::kAElems;
+      constexpr int kStep = sizeof(T) == 2 ? 16 : 8;
 #pragma unroll
-      for (int kb = 0; kb < kTS / 32; ++kb) {
-        Frag<T> fa[MB], fb[NB];
+      for (int c = 0; c < Cfg::kTokens; c += kStep) {
+        F fa[MB], fb[NB];
+        const int row0 = kg * Cfg::kTokens + c;
 #pragma unroll
-        for (int i = 0; i < MB; ++i) fa[i] = load_frag_tr(la, SA::kRow, kb * 32, (wm * MB + i) * 32, lane);
+        for (int m = 0; m < MB; ++m) tn_read<Cfg::CPA>(fa[m], la, row0, (wm * MB + m) * 32, lane);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) fb[j] = load_frag_tr(lb, SB::kRow, kb * 32, (wn * NB + j) * 32, lane);
+        for (int n = 0; n < NB; ++n) tn_read<Cfg::CPB>(fb[n], lb, row0, (wn * NB + n) * 32, lane);
+        if constexpr (sizeof(T) == 2) {
+          wait_lds();
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+          for (int m = 0; m < MB; ++m) tn_wait(fa[m]);
 #pragma unroll
-          for (int j = 0; j < NB; ++j) mma32(acc[i][j], fa[i], fb[j]);
+          for (int n = 0; n < NB; ++n) tn_wait(fb[n]);
+        }
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+          for (int n = 0; n < NB; ++n) tn_mma(acc[m][n], fa[m], fb[n]);
       }
-      sa.store(ra[S1], stageA(cur ^ 1));
-      sb.store(rb[S1], stageB(cur ^ 1));
-      sa.load(ra[S1], s + 1 + PF, s_end);
-      sb.load(rb[S1], s + 1 + PF, s_end);
-      __syncthreads();
-    };
-    int s = s0;
-    for (; s + PF <= s_end; s += PF) {
-      slice(std::integral_constant<int, 0>{}, s);
-      if (PF > 1) slice(std::integral_constant<int, 1 % PF>{}, s + 1);
-      if (PF > 2) slice(std::integral_constant<int, 2 % PF>{}, s + 2);
+      issue((i + ST - 1) % ST);                                 // behind the products: it would hold the wave before them
     }
-    if (s < s_end) slice(std::integral_constant<int, 0>{}, s);
-    if (PF > 2 && s + 1 < s_end) slice(std::integral_constant<int, 1 % PF>{}, s + 1);
+    wait_vm<0>();                                               // nothing may land in LDS from here on
   }
+  __syncthreads();
 
-  // partial tile -> part[z][n][Mp] (the layout splitk_reduce_kernel sums)
-  const int Mp = pad32(a.g.M), NC = a.g.Npad;
+  auto finish = [&](const f32x16& v, int m0, int n0) {
+    const int mb = pad32(p.M) / 32, nb = (p.cols + 31) / 32;
+    if (m0 / 32 >= mb || n0 / 32 >= nb) return;
+    if (a.ksplit > 1) {
+      f32x4* dst = reinterpret_cast<f32x4*>(a.part) + (((long)z * a.blocks + p.first_block + (m0 / 32) * nb + n0 / 32) * 256) + lane;
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int m0 = m_tile + (wm * MB + i) * 32;
-      const int n = n_tile + (wn * NB + j) * 32 + lr;
-      if (m0 >= Mp || n >= NC) continue;
-      float* dst = a.g.part + ((long)blockIdx.z * NC + n) * Mp + m0 + 4 * h;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        store4(dst + 8 * q, acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+      for (int q = 0; q < 4; ++q) dst[q * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    } else {
+      tn_store(p, v, m0, n0, lane);
     }
+  };
+  // RS blocks of every wave per round go through LDS; one wave per block adds the WGK parts in group order
+  constexpr int NBLK = Cfg::NBLK, RS = Cfg::RS, WMN = WGM * WGN;
+  static_assert(RS * WMN <= NW, "one wave per block of a round");
+  f32x4* red = reinterpret_cast<f32x4*>(smem_raw);
+#pragma clang loop unroll(disable)
+  for (int r0 = 0; r0 < NBLK; r0 += RS) {
+    if (r0 > 0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NBLK; ++u) {
+      if (u < r0 || u >= r0 + RS) continue;
+      f32x4* slot = red + (((long)kg * WMN + wn * WGM + wm) * RS + (u - r0)) * 256 + lane;
+      const f32x16 v = acc[u / NB][u % NB];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) slot[q * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    }
+    __syncthreads();
+    const int xs = wave % RS, wmn = wave / RS, u = r0 + xs;
+    if (wmn < WMN && u < NBLK) {
+      f32x16 v;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = 0.f;
+#pragma unroll
+      for (int o = 0; o < WGK; ++o) {
+        const f32x4* slot = red + (((long)o * WMN + wmn) * RS + xs) * 256 + lane;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 y = slot[q * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * q + e] += y[e];
+        }
+      }
+      finish(v, m_tile + ((wmn % WGM) * MB + u / NB) * 32, n_tile + ((wmn / WGM) * NB + u % NB) * 32);
+    }
+  }
 }
 
-template <typename T, int TM, int TN>
+// sum of the partial tiles of all products, in split order; one wave per 32x32 block
+__global__ __launch_bounds__(64) void tn_reduce_kernel(TnArgs a) {
+  const int lane = threadIdx.x, blk = blockIdx.x;
+  int pi = 0;
+  while (pi + 1 < a.n && blk >= a.p[pi + 1].first_block) ++pi;
+  const TnProduct& p = a.p[pi];
+  const f32x4* src = reinterpret_cast<const f32x4*>(a.part) + (long)blk * 256 + lane;
+  f32x16 v;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) v[e] = 0.f;
+  constexpr int U = 4;                                          // splits whose loads are in flight together
+  for (int z0 = 0; z0 < a.ksplit; z0 += U) {
+    f32x4 y[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[u][q] = src[(long)min(z0 + u, a.ksplit - 1) * a.blocks * 256 + q * 64];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (z0 + u < a.ksplit)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * q + e] += y[u][q][e];
+  }
+  const int nb = (p.cols + 31) / 32, lb = blk - p.first_block;
+  tn_store(p, v, lb / nb * 32, lb % nb * 32, lane);
+}
+
+// Tile edge: 128 where the products have enough 128-wide tiles to occupy half the chip (bf16), else 64.
+static int tn_edge(int dtype, const TnArgs& a) {
+  if (dtype == 0) return 64;
+  int tiles = 0;
+  for (int i = 0; i < a.n; ++i) tiles += (a.p[i].M / 128) * (a.p[i].cols / 128);
+  return tiles >= 128 ? 128 : 64;
+}
+static int tn_tiles(int edge, const TnArgs& a) {
+  int tiles = 0;
+  for (int i = 0; i < a.n; ++i) tiles += ((a.p[i].M + edge - 1) / edge) * ((a.p[i].cols + edge - 1) / edge);
+  return tiles;
+}
+static int tn_blocks(const TnArgs& a) {
+  int blocks = 0;
+  for (int i = 0; i < a.n; ++i) blocks += (pad32(a.p[i].M) / 32) * ((a.p[i].cols + 31) / 32);
+  return blocks;
+}
+// Parts the tokens are split into: the count with the least estimated time, from what was measured (us): a stage of
+// 64 tokens 0.76 with 128-wide tiles, 0.34 with 64-wide ones, 1.2 in fp32; 9, 5.4 and 7 for a workgroup's start and
+// reduction; 4.5 for the second launch and 0.001 per partial block.  A compute unit holds one workgroup, one and a
+// half effective ones of the 64-wide bf16 tiles (64 KB of LDS).  Measured, launch + second launch: LLaMA-7B shape
+// (192 tiles of 128, 128 stages) 102 unsplit, 107 + 9 in two, 116 + 11 in three, 106 + 16 in five parts; GPT-2 shape
+// (72 tiles of 64, 128 stages) 44, 25 + 5, 19 + 6, 19 + 7; the same in fp32 with 16 stages 26, 16 + 5, 14 + 6, 21 + 7.
+// (Before, one launch per product and one per reduction: 168 + 40, 55 + 25 and 42 + 24.)
+static int tn_ksplit(int dtype, const TnArgs& a) {
+  const int edge = tn_edge(dtype, a), tiles = tn_tiles(edge, a), blocks = tn_blocks(a), slices = a.Bsz * (a.Npad / kTS);
+  const double stage = dtype == 0 ? 1.2 : edge == 128 ? 0.76 : 0.34, fixed = dtype == 0 ? 7. : edge == 128 ? 9. : 5.4;
+  int best = 1;
+  double cost = 1e30;
+  for (int ks = 1; ks <= 16 && ks <= slices; ++ks) {
+    double rounds = dtype == 1 && edge == 64 ? tiles * ks / 384. : (tiles * ks + 255) / 256;
+    if (rounds < 1.) rounds = 1.;
+    const double c = rounds * ((slices + ks - 1) / ks * stage + fixed) + (ks > 1 ? 4.5 + 0.001 * ks * blocks : 0.);
+    if (c < cost) { cost = c; best = ks; }
+  }
+  return best;
+}
+size_t tn_part_bytes(int dtype, const TnArgs& a) {
+  const int ks = tn_ksplit(dtype, a);
+  return ks > 1 ? (size_t)ks * tn_blocks(a) * 4096 : 0;
+}
+
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST>
 static hipError_t tn_one(const TnArgs& a, hipStream_t s) {
-  dim3 grid((a.g.M + TM - 1) / TM, (a.g.Npad + TN - 1) / TN, a.g.ksplit);
-  const size_t smem = 2ul * kTS * (TnStager<T, TM>::kRow + TnStager<T, TN>::kRow) * sizeof(T);
-  auto kern = gemm_tn_kernel<T, TM, TN>;
+  using Cfg = TnCfg<T, TM, TN, WGM, WGN, WGK, ST>;
+  auto kern = gemm_tn_kernel<T, TM, TN, WGM, WGN, WGK, ST>;
   static LdsOnce lds_once;
-  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, a);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  return launch_splitk_reduce(sizeof(T) == 2 ? 1 : 0, a.g, s);
+  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, Cfg::kBytes); ae != hipSuccess) return ae;
+  hipLaunchKernelGGL(kern, dim3(a.tiles * a.ksplit), dim3(Cfg::kThreads), Cfg::kBytes, s, a);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || a.ksplit <= 1) return e;
+  hipLaunchKernelGGL(tn_reduce_kernel, dim3(a.blocks), dim3(64), 0, s, a);
+  return hipGetLastError();
 }
 
-// a.g describes the output side as for epilogue 3 of launch_gemm: M rows, Bsz = 1, N = Npad = number
-// of columns, ksplit >= 1 partial sums in part, out3 / out_scale / perm_m / perm_n.
-hipError_t launch_gemm_tn(int dtype, const TnArgs& a, hipStream_t s) {
-  const bool wide = a.g.Npad % 128 == 0;
-  if (dtype == 0) return tn_one<float, 128, 64>(a, s);
-  return wide ? tn_one<bf16, 128, 128>(a, s) : tn_one<bf16, 128, 64>(a, s);
+hipError_t launch_gemm_tn(int dtype, const TnArgs& args, hipStream_t s) {
+  TnArgs a = args;
+  const int edge = tn_edge(dtype, a);
+  a.ksplit = tn_ksplit(dtype, a);
+  a.tiles = a.blocks = 0;
+  for (int i = 0; i < a.n; ++i) {
+    a.p[i].first_tile = a.tiles;
+    a.p[i].first_block = a.blocks;
+    a.tiles += ((a.p[i].M + edge - 1) / edge) * ((a.p[i].cols + edge - 1) / edge);
+    a.blocks += (pad32(a.p[i].M) / 32) * ((a.p[i].cols + 31) / 32);
+  }
+  if (dtype == 0) return tn_one<float, 64, 64, 1, 1, 8, 4>(a, s);
+  if (edge == 128) return tn_one<bf16, 128, 128, 1, 2, 4, 4>(a, s);
+  return tn_one<bf16, 64, 64, 1, 1, 4, 4>(a, s);
 }
 
 }  // namespace ta

@@ -47,7 +47,7 @@ struct GemmArgs {
   int Bsz, N, Npad;
   int src_padded;       // 1: Bsrc rows are indexed by tp; 0: by b*N+n (caller's X)
   // epilogue outputs
-  int epi;              // 0 = projection, 1 = latent merge Z, 2 = output Y, 3 = fp32 matrix (gradients)
+  int epi;              // 0 = projection, 1 = latent merge Z, 2 = output Y
   // projection
   void* Qlat; int R2;           // [TP][R2] acc order
   void* Kr;   int D;            // [TP][D]  acc order, rotated
@@ -68,25 +68,29 @@ struct GemmArgs {
   // Z / Y
   void* Out; long ldo;          // Z: [TP][ldo] natural order;  Y: [B][N][ldo] natural order
   // split-K (decode-sized token counts): ksplit > 1 writes fp32 partial tiles to part
-  // [ksplit][TP][Mp] (Mp = weight rows padded to 32); a second kernel sums them and runs the
+  // [ksplit][TP][Mp] (Mp = weight rows padded to 32); the caller's next kernel sums them and runs the
   // epilogue
   int ksplit;
   float* part;
-  int defer_reduce;     // 1: no reduction launch here; the caller's next kernel sums the partial tiles
-  // epi 3: out_scale * acc[m][n] as fp32; column range [n0, n1) of the product goes to
-  // ptr[m * ld + (n - n0)] (up to three destinations; ptr null = unused)
-  struct Out3 { float* ptr; int n0, n1; long ld; } out3[3];
-  float out_scale;
-  int perm_m, perm_n;   // 1: rows / columns of the product are in acc order within 32-blocks; stored natural
 };
 
-// out[m][n] = sum over tokens t of At[t][m] * Bt[t][n]; both operands token-major.  g carries the
-// output side as for epilogue 3 (M, Bsz = 1, N = Npad = number of columns, ksplit, part, out3, ...).
-struct TnArgs {
-  GemmArgs g;
+// Products over tokens, out[m][n] = sum_t At[t][m] Bt[t][n], both operands token-major; all of a call in one launch.
+struct TnProduct {
   const void* At; long lda; int a_padded;   // padded: row of token (b, n) is b*Npad + n, else b*N + n
   const void* Bt; long ldb; int b_padded;
+  int M, M_ld;          // rows of the product; columns of At that exist (a multiple of 8, >= M)
+  int cols;             // columns of the product (columns of Bt)
+  int perm_m, perm_n;   // 1: rows / columns are in acc order within 32-blocks; stored natural
+  // column range [n0, n1) goes to ptr[m * ld + (n - n0)], fp32 (ptr null = unused)
+  struct Out { float* ptr; int n0, n1; long ld; } out[3];
+  int first_tile, first_block;              // set by the launcher
+};
+struct TnArgs {
+  TnProduct p[4];
+  int n;
   int Bsz, N, Npad;
+  float* part;          // tn_part_bytes of scratch
+  int ksplit, tiles, blocks;                // set by the launcher
 };
 
 // ---- prefill attention ---------------------------------------------------------------------
@@ -202,8 +206,8 @@ hipError_t launch_prep(int dtype, const PrepArgs& a, hipStream_t s);
 bool out_proj_supported(int dtype, const GemmArgs& a);
 hipError_t launch_out_proj(int dtype, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
-hipError_t launch_splitk_reduce(int dtype, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_tn(int dtype, const TnArgs& a, hipStream_t s);
+size_t tn_part_bytes(int dtype, const TnArgs& a);   // needs the sizes only (n, p[].M, p[].cols, Bsz, Npad)
 // k0, k1 (both or neither): events that take the start and the end of the kernel itself (profiling)
 hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipEvent_t k0 = nullptr, hipEvent_t k1 = nullptr);
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s);

@@ -4,6 +4,7 @@ contraction and the heads, against the CPU oracle.  Bars as in test_gpu_parity.p
 import pytest
 
 from paper_2603_30033_amd import workloads as wl
+from tests.test_gpu_backward import run_case
 from tests.test_gpu_parity import check, oracle_forward, run_forward
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +25,16 @@ def test_projection_tiles(dtype, B, N, d, r2, r3, shared):
                   shared_kv=shared, seed=51)
     inp = wl.make_inputs(w)
     check(run_forward(w, inp), oracle_forward(w, inp), dtype, repr(w))
+
+
+# products over tokens of the backward pass: 64- and 128-wide tiles, tokens whole and split over workgroups, columns and
+# rows that end inside a tile
+@pytest.mark.parametrize("dtype,B,N,d,heads,r2,r3", [
+    ("bf16", 1, 70, 136, 3, 48, 40),            # 64-wide, two stages, unsplit
+    ("bf16", 5, 400, 136, 3, 48, 40),           # 64-wide, split
+    ("bf16", 1, 130, 2056, 32, 128, 128),       # 128-wide, rows past the last whole tile
+    ("f32", 3, 130, 136, 3, 48, 40),            # fp32, split
+])
+def test_weight_gradient_tiles(dtype, B, N, d, heads, r2, r3):
+    run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=d, n_heads=heads, d_head=32, r1=2, r2=r2, r3=r3,
+                       dtype=dtype, seed=52))
