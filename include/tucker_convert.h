@@ -63,10 +63,13 @@ int tucker_convert_from_mla(int32_t dtype, int32_t d, int32_t nH, int32_t dH, in
 /* What one tucker_convert_from_mha_hosvd call did; plain host data. */
 typedef struct {
   int32_t sweeps[6];        /* Jacobi sweeps of the eigen-problems of W modes 1, 2, 3 and W~ modes 1, 2, 3    */
-                            /* (0: not solved -- one head, or mode 3 of W~ with shared_kv)                    */
-  int64_t jacobi_launches;  /* step kernels launched for the d x d problems (modes 2 and 3)                   */
-  double  jacobi_ms;        /* time of those launches on the stream, from HIP events around each iteration    */
-  double  jacobi_bytes;     /* bytes they read and wrote: every launch rotates all d rows once, 2 * 8 * d * d */
+                            /* (0: solved by reduction to tridiagonal form, or not solved -- one head, or     */
+                            /* mode 3 of W~ with shared_kv)                                                   */
+  int64_t jacobi_launches;  /* step kernels launched for the d x d problems (modes 2 and 3): columns reduced  */
+                            /* (all problems in one launch), Jacobi rounds where that path is taken           */
+  double  jacobi_ms;        /* time of those launches on the stream, from HIP events around them              */
+  double  jacobi_bytes;     /* bytes they read and wrote: the remaining matrix once per column, all rows per  */
+                            /* round                                                                          */
 } tucker_convert_hosvd_info;
 
 /* Bytes of device workspace tucker_convert_from_mha_hosvd needs; 0 if an argument is invalid. */
@@ -77,8 +80,9 @@ size_t tucker_convert_hosvd_workspace_bytes(int32_t d, int32_t nH, int32_t dH);
  * the stacked per-head products W_i = WQ_i WK_i^T and W~_i = (WV_i WO_i)^T (appendix
  * "Converting pretrained MHA parameters to approximate attention parameters").  Each factor is
  * the leading left singular vectors of a mode unfolding, computed as eigenvectors of its Gram
- * matrix (formed from the dH-wide factors, the d x d products are never built) by a one-sided
- * Jacobi iteration; the core is the tensor contracted with the transposed factors.  All
+ * matrix (formed from the dH-wide factors, the d x d products are never built): modes 2 and 3
+ * of both tensors together by a reduction to tridiagonal form (8 <= d <= 5056), mode 1, other
+ * sizes and problems with eigenvalues too close for it by a one-sided Jacobi iteration; the core is the tensor contracted with the transposed factors.  All
  * arithmetic in fp64; results rounded once to the storage type.  Columns are ordered by
  * decreasing singular value and signed so that the entry of largest magnitude is positive.
  *   WQ, WK, WV [d, nH*dH], WO [nH*dH, d]                       in

@@ -4,8 +4,9 @@
 //     up-projections as core slices).
 //   * MHA -> Tucker by a truncated higher-order SVD (appendix "Converting pretrained MHA
 //     parameters to approximate attention parameters"), in fp64: Gram matrices of the mode
-//     unfoldings from the dH-wide factors, eigenvectors by a one-sided Jacobi iteration, core by
-//     contraction with the transposed factors.
+//     unfoldings from the dH-wide factors, their leading eigenvectors (all the d x d problems side by side
+//     through a reduction to tridiagonal form, eigen.hip; the head mode and what that path does not take by a
+//     one-sided Jacobi iteration), core by contraction with the transposed factors.
 #include "../../include/tucker_attn.h"
 #include "../../include/tucker_convert.h"
 
@@ -17,6 +18,7 @@
 #include <vector>
 
 #include "common.h"
+#include "eigen.h"
 
 namespace ta {
 namespace {
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(256) void from_f64_kernel(const double* in, T* out,
 }
 
 // C[m][n] = sum_k A(m,k) B(k,n) with element strides for every index (any transposition is a
-// choice of strides) and a batch stride; 64x64 tile, 16-wide slices, 4x4 results per thread.
+// choice of strides) and a batch stride.
 struct DgemmArgs {
   const double* A; long a_m, a_k, a_b;
   const double* B; long b_k, b_n, b_b;
@@ -113,58 +115,83 @@ struct DgemmArgs {
   int M, N, K;
 };
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+// Tile of 32 BT x 32 BT, four waves with BT x BT blocks of the 16 x 16 x 4 fp64 matrix instruction each (lane l
+// supplies A[l%16][l/16] and B[l/16][l%16] and receives D[l/16 + 4i][l%16] in register i); the next slice is
+// loaded into registers while the current one is multiplied.  Bound by the matrix instruction (64 cycles) once
+// every SIMD has a wave.
+template <int BT>
 __global__ __launch_bounds__(256) void dgemm_kernel(DgemmArgs g) {
-  __shared__ double As[16][66], Bs[16][66];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  constexpr int TM = 32 * BT, KS = 32 / BT, E = TM * KS / 256;
+  __shared__ double As[2][KS][TM + 2], Bs[2][KS][TM + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
+  const int mw = (wave >> 1) * 16 * BT, nw = (wave & 1) * 16 * BT;
   const double* A = g.A + (long)blockIdx.z * g.a_b;
   const double* B = g.B + (long)blockIdx.z * g.b_b;
   double* C = g.C + (long)blockIdx.z * g.c_b;
-  double acc[4][4];
+  f64x4 acc[BT][BT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
-    double va[4], vb[4];
+    for (int j = 0; j < BT; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double va[E], vb[E];
+  // lanes run along the contiguous index of each operand
+  auto at_a = [&](int j, int& k, int& m) { const int e = tid + 256 * j; k = g.a_k == 1 ? e % KS : e / TM; m = g.a_k == 1 ? e / KS : e % TM; };
+  auto at_b = [&](int j, int& k, int& n) { const int e = tid + 256 * j; k = g.b_n == 1 ? e / TM : e % KS; n = g.b_n == 1 ? e % TM : e / KS; };
+  auto load = [&](int k0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {                       // lanes run along the contiguous index
-      const int e = tid + 256 * j;
-      const int ka = g.a_k == 1 ? (e & 15) : (e >> 6), ma = g.a_k == 1 ? (e >> 4) : (e & 63);
-      const int kb = g.b_n == 1 ? (e >> 6) : (e & 15), nb = g.b_n == 1 ? (e & 63) : (e >> 4);
-      va[j] = (m0 + ma < g.M && k0 + ka < g.K) ? A[(long)(m0 + ma) * g.a_m + (long)(k0 + ka) * g.a_k] : 0.0;
-      vb[j] = (n0 + nb < g.N && k0 + kb < g.K) ? B[(long)(k0 + kb) * g.b_k + (long)(n0 + nb) * g.b_n] : 0.0;
+    for (int j = 0; j < E; ++j) {
+      int k, m;
+      at_a(j, k, m);
+      va[j] = (m0 + m < g.M && k0 + k < g.K) ? A[(long)(m0 + m) * g.a_m + (long)(k0 + k) * g.a_k] : 0.0;
+      at_b(j, k, m);
+      vb[j] = (n0 + m < g.N && k0 + k < g.K) ? B[(long)(k0 + k) * g.b_k + (long)(n0 + m) * g.b_n] : 0.0;
     }
-    __syncthreads();                                    // the previous slice has been consumed
+  };
+  auto store = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = tid + 256 * j;
-      const int ka = g.a_k == 1 ? (e & 15) : (e >> 6), ma = g.a_k == 1 ? (e >> 4) : (e & 63);
-      const int kb = g.b_n == 1 ? (e >> 6) : (e & 15), nb = g.b_n == 1 ? (e & 63) : (e >> 4);
-      As[ka][ma] = va[j];
-      Bs[kb][nb] = vb[j];
+    for (int j = 0; j < E; ++j) {
+      int k, m;
+      at_a(j, k, m);
+      As[buf][k][m] = va[j];
+      at_b(j, k, m);
+      Bs[buf][k][m] = vb[j];
     }
+  };
+  const int ns = (g.K + KS - 1) / KS;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int s = 0; s < ns; ++s) {
+    if (s + 1 < ns) load((s + 1) * KS);
+    const int buf = s & 1;
+#pragma unroll
+    for (int kk = 0; kk < KS / 4; ++kk) {
+      double a[BT], b[BT];
+#pragma unroll
+      for (int i = 0; i < BT; ++i) a[i] = As[buf][4 * kk + lq][mw + 16 * i + lr];
+#pragma unroll
+      for (int j = 0; j < BT; ++j) b[j] = Bs[buf][4 * kk + lq][nw + 16 * j + lr];
+#pragma unroll
+      for (int i = 0; i < BT; ++i)
+#pragma unroll
+        for (int j = 0; j < BT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    if (s + 1 < ns) store((s + 1) & 1);                 // last read before the previous barrier
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      double a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-    }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < g.M && n < g.N) C[(long)m * g.c_m + (long)n * g.c_n] = acc[i][j];
-    }
+    for (int j = 0; j < BT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + mw + 16 * i + lq + 4 * r, n = n0 + nw + 16 * j + lr;
+        if (m < g.M && n < g.N) C[(long)m * g.c_m + (long)n * g.c_n] = acc[i][j][r];
+      }
 }
 
 // M1[i][j] = <W_i, W_j> = sum_{l,m} (A_i^T A_j)[l][m] (B_i^T B_j)[l][m]; GA = A^T A, GB = B^T B [n, n]
@@ -201,9 +228,6 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
   b = red[0][1] + red[1][1] + red[2][1] + red[3][1];
   c = red[0][2] + red[1][2] + red[2][2] + red[3][2];
 }
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // One step of a blocked one-sided Jacobi sweep on the rows of G [m, len].  The rows are grouped in
 // blocks of 8; workgroup k takes the k-th pair (P, Q) of round `step` of a round-robin tournament
@@ -347,7 +371,7 @@ __global__ __launch_bounds__(256) void row_norms_kernel(const double* G, int len
   if (threadIdx.x == 0) norms2[blockIdx.x] = a;
 }
 
-// Factor column k = row idx[k] of G, normalised, signed so that its entry of largest magnitude
+// Factor column k = row idx[k] (row k without idx) of G, normalised, signed so that its entry of largest magnitude
 // (the first one on ties) is positive: U64 [len, r] fp64 and U [len, r] in the storage type.
 template <typename T>
 __global__ __launch_bounds__(256) void extract_factor_kernel(const double* G, int len, const int* idx, const double* norms2,
@@ -355,7 +379,8 @@ __global__ __launch_bounds__(256) void extract_factor_kernel(const double* G, in
   __shared__ double best_v[256];
   __shared__ int best_j[256];
   const int k = blockIdx.x;
-  const double* g = G + (long)idx[k] * len;
+  const int src = idx ? idx[k] : k;
+  const double* g = G + (long)src * len;
   double bv = -1.0;
   int bj = 0x7fffffff;
   for (int j = threadIdx.x; j < len; j += 256) {
@@ -376,7 +401,7 @@ __global__ __launch_bounds__(256) void extract_factor_kernel(const double* G, in
     }
     __syncthreads();
   }
-  const double scale = (g[best_j[0]] < 0.0 ? -1.0 : 1.0) / sqrt(norms2[idx[k]]);
+  const double scale = (g[best_j[0]] < 0.0 ? -1.0 : 1.0) / sqrt(norms2[src]);
   for (int j = threadIdx.x; j < len; j += 256) {
     const double v = scale * g[j];
     U64[(long)j * r + k] = v;
@@ -389,7 +414,10 @@ inline int blocks_for(long total) { return (int)std::min<long>((total + 255) / 2
 hipError_t dgemm(hipStream_t s, int batch, int M, int N, int K, const double* A, long a_m, long a_k, long a_b,
                  const double* B, long b_k, long b_n, long b_b, double* C, long c_m, long c_n, long c_b) {
   DgemmArgs g{A, a_m, a_k, a_b, B, b_k, b_n, b_b, C, c_m, c_n, c_b, M, N, K};
-  hipLaunchKernelGGL(dgemm_kernel, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, s, g);
+  // small tiles until the large ones fill every compute unit twice
+  const long large = (long)((N + 63) / 64) * ((M + 63) / 64) * batch;
+  if (large >= 512) hipLaunchKernelGGL(dgemm_kernel<2>, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, s, g);
+  else hipLaunchKernelGGL(dgemm_kernel<1>, dim3((N + 31) / 32, (M + 31) / 32, batch), dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
@@ -407,6 +435,7 @@ struct JacobiStats {
   int sweeps = 0;
   long launches = 0;
   double ms = 0.0;
+  double bytes = 0.0;
 };
 
 template <typename T>
@@ -442,6 +471,7 @@ int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2,
     if (stats) {
       ++stats->sweeps;
       stats->launches += n_steps;
+      stats->bytes += 16.0 * m * m * n_steps;           // every round reads and writes all rows once
     }
     CK(hipMemsetAsync(counter, 0, sizeof(int), s));
     for (int step = 0; step < n_steps; ++step)
@@ -477,8 +507,34 @@ int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2,
   return TUCKER_ATTN_OK;
 }
 
+// Polish of nearly orthonormal rows, S = Z Z^T: S <- 1.5 I - 0.5 S in place, err[blockIdx.x] = largest |S - I| of a row
+__global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, double* err) {
+  __shared__ double red[4];
+  double* row = S + (long)blockIdx.x * r;
+  double worst = 0.0;
+  for (int j = threadIdx.x; j < r; j += 256) {
+    const double one = j == (int)blockIdx.x ? 1.0 : 0.0, off = fabs(row[j] - one);
+    worst = off > worst || off != off ? off : worst;    // a NaN stays
+    row[j] = 1.5 * one - 0.5 * row[j];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double x = __shfl_xor(worst, o);
+    worst = x > worst || x != x ? x : worst;
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = worst;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) worst = red[w] > worst || red[w] != red[w] ? red[w] : worst;
+    err[blockIdx.x] = worst;
+  }
+}
+
 struct HosvdWs {
-  double *A, *B, *T, *M, *GA, *GB, *SA, *SB, *M1, *U1, *U2, *U3, *P, *Q, *H, *C, *norms2;
+  double *A, *B, *T, *GA, *GB, *SA, *SB, *M1, *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
+  double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~
+  double *Z[4], *work[4], *host_side[4];                // eigenvector rows; scratch; value | resid | err, fetched together
+  double *S, *Z2;
   int *idx, *counter;
   size_t bytes;
 };
@@ -496,15 +552,24 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   w.A = (double*)take(D * n, 8);
   w.B = (double*)take(D * n, 8);
   w.T = (double*)take(D * n, 8);
-  w.M = (double*)take(D * D, 8);
   w.GA = (double*)take(n * n, 8);
   w.GB = (double*)take(n * n, 8);
   w.SA = (double*)take(n * dH, 8);
   w.SB = (double*)take(n * dH, 8);
   w.M1 = (double*)take((size_t)nH * nH, 8);
-  w.U1 = (double*)take((size_t)nH * nH, 8);
-  w.U2 = (double*)take(D * rmax, 8);
-  w.U3 = (double*)take(D * rmax, 8);
+  for (int t = 0; t < 2; ++t) {
+    w.U1[t] = (double*)take((size_t)nH * nH, 8);
+    w.U2[t] = (double*)take(D * rmax, 8);
+    w.U3[t] = (double*)take(D * rmax, 8);
+  }
+  for (int e = 0; e < 4; ++e) {
+    w.M[e] = (double*)take(D * D, 8);
+    w.Z[e] = (double*)take(D * rmax, 8);
+    w.work[e] = (double*)take(eigen_work_elems(d), 8);
+    w.host_side[e] = (double*)take(3 * D, 8);
+  }
+  w.S = (double*)take(rmax * rmax, 8);
+  w.Z2 = (double*)take(D * rmax, 8);
   w.P = (double*)take(rmax * n, 8);
   w.Q = (double*)take(rmax * n, 8);
   w.H = (double*)take((size_t)nH * rmax * rmax, 8);
@@ -516,43 +581,134 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   return w;
 }
 
-// One tensor (A_i B_i^T)_i, A and B [d, n] fp64 in the workspace: factors and core at the given
-// ranks.  `given_U3`: the mode-3 factor is already in w.U3 (shared latent) and is not recomputed.
-template <typename T>
-int hosvd_one(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, int r1, int r2, int r3, bool given_U3,
-              T* C, T* U1, T* U2, T* U3, double* sv, JacobiStats* st3) {
+// Gram matrices of the mode unfoldings of one tensor (A_i B_i^T)_i, A and B [d, n] fp64 in the workspace
+hipError_t head_products(hipStream_t s, const HosvdWs& w, int d, int nH, int dH) {
   const long n = (long)nH * dH;
   // per-head dH x dH Gram matrices  SA_i = A_i^T A_i, SB_i = B_i^T B_i
-  CK(dgemm(s, nH, dH, dH, d, w.A, 1, n, dH, w.A, n, 1, dH, w.SA, dH, 1, (long)dH * dH));
-  CK(dgemm(s, nH, dH, dH, d, w.B, 1, n, dH, w.B, n, 1, dH, w.SB, dH, 1, (long)dH * dH));
+  if (hipError_t e = dgemm(s, nH, dH, dH, d, w.A, 1, n, dH, w.A, n, 1, dH, w.SA, dH, 1, (long)dH * dH)) return e;
+  if (hipError_t e = dgemm(s, nH, dH, dH, d, w.B, 1, n, dH, w.B, n, 1, dH, w.SB, dH, 1, (long)dH * dH)) return e;
   // mode 1: <W_i, W_j> from the full Gram matrices of the factors
-  CK(dgemm(s, 1, (int)n, (int)n, d, w.A, 1, n, 0, w.A, n, 1, 0, w.GA, n, 1, 0));
-  CK(dgemm(s, 1, (int)n, (int)n, d, w.B, 1, n, 0, w.B, n, 1, 0, w.GB, n, 1, 0));
+  if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.A, 1, n, 0, w.A, n, 1, 0, w.GA, n, 1, 0)) return e;
+  if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.B, 1, n, 0, w.B, n, 1, 0, w.GB, n, 1, 0)) return e;
   hipLaunchKernelGGL(head_gram_kernel, dim3(nH, nH), dim3(256), 0, s, w.GA, w.GB, w.M1, nH, dH);
-  CK(hipGetLastError());
-  int st = leading_eigenvectors<T>(s, w.M1, nH, r1, w.norms2, w.idx, w.counter, w.U1, U1, sv, st3 ? &st3[0] : nullptr);
-  if (st != TUCKER_ATTN_OK) return st;
-  // mode 2: sum_i W_i W_i^T = sum_i (A_i SB_i) A_i^T
-  CK(dgemm(s, nH, d, dH, dH, w.A, n, 1, dH, w.SB, dH, 1, (long)dH * dH, w.T, n, 1, dH));
-  CK(dgemm(s, 1, d, d, (int)n, w.T, n, 1, 0, w.A, 1, n, 0, w.M, d, 1, 0));
-  st = leading_eigenvectors<T>(s, w.M, d, r2, w.norms2, w.idx, w.counter, w.U2, U2, sv ? sv + nH : nullptr,
-                                st3 ? &st3[1] : nullptr);
-  if (st != TUCKER_ATTN_OK) return st;
-  // mode 3: sum_i W_i^T W_i = sum_i (B_i SA_i) B_i^T
-  if (!given_U3) {
-    CK(dgemm(s, nH, d, dH, dH, w.B, n, 1, dH, w.SA, dH, 1, (long)dH * dH, w.T, n, 1, dH));
-    CK(dgemm(s, 1, d, d, (int)n, w.T, n, 1, 0, w.B, 1, n, 0, w.M, d, 1, 0));
-    st = leading_eigenvectors<T>(s, w.M, d, r3, w.norms2, w.idx, w.counter, w.U3, U3, sv ? sv + nH + d : nullptr,
-                                  st3 ? &st3[2] : nullptr);
-    if (st != TUCKER_ATTN_OK) return st;
-  } else if (sv) {
-    for (int k = 0; k < d; ++k) sv[nH + d + k] = 0.0;
+  return hipGetLastError();
+}
+hipError_t mode_gram(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, int mode, double* M) {
+  const long n = (long)nH * dH;
+  // mode 2: sum_i W_i W_i^T = sum_i (A_i SB_i) A_i^T;  mode 3: sum_i W_i^T W_i = sum_i (B_i SA_i) B_i^T
+  const double *F = mode == 2 ? w.A : w.B, *S = mode == 2 ? w.SB : w.SA;
+  if (hipError_t e = dgemm(s, nH, d, dH, dH, F, n, 1, dH, S, dH, 1, (long)dH * dH, w.T, n, 1, dH)) return e;
+  return dgemm(s, 1, d, d, (int)n, w.T, n, 1, 0, F, 1, n, 0, M, d, 1, 0);
+}
+
+// one d x d eigen-problem of a conversion
+template <typename T> struct EigenJob {
+  int tensor, mode;                                     // 0: W, 1: W~; 2 or 3
+  int r;
+  double* U64;
+  T* U;
+  double* sv;                                           // host, nullable
+  JacobiStats* stats;                                   // nullable
+};
+
+// The problems of `jobs` (Gram matrices in w.M[j]) through the reduction to tridiagonal form.  done[j] is left false
+// where the vectors are no certified answer (eigenvalues too close for the twisted factorisation); w.M[j] is lost
+// either way.  Synchronises the stream.
+template <typename T>
+int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* jobs, int n_jobs, bool* done) {
+  EigenBatch b;
+  b.n = n_jobs;
+  b.m = d;
+  const bool timed = jobs[0].stats != nullptr;
+  for (int j = 0; j < n_jobs; ++j) {
+    done[j] = false;
+    b.r[j] = jobs[j].r;
+    b.n_values[j] = jobs[j].sv ? d : jobs[j].r;
+    b.G[j] = w.M[j];
+    b.Z[j] = w.Z[j];
+    b.work[j] = w.work[j];
+    b.value[j] = w.host_side[j];
+    b.resid[j] = w.host_side[j] + d;
   }
-  // core: C[a] = sum_i U1[i][a] (U2^T A_i)(U3^T B_i)^T
-  CK(dgemm(s, 1, r2, (int)n, d, w.U2, 1, r2, 0, w.A, n, 1, 0, w.P, n, 1, 0));
-  CK(dgemm(s, 1, r3, (int)n, d, w.U3, 1, r3, 0, w.B, n, 1, 0, w.Q, n, 1, 0));
+  struct Events {
+    hipEvent_t e[2] = {nullptr, nullptr};
+    ~Events() {
+      for (hipEvent_t x : e)
+        if (x) (void)hipEventDestroy(x);
+    }
+  } ev;
+  if (timed) {
+    for (hipEvent_t& x : ev.e) CK(hipEventCreate(&x));
+    CK(hipEventRecord(ev.e[0], s));
+  }
+  CK(launch_tridiag(b, s));
+  if (timed) CK(hipEventRecord(ev.e[1], s));
+  CK(launch_tridiag_vectors(b, s));
+  // rows of close eigenvalues are orthogonal only to rounding / gap: one Newton-Schulz step Z <- (1.5 I - 0.5 Z Z^T) Z,
+  // which squares what is missing and moves no vector by more than its own uncertainty
+  auto polish = [&](int j) -> hipError_t {
+    const int r = b.r[j];
+    if (hipError_t e = dgemm(s, 1, r, r, d, w.Z[j], d, 1, 0, w.Z[j], 1, d, 0, w.S, r, 1, 0)) return e;
+    hipLaunchKernelGGL(newton_schulz_kernel, dim3(r), dim3(256), 0, s, w.S, r, w.host_side[j] + 2 * (size_t)d);
+    if (hipError_t e = dgemm(s, 1, r, d, r, w.S, r, 1, 0, w.Z[j], d, 1, 0, w.Z2, d, 1, 0)) return e;
+    return hipMemcpyAsync(w.Z[j], w.Z2, sizeof(double) * r * d, hipMemcpyDeviceToDevice, s);
+  };
+  std::vector<std::vector<double>> host(n_jobs), tri(n_jobs);
+  for (int j = 0; j < n_jobs; ++j) {
+    CK(polish(j));
+    host[j].resize(3 * (size_t)d);
+    tri[j].resize(2 * (size_t)d);
+    CK(hipMemcpyAsync(host[j].data(), w.host_side[j], sizeof(double) * 3 * d, hipMemcpyDeviceToHost, s));
+    CK(hipMemcpyAsync(tri[j].data(), eigen_diag(w.work[j], d), sizeof(double) * 2 * d, hipMemcpyDeviceToHost, s));
+  }
+  CK(hipStreamSynchronize(s));
+  if (timed) {
+    float ms = 0.f;
+    CK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+    jobs[0].stats->ms += ms;                            // one set of launches for all
+    jobs[0].stats->launches += d;
+    jobs[0].stats->bytes += 16.0 * n_jobs * d * (double)d * d / 3;   // every step reads and writes what remains
+  }
+  auto worst_of = [](const double* x, int n) {
+    double worst = 0.0;
+    for (int k = 0; k < n; ++k) worst = x[k] > worst || x[k] != x[k] ? x[k] : worst;
+    return worst;
+  };
+  for (int j = 0; j < n_jobs; ++j) {
+    const int r = b.r[j];
+    double fro2 = 0.0, top = 0.0;
+    for (int k = 0; k < d; ++k) {
+      const double off = k + 1 < d ? tri[j][d + k] : 0.0;
+      fro2 += tri[j][k] * tri[j][k] + 2.0 * off * off;
+    }
+    std::vector<double> value(host[j].begin(), host[j].begin() + b.n_values[j]);
+    std::sort(value.begin(), value.end(), [](double x, double y) { return x > y; });
+    top = std::sqrt(fro2);
+    // the rank test of the Jacobi path, on the squared eigenvalue
+    if (!(value[r - 1] > 0.0) || !(value[r - 1] * value[r - 1] > 1e8 * 1e-28 * d * fro2)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
+    double missing = worst_of(host[j].data() + 2 * (size_t)d, r);
+    const double resid = worst_of(host[j].data() + d, r);
+    if (!(resid <= 1e-13 * std::sqrt((double)d) * top) || !(missing <= 1e-3 / r)) continue;
+    for (; missing > 1e-8 / r; missing = r * missing * missing) CK(polish(j));   // rare: very close eigenvalues
+    if (jobs[j].sv)
+      for (int k = 0; k < d; ++k) jobs[j].sv[k] = std::sqrt(std::max(value[k], 0.0));
+    hipLaunchKernelGGL(row_norms_kernel, dim3(r), dim3(256), 0, s, w.Z[j], d, w.norms2);
+    hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, w.Z[j], d, nullptr, w.norms2, r, jobs[j].U64, jobs[j].U);
+    CK(hipGetLastError());
+    done[j] = true;
+  }
+  return TUCKER_ATTN_OK;
+}
+
+// core: C[a] = sum_i U1[i][a] (U2^T A_i)(U3^T B_i)^T
+template <typename T>
+int core_of(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, int r1, int r2, int r3, const double* U1, const double* U2,
+            const double* U3, T* C) {
+  const long n = (long)nH * dH;
+  CK(dgemm(s, 1, r2, (int)n, d, U2, 1, r2, 0, w.A, n, 1, 0, w.P, n, 1, 0));
+  CK(dgemm(s, 1, r3, (int)n, d, U3, 1, r3, 0, w.B, n, 1, 0, w.Q, n, 1, 0));
   CK(dgemm(s, nH, r2, r3, dH, w.P, n, 1, dH, w.Q, 1, n, dH, w.H, r3, 1, (long)r2 * r3));
-  CK(dgemm(s, 1, r1, r2 * r3, nH, w.U1, 1, r1, 0, w.H, (long)r2 * r3, 1, 0, w.C, (long)r2 * r3, 1, 0));
+  CK(dgemm(s, 1, r1, r2 * r3, nH, U1, 1, r1, 0, w.H, (long)r2 * r3, 1, 0, w.C, (long)r2 * r3, 1, 0));
   const long total = (long)r1 * r2 * r3;
   hipLaunchKernelGGL((from_f64_kernel<T>), dim3(blocks_for(total)), dim3(256), 0, s, w.C, C, total);
   CK(hipGetLastError());
@@ -600,37 +756,79 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
   struct Report {                                       // filled on every return path
     tucker_convert_hosvd_info* info;
     const JacobiStats* st;
-    int d;
     ~Report() {
       if (!info) return;
       info->jacobi_launches = 0;
+      info->jacobi_bytes = 0.0;
       info->jacobi_ms = 0.0;
       for (int k = 0; k < 6; ++k) {
         info->sweeps[k] = st[k].sweeps;
         if (k % 3 != 0) {
           info->jacobi_launches += st[k].launches;
           info->jacobi_ms += st[k].ms;
+          info->jacobi_bytes += st[k].bytes;
         }
       }
-      info->jacobi_bytes = 16.0 * d * d * (double)info->jacobi_launches;
     }
-  } report{info, stats, d};
+  } report{info, stats};
   const HosvdWs w = carve_hosvd(workspace, d, nH, dH);
   const long n = (long)nH * dH;
   const int cb = blocks_for((long)d * n);
-  // pre-softmax tensor: A = WQ, B = WK
-  hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, WQ, n, 1, w.A, d, (int)n);
-  hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, WK, n, 1, w.B, d, (int)n);
-  CK(hipGetLastError());
-  int st = hosvd_one<T>(s, w, d, nH, dH, r1, r2, r3, false, (T*)o.C, (T*)o.U1, (T*)o.U2, (T*)o.U3, sv, info ? stats : nullptr);
-  if (st != TUCKER_ATTN_OK) return st;
-  // post-softmax tensor, output index first: A = WO^T, B = WV
-  hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, WO, 1, (long)d, w.A, d, (int)n);
-  hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, WV, n, 1, w.B, d, (int)n);
-  CK(hipGetLastError());
-  st = hosvd_one<T>(s, w, d, nH, dH, rt1, rt2, rt3, shared, (T*)o.Ct, (T*)o.Ut1, (T*)o.Ut2, (T*)o.Ut3,
-                    sv ? sv + nH + 2 * d : nullptr, info ? stats + 3 : nullptr);
-  if (st != TUCKER_ATTN_OK) return st;
+  // the two tensors: A = WQ, B = WK before the softmax; A = WO^T (output index first), B = WV behind it
+  auto load = [&](int t) -> hipError_t {
+    hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, t ? WO : WQ, t ? 1 : n, t ? (long)d : 1, w.A, d, (int)n);
+    hipLaunchKernelGGL((to_f64_kernel<T>), dim3(cb), dim3(256), 0, s, t ? WV : WK, n, 1, w.B, d, (int)n);
+    return hipGetLastError();
+  };
+  EigenJob<T> jobs[4];
+  int n_jobs = 0;
+  for (int t = 0; t < 2; ++t)
+    for (int mode = 2; mode <= 3; ++mode) {
+      const long at = t * (nH + 2l * d) + nH + (mode - 2) * (long)d;
+      if (t && mode == 3 && shared) {
+        if (sv) std::fill(sv + at, sv + at + d, 0.0);
+        continue;
+      }
+      jobs[n_jobs++] = EigenJob<T>{t, mode, t ? (mode == 2 ? rt2 : rt3) : (mode == 2 ? r2 : r3), mode == 2 ? w.U2[t] : w.U3[t],
+                                   (T*)(t ? (mode == 2 ? o.Ut2 : o.Ut3) : (mode == 2 ? o.U2 : o.U3)), sv ? sv + at : nullptr,
+                                   info ? &stats[3 * t + mode - 1] : nullptr};
+    }
+  for (int t = 0; t < 2; ++t) {
+    CK(load(t));
+    CK(head_products(s, w, d, nH, dH));
+    const int st = leading_eigenvectors<T>(s, w.M1, nH, t ? rt1 : r1, w.norms2, w.idx, w.counter, w.U1[t], (T*)(t ? o.Ut1 : o.U1),
+                                           sv ? sv + t * (nH + 2l * d) : nullptr, info ? &stats[3 * t] : nullptr);
+    if (st != TUCKER_ATTN_OK) return st;
+    for (int j = 0; j < n_jobs; ++j)
+      if (jobs[j].tensor == t) CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
+  }
+  // The reduction to tridiagonal form takes the sizes whose vectors fit the LDS (whole conversions: d = 768 7.6 ms
+  // against 206 ms by the Jacobi iteration, d = 4096 0.36 s against 4.3 s).  A problem that it cannot certify (on a
+  // Gram matrix formed anew) and every other size go through the Jacobi iteration.
+  bool done[4] = {false, false, false, false};
+  const bool tridiagonal = d >= kEigenMinSize && d <= kEigenMaxSize;
+  if (tridiagonal)
+    if (const int st = tridiagonal_jobs<T>(s, w, d, jobs, n_jobs, done); st != TUCKER_ATTN_OK) return st;
+  int loaded = 1;
+  for (int j = n_jobs - 1; j >= 0; --j) {
+    if (done[j]) continue;
+    if (tridiagonal) {
+      if (loaded != jobs[j].tensor) CK(load(jobs[j].tensor));
+      loaded = jobs[j].tensor;
+      CK(head_products(s, w, d, nH, dH));
+      CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
+    }
+    const int st = leading_eigenvectors<T>(s, w.M[j], d, jobs[j].r, w.norms2, w.idx, w.counter, jobs[j].U64, jobs[j].U,
+                                           jobs[j].sv, jobs[j].stats);
+    if (st != TUCKER_ATTN_OK) return st;
+  }
+  for (int t = 1; t >= 0; --t) {
+    if (loaded != t) CK(load(t));
+    loaded = t;
+    const int st = core_of<T>(s, w, d, nH, dH, t ? rt1 : r1, t ? rt2 : r2, t ? rt3 : r3, w.U1[t], w.U2[t],
+                              t && !shared ? w.U3[1] : w.U3[0], (T*)(t ? o.Ct : o.C));
+    if (st != TUCKER_ATTN_OK) return st;
+  }
   CK(hipStreamSynchronize(s));
   return TUCKER_ATTN_OK;
 }

@@ -1,0 +1,32 @@
+// Leading eigenpairs of a batch of symmetric positive semi-definite fp64 matrices of one size (eigen.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace ta {
+
+constexpr int kEigenBatch = 4;                          // matrices solved side by side
+// four vectors of the matrix size have to fit the LDS of a workgroup
+constexpr int kEigenMinSize = 8, kEigenMaxSize = 5056;
+
+struct EigenBatch {
+  int n, m;                                             // matrices in the batch, size of each
+  int r[kEigenBatch];                                   // eigenvectors wanted of each, 1 .. m
+  double* G[kEigenBatch];                               // [m, m], full storage; destroyed (holds the reflectors)
+  double* Z[kEigenBatch];                               // [r, m] eigenvectors, largest eigenvalue first
+  double* work[kEigenBatch];                            // eigen_work_elems(m) doubles each
+  double* value[kEigenBatch];                           // [m] eigenvalues, largest first (the first n_values written)
+  double* resid[kEigenBatch];                           // [m] residual of each vector in the tridiagonal matrix
+  int n_values[kEigenBatch];                            // eigenvalues wanted of each, r .. m
+};
+inline size_t eigen_work_elems(int m) { return 8ul * m; }
+// diagonal and subdiagonal of the tridiagonal matrix inside `work`
+inline double* eigen_diag(double* work, int) { return work; }
+inline double* eigen_offdiag(double* work, int m) { return work + m; }
+
+// Enqueues the reduction to tridiagonal form; G and work are written.
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s);
+// Enqueues eigenvalues and eigenvectors of the tridiagonal matrices, vectors carried back to the basis of G.
+// The vectors are unit rows; rows of close eigenvalues are orthogonal only up to (rounding / gap).
+hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s);
+
+}  // namespace ta

@@ -1,0 +1,423 @@
+// Leading eigenpairs of symmetric matrices in fp64: Householder reduction to tridiagonal form, eigenvalues by
+// multisection on Sturm counts, eigenvectors of the tridiagonal matrix from its twisted factorisation, and the
+// reflectors applied back.  Up to four matrices of one size go through every launch side by side.
+//
+// The reduction is a chain of m dependent steps (each needs a product of the whole remaining matrix with a vector
+// that the previous step determines), so a step is ONE launch: the rank-two update of step k-1, the column of
+// step k and the product with its reflector are fused, every workgroup working out the reflector for itself.
+#include "eigen.h"
+
+#include "common.h"
+#include "params.h"
+
+namespace ta {
+namespace {
+
+// layout of a problem's work array, in vectors of m doubles
+constexpr int kDiag = 0, kOff = 1, kTau = 2, kV = 3, kY = 5;   // kV, kY: two vectors each, used in turn
+
+// x of the lane that the DPP control CTRL names
+template <int CTRL> __device__ __forceinline__ double dpp(double x) {
+  const long b = __builtin_bit_cast(long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (long)(((unsigned long)hi << 32) | lo));
+}
+// sum over a wave, every lane receives it (register moves: with LDS permutes a step of four 768 x 768 matrices takes 7.1 us, not 6.4)
+__device__ __forceinline__ double wave_sum(double x) {
+  x += dpp<0xb1>(x);                                    // lane ^ 1, lane ^ 2
+  x += dpp<0x4e>(x);
+  x += dpp<0x141>(x);                                   // mirrored in 8, in 16
+  x += dpp<0x140>(x);
+  {
+    const long b = __builtin_bit_cast(long, x);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    x = __builtin_bit_cast(double, (long)(((unsigned long)hi[0] << 32) | lo[0])) +
+        __builtin_bit_cast(double, (long)(((unsigned long)hi[1] << 32) | lo[1]));
+  }
+  const long b = __builtin_bit_cast(long, x);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return __builtin_bit_cast(double, (long)(((unsigned long)hi[0] << 32) | lo[0])) +
+         __builtin_bit_cast(double, (long)(((unsigned long)hi[1] << 32) | lo[1]));
+}
+// sum over a workgroup of NW waves; every thread receives it.  `red` [NW] is not shared with the next call.
+template <int NW> __device__ __forceinline__ double block_sum(double x, double* red) {
+  x = wave_sum(x);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) s += red[w];
+  return s;
+}
+
+// Step k of the reduction.  With v = the reflector of step k-1 (v_k = 1, zero before k), y = A v and
+// w = tau (y - tau/2 (v.y) v), the remaining matrix becomes A - v w^T - w v^T; its row k gives the diagonal and
+// subdiagonal entry k and the next reflector u, and the launch leaves A u for step k+1.
+// Workgroup = 16 waves, RW rows each (fixed rows per workgroup; grid.x shrinks with the matrix).  Row k is read by
+// every workgroup and written by none; row k-1, read by none any more, receives v for the way back.
+// NC > 0: a row fits NC chunks of 64 lanes and is loaded before the reflector is known.
+// Small matrices are bound by the latency of a launch, its loads and its two workgroup sums (four of 768: 6.5 us a
+// step on average, 0.24 of the memory rate), large ones by memory (four of 4096: 78 us a step, 4.6 TB/s).
+template <int NC, int RW>
+__global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k, int first_wg) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  __shared__ double red[2][16];
+  const int m = b.m, p = blockIdx.y;
+  double* A = b.G[p];
+  double* work = b.work[p];
+  double* v = reinterpret_cast<double*>(smem_raw);
+  double* w = v + m;
+  double* u = w + m;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = (first_wg + blockIdx.x) * 16 * RW + wave;    // this wave's rows: row0 + 16 t
+  const int c0 = k + 1;                                         // first column that is still needed
+
+  double x[NC > 0 ? NC : 1];
+  if constexpr (NC > 0) {
+    if (row0 >= c0 && row0 < m) {
+#pragma unroll
+      for (int t = 0; t < NC; ++t) {
+        const int j = c0 + lane + 64 * t;
+        x[t] = j < m ? A[(long)row0 * m + j] : 0.0;
+      }
+    }
+  }
+  const double* vp = work + (long)(kV + ((k + 1) & 1)) * m;
+  const double* yp = work + (long)(kY + ((k + 1) & 1)) * m;
+  const double tau = k > 0 ? work[(long)kTau * m + k - 1] : 0.0;
+  const double yk = k > 0 ? yp[k] : 0.0;                        // v_k = 1
+  double dot = 0.0;
+  for (int i = k + tid; i < m; i += 1024) {
+    const double vi = k > 0 ? vp[i] : 0.0, yi = k > 0 ? yp[i] : 0.0;
+    v[i] = vi;
+    w[i] = yi;
+    u[i] = A[(long)k * m + i];
+    dot += vi * yi;
+  }
+  const double half = 0.5 * tau * block_sum<16>(dot, red[0]);
+  const double wk = tau * (yk - half);
+  double tail = 0.0;
+  for (int i = k + tid; i < m; i += 1024) {
+    const double vi = v[i], wi = tau * (w[i] - half * vi);
+    const double c = u[i] - vi * wk - wi;                       // row k of the updated matrix (v_k = 1)
+    w[i] = wi;
+    u[i] = c;
+    if (i > c0) tail += c * c;
+    if (i == k && blockIdx.x == 0) work[(long)kDiag * m + k] = c;
+  }
+  tail = block_sum<16>(tail, red[1]);
+  if (c0 >= m) {                                                // the last diagonal entry
+    if (blockIdx.x == 0 && k > 0)
+      for (int i = k + tid; i < m; i += 1024) A[(long)(k - 1) * m + i] = v[i];
+    return;
+  }
+  const double x0 = u[c0];
+  double beta = x0, tau_k = 0.0, scale = 0.0;
+  if (tail > 0.0) {
+    beta = -copysign(sqrt(x0 * x0 + tail), x0);
+    tau_k = (beta - x0) / beta;
+    scale = 1.0 / (x0 - beta);
+  }
+  __syncthreads();                                              // x0 has been read
+  for (int i = c0 + tid; i < m; i += 1024) u[i] = i == c0 ? 1.0 : u[i] * scale;
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (tid == 0) {
+      work[(long)kOff * m + k] = beta;
+      work[(long)kTau * m + k] = tau_k;
+    }
+    double* vn = work + (long)(kV + (k & 1)) * m;
+    for (int i = c0 + tid; i < m; i += 1024) vn[i] = u[i];
+    if (k > 0)
+      for (int i = k + tid; i < m; i += 1024) A[(long)(k - 1) * m + i] = v[i];
+  }
+  double* yn = work + (long)(kY + (k & 1)) * m;
+#pragma unroll 1
+  for (int t = 0; t < RW; ++t) {
+    const int row = row0 + 16 * t;
+    if (row < c0 || row >= m) continue;
+    const double vi = v[row], wi = w[row];
+    double* Ar = A + (long)row * m;
+    double sum = 0.0;
+    if constexpr (NC > 0) {
+      static_assert(NC == 0 || RW == 1, "one row in registers");
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int j = c0 + lane + 64 * c;
+        if (j < m) {
+          const double z = x[c] - vi * w[j] - wi * v[j];
+          Ar[j] = z;
+          sum += z * u[j];
+        }
+      }
+    } else {
+      // eight loads in flight per lane
+      for (int j0 = c0 + lane; j0 < m; j0 += 512) {
+        double q[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) q[c] = j0 + 64 * c < m ? Ar[j0 + 64 * c] : 0.0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int j = j0 + 64 * c;
+          if (j < m) {
+            const double z = q[c] - vi * w[j] - wi * v[j];
+            Ar[j] = z;
+            sum += z * u[j];
+          }
+        }
+      }
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) yn[row] = sum;
+  }
+}
+
+// 1/x to about two units in the last place: hardware estimate and two Newton steps
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// interval that holds every eigenvalue, from Gershgorin's circles of the tridiagonal matrix (all lanes alike)
+__device__ __forceinline__ void spectrum_bounds(const double* d, const double* e, int m, int lane, double& lo, double& hi) {
+  lo = INFINITY;
+  hi = -INFINITY;
+  for (int i = lane; i < m; i += 64) {
+    const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < m ? fabs(e[i]) : 0.0);
+    lo = fmin(lo, d[i] - r);
+    hi = fmax(hi, d[i] + r);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o));
+    hi = fmax(hi, __shfl_xor(hi, o));
+  }
+  const double slack = 4e-16 * m * fmax(fabs(lo), fabs(hi)) + 1e-300;
+  lo -= slack;
+  hi += slack;
+}
+constexpr double kPivot = 1e-290;                       // smallest pivot magnitude, relative to max(1, e^2)
+
+// Eigenvalue number 4 blockIdx.x + wave of a problem, counted from the largest: the 64 lanes of a wave count the
+// eigenvalues below 64 points of the current interval, which shrinks 65-fold per round (10 rounds: below the
+// rounding of the largest eigenvalue).  A serial chain of m pivots per round: 30 us a round at m = 768.
+__global__ __launch_bounds__(256) void tridiag_values_kernel(EigenBatch b) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int m = b.m, p = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double* d = b.work[p] + (long)kDiag * m;
+  const double* e = b.work[p] + (long)kOff * m;
+  double* pd = reinterpret_cast<double*>(smem_raw);     // (d_i, e_{i-1}^2) pairs
+  double e2max = 0.0;
+  for (int i = threadIdx.x; i < m; i += 256) {
+    const double o = i > 0 ? e[i - 1] : 0.0;
+    pd[2 * i] = d[i];
+    pd[2 * i + 1] = o * o;
+  }
+  for (int i = lane; i + 1 < m; i += 64) e2max = fmax(e2max, e[i] * e[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) e2max = fmax(e2max, __shfl_xor(e2max, o));
+  __syncthreads();
+  const int idx = blockIdx.x * 4 + wave;
+  if (idx >= b.n_values[p]) return;
+  const double pivot = kPivot * fmax(1.0, e2max);
+  double lo, hi;
+  spectrum_bounds(d, e, m, lane, lo, hi);
+  const int below = m - idx;                            // count at and above the eigenvalue wanted
+  for (int round = 0; round < 10; ++round) {
+    const double x = lo + (hi - lo) * ((lane + 1) / 65.0);
+    double q = pd[0] - x;
+    int cnt = 0;
+    if (fabs(q) < pivot) q = -pivot;
+    cnt += q < 0.0;
+#pragma unroll 8
+    for (int i = 1; i < m; ++i) {
+      q = (pd[2 * i] - x) - pd[2 * i + 1] * recip(q);
+      if (fabs(q) < pivot) q = -pivot;
+      cnt += q < 0.0;
+    }
+    const unsigned long long up = __builtin_amdgcn_ballot_w64(cnt >= below);
+    const int f = up == 0ull ? 64 : __builtin_ctzll(up);
+    const double nhi = f < 64 ? __shfl(x, f & 63) : hi;
+    const double nlo = f > 0 ? __shfl(x, (f - 1) & 63) : lo;
+    lo = nlo;
+    hi = nhi;
+  }
+  if (lane == 0) b.value[p][idx] = 0.5 * (lo + hi);
+}
+
+// Unit eigenvector of the tridiagonal matrix for its eigenvalue blockIdx.x: pivots of the factorisations from the top
+// (D+) and from the bottom (D-) are worked out by two lanes side by side; the vector starts from 1 where
+// |D+ + D- - (d - lambda)| is least and follows the factors both ways.  That least value over the norm is the
+// residual.  Row blockIdx.x of Z [r, m] receives the vector.
+__global__ __launch_bounds__(64) void tridiag_vector_kernel(EigenBatch b) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int m = b.m, p = blockIdx.y, idx = blockIdx.x, lane = threadIdx.x;
+  if (idx >= b.r[p]) return;
+  double* d = reinterpret_cast<double*>(smem_raw);
+  double* e = d + m;                                    // e[m-1] unused
+  double* up = e + m;                                   // D+, then the factor from i+1 to i
+  double* dn = up + m;                                  // D-, then the factor from i-1 to i
+  const double lam = b.value[p][idx];
+  double e2max = 0.0;
+  for (int i = lane; i < m; i += 64) {
+    d[i] = b.work[p][(long)kDiag * m + i] - lam;
+    const double o = i + 1 < m ? b.work[p][(long)kOff * m + i] : 0.0;
+    e[i] = o;
+    e2max = fmax(e2max, o * o);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) e2max = fmax(e2max, __shfl_xor(e2max, o));
+  const double pivot = kPivot * fmax(1.0, e2max);
+  __syncthreads();
+  if (lane < 2) {
+    double* out = lane == 0 ? up : dn;
+    double q = 1.0;
+#pragma unroll 4
+    for (int i = 0; i < m; ++i) {
+      const int at = lane == 0 ? i : m - 1 - i, prev = lane == 0 ? i - 1 : m - 1 - i;
+      const double o = i > 0 ? e[prev] : 0.0;
+      q = d[at] - o * o / q;
+      if (fabs(q) < pivot) q = -pivot;
+      out[at] = q;
+    }
+  }
+  __syncthreads();
+  double best = INFINITY;
+  int at = 0;
+  for (int i = lane; i < m; i += 64) {
+    const double g = fabs(up[i] + dn[i] - d[i]);
+    if (g < best) { best = g; at = i; }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double ob = __shfl_xor(best, o);
+    const int oa = __shfl_xor(at, o);
+    if (ob < best || (ob == best && oa < at)) { best = ob; at = oa; }
+  }
+  // factors: z_i = up[i] z_{i+1} above the twist, z_i = dn[i] z_{i-1} below it
+  for (int i = lane; i < m; i += 64) {
+    const double f = i < at ? -e[i] / up[i] : 0.0;
+    const double g = i > at ? -e[i - 1] / dn[i] : 0.0;
+    up[i] = f;
+    dn[i] = g;
+  }
+  __syncthreads();
+  if (lane < 2) {
+    double z = 1.0;
+    const int n = lane == 0 ? at : m - 1 - at;
+    if (lane == 0) d[at] = 1.0;
+#pragma unroll 4
+    for (int i = 1; i <= n; ++i) {
+      const int j = lane == 0 ? at - i : at + i;
+      z *= lane == 0 ? up[j] : dn[j];
+      d[j] = z;
+    }
+  }
+  __syncthreads();
+  double n2 = 0.0;
+  for (int i = lane; i < m; i += 64) n2 += d[i] * d[i];
+  n2 = wave_sum(n2);
+  const double inv = 1.0 / sqrt(n2);
+  double* z = b.Z[p] + (long)idx * m;
+  for (int i = lane; i < m; i += 64) z[i] = d[i] * inv;
+  if (lane == 0) b.resid[p][idx] = best * inv;
+}
+
+// Row blockIdx.x of Z times the reflectors, last to first: z -= tau_k v_k (v_k . z), v_k in row k of G from column
+// k+1 on.  NW waves hold the row, NC elements per thread; PF reflectors are in flight.
+template <int NW, int NC, int PF>
+__global__ __launch_bounds__(64 * NW) void apply_reflectors_kernel(EigenBatch b) {
+  __shared__ double red[2][NW];
+  const int m = b.m, p = blockIdx.y, tid = threadIdx.x;
+  if ((int)blockIdx.x >= b.r[p]) return;
+  const double* G = b.G[p];
+  const double* tau = b.work[p] + (long)kTau * m;
+  double* zr = b.Z[p] + (long)blockIdx.x * m;
+  double z[NC], v[PF][NC], t[PF];
+  auto load = [&](double (&q)[NC], double& tk, int k) {
+    tk = k >= 0 ? tau[k] : 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int i = tid + 64 * NW * c;
+      q[c] = k >= 0 && i > k && i < m ? G[(long)k * m + i] : 0.0;
+    }
+  };
+#pragma unroll
+  for (int c = 0; c < NC; ++c) z[c] = tid + 64 * NW * c < m ? zr[tid + 64 * NW * c] : 0.0;
+  const int last = m - 3;                               // the reflectors of the last two steps are the identity
+#pragma unroll
+  for (int f = 0; f < PF; ++f) load(v[f], t[f], last - f);
+  for (int k = last; k >= 0; k -= PF) {
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {                      // past the first reflector: zeros
+      double dot = 0.0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) dot += v[f][c] * z[c];
+      if constexpr (NW == 1) dot = wave_sum(dot);
+      else dot = block_sum<NW>(dot, red[f & 1]);
+      dot *= t[f];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) z[c] -= dot * v[f][c];
+      load(v[f], t[f], k - f - PF);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (tid + 64 * NW * c < m) zr[tid + 64 * NW * c] = z[c];
+}
+
+template <int NC, int RW> hipError_t tridiag_steps(const EigenBatch& b, hipStream_t s) {
+  const size_t lds = 3ul * b.m * sizeof(double);
+  auto kern = tridiag_step_kernel<NC, RW>;
+  static LdsOnce lds_once;
+  if (hipError_t e = allow_dynamic_lds(lds_once, kern, 3ul * kEigenMaxSize * sizeof(double)); e != hipSuccess) return e;
+  constexpr int kRows = 16 * RW;
+  const int wgs = (b.m + kRows - 1) / kRows;
+  for (int k = 0; k < b.m; ++k) {
+    const int first = k + 1 < b.m ? (k + 1) / kRows : wgs - 1;
+    hipLaunchKernelGGL(kern, dim3(wgs - first, b.n), dim3(1024), lds, s, b, k, first);
+  }
+  return hipGetLastError();
+}
+
+template <int NW, int NC, int PF> void apply_reflectors(const EigenBatch& b, int r, hipStream_t s) {
+  hipLaunchKernelGGL((apply_reflectors_kernel<NW, NC, PF>), dim3(r, b.n), dim3(64 * NW), 0, s, b);
+}
+
+}  // namespace
+
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s) {
+  if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
+  if (b.m <= 512) return tridiag_steps<8, 1>(b, s);
+  if (b.m <= 1024) return tridiag_steps<16, 1>(b, s);
+  return tridiag_steps<0, 4>(b, s);
+}
+
+hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s) {
+  if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
+  int r = 0, nv = 0;
+  for (int p = 0; p < b.n; ++p) {
+    if (b.r[p] < 1 || b.n_values[p] < b.r[p] || b.n_values[p] > b.m) return hipErrorInvalidValue;
+    r = b.r[p] > r ? b.r[p] : r;
+    nv = b.n_values[p] > nv ? b.n_values[p] : nv;
+  }
+  const size_t lv = 2ul * b.m * sizeof(double), lt = 4ul * b.m * sizeof(double);
+  static LdsOnce values_once, vector_once;
+  if (hipError_t e = allow_dynamic_lds(values_once, tridiag_values_kernel, 2ul * kEigenMaxSize * sizeof(double)); e != hipSuccess) return e;
+  if (hipError_t e = allow_dynamic_lds(vector_once, tridiag_vector_kernel, 4ul * kEigenMaxSize * sizeof(double)); e != hipSuccess) return e;
+  hipLaunchKernelGGL(tridiag_values_kernel, dim3((nv + 3) / 4, b.n), dim3(256), lv, s, b);
+  hipLaunchKernelGGL(tridiag_vector_kernel, dim3(r, b.n), dim3(64), lt, s, b);
+  static_assert(kEigenMaxSize <= 64 * 8 * 10, "a row fits the workgroup");
+  if (b.m <= 256) apply_reflectors<1, 4, 8>(b, r, s);
+  else if (b.m <= 512) apply_reflectors<1, 8, 6>(b, r, s);
+  else if (b.m <= 1024) apply_reflectors<1, 16, 4>(b, r, s);
+  else if (b.m <= 2048) apply_reflectors<4, 8, 4>(b, r, s);
+  else apply_reflectors<8, 10, 4>(b, r, s);                // 5120 elements
+  return hipGetLastError();
+}
+
+}  // namespace ta

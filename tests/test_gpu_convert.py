@@ -261,3 +261,45 @@ def test_gpt2_sized_layer_converted_on_the_gpu_runs_like_the_oracle_layer_on_ora
     stored = {k: wl.round_to_storage(v.astype(np.float32), "bf16") for k, v in ref.items()}
     want = orc.per_head_forward(X, stored, dH, True, base.rope_base)
     assert orc.relative_l2(y, want) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("d,nH,dH,r", [
+    (7, 2, 3, 3),                                                # below the smallest size of the tridiagonal reduction
+    (8, 2, 4, 5), (17, 3, 5, 15),                                # one workgroup of rows, and one row more
+    (256, 4, 16, 20), (257, 4, 16, 20),                          # edges of the row lengths held in registers
+    (512, 2, 32, 33), (513, 2, 32, 33), (1025, 2, 16, 20),       # and of the rows streamed from memory
+])
+def test_hosvd_at_the_edges_of_the_eigen_solver(d, nH, dH, r):
+    ranks = (min(2, nH), r, r - 1)
+    host, got, sv, _ = hosvd_case(d, nH, dH, ranks, ranks, False, "f32", 90 + d)
+    ref = cv.mha_to_tucker_hosvd(host["WQ"], host["WK"], host["WV"], host["WO"], nH, ranks, ranks)
+    check_spectra(sv, host, nH, d, False)
+    for k in ref:
+        assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
+
+
+@pytest.mark.parametrize("kind", ["all_equal", "pairs", "blocks"])
+def test_hosvd_with_repeated_singular_values_keeps_the_tensor(kind):
+    # vectors of repeated values are not unique: the factors must be orthonormal and, at full ranks, the core
+    # contracted with them must give the tensor back (fp64 inside, one rounding to fp32: 6e-8 per factor)
+    d, nH, dH = 64, 4, 16
+    rng = np.random.default_rng(97)
+    q = lambda: np.linalg.qr(rng.standard_normal((d, d)))[0]
+    A, B = q(), q()
+    if kind == "pairs":
+        s = np.repeat(2.0 ** -(np.arange(d // 2) / 8.0), 2)
+        A, B = A * s, B * s
+    elif kind == "blocks":                                       # heads on disjoint channels: the Gram matrices split
+        A = np.kron(np.eye(nH), rng.standard_normal((dH, dH)))
+        B = np.kron(np.eye(nH), rng.standard_normal((dH, dH)))
+    host = dict(WQ=A, WK=B, WV=B.copy(), WO=A.T.copy())
+    host = {k: np.ascontiguousarray(v, dtype=np.float32) for k, v in host.items()}
+    devw = {k: to_device(v, "f32") for k, v in host.items()}
+    out, _ = dev.from_mha_hosvd(devw["WQ"], devw["WK"], devw["WV"], devw["WO"], nH, (nH, d, d), (nH, d, d))
+    got = {k: to_host(v).astype(np.float64) for k, v in out.items()}
+    for core, f1, f2, f3, W in (("C", "U1", "U2", "U3", 0), ("Ct", "Ut1", "Ut2", "Ut3", 1)):
+        for k in (f1, f2, f3):
+            assert np.max(np.abs(got[k].T @ got[k] - np.eye(got[k].shape[1]))) <= 1e-6, k
+        back = np.einsum("abc,ia,jb,kc->ijk", got[core], got[f1], got[f2], got[f3], optimize=True)
+        want = cv.attention_tensors(host["WQ"], host["WK"], host["WV"], host["WO"], nH)[W]
+        assert orc.relative_l2(back, want) <= 2e-6
