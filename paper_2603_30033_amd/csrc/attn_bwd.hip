@@ -86,12 +86,13 @@ template <typename T, int D, int BC> struct DqLds {
   static constexpr size_t kBytes = 2ul * kStage * sizeof(T);
 };
 
-// Workgroup = 8 waves = 4 heads x 2 blocks of 32 queries (waves w and w+4 share a SIMD); key tiles
+// Workgroup = 4 heads x QW blocks of 32 queries (two: waves w and w+4 share a SIMD; one for calls with few
+// workgroups); key tiles
 // of BC keys are staged once per workgroup and walked in 32-key halves, so that only one half's
 // scores live in registers at a time.
-template <typename T, int D, int BC>
-__global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs p) {
-  constexpr int CB = D / 32, NB = BC / 32, HW = 4, QW = 2, TQ = 32 * QW, NT = 64 * HW * QW;
+template <typename T, int D, int BC, int QW>
+__global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
+  constexpr int CB = D / 32, NB = BC / 32, HW = 4, TQ = 32 * QW, NT = 64 * HW * QW;
   constexpr int CE = 16 / sizeof(T);
   using L = DqLds<T, D, BC>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -248,31 +249,32 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs p) {
 }
 
 // ---- dK, dV ------------------------------------------------------------------------------------------
-template <typename T, int D, int TQ> struct DkvLds {
+template <typename T, int D, int TQ, int KB> struct DkvLds {
   static constexpr int kStages = 3;
   static constexpr int kRow = D;                                // Q / dO rows, unpadded, chunks swizzled
   static constexpr int kRElems = TQ * kRow;
   static constexpr int kStageElems = 2 * kRElems;
   static constexpr size_t kStageBytes = kStageElems * sizeof(T) + 2ul * TQ * sizeof(float);
-  // probabilities handed from the dV^T waves to the dK^T waves: [2][4 key blocks][TQ/32] fragment blocks
-  static constexpr size_t kPBytes = 2ul * 4 * (TQ / 32) * kFragBlockElems * sizeof(T);
+  // probabilities handed from the dV^T waves to the dK^T waves: [2][KB key blocks][TQ/32] fragment blocks
+  static constexpr size_t kPBytes = 2ul * KB * (TQ / 32) * kFragBlockElems * sizeof(T);
   static constexpr size_t kBytes = kStages * kStageBytes + kPBytes;
 };
 
-// Workgroup = 8 waves over 128 keys: waves w and w+4 (one SIMD) own the same 32 keys.  Wave w holds
+// Workgroup = 2 KB waves over 32 KB keys (KB = 4, or 2 for calls with few workgroups): waves w and w+KB own the same
+// 32 keys (KB = 4: on one SIMD).  Wave w holds
 // the keys in registers as MFMA column operands, forms the probabilities P of a (head, query block)
-// pair, leaves them in LDS and accumulates dV^T += dO^T P; wave w+4 holds the values, forms dP one
+// pair, leaves them in LDS and accumulates dV^T += dO^T P; wave w+KB holds the values, forms dP one
 // interval later, takes P from LDS, and accumulates dK^T += Q^T (P (dP - delta)).  Two resident
 // waves per SIMD let one wave's exponentials overlap the other's matrix products.  The Q and dO rows
 // of a pair are staged once, row-major (straight from global memory into LDS, three stages, two pairs
 // ahead); the transposed operands Q^T and dO^T are read from the same
 // tiles with transposing LDS loads, so their rows (the channels) come out in the stored channel
 // order of Q and dO (acc order within 32-blocks), which kv_reduce undoes.
-template <typename T, int D, int TQ>
-__global__ __launch_bounds__(512) void bwd_dkv_kernel(BwdArgs p) {
-  constexpr int CB = D / 32, QBN = TQ / 32, KT = 128, NT = 512;
+template <typename T, int D, int TQ, int KB>
+__global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
+  constexpr int CB = D / 32, QBN = TQ / 32, KT = 32 * KB, NT = 128 * KB;
   constexpr int CE = 16 / sizeof(T);
-  using L = DkvLds<T, D, TQ>;
+  using L = DkvLds<T, D, TQ, KB>;
   constexpr int NS = L::kStages;
   static_assert(L::kStageBytes % 16 == 0, "stages stay 16-byte aligned");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -280,8 +282,8 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(BwdArgs p) {
 
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int h = lane / 32, lr = lane % 32;
-  const bool k_role = wave >= 4;                                // dK^T wave (else dV^T wave)
-  const int kb = wave % 4;                                      // key block of this wave
+  const bool k_role = wave >= KB;                               // dK^T wave (else dV^T wave)
+  const int kb = wave % KB;                                     // key block of this wave
   const int b = blockIdx.x / p.n_hg, hg = blockIdx.x % p.n_hg;
   const int key0 = blockIdx.y * KT + 32 * kb;                   // first key of this wave
   const int nk = key0 + lr;                                     // this lane's key
@@ -333,23 +335,23 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(BwdArgs p) {
     T* os = qs + L::kRElems;
     const long rs = (long)p.nH * D;
 #pragma unroll
-    for (int i = 0; i < (PIECES + 7) / 8; ++i) {
-      const int q = i * 8 + wave;
+    for (int i = 0; i < (PIECES + 2 * KB - 1) / (2 * KB); ++i) {
+      const int q = i * 2 * KB + wave;
       if (q < PIECES) {
         dma_piece<T, CPR>(qs, q, lane, [&](int row) { return Qg + row * rs; });
         dma_piece<T, CPR>(os, q, lane, [&](int row) { return Og + row * rs; });
       }
     }
-    // threads 0..255 fetch the log-sum-exp of the block's queries, threads 256.. their delta (TQ of
-    // each are kept)
+    // the first half of the threads fetch the log-sum-exp of the block's queries, the second half their delta (TQ
+    // of each are kept)
     const long so = ((long)b * p.nH + head) * p.Npad + q0 + threadIdx.x % TQ;
-    st_reg = (threadIdx.x < 256 ? p.lse : p.delta)[so];
+    st_reg = (threadIdx.x < NT / 2 ? p.lse : p.delta)[so];
   };
   auto s_store = [&](float st_reg, int stage) {
     float* st = reinterpret_cast<float*>(smem_raw + (size_t)stage * L::kStageBytes + L::kStageElems * sizeof(T));
     // stored negated: a score block starts from -log-sum-exp, a dP block from -delta
     if (threadIdx.x < TQ) st[threadIdx.x] = -st_reg;
-    else if (threadIdx.x >= 256 && threadIdx.x < 256 + TQ) st[TQ + threadIdx.x - 256] = -st_reg;
+    else if (threadIdx.x >= NT / 2 && threadIdx.x < NT / 2 + TQ) st[TQ + threadIdx.x - NT / 2] = -st_reg;
   };
 
   g_load(stat[0], 0, 0);
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(BwdArgs p) {
         const int qfirst = q0 + 32 * qb;
         // all 32 keys of the wave lie after all 32 queries of the block: nothing to do
         if (p.causal && key0 > qfirst + 31) continue;
-        T* pblk = pbuf + (long)(((it & 1) * 4 + kb) * QBN + qb) * kFragBlockElems;
+        T* pblk = pbuf + (long)(((it & 1) * KB + kb) * QBN + qb) * kFragBlockElems;
         // rows of the block start from -log-sum-exp (scores) or -delta (dP)
         f32x16 a;
         const float* st4 = stat + (k_role ? TQ : 0) + qb * 32 + 4 * h;
@@ -479,15 +481,22 @@ __global__ __launch_bounds__(256) void kv_reduce_kernel(KvReduceArgs a) {
 }
 
 // ---- launchers ---------------------------------------------------------------------------------------
-template <typename T, int D, int BC>
-static hipError_t dq_one(const BwdArgs& a, hipStream_t s) {
-  dim3 grid(((a.nH + 3) / 4) * a.Bsz, a.Npad / 64);
+template <typename T, int D, int BC, int QW>
+static hipError_t dq_launch(const BwdArgs& a, hipStream_t s) {
+  dim3 grid(((a.nH + 3) / 4) * a.Bsz, a.Npad / (32 * QW));
   const size_t smem = DqLds<T, D, BC>::kBytes;
-  auto kern = bwd_dq_kernel<T, D, BC>;
+  auto kern = bwd_dq_kernel<T, D, BC, QW>;
   static LdsOnce lds_once;
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, grid, dim3(512), smem, s, a);
+  hipLaunchKernelGGL(kern, grid, dim3(256 * QW), smem, s, a);
   return hipGetLastError();
+}
+// Fewer workgroups than compute units: one block of queries each, so that a wave has a SIMD to itself (two sequences
+// of 509 tokens, 12 heads, D = 64 in fp32: 112 -> 70 us).  The same below with the keys (81 -> 54 us).
+template <typename T, int D, int BC>
+static hipError_t dq_one(const BwdArgs& a, hipStream_t s) {
+  const long wgs = (long)((a.nH + 3) / 4) * a.Bsz * (a.Npad / 64);
+  return wgs < 256 ? dq_launch<T, D, BC, 1>(a, s) : dq_launch<T, D, BC, 2>(a, s);
 }
 
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {
@@ -507,16 +516,22 @@ hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+template <typename T, int D, int TQ, int KB>
+static hipError_t dkv_launch(const BwdArgs& a, hipStream_t s) {
+  using L = DkvLds<T, D, TQ, KB>;
+  static_assert(L::kBytes <= 160 * 1024, "fits the LDS of a compute unit");
+  static_assert(TQ <= 64 * KB, "half the threads hold a block's vector");
+  dim3 grid(a.n_hg * a.Bsz, (a.Npad + 32 * KB - 1) / (32 * KB));
+  auto kern = bwd_dkv_kernel<T, D, TQ, KB>;
+  static LdsOnce lds_once;
+  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, L::kBytes); ae != hipSuccess) return ae;
+  hipLaunchKernelGGL(kern, grid, dim3(128 * KB), L::kBytes, s, a);
+  return hipGetLastError();
+}
 template <typename T, int D, int TQ>
 static hipError_t dkv_one(const BwdArgs& a, hipStream_t s) {
-  dim3 grid(a.n_hg * a.Bsz, (a.Npad + 127) / 128);
-  const size_t smem = DkvLds<T, D, TQ>::kBytes;
-  static_assert(DkvLds<T, D, TQ>::kBytes <= 160 * 1024, "fits the LDS of a compute unit");
-  auto kern = bwd_dkv_kernel<T, D, TQ>;
-  static LdsOnce lds_once;
-  if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, grid, dim3(512), smem, s, a);
-  return hipGetLastError();
+  const long wgs = (long)a.n_hg * a.Bsz * ((a.Npad + 127) / 128);
+  return wgs < 256 ? dkv_launch<T, D, TQ, 2>(a, s) : dkv_launch<T, D, TQ, 4>(a, s);
 }
 
 hipError_t launch_bwd_dkv(int dtype, const BwdArgs& a, hipStream_t s) {

@@ -38,3 +38,14 @@ def test_projection_tiles(dtype, B, N, d, r2, r3, shared):
 def test_weight_gradient_tiles(dtype, B, N, d, heads, r2, r3):
     run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=d, n_heads=heads, d_head=32, r1=2, r2=r2, r3=r3,
                        dtype=dtype, seed=52))
+
+
+# attention forward and backward: workgroups for few and for many (sequence, head, token) tiles, the last block of 32
+# tokens partly filled and all padding
+@pytest.mark.parametrize("dtype,B,N,heads,r3", [
+    ("bf16", 1, 70, 3, 64), ("bf16", 2, 129, 5, 128), ("f32", 1, 97, 3, 32), ("f32", 3, 33, 4, 64),      # few
+    ("bf16", 90, 130, 3, 32), ("bf16", 130, 70, 5, 64), ("f32", 90, 130, 3, 32),                         # many
+])
+def test_attention_workgroups(dtype, B, N, heads, r3):
+    run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
+                       dtype=dtype, seed=53))
