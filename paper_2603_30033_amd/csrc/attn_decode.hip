@@ -14,6 +14,14 @@
 
 namespace ta {
 
+// Sequences per workgroup of the query, merge and output launches.  Their workgroups each sum or merge fp32 parts
+// that grow with the sequences they serve (a few hundred KB through one compute unit's port at 16 sequences) and there
+// are only as many as heads or 128-channel blocks, so eight sequences at a time go to workgroups of their own.
+// Measured (before, with all sequences in every workgroup -> now), query / merge / output launch: 24 sequences, 32 heads,
+// D = 128, d = 2048: 8.6 / 7.8 / 10.0 -> 6.7 / 5.0 / 5.8 us; 16 sequences, d = 4096: 6.9 / 6.5 / 8.4 -> 5.5 / 5.4 / 5.8 us.
+constexpr int kSeqGroup = 8;
+static int seq_groups(const DecodeArgs& a) { return (a.Bsz + kSeqGroup - 1) / kSeqGroup; }
+
 // ---------------------------------------------------------------------------------------
 // Qhat^T[c][tok] = sum_b Gt_i[c][b] Qlat[tok][b];  one workgroup per head slot, wave = c-block
 // ---------------------------------------------------------------------------------------
@@ -27,7 +35,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs g) {
   constexpr int CB = D / 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  T* Ql = reinterpret_cast<T*>(smem_raw);                         // [32][R2 + pad], acc order inside 32-blocks
+  T* Ql = reinterpret_cast<T*>(smem_raw);                         // [kSeqGroup][R2 + pad], acc order inside 32-blocks
   const int RE = p.R2 + 16 / (int)sizeof(T);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int h = lane / 32, tok = lane % 32;
@@ -35,8 +43,9 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
   const int Mp = g.R2 + (g.shared_kv ? 1 : 2) * g.D;
   constexpr int U = 8;                                            // partial tiles whose loads are issued together
 
+  const int t0 = blockIdx.y * kSeqGroup, nt = min(kSeqGroup, p.Bsz - t0);   // sequences of this workgroup
   if ((int)blockIdx.x >= n_heads_wg) {                            // ---- a key / value block of the projection
-    if (wave != 0) return;
+    if (wave != 0 || t0 != 0) return;                             // (all sequences)
     const int m0 = g.R2 + ((int)blockIdx.x - n_heads_wg) * 32;
     f32x16 acc;
 #pragma unroll
@@ -74,17 +83,17 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
     gf0[bb] = load_frag_major<T>(Gt + (long)(min(wave, CB - 1) * nbb + min(bb, nbb - 1)) * kFragBlockElems, lane);
 
   // ---- Qlat [sequence][R2] in the storage type, acc order -> LDS ----
-  for (int ci = threadIdx.x; ci < 32 * (p.R2 / 4); ci += 256) {
+  for (int ci = threadIdx.x; ci < kSeqGroup * (p.R2 / 4); ci += 256) {
     const int t = ci / (p.R2 / 4), k = (ci % (p.R2 / 4)) * 4;     // four natural indices k..k+3 keep their order
     const int pos = (k & ~31) + acc_pos(k & 31);
     if (g.ksplit > 1) {
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-      if (t < p.Bsz) {
+      if (t < nt) {
         for (int z0 = 0; z0 < g.ksplit; z0 += 2 * U) {
           f32x4 v[2 * U];
 #pragma unroll
           for (int u = 0; u < 2 * U; ++u)
-            v[u] = *reinterpret_cast<const f32x4*>(g.part + ((long)min(z0 + u, g.ksplit - 1) * p.Bsz + t) * Mp + k);
+            v[u] = *reinterpret_cast<const f32x4*>(g.part + ((long)min(z0 + u, g.ksplit - 1) * p.Bsz + t0 + t) * Mp + k);
 #pragma unroll
           for (int u = 0; u < 2 * U; ++u)
             if (z0 + u < g.ksplit) sum += v[u];
@@ -92,14 +101,15 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
       }
       store4(Ql + t * RE + pos, sum[0], sum[1], sum[2], sum[3]);
     } else {
-      const T* src = static_cast<const T*>(p.Qlat) + (long)t * p.R2 + pos;   // already in acc order
-      if (t < p.Bsz) store4(Ql + t * RE + pos, to_f32(src[0]), to_f32(src[1]), to_f32(src[2]), to_f32(src[3]));
+      const T* src = static_cast<const T*>(p.Qlat) + (long)(t0 + t) * p.R2 + pos;   // already in acc order
+      if (t < nt) store4(Ql + t * RE + pos, to_f32(src[0]), to_f32(src[1]), to_f32(src[2]), to_f32(src[3]));
       else store4(Ql + t * RE + pos, 0.f, 0.f, 0.f, 0.f);
     }
   }
   __syncthreads();
 
   T* Qh = static_cast<T*>(p.Qh);
+  const T* qrow = Ql + (tok % kSeqGroup) * RE + 16 * h;           // columns from nt on are computed and dropped
   for (int cb = wave; cb < CB; cb += 4) {
     f32x16 acc;
 #pragma unroll
@@ -109,13 +119,13 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
       for (int bb = 0; bb < PRE; ++bb)
         if (bb < nbb) {
           const Frag<T> gf = cb == wave ? gf0[bb] : load_frag_major<T>(Gt + (long)(cb * nbb + bb) * kFragBlockElems, lane);
-          mma32(acc, gf, load_frag<T>(Ql + tok * RE + bb * 32 + 16 * h));
+          mma32(acc, gf, load_frag<T>(qrow + bb * 32));
         }
       for (int bb = PRE; bb < nbb; ++bb)
         mma32(acc, load_frag_major<T>(Gt + (long)(cb * nbb + bb) * kFragBlockElems, lane),
-              load_frag<T>(Ql + tok * RE + bb * 32 + 16 * h));
-      if (p.rope != nullptr && tok < p.Bsz) {
-        const f32x4* tab = reinterpret_cast<const f32x4*>(p.rope) + (long)(cb * 8 + h) * p.rope_ld + (p.kv_len[tok] - 1);
+              load_frag<T>(qrow + bb * 32));
+      if (p.rope != nullptr && tok < nt) {
+        const f32x4* tab = reinterpret_cast<const f32x4*>(p.rope) + (long)(cb * 8 + h) * p.rope_ld + (p.kv_len[t0 + tok] - 1);
         f32x4 cs[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) cs[q] = tab[(long)2 * q * p.rope_ld];
@@ -129,8 +139,8 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
           }
       }
     }
-    if (tok < p.Bsz) {
-      T* row = Qh + ((long)tok * p.HB * 32 + head) * D;
+    if (tok < nt) {
+      T* row = Qh + ((long)(t0 + tok) * p.HB * 32 + head) * D;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         store4(row + cb * 32 + 8 * q + 4 * h, acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
@@ -708,6 +718,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
   __shared__ __attribute__((aligned(16))) T Ol[32 * RE];
   __shared__ float px[256 * (CPT + 2)];                           // partial merges of the thread groups of a sequence
   const int head = blockIdx.x;
+  const int t0 = blockIdx.y * kSeqGroup, nt = min(kSeqGroup, p.Bsz - t0);   // sequences of this workgroup
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int h = lane / 32, lr = lane % 32;
   const int HB32 = p.HB * 32;
@@ -729,7 +740,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
   // result does not depend on timing.
   {
     int Bp = 1;
-    while (Bp < p.Bsz) Bp *= 2;                                   // batch rounded up to a power of two, 1 .. 32
+    while (Bp < nt) Bp *= 2;                                      // sequences rounded up to a power of two, 1 .. 8
     int S = 1;
     while (S * 16 < p.nsplit && 2 * S * Bp <= 32) S *= 2;
     const int row = threadIdx.x / 8, cg = threadIdx.x % 8, c0 = cg * CPT;
@@ -738,7 +749,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
 #pragma unroll
     for (int e = 0; e < CPT; ++e) num[e] = 0.f;
     float mrun = -INFINITY, den = 0.f;
-    if (tok < p.Bsz && sg < S) {
+    if (tok < nt && sg < S) {
       constexpr int U = 16;                                       // splits whose loads are issued together (one
                                                                   // workgroup per compute unit: registers are plentiful)
       for (int s0 = sg; s0 < p.nsplit; s0 += U * S) {
@@ -746,7 +757,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
         f32x4 ov[U][CPT / 4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const long ps = ((long)tok * p.nsplit + min(s0 + u * S, p.nsplit - 1)) * HB32 + head;
+          const long ps = ((long)(t0 + tok) * p.nsplit + min(s0 + u * S, p.nsplit - 1)) * HB32 + head;
           mv[u] = p.part_m[ps];
           lv[u] = p.part_l[ps];
 #pragma unroll
@@ -781,7 +792,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
       mine[CPT] = mrun;
       mine[CPT + 1] = den;
       __syncthreads();
-      if (sg == 0 && tok < p.Bsz) {
+      if (sg == 0 && tok < nt) {
         // reference = the largest of the groups' references; then the parts are scaled and added in group order
         float mall = mrun;
         for (int j = 1; j < S; ++j) mall = fmaxf(mall, px[((tok + j * Bp) * 8 + cg) * (CPT + 2) + CPT]);
@@ -799,7 +810,7 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
       }
     }
     // thread row `row` writes LDS row `row`: a sequence's merged output from its group 0, zeros elsewhere
-    const float inv = (sg == 0 && tok < p.Bsz) ? 1.f / den : 0.f;
+    const float inv = (sg == 0 && tok < nt) ? 1.f / den : 0.f;
 #pragma unroll
     for (int q = 0; q < CPT / 4; ++q) {
       const int c = c0 + 4 * q;                                   // four consecutive channels keep their order
@@ -820,8 +831,8 @@ __global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs p) {
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) mma32(acc, gf[cb], load_frag<T>(Ol + lr * RE + cb * 32 + 16 * h));
-    if (lr < p.Bsz) {
-      float* dst = p.zpart + ((long)head * p.Bsz + lr) * p.RT2 + rb * 32 + 4 * h;
+    if (lr < nt) {
+      float* dst = p.zpart + ((long)head * p.Bsz + t0 + lr) * p.RT2 + rb * 32 + 4 * h;
 #pragma unroll
       for (int q = 0; q < 4; ++q) store4(dst + 8 * q, acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
     }
@@ -839,7 +850,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void decode_out_kernel(DecodeArgs p) {
   constexpr int PRE = 4;                                          // contraction blocks requested up front
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  T* Zl = reinterpret_cast<T*>(smem_raw);                         // [32][RT2 + pad]
+  T* Zl = reinterpret_cast<T*>(smem_raw);                         // [kSeqGroup][RT2 + pad]
+  const int t0 = blockIdx.y * kSeqGroup, nt = min(kSeqGroup, p.Bsz - t0);   // sequences of this workgroup
   const int RE = p.RT2 + 16 / (int)sizeof(T);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int h = lane / 32, lr = lane % 32;
@@ -854,16 +866,16 @@ __global__ __launch_bounds__(256) void decode_out_kernel(DecodeArgs p) {
   // ---- Z = sum over heads, rounded to T as the stored Z of a prefill is ----
   {
     constexpr int U = 16;
-    const int chunks = 32 * (p.RT2 / 4);                          // (sequence, 4 contraction indices)
+    const int chunks = kSeqGroup * (p.RT2 / 4);                          // (sequence, 4 contraction indices)
     for (int ci = threadIdx.x; ci < chunks; ci += 256) {
       const int tok = ci / (p.RT2 / 4), k = (ci % (p.RT2 / 4)) * 4;
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-      if (tok < p.Bsz) {
+      if (tok < nt) {
         for (int h0 = 0; h0 < p.nH; h0 += U) {
           f32x4 v[U];
 #pragma unroll
           for (int u = 0; u < U; ++u)
-            v[u] = *reinterpret_cast<const f32x4*>(p.zpart + ((long)min(h0 + u, p.nH - 1) * p.Bsz + tok) * p.RT2 + k);
+            v[u] = *reinterpret_cast<const f32x4*>(p.zpart + ((long)min(h0 + u, p.nH - 1) * p.Bsz + t0 + tok) * p.RT2 + k);
 #pragma unroll
           for (int u = 0; u < U; ++u)
             if (h0 + u < p.nH) sum += v[u];
@@ -874,19 +886,20 @@ __global__ __launch_bounds__(256) void decode_out_kernel(DecodeArgs p) {
   }
   __syncthreads();
 
+  const T* zrow = Zl + (lr % kSeqGroup) * RE + 16 * h;            // columns from nt on are computed and dropped
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
   for (int kb = 0; kb < PRE; ++kb)
-    if (kb < KB) mma32(acc, uf[kb], load_frag<T>(Zl + lr * RE + kb * 32 + 16 * h));
+    if (kb < KB) mma32(acc, uf[kb], load_frag<T>(zrow + kb * 32));
   for (int kb = PRE; kb < KB; ++kb) {
     const Frag<T> u = row_ok ? load_frag<T>(urow + kb * 32) : zero_frag<T>();
-    mma32(acc, u, load_frag<T>(Zl + lr * RE + kb * 32 + 16 * h));
+    mma32(acc, u, load_frag<T>(zrow + kb * 32));
   }
   // lane = sequence, rows = output channels 8q+4h+r of this wave's block
-  if (lr < p.Bsz) {
-    T* yrow = static_cast<T*>(p.Y) + (long)lr * p.d_model + blockIdx.x * 128 + wave * 32 + 4 * h;
+  if (lr < nt) {
+    T* yrow = static_cast<T*>(p.Y) + (long)(t0 + lr) * p.d_model + blockIdx.x * 128 + wave * 32 + 4 * h;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (blockIdx.x * 128 + wave * 32 + 8 * q + 4 * h < p.d_model)
@@ -897,13 +910,13 @@ __global__ __launch_bounds__(256) void decode_out_kernel(DecodeArgs p) {
 // ---------------------------------------------------------------------------------------
 template <typename T, int D>
 static hipError_t qhat_one(const DecodeArgs& a, const GemmArgs& proj, hipStream_t s) {
-  const size_t smem = 32ul * (a.R2 + 16 / sizeof(T)) * sizeof(T);
+  const size_t smem = (size_t)kSeqGroup * (a.R2 + 16 / sizeof(T)) * sizeof(T);
   auto kern = decode_qhat_kernel<T, D>;
   static LdsOnce lds_once;                                       // one per kernel instantiation
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
   // behind the heads' workgroups: one per 32-column block of the projection's key (and value) part
   const int kv_blocks = proj.ksplit > 1 ? (proj.shared_kv ? 1 : 2) * proj.D / 32 : 0;
-  hipLaunchKernelGGL(kern, dim3(a.HB * 32 + kv_blocks), dim3(256), smem, s, a, proj);
+  hipLaunchKernelGGL(kern, dim3(a.HB * 32 + kv_blocks, seq_groups(a)), dim3(256), smem, s, a, proj);
   return hipGetLastError();
 }
 hipError_t launch_decode_qhat(int dtype, const DecodeArgs& a, const GemmArgs& proj, hipStream_t s) {
@@ -993,9 +1006,9 @@ hipError_t launch_decode_attn(int dtype, const DecodeArgs& a, hipStream_t s, hip
 template <typename T>
 static hipError_t merge_heads_dispatch(const DecodeArgs& a, hipStream_t s) {
   switch (a.D) {
-    case 32: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 32>), dim3(a.nH), dim3(256), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 64>), dim3(a.nH), dim3(256), 0, s, a); break;
-    case 128: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 128>), dim3(a.nH), dim3(256), 0, s, a); break;
+    case 32: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 32>), dim3(a.nH, seq_groups(a)), dim3(256), 0, s, a); break;
+    case 64: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 64>), dim3(a.nH, seq_groups(a)), dim3(256), 0, s, a); break;
+    case 128: hipLaunchKernelGGL((decode_merge_heads_kernel<T, 128>), dim3(a.nH, seq_groups(a)), dim3(256), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1006,11 +1019,11 @@ hipError_t launch_decode_merge_heads(int dtype, const DecodeArgs& a, hipStream_t
 
 template <typename T>
 static hipError_t out_one(const DecodeArgs& a, hipStream_t s) {
-  const size_t smem = 32ul * (a.RT2 + 16 / sizeof(T)) * sizeof(T);
+  const size_t smem = (size_t)kSeqGroup * (a.RT2 + 16 / sizeof(T)) * sizeof(T);
   auto kern = decode_out_kernel<T>;
   static LdsOnce lds_once;                                       // one per kernel instantiation
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, dim3((a.d_model + 127) / 128), dim3(256), smem, s, a);
+  hipLaunchKernelGGL(kern, dim3((a.d_model + 127) / 128, seq_groups(a)), dim3(256), smem, s, a);
   return hipGetLastError();
 }
 hipError_t launch_decode_out(int dtype, const DecodeArgs& a, hipStream_t s) {

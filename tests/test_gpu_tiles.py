@@ -1,9 +1,12 @@
 """Sizes at which the kernels' tilings change: every tile of a dispatch rule, with remainders in the tokens, the
 contraction and the heads, against the CPU oracle.  Bars as in test_gpu_parity.py (relative L2 at most 1e-5 in fp32 and
 2e-2 in bf16 storage, every row within four times that)."""
+import numpy as np
 import pytest
 
+from oracle import tucker_oracle as orc
 from paper_2603_30033_amd import workloads as wl
+from paper_2603_30033_amd.device import Layer, to_device, to_host
 from tests.test_gpu_backward import run_case
 from tests.test_gpu_parity import check, oracle_forward, run_forward
 
@@ -49,3 +52,20 @@ def test_weight_gradient_tiles(dtype, B, N, d, heads, r2, r3):
 def test_attention_workgroups(dtype, B, N, heads, r3):
     run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
                        dtype=dtype, seed=53))
+
+
+# sequences of a decode step in groups of eight: a full group, one sequence more, several groups with a partial one
+@pytest.mark.parametrize("B,dtype,r2,r3", [(8, "bf16", 64, 64), (9, "bf16", 160, 128), (31, "f32", 40, 32), (45, "bf16", 32, 48)])
+def test_decode_sequence_groups(B, dtype, r2, r3):
+    w = wl.scaled(wl.WORKLOADS["decode_32k"], B=B, kv_len=150, d_model=136, n_heads=5, d_head=32, r1=2, r2=r2, r3=r3,
+                  rt1=2, rt2=r2, rt3=r3, dtype=dtype, recipe="fan_in", seed=54)
+    inp = wl.make_inputs(w)
+    inp["kv_len"] = np.array([1 + (37 * b) % 150 for b in range(B)], dtype=np.int32)
+    with Layer(w, inp, max_positions=151) as layer:
+        y = layer.decode(to_device(inp["X"][:, 0], dtype), to_device(inp["Kcache"], dtype), to_device(inp["Vcache"], dtype),
+                         inp["kv_len"])
+        y = to_host(y)
+    ref = orc.decode_step(inp["X"][:, 0], inp["Kcache"], inp["Vcache"], inp["kv_len"], wl.weights_of(inp), w.d_head,
+                          w.rope_base)[0]
+    for b in range(B):
+        assert orc.relative_l2(y[b], ref[b]) <= 4 * {"f32": 1e-5, "bf16": 2e-2}[dtype], b
