@@ -242,8 +242,12 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
 // relative test, which keeps the small rows accurate relative to their own size).  Rows whose squared
 // norm is at most `tiny` are numerically zero and are left alone.  Rows >= m of the last block
 // read as zero and are never written.  `rotations` counts the rotations applied.
-template <int NW>   // waves per workgroup: they share the columns in steps 1 and 3; the first four run step 2
-__global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m, int len, int step, double tol, double tiny, int* rotations) {
+// One workgroup holds all rows of a matrix of at most 16 (m <= 16, step 0): with LOOP it goes on until a sweep finds
+// nothing to rotate, and `rotations` receives the number of sweeps, 0 if `max_sweeps` were not enough; tol and tiny are
+// then worked out from the rows themselves.
+template <int NW, bool LOOP>   // NW waves per workgroup: they share the columns in steps 1 and 3; the first four run step 2
+__global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m, int len, int step, double tol, double tiny,
+                                                               int* rotations, int max_sweeps) {
   __shared__ double part[NW][16][17];                   // per-wave partial Gram matrices
   __shared__ double S[2][16][17];                       // double-buffered Gram matrix
   __shared__ double V[2][16][17];                       // accumulated rotations
@@ -258,6 +262,11 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m,
   const int lr = lane & 15, lq = lane >> 4;
   auto row_of = [&](int r) { return (r < 8 ? P * 8 : Q * 8 - 8) + r; };
   const int chunks = (len + 15) / 16;
+  for (int sweep = 0;; ++sweep) {
+  if (LOOP && sweep == max_sweeps) {
+    if (tid == 0) *rotations = 0;
+    return;
+  }
 
   // 1. Gram matrix: lane (lr, lq) of a wave loads columns c0 + 4 lq .. + 3 of row lr of a 16-column chunk
   {
@@ -300,6 +309,11 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m,
     V[0][ti][tj] = ti == tj ? 1.0 : 0.0;
   }
   __syncthreads();
+  if (LOOP && sweep == 0) {
+    double fro2 = 0.0;
+    for (int i = 0; i < 16; ++i) fro2 += S[0][i][i];
+    tiny = 1e-28 * m * fro2;
+  }
 
   // 2. one sweep over the 120 pairs of the 16 rows: 15 rounds of 8 disjoint rotations.  Eight threads work
   // out the rotations of a round (new_x = co[x] old_x + si[x] old_partner), then the 256 solver threads
@@ -335,8 +349,11 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m,
     __syncthreads();
     cur ^= 1;
   }
-  if (n_rot == 0) return;                               // uniform: read after the barrier
-  if (tid == 0) atomicAdd(rotations, n_rot);
+  if (n_rot == 0) {                                     // uniform: read after the barrier
+    if (LOOP && tid == 0) *rotations = sweep + 1;
+    return;
+  }
+  if (!LOOP && tid == 0) atomicAdd(rotations, n_rot);
 
   // 3. rows <- V^T R, 16 columns at a time: A[r][k] = V[k][r], B[k][n] = R[k][c0 + n]
   double va[4];
@@ -358,6 +375,10 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m,
       const int grow = row_of(lq + 4 * i);
       if (grow < m && c < len) G[(long)grow * len + c] = acc[i];
     }
+  }
+  if (!LOOP) return;
+  __threadfence_block();
+  __syncthreads();                                      // the rows are whole; n_rot has been read
   }
 }
 
@@ -438,6 +459,48 @@ struct JacobiStats {
   double bytes = 0.0;
 };
 
+// The second half of an iteration: rows of G ordered by norm, the r longest -> U64 / U; synchronises the stream.
+// (Rotations keep the sum of the squared norms, so the threshold is the one of the iteration.)
+template <typename T>
+int order_and_extract(hipStream_t s, const double* G, int m, int r, double* norms2, int* idx, double* U64, T* U, double* sv) {
+  std::vector<double> h(m);
+  hipLaunchKernelGGL(row_norms_kernel, dim3(m), dim3(256), 0, s, G, m, norms2);
+  CK(hipGetLastError());
+  CK(hipMemcpyAsync(h.data(), norms2, sizeof(double) * m, hipMemcpyDeviceToHost, s));
+  CK(hipStreamSynchronize(s));
+  const double tiny = 1e-28 * m * std::accumulate(h.begin(), h.end(), 0.0);
+  std::vector<int> order(m);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return h[x] > h[y]; });
+  if (sv)
+    for (int k = 0; k < m; ++k) sv[k] = std::sqrt(std::sqrt(h[order[k]]));   // row norm = eigenvalue = sigma^2
+  if (!(h[order[r - 1]] > 1e8 * tiny) || !(h[order[r - 1]] > 0.0)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
+  CK(hipMemcpyAsync(idx, order.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
+  CK(hipStreamSynchronize(s));                          // `order` is pageable host memory
+  hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, G, m, idx, norms2, r, U64, U);
+  CK(hipGetLastError());
+  return TUCKER_ATTN_OK;
+}
+
+// The head mode (m = heads) where one workgroup holds the matrix: enqueued without a wait, finished behind the d x d
+// problems.  counter receives the sweeps, 0 without convergence.
+constexpr int kSmallJacobi = 16;
+hipError_t enqueue_small_jacobi(hipStream_t s, double* G, int m, int* counter) {
+  const double tol = std::max(2e-15, std::sqrt((double)m) * 2.3e-16);
+  hipLaunchKernelGGL((jacobi_block_kernel<4, true>), dim3(1), dim3(256), 0, s, G, m, m, 0, tol, 0.0, counter, 60);
+  return hipGetLastError();
+}
+template <typename T>
+int finish_small_jacobi(hipStream_t s, const double* G, int m, int r, double* norms2, int* idx, const int* counter, double* U64,
+                        T* U, double* sv, JacobiStats* stats) {
+  int sweeps = 0;
+  CK(hipMemcpyAsync(&sweeps, counter, sizeof(int), hipMemcpyDeviceToHost, s));
+  CK(hipStreamSynchronize(s));
+  if (stats) stats->sweeps += m > 1 ? sweeps : 0;
+  if (sweeps == 0) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
+  return order_and_extract<T>(s, G, m, r, norms2, idx, U64, U, sv);
+}
+
 template <typename T>
 int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2, int* idx, int* counter,
                          double* U64, T* U, double* sv, JacobiStats* stats) {
@@ -475,8 +538,8 @@ int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2,
     }
     CK(hipMemsetAsync(counter, 0, sizeof(int), s));
     for (int step = 0; step < n_steps; ++step)
-      hipLaunchKernelGGL((jacobi_block_kernel<kJacobiWaves>), dim3(nbp / 2), dim3(64 * kJacobiWaves), 0, s, G, m, m, step, tol,
-                         tiny, counter);
+      hipLaunchKernelGGL((jacobi_block_kernel<kJacobiWaves, false>), dim3(nbp / 2), dim3(64 * kJacobiWaves), 0, s, G, m, m, step,
+                         tol, tiny, counter, 1);
     CK(hipGetLastError());
     CK(hipMemcpyAsync(&rotated, counter, sizeof(int), hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
@@ -490,21 +553,7 @@ int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2,
     stats->ms += ms;
   }
   if (rotated != 0) return TUCKER_ATTN_UNSUPPORTED_SHAPE;   // no convergence within the sweep limit
-  hipLaunchKernelGGL(row_norms_kernel, dim3(m), dim3(256), 0, s, G, m, norms2);
-  CK(hipGetLastError());
-  CK(hipMemcpyAsync(h.data(), norms2, sizeof(double) * m, hipMemcpyDeviceToHost, s));
-  CK(hipStreamSynchronize(s));
-  std::vector<int> order(m);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return h[x] > h[y]; });
-  if (sv)
-    for (int k = 0; k < m; ++k) sv[k] = std::sqrt(std::sqrt(h[order[k]]));   // row norm = eigenvalue = sigma^2
-  if (!(h[order[r - 1]] > 1e8 * tiny) || !(h[order[r - 1]] > 0.0)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
-  CK(hipMemcpyAsync(idx, order.data(), sizeof(int) * r, hipMemcpyHostToDevice, s));
-  CK(hipStreamSynchronize(s));                          // `order` is pageable host memory
-  hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, G, m, idx, norms2, r, U64, U);
-  CK(hipGetLastError());
-  return TUCKER_ATTN_OK;
+  return order_and_extract<T>(s, G, m, r, norms2, idx, U64, U, sv);
 }
 
 // Polish of nearly orthonormal rows, S = Z Z^T: S <- 1.5 I - 0.5 S in place, err[blockIdx.x] = largest |S - I| of a row
@@ -531,10 +580,11 @@ __global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, do
 }
 
 struct HosvdWs {
-  double *A, *B, *T, *GA, *GB, *SA, *SB, *M1, *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
+  double *A, *B, *T, *GA, *GB, *SA, *SB, *M1[2], *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
   double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~
-  double *Z[4], *work[4], *host_side[4];                // eigenvector rows; scratch; value | resid | err, fetched together
-  double *S, *Z2;
+  double *Z[4], *Z2[4], *work[4];                       // eigenvector rows before and behind the polish; scratch
+  double* report;                                       // value | resid | err | diagonal | subdiagonal of each problem
+  double* S;
   int *idx, *counter;
   size_t bytes;
 };
@@ -556,8 +606,8 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   w.GB = (double*)take(n * n, 8);
   w.SA = (double*)take(n * dH, 8);
   w.SB = (double*)take(n * dH, 8);
-  w.M1 = (double*)take((size_t)nH * nH, 8);
   for (int t = 0; t < 2; ++t) {
+    w.M1[t] = (double*)take((size_t)nH * nH, 8);
     w.U1[t] = (double*)take((size_t)nH * nH, 8);
     w.U2[t] = (double*)take(D * rmax, 8);
     w.U3[t] = (double*)take(D * rmax, 8);
@@ -565,11 +615,11 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   for (int e = 0; e < 4; ++e) {
     w.M[e] = (double*)take(D * D, 8);
     w.Z[e] = (double*)take(D * rmax, 8);
+    w.Z2[e] = (double*)take(D * rmax, 8);
     w.work[e] = (double*)take(eigen_work_elems(d), 8);
-    w.host_side[e] = (double*)take(3 * D, 8);
   }
+  w.report = (double*)take(4 * 5 * D, 8);
   w.S = (double*)take(rmax * rmax, 8);
-  w.Z2 = (double*)take(D * rmax, 8);
   w.P = (double*)take(rmax * n, 8);
   w.Q = (double*)take(rmax * n, 8);
   w.H = (double*)take((size_t)nH * rmax * rmax, 8);
@@ -581,16 +631,19 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   return w;
 }
 
-// Gram matrices of the mode unfoldings of one tensor (A_i B_i^T)_i, A and B [d, n] fp64 in the workspace
+// Gram matrices of the mode unfoldings of one tensor (A_i B_i^T)_i, A and B [d, n] fp64 in the workspace.
+// Per-head dH x dH Gram matrices SA_i = A_i^T A_i, SB_i = B_i^T B_i, which modes 2 and 3 start from:
 hipError_t head_products(hipStream_t s, const HosvdWs& w, int d, int nH, int dH) {
   const long n = (long)nH * dH;
-  // per-head dH x dH Gram matrices  SA_i = A_i^T A_i, SB_i = B_i^T B_i
   if (hipError_t e = dgemm(s, nH, dH, dH, d, w.A, 1, n, dH, w.A, n, 1, dH, w.SA, dH, 1, (long)dH * dH)) return e;
-  if (hipError_t e = dgemm(s, nH, dH, dH, d, w.B, 1, n, dH, w.B, n, 1, dH, w.SB, dH, 1, (long)dH * dH)) return e;
-  // mode 1: <W_i, W_j> from the full Gram matrices of the factors
+  return dgemm(s, nH, dH, dH, d, w.B, 1, n, dH, w.B, n, 1, dH, w.SB, dH, 1, (long)dH * dH);
+}
+// mode 1: <W_i, W_j> from the full Gram matrices of the factors
+hipError_t head_mode_gram(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, double* M1) {
+  const long n = (long)nH * dH;
   if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.A, 1, n, 0, w.A, n, 1, 0, w.GA, n, 1, 0)) return e;
   if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.B, 1, n, 0, w.B, n, 1, 0, w.GB, n, 1, 0)) return e;
-  hipLaunchKernelGGL(head_gram_kernel, dim3(nH, nH), dim3(256), 0, s, w.GA, w.GB, w.M1, nH, dH);
+  hipLaunchKernelGGL(head_gram_kernel, dim3(nH, nH), dim3(256), 0, s, w.GA, w.GB, M1, nH, dH);
   return hipGetLastError();
 }
 hipError_t mode_gram(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, int mode, double* M) {
@@ -627,9 +680,12 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     b.G[j] = w.M[j];
     b.Z[j] = w.Z[j];
     b.work[j] = w.work[j];
-    b.value[j] = w.host_side[j];
-    b.resid[j] = w.host_side[j] + d;
+    b.value[j] = w.report + 5 * (size_t)d * j;
+    b.resid[j] = b.value[j] + d;
+    b.tri[j] = b.value[j] + 3 * (size_t)d;
   }
+  double *from[4], *to[4];                              // eigenvector rows, before and behind a polish
+  for (int j = 0; j < n_jobs; ++j) { from[j] = w.Z[j]; to[j] = w.Z2[j]; }
   struct Events {
     hipEvent_t e[2] = {nullptr, nullptr};
     ~Events() {
@@ -648,19 +704,14 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
   // which squares what is missing and moves no vector by more than its own uncertainty
   auto polish = [&](int j) -> hipError_t {
     const int r = b.r[j];
-    if (hipError_t e = dgemm(s, 1, r, r, d, w.Z[j], d, 1, 0, w.Z[j], 1, d, 0, w.S, r, 1, 0)) return e;
-    hipLaunchKernelGGL(newton_schulz_kernel, dim3(r), dim3(256), 0, s, w.S, r, w.host_side[j] + 2 * (size_t)d);
-    if (hipError_t e = dgemm(s, 1, r, d, r, w.S, r, 1, 0, w.Z[j], d, 1, 0, w.Z2, d, 1, 0)) return e;
-    return hipMemcpyAsync(w.Z[j], w.Z2, sizeof(double) * r * d, hipMemcpyDeviceToDevice, s);
+    if (hipError_t e = dgemm(s, 1, r, r, d, from[j], d, 1, 0, from[j], 1, d, 0, w.S, r, 1, 0)) return e;
+    hipLaunchKernelGGL(newton_schulz_kernel, dim3(r), dim3(256), 0, s, w.S, r, b.value[j] + 2 * (size_t)d);
+    std::swap(from[j], to[j]);
+    return dgemm(s, 1, r, d, r, w.S, r, 1, 0, to[j], d, 1, 0, from[j], d, 1, 0);
   };
-  std::vector<std::vector<double>> host(n_jobs), tri(n_jobs);
-  for (int j = 0; j < n_jobs; ++j) {
-    CK(polish(j));
-    host[j].resize(3 * (size_t)d);
-    tri[j].resize(2 * (size_t)d);
-    CK(hipMemcpyAsync(host[j].data(), w.host_side[j], sizeof(double) * 3 * d, hipMemcpyDeviceToHost, s));
-    CK(hipMemcpyAsync(tri[j].data(), eigen_diag(w.work[j], d), sizeof(double) * 2 * d, hipMemcpyDeviceToHost, s));
-  }
+  for (int j = 0; j < n_jobs; ++j) CK(polish(j));
+  std::vector<double> report(5 * (size_t)d * n_jobs);
+  CK(hipMemcpyAsync(report.data(), w.report, sizeof(double) * report.size(), hipMemcpyDeviceToHost, s));
   CK(hipStreamSynchronize(s));
   if (timed) {
     float ms = 0.f;
@@ -676,24 +727,25 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
   };
   for (int j = 0; j < n_jobs; ++j) {
     const int r = b.r[j];
-    double fro2 = 0.0, top = 0.0;
+    const double* rep = report.data() + 5 * (size_t)d * j;
+    double fro2 = 0.0;
     for (int k = 0; k < d; ++k) {
-      const double off = k + 1 < d ? tri[j][d + k] : 0.0;
-      fro2 += tri[j][k] * tri[j][k] + 2.0 * off * off;
+      const double on = rep[3 * (size_t)d + k], off = k + 1 < d ? rep[4 * (size_t)d + k] : 0.0;
+      fro2 += on * on + 2.0 * off * off;
     }
-    std::vector<double> value(host[j].begin(), host[j].begin() + b.n_values[j]);
+    std::vector<double> value(rep, rep + b.n_values[j]);
     std::sort(value.begin(), value.end(), [](double x, double y) { return x > y; });
-    top = std::sqrt(fro2);
+    const double top = std::sqrt(fro2);
     // the rank test of the Jacobi path, on the squared eigenvalue
     if (!(value[r - 1] > 0.0) || !(value[r - 1] * value[r - 1] > 1e8 * 1e-28 * d * fro2)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
-    double missing = worst_of(host[j].data() + 2 * (size_t)d, r);
-    const double resid = worst_of(host[j].data() + d, r);
+    double missing = worst_of(rep + 2 * (size_t)d, r);
+    const double resid = worst_of(rep + d, r);
     if (!(resid <= 1e-13 * std::sqrt((double)d) * top) || !(missing <= 1e-3 / r)) continue;
     for (; missing > 1e-8 / r; missing = r * missing * missing) CK(polish(j));   // rare: very close eigenvalues
     if (jobs[j].sv)
       for (int k = 0; k < d; ++k) jobs[j].sv[k] = std::sqrt(std::max(value[k], 0.0));
-    hipLaunchKernelGGL(row_norms_kernel, dim3(r), dim3(256), 0, s, w.Z[j], d, w.norms2);
-    hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, w.Z[j], d, nullptr, w.norms2, r, jobs[j].U64, jobs[j].U);
+    hipLaunchKernelGGL(row_norms_kernel, dim3(r), dim3(256), 0, s, from[j], d, w.norms2);
+    hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, from[j], d, nullptr, w.norms2, r, jobs[j].U64, jobs[j].U);
     CK(hipGetLastError());
     done[j] = true;
   }
@@ -796,13 +848,19 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
   for (int t = 0; t < 2; ++t) {
     CK(load(t));
     CK(head_products(s, w, d, nH, dH));
-    const int st = leading_eigenvectors<T>(s, w.M1, nH, t ? rt1 : r1, w.norms2, w.idx, w.counter, w.U1[t], (T*)(t ? o.Ut1 : o.U1),
-                                           sv ? sv + t * (nH + 2l * d) : nullptr, info ? &stats[3 * t] : nullptr);
-    if (st != TUCKER_ATTN_OK) return st;
+    CK(head_mode_gram(s, w, d, nH, dH, w.M1[t]));
+    if (nH <= kSmallJacobi) {
+      CK(enqueue_small_jacobi(s, w.M1[t], nH, w.counter + 1 + t));
+    } else {
+      const int st = leading_eigenvectors<T>(s, w.M1[t], nH, t ? rt1 : r1, w.norms2, w.idx, w.counter, w.U1[t],
+                                             (T*)(t ? o.Ut1 : o.U1), sv ? sv + t * (nH + 2l * d) : nullptr,
+                                             info ? &stats[3 * t] : nullptr);
+      if (st != TUCKER_ATTN_OK) return st;
+    }
     for (int j = 0; j < n_jobs; ++j)
       if (jobs[j].tensor == t) CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
   }
-  // The reduction to tridiagonal form takes the sizes whose vectors fit the LDS (whole conversions: d = 768 7.6 ms
+  // The reduction to tridiagonal form takes the sizes whose vectors fit the LDS (whole conversions: d = 768 6.7 ms
   // against 206 ms by the Jacobi iteration, d = 4096 0.36 s against 4.3 s).  A problem that it cannot certify (on a
   // Gram matrix formed anew) and every other size go through the Jacobi iteration.
   bool done[4] = {false, false, false, false};
@@ -820,6 +878,12 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
     }
     const int st = leading_eigenvectors<T>(s, w.M[j], d, jobs[j].r, w.norms2, w.idx, w.counter, jobs[j].U64, jobs[j].U,
                                            jobs[j].sv, jobs[j].stats);
+    if (st != TUCKER_ATTN_OK) return st;
+  }
+  for (int t = 0; t < 2 && nH <= kSmallJacobi; ++t) {
+    const int st = finish_small_jacobi<T>(s, w.M1[t], nH, t ? rt1 : r1, w.norms2, w.idx, w.counter + 1 + t, w.U1[t],
+                                          (T*)(t ? o.Ut1 : o.U1), sv ? sv + t * (nH + 2l * d) : nullptr,
+                                          info ? &stats[3 * t] : nullptr);
     if (st != TUCKER_ATTN_OK) return st;
   }
   for (int t = 1; t >= 0; --t) {

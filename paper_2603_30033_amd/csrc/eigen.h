@@ -14,16 +14,14 @@ struct EigenBatch {
   double* G[kEigenBatch];                               // [m, m], full storage; destroyed (holds the reflectors)
   double* Z[kEigenBatch];                               // [r, m] eigenvectors, largest eigenvalue first
   double* work[kEigenBatch];                            // eigen_work_elems(m) doubles each
+  double* tri[kEigenBatch];                             // [2, m] diagonal and subdiagonal of the tridiagonal matrix
   double* value[kEigenBatch];                           // [m] eigenvalues, largest first (the first n_values written)
   double* resid[kEigenBatch];                           // [m] residual of each vector in the tridiagonal matrix
   int n_values[kEigenBatch];                            // eigenvalues wanted of each, r .. m
 };
-inline size_t eigen_work_elems(int m) { return 8ul * m; }
-// diagonal and subdiagonal of the tridiagonal matrix inside `work`
-inline double* eigen_diag(double* work, int) { return work; }
-inline double* eigen_offdiag(double* work, int m) { return work + m; }
+inline size_t eigen_work_elems(int m) { return 5ul * m; }
 
-// Enqueues the reduction to tridiagonal form; G and work are written.
+// Enqueues the reduction to tridiagonal form; G, work and tri are written.
 hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s);
 // Enqueues eigenvalues and eigenvectors of the tridiagonal matrices, vectors carried back to the basis of G.
 // The vectors are unit rows; rows of close eigenvalues are orthogonal only up to (rounding / gap).

@@ -14,7 +14,7 @@ namespace ta {
 namespace {
 
 // layout of a problem's work array, in vectors of m doubles
-constexpr int kDiag = 0, kOff = 1, kTau = 2, kV = 3, kY = 5;   // kV, kY: two vectors each, used in turn
+constexpr int kTau = 0, kV = 1, kY = 3;                 // kV, kY: two vectors each, used in turn
 
 // x of the lane that the DPP control CTRL names
 template <int CTRL> __device__ __forceinline__ double dpp(double x) {
@@ -56,13 +56,14 @@ template <int NW> __device__ __forceinline__ double block_sum(double x, double* 
 // Step k of the reduction.  With v = the reflector of step k-1 (v_k = 1, zero before k), y = A v and
 // w = tau (y - tau/2 (v.y) v), the remaining matrix becomes A - v w^T - w v^T; its row k gives the diagonal and
 // subdiagonal entry k and the next reflector u, and the launch leaves A u for step k+1.
-// Workgroup = 16 waves, RW rows each (fixed rows per workgroup; grid.x shrinks with the matrix).  Row k is read by
-// every workgroup and written by none; row k-1, read by none any more, receives v for the way back.
+// Workgroup = 16 waves, RW rows each.  The grid stays the same for all steps; workgroups above the
+// remaining matrix return, the last one stores what all work out.  Row k is read by every workgroup and
+// written by none; row k-1, read by none any more, receives v for the way back.
 // NC > 0: a row fits NC chunks of 64 lanes and is loaded before the reflector is known.
-// Small matrices are bound by the latency of a launch, its loads and its two workgroup sums (four of 768: 6.5 us a
-// step on average, 0.24 of the memory rate), large ones by memory (four of 4096: 78 us a step, 4.6 TB/s).
+// Small matrices are bound by the latency of a launch, its loads and its two workgroup sums (four of 768: 9.6 us for
+// the first steps, 6.3 for the last before the tail), large ones by memory (four of 4096: 78 us a step, 4.6 TB/s).
 template <int NC, int RW>
-__global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k, int first_wg) {
+__global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ double red[2][16];
   const int m = b.m, p = blockIdx.y;
@@ -72,8 +73,10 @@ __global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k,
   double* w = v + m;
   double* u = w + m;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = (first_wg + blockIdx.x) * 16 * RW + wave;    // this wave's rows: row0 + 16 t
+  const int row0 = blockIdx.x * 16 * RW + wave;                 // this wave's rows: row0 + 16 t
   const int c0 = k + 1;                                         // first column that is still needed
+  const bool writer = blockIdx.x == gridDim.x - 1;
+  if (!writer && (int)(blockIdx.x + 1) * 16 * RW <= c0) return;
 
   double x[NC > 0 ? NC : 1];
   if constexpr (NC > 0) {
@@ -106,14 +109,10 @@ __global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k,
     w[i] = wi;
     u[i] = c;
     if (i > c0) tail += c * c;
-    if (i == k && blockIdx.x == 0) work[(long)kDiag * m + k] = c;
+    if (i == k && writer) b.tri[p][k] = c;
   }
   tail = block_sum<16>(tail, red[1]);
-  if (c0 >= m) {                                                // the last diagonal entry
-    if (blockIdx.x == 0 && k > 0)
-      for (int i = k + tid; i < m; i += 1024) A[(long)(k - 1) * m + i] = v[i];
-    return;
-  }
+  if (c0 >= m) return;                                          // the last diagonal entry (v is the unit vector by then)
   const double x0 = u[c0];
   double beta = x0, tau_k = 0.0, scale = 0.0;
   if (tail > 0.0) {
@@ -124,9 +123,9 @@ __global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k,
   __syncthreads();                                              // x0 has been read
   for (int i = c0 + tid; i < m; i += 1024) u[i] = i == c0 ? 1.0 : u[i] * scale;
   __syncthreads();
-  if (blockIdx.x == 0) {
+  if (writer) {
     if (tid == 0) {
-      work[(long)kOff * m + k] = beta;
+      b.tri[p][m + k] = beta;
       work[(long)kTau * m + k] = tau_k;
     }
     double* vn = work + (long)(kV + (k & 1)) * m;
@@ -208,8 +207,8 @@ constexpr double kPivot = 1e-290;                       // smallest pivot magnit
 __global__ __launch_bounds__(256) void tridiag_values_kernel(EigenBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int m = b.m, p = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const double* d = b.work[p] + (long)kDiag * m;
-  const double* e = b.work[p] + (long)kOff * m;
+  const double* d = b.tri[p];
+  const double* e = b.tri[p] + m;
   double* pd = reinterpret_cast<double*>(smem_raw);     // (d_i, e_{i-1}^2) pairs
   double e2max = 0.0;
   for (int i = threadIdx.x; i < m; i += 256) {
@@ -264,8 +263,8 @@ __global__ __launch_bounds__(64) void tridiag_vector_kernel(EigenBatch b) {
   const double lam = b.value[p][idx];
   double e2max = 0.0;
   for (int i = lane; i < m; i += 64) {
-    d[i] = b.work[p][(long)kDiag * m + i] - lam;
-    const double o = i + 1 < m ? b.work[p][(long)kOff * m + i] : 0.0;
+    d[i] = b.tri[p][i] - lam;
+    const double o = i + 1 < m ? b.tri[p][m + i] : 0.0;
     e[i] = o;
     e2max = fmax(e2max, o * o);
   }
@@ -370,17 +369,115 @@ __global__ __launch_bounds__(64 * NW) void apply_reflectors_kernel(EigenBatch b)
     if (tid + 64 * NW * c < m) zr[tid + 64 * NW * c] = z[c];
 }
 
-template <int NC, int RW> hipError_t tridiag_steps(const EigenBatch& b, hipStream_t s) {
+// The last kTail steps (k0 = m - kTail, or all of them with k0 = 0 in a smaller matrix) in one launch, one workgroup per
+// problem: wave w holds the rows k0 + w, k0 + w + 16, ... in registers, and A u is summed over rows (A is symmetric), so
+// that no sum runs across lanes.  Otherwise a step is the one of tridiag_step_kernel.
+// The last 192 steps of four problems: 0.58 ms; as launches of their own 4.8 us each plus the gaps, 1.0 ms.
+constexpr int kTail = 192;                              // 72 of a thread's 128 registers
+__global__ __launch_bounds__(1024) void tridiag_tail_kernel(EigenBatch b, int k0) {
+  constexpr int R = kTail / 16, C = kTail / 64;                 // rows per wave, chunks of 64 columns per row
+  __shared__ double red[2][16], v[kTail], w[kTail], u[kTail], part[16][kTail];
+  const int m = b.m, p = blockIdx.x, n = m - k0;                // all indices below count from k0
+  double* A = b.G[p] + (long)k0 * m + k0;
+  double* work = b.work[p];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double x[R][C];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = wave + 16 * r, j = lane + 64 * c;
+      x[r][c] = i < n && j < n ? A[(long)i * m + j] : 0.0;
+    }
+  double tau = 0.0;
+  if (tid < kTail) {                                            // the step before this launch
+    const bool live = k0 > 0 && tid < n;
+    v[tid] = live ? work[(long)(kV + ((k0 + 1) & 1)) * m + k0 + tid] : 0.0;
+    w[tid] = live ? work[(long)(kY + ((k0 + 1) & 1)) * m + k0 + tid] : 0.0;
+    u[tid] = 0.0;
+  }
+  if (k0 > 0) tau = work[(long)kTau * m + k0 - 1];
+  if (k0 > 0 && tid < n) A[(long)tid - m] = work[(long)(kV + ((k0 + 1) & 1)) * m + k0 + tid];   // row k0 - 1 keeps v
+  __syncthreads();
+  for (int k = 0; k < n; ++k) {
+    const int c0 = k + 1;
+    // row k of the matrix before the update, from its owner
+    if (wave == (k & 15)) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (r == (k >> 4))
+#pragma unroll
+          for (int c = 0; c < C; ++c) part[0][lane + 64 * c] = x[r][c];
+    }
+    const bool mine = tid >= k && tid < n;                      // the vector element of this thread (tid < kTail)
+    const double vi = mine ? v[tid] : 0.0, yi = mine ? w[tid] : 0.0, yk = w[k];
+    const double half = 0.5 * tau * block_sum<16>(vi * yi, red[0]);
+    const double wk = tau * (yk - half), wi = tau * (yi - half * vi);
+    const double cur = mine ? part[0][tid] - vi * wk - wi : 0.0;   // v_k = 1
+    const double tail = block_sum<16>(mine && tid > c0 ? cur * cur : 0.0, red[1]);
+    if (mine) u[tid] = cur;
+    if (tid < kTail) w[tid] = mine ? wi : 0.0;
+    if (tid == k) b.tri[p][k0 + k] = cur;
+    if (c0 >= n) break;
+    __syncthreads();
+    const double x0 = u[c0];
+    double beta = x0, tau_k = 0.0, scale = 0.0;
+    if (tail > 0.0) {
+      beta = -copysign(sqrt(x0 * x0 + tail), x0);
+      tau_k = (beta - x0) / beta;
+      scale = 1.0 / (x0 - beta);
+    }
+    __syncthreads();                                            // x0 has been read
+    const double un = mine && tid > k ? (tid == c0 ? 1.0 : cur * scale) : 0.0;
+    if (tid < kTail) u[tid] = un;
+    if (tid == 0) {
+      b.tri[p][m + k0 + k] = beta;
+      work[(long)kTau * m + k0 + k] = tau_k;
+    }
+    if (mine && tid > k) A[(long)k * m + tid] = un;             // row k keeps its reflector for the way back
+    __syncthreads();
+    // update and product
+    double sum[C], vj[C], wj[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      sum[c] = 0.0;
+      vj[c] = v[lane + 64 * c];
+      wj[c] = w[lane + 64 * c];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = wave + 16 * r;
+      if (i < c0 || i >= n) continue;                           // (the same for the whole wave)
+      const double vr = v[i], wr = w[i], ur = u[i];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        x[r][c] = x[r][c] - vr * wj[c] - wr * vj[c];
+        sum[c] += ur * x[r][c];
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) part[wave][lane + 64 * c] = sum[c];
+    __syncthreads();
+    if (tid < kTail) {
+      double y = 0.0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) y += part[q][tid];
+      v[tid] = un;
+      w[tid] = y;
+    }
+    tau = tau_k;
+    __syncthreads();
+  }
+}
+
+template <int NC, int RW> hipError_t tridiag_steps(const EigenBatch& b, int steps, hipStream_t s) {
   const size_t lds = 3ul * b.m * sizeof(double);
   auto kern = tridiag_step_kernel<NC, RW>;
   static LdsOnce lds_once;
   if (hipError_t e = allow_dynamic_lds(lds_once, kern, 3ul * kEigenMaxSize * sizeof(double)); e != hipSuccess) return e;
   constexpr int kRows = 16 * RW;
   const int wgs = (b.m + kRows - 1) / kRows;
-  for (int k = 0; k < b.m; ++k) {
-    const int first = k + 1 < b.m ? (k + 1) / kRows : wgs - 1;
-    hipLaunchKernelGGL(kern, dim3(wgs - first, b.n), dim3(1024), lds, s, b, k, first);
-  }
+  for (int k = 0; k < steps; ++k) hipLaunchKernelGGL(kern, dim3(wgs, b.n), dim3(1024), lds, s, b, k);
   return hipGetLastError();
 }
 
@@ -392,9 +489,12 @@ template <int NW, int NC, int PF> void apply_reflectors(const EigenBatch& b, int
 
 hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s) {
   if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
-  if (b.m <= 512) return tridiag_steps<8, 1>(b, s);
-  if (b.m <= 1024) return tridiag_steps<16, 1>(b, s);
-  return tridiag_steps<0, 4>(b, s);
+  const int steps = b.m > kTail ? b.m - kTail : 0;
+  hipError_t e = hipSuccess;
+  if (steps > 0) e = b.m <= 512 ? tridiag_steps<8, 1>(b, steps, s) : (b.m <= 1024 ? tridiag_steps<16, 1>(b, steps, s) : tridiag_steps<0, 4>(b, steps, s));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tridiag_tail_kernel, dim3(b.n), dim3(1024), 0, s, b, steps);
+  return hipGetLastError();
 }
 
 hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s) {
@@ -413,8 +513,8 @@ hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s) {
   hipLaunchKernelGGL(tridiag_vector_kernel, dim3(r, b.n), dim3(64), lt, s, b);
   static_assert(kEigenMaxSize <= 64 * 8 * 10, "a row fits the workgroup");
   if (b.m <= 256) apply_reflectors<1, 4, 8>(b, r, s);
-  else if (b.m <= 512) apply_reflectors<1, 8, 6>(b, r, s);
-  else if (b.m <= 1024) apply_reflectors<1, 16, 4>(b, r, s);
+  else if (b.m <= 512) apply_reflectors<4, 2, 8>(b, r, s);
+  else if (b.m <= 1024) apply_reflectors<4, 4, 4>(b, r, s);
   else if (b.m <= 2048) apply_reflectors<4, 8, 4>(b, r, s);
   else apply_reflectors<8, 10, 4>(b, r, s);                // 5120 elements
   return hipGetLastError();
