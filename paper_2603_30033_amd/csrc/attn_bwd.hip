@@ -179,11 +179,11 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
       for (int e = 0; e < 16; ++e) dsum += frag_elem(dof[cb], e) * frag_elem(of, e);   // the rounded dO that forms dP
     }
     const float delta = halves_sum(dsum);
-    const float lse = p.lse[((long)b * p.nH + head) * p.Npad + m];    // +inf for padding tokens
+    const float nlse = p.lse[((long)b * p.nH + head) * p.Npad + m];   // -inf for padding tokens
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { negl[e] = -lse; negd[e] = -delta; }
+    for (int e = 0; e < 16; ++e) { negl[e] = nlse; negd[e] = -delta; }
     if (head_ok) {
-      if (h == 0) p.delta[((long)b * p.nH + head) * p.Npad + m] = delta;
+      if (h == 0) p.delta[((long)b * p.nH + head) * p.Npad + m] = -delta;
       T* Qr = static_cast<T*>(p.Qr) + ((tok_base + m) * p.nH + head) * D + 16 * h;
       T* dOr = static_cast<T*>(p.dO) + ((tok_base + m) * p.nH + head) * D + 16 * h;
 #pragma unroll
@@ -254,7 +254,9 @@ template <typename T, int D, int TQ, int KB> struct DkvLds {
   static constexpr int kRow = D;                                // Q / dO rows, unpadded, chunks swizzled
   static constexpr int kRElems = TQ * kRow;
   static constexpr int kStageElems = 2 * kRElems;
-  static constexpr size_t kStageBytes = kStageElems * sizeof(T) + 2ul * TQ * sizeof(float);
+  // behind the rows: -log-sum-exp and -delta of the queries, 64 places each (a direct-to-LDS load fills 64)
+  static constexpr size_t kStageBytes = kStageElems * sizeof(T) + 2ul * 64 * sizeof(float);
+  static_assert(TQ <= 64, "one load per vector");
   // probabilities handed from the dV^T waves to the dK^T waves: [2][KB key blocks][TQ/32] fragment blocks
   static constexpr size_t kPBytes = 2ul * KB * (TQ / 32) * kFragBlockElems * sizeof(T);
   static constexpr size_t kBytes = kStages * kStageBytes + kPBytes;
@@ -276,11 +278,12 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
   constexpr int CE = 16 / sizeof(T);
   using L = DkvLds<T, D, TQ, KB>;
   constexpr int NS = L::kStages;
+  static_assert(sizeof(T) == 2 || QBN == 1, "one block of 32 queries in fp32");
   static_assert(L::kStageBytes % 16 == 0, "stages stay 16-byte aligned");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* pbuf = reinterpret_cast<T*>(smem_raw + NS * L::kStageBytes);
 
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int h = lane / 32, lr = lane % 32;
   const bool k_role = wave >= KB;                               // dK^T wave (else dV^T wave)
   const int kb = wave % KB;                                     // key block of this wave
@@ -317,17 +320,17 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
   // (with causal masking their ranges start at different blocks but all end at the last).
   auto q_of = [&](int it) { return (qb_first + n_qb - 1 - it % n_qb) * TQ; };
 
-  // The Q and dO rows of a pair go from global memory straight into LDS (see dma_piece in common.h),
-  // into the stage that the lagging dK^T waves have just left, one interval before the dV^T waves
-  // need them; only the two small per-query vectors pass through a register.  That register load is
-  // issued last and waited for before it is stored, and loads return in order, so the tiles of a
-  // pair have landed when its vectors are stored (and the barrier that follows publishes both).
+  // The Q and dO rows of a pair and its two per-query vectors go from global memory straight into LDS (see dma_piece in
+  // common.h), into the stage that the lagging dK^T waves have just left, one interval before the dV^T waves need
+  // them.  Nothing else of the loop is in flight in vector memory, and the interval waits for it only at its end: the
+  // compiler's own wait in front of a transposing read (every direct-to-LDS load has landed) would come in the
+  // middle, hence load_frags_tr_swz.  Two sequences of 4096 tokens, 32 heads, D = 128:
+  // 763 -> 716 us, and with the query blocks of a pair in step (below) 650 us; eight of 1024 tokens, 12 heads, D = 64: 66.1 ->
+  // 62.1 -> 58.5 us.
   constexpr int CPR = D / CE;                                    // chunks per row
   constexpr int PIECES = TQ * CPR / 64;                          // 1 KB pieces per tensor
-  constexpr int PF = 2;                                         // pairs in flight
-  float stat[PF];
-  auto g_load = [&](float& st_reg, int it_raw, int stage) {
-    const int it = min(it_raw, n_it - 1);                       // past the end: the last pair again, never read
+  constexpr int NW = NT / 64;
+  auto issue = [&](int it, int stage) {
     const int head = head0 + it / n_qb, q0 = q_of(it);
     const T* Qg = static_cast<const T*>(p.Qr) + ((tok_base + q0) * p.nH + head) * D;
     const T* Og = static_cast<const T*>(p.dO) + ((tok_base + q0) * p.nH + head) * D;
@@ -335,34 +338,34 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
     T* os = qs + L::kRElems;
     const long rs = (long)p.nH * D;
 #pragma unroll
-    for (int i = 0; i < (PIECES + 2 * KB - 1) / (2 * KB); ++i) {
-      const int q = i * 2 * KB + wave;
+    for (int i = 0; i < (PIECES + NW - 1) / NW; ++i) {
+      const int q = i * NW + wave;
       if (q < PIECES) {
         dma_piece<T, CPR>(qs, q, lane, [&](int row) { return Qg + row * rs; });
         dma_piece<T, CPR>(os, q, lane, [&](int row) { return Og + row * rs; });
       }
     }
-    // the first half of the threads fetch the log-sum-exp of the block's queries, the second half their delta (TQ
-    // of each are kept)
-    const long so = ((long)b * p.nH + head) * p.Npad + q0 + threadIdx.x % TQ;
-    st_reg = (threadIdx.x < NT / 2 ? p.lse : p.delta)[so];
+    if (wave < 2) {                                             // (lanes past TQ fetch the first ones again)
+      const float* src = (wave == 0 ? p.lse : p.delta) + ((long)b * p.nH + head) * p.Npad + q0 + lane % TQ;
+      float* st = reinterpret_cast<float*>(os + L::kRElems) + 64 * wave;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                       (__attribute__((address_space(3))) void*)st, 4, 0, 0);
+    }
   };
-  auto s_store = [&](float st_reg, int stage) {
-    float* st = reinterpret_cast<float*>(smem_raw + (size_t)stage * L::kStageBytes + L::kStageElems * sizeof(T));
-    // stored negated: a score block starts from -log-sum-exp, a dP block from -delta
-    if (threadIdx.x < TQ) st[threadIdx.x] = -st_reg;
-    else if (threadIdx.x >= NT / 2 && threadIdx.x < NT / 2 + TQ) st[TQ + threadIdx.x - NT / 2] = -st_reg;
+  auto meet = [&]() {                                           // loads landed, LDS reads and writes done, all waves here
+    wait_vm<0>();
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   };
 
-  g_load(stat[0], 0, 0);
-  g_load(stat[1], 1, 1);
-  s_store(stat[0], 0);
-  __syncthreads();
-  // one interval: the dV^T waves work on pair t (stage t % 3), the dK^T waves on pair t-1; then the
-  // vectors of pair t+1 are stored, and after the barrier pair t+2 is fetched into stage (t+2) % 3,
-  // which held pair t-1.
-  auto interval = [&](auto slot_c, int t) {
-    constexpr int S1 = (decltype(slot_c)::value + 1) % PF;      // slot of pair t + 1
+  issue(0, 0);
+  meet();
+  if (1 < n_it) issue(1, 1);
+  // one interval: the dV^T waves work on pair t (stage t % 3), the dK^T waves on pair t-1; behind the meeting pair t+2
+  // is fetched into stage (t+2) % 3, which held pair t-1.
+  const int n_int = n_it + 1;
+  for (int t = 0; t < n_int; ++t) {
     const int it = k_role ? t - 1 : t;                          // pair this wave works on in this interval
     if (it >= 0 && it < n_it) {
       const unsigned char* sb = smem_raw + (size_t)(it % NS) * L::kStageBytes;
@@ -370,61 +373,81 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
       const T* os = qs + L::kRElems;
       const float* stat = reinterpret_cast<const float*>(os + L::kRElems);
       const int q0 = q_of(it);
-#pragma unroll
-      for (int qb = 0; qb < QBN; ++qb) {
-        const int qfirst = q0 + 32 * qb;
-        // all 32 keys of the wave lie after all 32 queries of the block: nothing to do
-        if (p.causal && key0 > qfirst + 31) continue;
-        T* pblk = pbuf + (long)(((it & 1) * KB + kb) * QBN + qb) * kFragBlockElems;
-        // rows of the block start from -log-sum-exp (scores) or -delta (dP)
-        f32x16 a;
-        const float* st4 = stat + (k_role ? TQ : 0) + qb * 32 + 4 * h;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v4 = *reinterpret_cast<const f32x4*>(st4 + 8 * q);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) a[4 * q + e] = v4[e];
-        }
-        const T* rows = (k_role ? os : qs) + (qb * 32 + lr) * L::kRow;
+      // all 32 keys of the wave lie after all queries of the pair: nothing to do
+      if (!p.causal || key0 <= q0 + TQ - 1) {
         constexpr int FC = 16 / CE;                             // chunks per fragment half
+        constexpr int TF = CB < 2 ? 1 : 2;
+        // The query blocks of the pair go through every phase together: their products are independent chains, and the
+        // first transposed operands are read while those of the scores are still in the matrix pipe.
+        f32x16 a[QBN];
+        Frag<T> rf[QBN][CB];
+#pragma unroll
+        for (int qb = 0; qb < QBN; ++qb) {
+          // rows of a block start from -log-sum-exp (scores) or -delta (dP)
+          const float* st4 = stat + (k_role ? 64 : 0) + qb * 32 + 4 * h;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v4 = *reinterpret_cast<const f32x4*>(st4 + 8 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[qb][4 * q + e] = v4[e];
+          }
+        }
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
-          mma32(a, load_frag_swz<T>(rows, cb * 2 * FC + h * FC, swz_x<CPR>(qb * 32 + lr)), kop[cb]);
-        Frag<T> bf;                                             // P (dV^T wave) or dS (dK^T wave), k = queries
-        if (!k_role) {
-          if (key0 + 31 >= p.N || (p.causal && key0 + 31 > qfirst)) {   // a key past the sequence or after a query
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const int mq = qfirst + 8 * (e / 4) + 4 * h + (e % 4);    // query of this register
-              if (nk >= p.N || (p.causal && nk > mq)) a[e] = -INFINITY;
-            }
-          }
+          for (int qb = 0; qb < QBN; ++qb)
+            rf[qb][cb] = load_frag_swz<T>((k_role ? os : qs) + (qb * 32 + lr) * L::kRow, cb * 2 * FC + h * FC, swz_x<CPR>(qb * 32 + lr));
+        if constexpr (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);   // all reads on their way before the first product
 #pragma unroll
-          for (int e = 0; e < 16; ++e) a[e] = fast_exp2(a[e]);
-          bf = to_frag<T>(a);
-          store_frag_major<T>(pblk, lane, bf);
-        } else {
-          const Frag<T> pf = load_frag_major<T>(pblk, lane);
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) a[e] *= frag_elem(pf, e);
-          bf = to_frag<T>(a);
-        }
+          for (int qb = 0; qb < QBN; ++qb) mma32(a[qb], rf[qb][cb], kop[cb]);
+        if constexpr (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);
         const T* tile = k_role ? qs : os;                       // dK^T += Q^T dS,  dV^T += dO^T P
+        Frag<T> tf[QBN][TF];
+        if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) mma32(acc[cb], load_frag_tr_swz<CPR>(tile, qb * 32, cb * 32, lane), bf);
+          for (int qb = 0; qb < QBN; ++qb) load_frags_tr_swz<CPR>(tf[qb], tile, qb * 32, 0, lane);
+        }
+        Frag<T> bf[QBN];                                        // P (dV^T wave) or dS (dK^T wave), k = queries
+#pragma unroll
+        for (int qb = 0; qb < QBN; ++qb) {
+          const int qfirst = q0 + 32 * qb;
+          T* pblk = pbuf + (long)(((it & 1) * KB + kb) * QBN + qb) * kFragBlockElems;
+          if (!k_role) {
+            if (key0 + 31 >= p.N || (p.causal && key0 + 31 > qfirst)) {   // a key past the sequence or after a query
+              // register e holds query qfirst + 4 h + 8 (e / 4) + e % 4
+              const int first = nk >= p.N ? 64 : (p.causal ? nk - qfirst - 4 * h : 0);
+#pragma unroll
+              for (int e = 0; e < 16; ++e) a[qb][e] = 8 * (e / 4) + (e % 4) < first ? -INFINITY : a[qb][e];
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) a[qb][e] = fast_exp2(a[qb][e]);
+            bf[qb] = to_frag<T>(a[qb]);
+            store_frag_major<T>(pblk, lane, bf[qb]);
+          } else {
+            const Frag<T> pf = load_frag_major<T>(pblk, lane);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) a[qb][e] *= frag_elem(pf, e);
+            bf[qb] = to_frag<T>(a[qb]);
+          }
+        }
+        if constexpr (sizeof(T) == 4) load_frags_tr_swz<CPR>(tf[0], tile, 0, 0, lane);   // (no registers for it earlier)
+#pragma unroll
+        for (int cb = 0; cb < CB; cb += TF) {
+#pragma unroll
+          for (int qb = 0; qb < QBN; ++qb)
+#pragma unroll
+            for (int n = 0; n < TF; ++n) mma32(acc[cb + n], tf[qb][n], bf[qb]);
+          if (cb + TF < CB)
+#pragma unroll
+            for (int qb = 0; qb < QBN; ++qb) load_frags_tr_swz<CPR>(tf[qb], tile, qb * 32, (cb + TF) * 32, lane);
+        }
       }
     }
-    s_store(stat[S1], (t + 1) % NS);
-    __syncthreads();
-    if (t + 2 < n_it) g_load(stat[decltype(slot_c)::value], t + 2, (t + 2) % NS);   // nothing is left in flight at the end
-  };
-  const int n_int = n_it + 1;
-  int t = 0;
-  for (; t + PF <= n_int; t += PF) {
-    interval(std::integral_constant<int, 0>{}, t);
-    interval(std::integral_constant<int, 1>{}, t + 1);
+    meet();
+    if (t + 2 < n_it) issue(t + 2, (t + 2) % NS);               // nothing is left in flight at the end
   }
-  if (t < n_int) interval(std::integral_constant<int, 0>{}, t);
 
   // rows of the accumulators are stored channel positions: position 16h'+4q'+r of a 32-block
   if (key_ok) {
@@ -520,7 +543,6 @@ template <typename T, int D, int TQ, int KB>
 static hipError_t dkv_launch(const BwdArgs& a, hipStream_t s) {
   using L = DkvLds<T, D, TQ, KB>;
   static_assert(L::kBytes <= 160 * 1024, "fits the LDS of a compute unit");
-  static_assert(TQ <= 64 * KB, "half the threads hold a block's vector");
   dim3 grid(a.n_hg * a.Bsz, (a.Npad + 32 * KB - 1) / (32 * KB));
   auto kern = bwd_dkv_kernel<T, D, TQ, KB>;
   static LdsOnce lds_once;

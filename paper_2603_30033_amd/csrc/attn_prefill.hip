@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
         store_frag<T>(static_cast<T*>(p.O) + ((tok_base + m) * p.nH + head) * D + cb * 32 + 16 * h, zero_frag<T>());
-      if (p.lse != nullptr && h == 0) p.lse[((long)b * p.nH + head) * p.Npad + m] = INFINITY;
+      if (p.lse != nullptr && h == 0) p.lse[((long)b * p.nH + head) * p.Npad + m] = -INFINITY;
     }
     return;
   }
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   }
 
   // ---- epilogue: normalise, store O[tok][head][c] (acc order in c) -------------------------
-  // Rows of padding tokens (N <= m < Npad) are written as zeros, and their log-sum-exp as +inf,
+  // Rows of padding tokens (N <= m < Npad) are written as zeros, and their negated log-sum-exp as -inf,
   // so that a pass over all padded rows (the backward kernels) sees no undefined values.
   if (head_ok) {
     T* O = static_cast<T*>(p.O);
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
         store_frag<T>(O + ((tok_base + m) * p.nH + head) * D + cb * 32 + 16 * h, to_frag<T>(o));
       }
       if (p.lse != nullptr && h == 0)
-        p.lse[((long)b * p.nH + head) * p.Npad + m] = m < p.N ? m_ref[qb] + log2f(l_tot) : INFINITY;
+        p.lse[((long)b * p.nH + head) * p.Npad + m] = m < p.N ? -(m_ref[qb] + log2f(l_tot)) : -INFINITY;
     }
   }
 }

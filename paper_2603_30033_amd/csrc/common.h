@@ -287,6 +287,50 @@ __device__ __forceinline__ Frag<bf16> load_frag_tr_finish(FragTrPending& f) {
   r.v[1] = __builtin_bit_cast(bf16x8, u32x4{f.q[2][0], f.q[2][1], f.q[3][0], f.q[3][1]});
   return r;
 }
+// Two (or one) transposed fragments, columns col0 and col0 + 32, read and waited for in one piece: as above the wait for
+// direct-to-LDS loads in flight is kept out, and matrix instructions issued before run on meanwhile.
+template <int CPR, int N>
+__device__ __forceinline__ void load_frags_tr_swz(Frag<bf16> (&f)[N], const bf16* tile, int row0, int col0, int lane) {
+  static_assert(N == 1 || N == 2, "");
+  const int h = lane / 32, i = lane % 16;
+  uint32_t at[N][4];
+  u32x2 v[N][4];
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = col0 + 32 * n + (lane & 16) + 4 * (i % 4), row = row0 + 8 * q + 4 * h + i / 4;
+      const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
+      at[n][q] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16*)src;
+    }
+  if constexpr (N == 2)
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %3, %11\n\t"
+        "ds_read_b64_tr_b16 %4, %12\n\tds_read_b64_tr_b16 %5, %13\n\tds_read_b64_tr_b16 %6, %14\n\tds_read_b64_tr_b16 %7, %15\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[0][2]), "=&v"(v[0][3]), "=&v"(v[N - 1][0]), "=&v"(v[N - 1][1]),
+          "=&v"(v[N - 1][2]), "=&v"(v[N - 1][3])
+        : "v"(at[0][0]), "v"(at[0][1]), "v"(at[0][2]), "v"(at[0][3]), "v"(at[N - 1][0]), "v"(at[N - 1][1]), "v"(at[N - 1][2]),
+          "v"(at[N - 1][3])
+        : "memory");
+  else
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %5\n\tds_read_b64_tr_b16 %2, %6\n\tds_read_b64_tr_b16 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[0][2]), "=&v"(v[0][3])
+        : "v"(at[0][0]), "v"(at[0][1]), "v"(at[0][2]), "v"(at[0][3])
+        : "memory");
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    f[n].v[0] = __builtin_bit_cast(bf16x8, u32x4{v[n][0][0], v[n][0][1], v[n][1][0], v[n][1][1]});
+    f[n].v[1] = __builtin_bit_cast(bf16x8, u32x4{v[n][2][0], v[n][2][1], v[n][3][0], v[n][3][1]});
+  }
+}
+template <int CPR, int N>
+__device__ __forceinline__ void load_frags_tr_swz(Frag<float> (&f)[N], const float* tile, int row0, int col0, int lane) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) f[n] = load_frag_tr_swz<CPR>(tile, row0, col0 + 32 * n, lane);
+}
 // one direct global-to-LDS load of this wave: 64 consecutive chunks of a swizzled tile starting at
 // chunk q*64; `row_ptr(row)` gives the global address of tile row `row`
 template <typename T, int CPR, class RowPtr>

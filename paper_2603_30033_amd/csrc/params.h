@@ -100,7 +100,7 @@ struct AttnArgs {
   const void* Kr;     // [TP][D]
   const void* Vt;     // [B][D][Npad]
   void* O;            // [TP][nH][D] acc order in c, normalised; rows of padding tokens are zero
-  float* lse;         // nullable [B][nH][Npad]: log2 of the softmax denominator (+inf for padding tokens)
+  float* lse;         // nullable [B][nH][Npad]: -log2 of the softmax denominator (-inf for padding tokens)
   const float4* rope; // [D/4][rope_ld] as in GemmArgs, or null
   int rope_ld;
   int Bsz, N, Npad, nH, R2, r3, D;   // D = padded common width of K and V (32, 64 or 128)
@@ -117,8 +117,8 @@ struct BwdArgs {
   const void* Vr;      // [TP][D] values, acc order in c
   const void* Krt;     // [B][D][Npad] rotated keys transposed, n acc order
   const void* O;       // [TP][nH][D]
-  const float* lse;    // [B][nH][Npad]
-  float* delta;        // [B][nH][Npad]  sum_c dO O
+  const float* lse;    // [B][nH][Npad], negated as the forward stores it
+  float* delta;        // [B][nH][Npad]  -sum_c dO O
   void* Qr;            // [TP][nH][D] rotated, scaled per-head queries (acc order in c)
   void* dO;            // [TP][nH][D] (acc order in c)
   void* dQ;            // [TP][nH][D] dS K with the rotation removed (the 1/sqrt(d_head) is applied later), acc order in c
