@@ -771,14 +771,14 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
 
   // ---- G_i = sum_a U1[i,a] C[a]: gradients of the core and of the head factor ----------------------------------
   {
-    CoreGradArgs k;
+    CoreGradArgs k, kt;
     std::memset(&k, 0, sizeof(k));
     k.dG = ws.dG; k.D = c->D; k.nH = f.n_heads; k.C = w->C; k.U1 = w->U1; k.r1 = f.r1; k.r2 = f.r2; k.r3 = f.r3;
     k.scale = (float)(1.0 / std::sqrt((double)f.d_head)); k.dC = gr->dC; k.dU1 = gr->dU1;
-    if (launch_core_grad(f.dtype, k, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
-    k.dG = ws.dGt; k.C = w->Ct; k.U1 = w->Ut1; k.r1 = f.rt1; k.r2 = f.rt2; k.r3 = f.rt3;
-    k.scale = 1.f; k.dC = gr->dCt; k.dU1 = gr->dUt1;
-    if (launch_core_grad(f.dtype, k, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
+    kt = k;
+    kt.dG = ws.dGt; kt.C = w->Ct; kt.U1 = w->Ut1; kt.r1 = f.rt1; kt.r2 = f.rt2; kt.r3 = f.rt3;
+    kt.scale = 1.f; kt.dC = gr->dCt; kt.dU1 = gr->dUt1;
+    if (launch_core_grad(f.dtype, k, kt, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     rec.after("grad_core_and_head_factor");
   }
   return TUCKER_ATTN_OK;

@@ -213,7 +213,7 @@ hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipE
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_dkv(int dtype, const BwdArgs& a, hipStream_t s);
 hipError_t launch_kv_reduce(int dtype, const KvReduceArgs& a, hipStream_t s);
-hipError_t launch_core_grad(int dtype, const CoreGradArgs& a, hipStream_t s);
+hipError_t launch_core_grad(int dtype, const CoreGradArgs& a, const CoreGradArgs& b, hipStream_t s);   // both tensors
 // Factor projection of a decode step straight from the caller's factor matrices (no transposed copies):
 // rows [0,R2) of the product are Qlat, [R2,R2+D) the key latent, [R2+D,R2+2D) the value latent; it leaves
 // split-K partial tiles for the query launch to sum.  Needs factor rows that are whole 16-byte chunks.
