@@ -62,13 +62,15 @@ __device__ __forceinline__ void mma32_from(f32x16& out, const f32x16& c, const F
   out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v[0], b.v[0], c, 0, 0, 0);
   out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v[1], b.v[1], out, 0, 0, 0);
 }
+// fp32: the constant is copied into the result's registers, so that the matrix instruction reads its start value from
+// where it writes.  A start value in registers of its own, dead behind the instruction (a constant that the compiler keeps in
+// scratch memory and reloads for it), may be overwritten by the next LDS read before this long instruction (64 cycles)
+// has taken it: the compiler leaves no room between the two, and D = 128 lost its log-sum-exp this way.  The 16 moves hide
+// behind 2048 cycles of products and more.
 __device__ __forceinline__ void mma32_from(f32x16& out, const f32x16& c, const Frag<float>& a, const Frag<float>& b) {
-  out = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[0][0], b.v[0][0], c, 0, 0, 0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (i + j > 0) out = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[i][j], b.v[i][j], out, 0, 0, 0);
+  out = c;
+  asm volatile("" : "+v"(out));
+  mma32(out, a, b);
 }
 
 // accumulator block -> operand fragment (acc order), with rounding to T

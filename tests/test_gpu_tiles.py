@@ -69,3 +69,10 @@ def test_decode_sequence_groups(B, dtype, r2, r3):
                           w.rope_base)[0]
     for b in range(B):
         assert orc.relative_l2(y[b], ref[b]) <= 4 * {"f32": 1e-5, "bf16": 2e-2}[dtype], b
+
+
+# the same at the widths whose kernels are the tightest on registers, with enough workgroups for the large form
+@pytest.mark.parametrize("dtype,r3", [("f32", 64), ("f32", 128), ("bf16", 128)])
+def test_attention_workgroups_of_wide_latents(dtype, r3):
+    run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=130, N=70, d_model=64, n_heads=5, d_head=32, r1=2, r2=32, r3=r3,
+                       dtype=dtype, seed=55))
