@@ -289,43 +289,59 @@ __device__ __forceinline__ Frag<bf16> load_frag_tr_finish(FragTrPending& f) {
   r.v[1] = __builtin_bit_cast(bf16x8, u32x4{f.q[2][0], f.q[2][1], f.q[3][0], f.q[3][1]});
   return r;
 }
-// Two (or one) transposed fragments, columns col0 and col0 + 32, read and waited for in one piece: as above the wait for
-// direct-to-LDS loads in flight is kept out, and matrix instructions issued before run on meanwhile.
-template <int CPR, int N>
-__device__ __forceinline__ void load_frags_tr_swz(Frag<bf16> (&f)[N], const bf16* tile, int row0, int col0, int lane) {
-  static_assert(N == 1 || N == 2, "");
-  const int h = lane / 32, i = lane % 16;
-  uint32_t at[N][4];
-  u32x2 v[N][4];
-#pragma unroll
-  for (int n = 0; n < N; ++n)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = col0 + 32 * n + (lane & 16) + 4 * (i % 4), row = row0 + 8 * q + 4 * h + i / 4;
-      const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
-      at[n][q] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16*)src;
-    }
-  if constexpr (N == 2)
+// R transposing LDS reads and the wait for them in one statement: an output register of inline assembly counts as written
+// when the statement ends, so a read whose wait stands elsewhere may be copied or spilled before its data is there.
+// The compiler does not see LDS reads here, and puts no wait for direct-to-LDS loads in front of them; matrix
+// instructions issued before run on meanwhile.
+template <int R> __device__ __forceinline__ void lds_read_tr16(u32x2 (&v)[R], const uint32_t (&at)[R]) {
+  static_assert(R == 4 || R == 8 || R == 12, "");
+  if constexpr (R == 4)
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %5\n\tds_read_b64_tr_b16 %2, %6\n\tds_read_b64_tr_b16 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+        : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3])
+        : "memory");
+  else if constexpr (R == 8)
     asm volatile(
         "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %3, %11\n\t"
         "ds_read_b64_tr_b16 %4, %12\n\tds_read_b64_tr_b16 %5, %13\n\tds_read_b64_tr_b16 %6, %14\n\tds_read_b64_tr_b16 %7, %15\n\t"
         "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[0][2]), "=&v"(v[0][3]), "=&v"(v[N - 1][0]), "=&v"(v[N - 1][1]),
-          "=&v"(v[N - 1][2]), "=&v"(v[N - 1][3])
-        : "v"(at[0][0]), "v"(at[0][1]), "v"(at[0][2]), "v"(at[0][3]), "v"(at[N - 1][0]), "v"(at[N - 1][1]), "v"(at[N - 1][2]),
-          "v"(at[N - 1][3])
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[R - 4]), "=&v"(v[R - 3]), "=&v"(v[R - 2]), "=&v"(v[R - 1])
+        : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[R - 4]), "v"(at[R - 3]), "v"(at[R - 2]), "v"(at[R - 1])
         : "memory");
   else
     asm volatile(
-        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %5\n\tds_read_b64_tr_b16 %2, %6\n\tds_read_b64_tr_b16 %3, %7\n\t"
+        "ds_read_b64_tr_b16 %0, %12\n\tds_read_b64_tr_b16 %1, %13\n\tds_read_b64_tr_b16 %2, %14\n\tds_read_b64_tr_b16 %3, %15\n\t"
+        "ds_read_b64_tr_b16 %4, %16\n\tds_read_b64_tr_b16 %5, %17\n\tds_read_b64_tr_b16 %6, %18\n\tds_read_b64_tr_b16 %7, %19\n\t"
+        "ds_read_b64_tr_b16 %8, %20\n\tds_read_b64_tr_b16 %9, %21\n\tds_read_b64_tr_b16 %10, %22\n\tds_read_b64_tr_b16 %11, %23\n\t"
         "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[0][2]), "=&v"(v[0][3])
-        : "v"(at[0][0]), "v"(at[0][1]), "v"(at[0][2]), "v"(at[0][3])
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[R - 8]), "=&v"(v[R - 7]), "=&v"(v[R - 6]), "=&v"(v[R - 5]),
+          "=&v"(v[R - 4]), "=&v"(v[R - 3]), "=&v"(v[R - 2]), "=&v"(v[R - 1])
+        : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[R - 8]), "v"(at[R - 7]), "v"(at[R - 6]), "v"(at[R - 5]),
+          "v"(at[R - 4]), "v"(at[R - 3]), "v"(at[R - 2]), "v"(at[R - 1])
         : "memory");
+}
+// LDS address of what lane `lane` supplies to read q of a transposed fragment (rows row0 + 8q .., columns col0 ..) of a
+// swizzled tile
+template <int CPR> __device__ __forceinline__ uint32_t tr16_address(const bf16* tile, int row0, int col0, int q, int lane) {
+  const int h = lane / 32, i = lane % 16;
+  const int col = col0 + (lane & 16) + 4 * (i % 4), row = row0 + 8 * q + 4 * h + i / 4;
+  const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16*)src;
+}
+// Two (or one) transposed fragments, columns col0 and col0 + 32
+template <int CPR, int N>
+__device__ __forceinline__ void load_frags_tr_swz(Frag<bf16> (&f)[N], const bf16* tile, int row0, int col0, int lane) {
+  uint32_t at[4 * N];
+  u32x2 v[4 * N];
+#pragma unroll
+  for (int k = 0; k < 4 * N; ++k) at[k] = tr16_address<CPR>(tile, row0, col0 + 32 * (k / 4), k % 4, lane);
+  lds_read_tr16(v, at);
 #pragma unroll
   for (int n = 0; n < N; ++n) {
-    f[n].v[0] = __builtin_bit_cast(bf16x8, u32x4{v[n][0][0], v[n][0][1], v[n][1][0], v[n][1][1]});
-    f[n].v[1] = __builtin_bit_cast(bf16x8, u32x4{v[n][2][0], v[n][2][1], v[n][3][0], v[n][3][1]});
+    f[n].v[0] = __builtin_bit_cast(bf16x8, u32x4{v[4 * n][0], v[4 * n][1], v[4 * n + 1][0], v[4 * n + 1][1]});
+    f[n].v[1] = __builtin_bit_cast(bf16x8, u32x4{v[4 * n + 2][0], v[4 * n + 2][1], v[4 * n + 3][0], v[4 * n + 3][1]});
   }
 }
 template <int CPR, int N>

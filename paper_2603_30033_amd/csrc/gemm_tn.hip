@@ -45,26 +45,24 @@ template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST> struct 
 // operand pieces of one 32-column block for the tokens row0 .. of a swizzled [token][column] tile: bf16 16 tokens
 // (two transposing reads, which hand a lane tokens 4h + r and 8 + 4h + r of its column), fp32 8 tokens
 struct TnFrag16 { u32x2 q[2]; };
-template <int CPR> __device__ __forceinline__ void tn_read(TnFrag16& f, const bf16* tile, int row0, int col0, int lane) {
-  const int h = lane / 32, i = lane % 16;
-  const int col = col0 + (lane & 16) + 4 * (i % 4);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int row = row0 + 8 * q + 4 * h + i / 4;
-    const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
-    const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16*)src;
-    // (assembly, not the builtin: in front of that the compiler waits for every direct-to-LDS load in flight)
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.q[q]) : "v"(addr) : "memory");
-  }
-}
-__device__ __forceinline__ void tn_wait(TnFrag16& f) { asm volatile("" : "+v"(f.q[0]), "+v"(f.q[1])); }
-__device__ __forceinline__ void tn_mma(f32x16& acc, const TnFrag16& a, const TnFrag16& b) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-      __builtin_bit_cast(bf16x8, u32x4{a.q[0][0], a.q[0][1], a.q[1][0], a.q[1][1]}),
-      __builtin_bit_cast(bf16x8, u32x4{b.q[0][0], b.q[0][1], b.q[1][0], b.q[1][1]}), acc, 0, 0, 0);
-}
 struct TnFrag32 { float v[4]; };
-template <int CPR> __device__ __forceinline__ void tn_read(TnFrag32& f, const float* tile, int row0, int col0, int lane) {
+// the pieces of one step: MB blocks of A from column ca on, NB blocks of B from column cb on
+template <int CPA, int CPB, int MB, int NB>
+__device__ __forceinline__ void tn_read(TnFrag16 (&fa)[MB], TnFrag16 (&fb)[NB], const bf16* la, const bf16* lb, int row0, int ca,
+                                        int cb, int lane) {
+  uint32_t at[2 * (MB + NB)];
+  u32x2 v[2 * (MB + NB)];
+#pragma unroll
+  for (int k = 0; k < 2 * MB; ++k) at[k] = tr16_address<CPA>(la, row0, ca + 32 * (k / 2), k % 2, lane);
+#pragma unroll
+  for (int k = 0; k < 2 * NB; ++k) at[2 * MB + k] = tr16_address<CPB>(lb, row0, cb + 32 * (k / 2), k % 2, lane);
+  lds_read_tr16(v, at);
+#pragma unroll
+  for (int k = 0; k < 2 * MB; ++k) fa[k / 2].q[k % 2] = v[k];
+#pragma unroll
+  for (int k = 0; k < 2 * NB; ++k) fb[k / 2].q[k % 2] = v[2 * MB + k];
+}
+template <int CPR> __device__ __forceinline__ void tn_read_one(TnFrag32& f, const float* tile, int row0, int col0, int lane) {
   const int h = lane / 32, col = col0 + lane % 32;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -72,7 +70,19 @@ template <int CPR> __device__ __forceinline__ void tn_read(TnFrag32& f, const fl
     f.v[r] = tile[row * (CPR * 4) + (((col / 4) ^ swz_x<CPR>(row)) * 4) + col % 4];
   }
 }
-__device__ __forceinline__ void tn_wait(TnFrag32&) {}
+template <int CPA, int CPB, int MB, int NB>
+__device__ __forceinline__ void tn_read(TnFrag32 (&fa)[MB], TnFrag32 (&fb)[NB], const float* la, const float* lb, int row0, int ca,
+                                        int cb, int lane) {
+#pragma unroll
+  for (int m = 0; m < MB; ++m) tn_read_one<CPA>(fa[m], la, row0, ca + 32 * m, lane);
+#pragma unroll
+  for (int n = 0; n < NB; ++n) tn_read_one<CPB>(fb[n], lb, row0, cb + 32 * n, lane);
+}
+__device__ __forceinline__ void tn_mma(f32x16& acc, const TnFrag16& a, const TnFrag16& b) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+      __builtin_bit_cast(bf16x8, u32x4{a.q[0][0], a.q[0][1], a.q[1][0], a.q[1][1]}),
+      __builtin_bit_cast(bf16x8, u32x4{b.q[0][0], b.q[0][1], b.q[1][0], b.q[1][1]}), acc, 0, 0, 0);
+}
 __device__ __forceinline__ void tn_mma(f32x16& acc, const TnFrag32& a, const TnFrag32& b) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[r], b.v[r], acc, 0, 0, 0);
@@ -187,18 +197,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_tn_kernel(TnArgs a)
 #pragma unroll
       for (int c = 0; c < Cfg::kTokens; c += kStep) {
         F fa[MB], fb[NB];
-        const int row0 = kg * Cfg::kTokens + c;
-#pragma unroll
-        for (int m = 0; m < MB; ++m) tn_read<Cfg::CPA>(fa[m], la, row0, (wm * MB + m) * 32, lane);
-#pragma unroll
-        for (int n = 0; n < NB; ++n) tn_read<Cfg::CPB>(fb[n], lb, row0, (wn * NB + n) * 32, lane);
-        if constexpr (sizeof(T) == 2) {
-          wait_lds();
-#pragma unroll
-          for (int m = 0; m < MB; ++m) tn_wait(fa[m]);
-#pragma unroll
-          for (int n = 0; n < NB; ++n) tn_wait(fb[n]);
-        }
+        tn_read<Cfg::CPA, Cfg::CPB>(fa, fb, la, lb, kg * Cfg::kTokens + c, wm * MB * 32, wn * NB * 32, lane);
 #pragma unroll
         for (int m = 0; m < MB; ++m)
 #pragma unroll
