@@ -590,14 +590,12 @@ void decode_attn_shared_kernel(DecodeArgs p) {
         }
       }
       // the value fragments (transposing reads of the same tile) are taken before the stage is refilled
-      FragTrPending vp[CB];
+      constexpr int TF = CB < 2 ? 1 : 2;
+      Frag<T> vf[CB / TF][TF];
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) vp[cb] = load_frag_tr_swz_start<CPR>(kt, 0, cb * 32, lane);
+      for (int k = 0; k < CB / TF; ++k) load_frags_tr_swz<CPR>(vf[k], kt, 0, k * TF * 32, lane);
       wait_lds();
       issue(j + 2, st);
-      Frag<T> vf[CB];
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) vf[cb] = load_frag_tr_finish(vp[cb]);
 
       if (n0 + 32 > Lb) {
 #pragma unroll
@@ -638,7 +636,7 @@ void decode_attn_shared_kernel(DecodeArgs p) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int hb = 0; hb < HB; ++hb) mma32(oacc[hb][cb], vf[cb], pf[hb]);
+        for (int hb = 0; hb < HB; ++hb) mma32(oacc[hb][cb], vf[cb / TF][cb % TF], pf[hb]);
     };
     for (int j = 0; j < cnt; j += 2) {                            // the stage index is a constant in each call
       round(j, 0);

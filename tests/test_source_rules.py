@@ -18,7 +18,7 @@ def asm_statements(text):
         yield text.count("\n", 0, m.start()) + 1, text[m.end():at - 1]
 
 
-@pytest.mark.parametrize("name", ["gemm_tn.hip"])
+@pytest.mark.parametrize("name", sorted(n for n in os.listdir(CSRC) if n.endswith((".hip", ".h"))))
 def test_loads_in_inline_assembly_wait_in_the_same_statement(name):
     # an output register counts as written when the statement ends: a load that is waited for elsewhere may be copied,
     # spilled or its register handed on before its data has arrived
