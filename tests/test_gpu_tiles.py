@@ -7,7 +7,7 @@ import pytest
 from oracle import tucker_oracle as orc
 from paper_2603_30033_amd import workloads as wl
 from paper_2603_30033_amd.device import Layer, to_device, to_host
-from tests.test_gpu_backward import run_case
+from tests.test_gpu_backward import run_backward, run_case, upstream
 from tests.test_gpu_parity import check, oracle_forward, run_forward
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +76,14 @@ def test_decode_sequence_groups(B, dtype, r2, r3):
 def test_attention_workgroups_of_wide_latents(dtype, r3):
     run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=130, N=70, d_model=64, n_heads=5, d_head=32, r1=2, r2=32, r3=r3,
                        dtype=dtype, seed=55))
+
+
+# an overflown upstream gradient reaches the keys of its own block of 32 tokens and earlier ones, not later blocks
+@pytest.mark.parametrize("dtype,r3", [("f32", 64), ("bf16", 32), ("bf16", 64), ("bf16", 128)])
+def test_non_finite_gradients_stay_before_later_tokens(dtype, r3):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=1, N=160, d_model=64, n_heads=3, d_head=32, r1=2, r2=32, r3=r3, dtype=dtype,
+                  causal=True, seed=56)
+    dY = upstream(w, 101)
+    dY[0, 70] = np.inf
+    dX = run_backward(w, wl.make_inputs(w), dY)["dX"]
+    assert np.all(np.isfinite(dX[0, 96:])) and not np.all(np.isfinite(dX[0, 70]))
