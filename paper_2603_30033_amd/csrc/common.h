@@ -338,6 +338,11 @@ __device__ __forceinline__ void dma_piece(T* tile, int q, int lane, RowPtr row_p
 template <typename T> __device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t buf, T* lds, uint32_t off) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
 }
+// the same through a register, for memory that does not start on 16 bytes
+template <typename T>
+__device__ __forceinline__ void buffer_to_lds_by_register(__amdgpu_buffer_rsrc_t buf, T* lds, uint32_t off, int lane) {
+  *reinterpret_cast<u32x4*>(lds + lane * (16 / (int)sizeof(T))) = __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0);
+}
 
 // at most N vector-memory operations of this wave (loads, direct-to-LDS loads) still in flight
 template <int N> __device__ __forceinline__ void wait_vm() {

@@ -100,7 +100,8 @@ __device__ __forceinline__ void store_rows_y(const GemmArgs& g, const f32x16 (&a
   }
 }
 
-template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST>
+// DIRECT: both operands start on 16 bytes, and stages go straight into LDS.
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST, bool DIRECT>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_kernel(GemmArgs g) {
   using Cfg = GemmCfg<T, TM, TN, WGM, WGN, WGK, RB, ST>;
   constexpr int MB = Cfg::MB, NB = Cfg::NB, CE = Cfg::CE, CPR = Cfg::CPR, NW = Cfg::kWaves;
@@ -181,12 +182,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_kernel(GemmArgs g) 
     const int k0 = (s0 + i) * Cfg::KS;
     const bool ok = i < cnt && k0 + koff < g.K;
     const uint32_t kb = (uint32_t)k0 * (uint32_t)sizeof(T);
+    auto move = [&](__amdgpu_buffer_rsrc_t r, T* to, uint32_t off) {
+      off = ok && off != kNone ? off + kb : kNone;
+      if constexpr (DIRECT) buffer_to_lds(r, to, off);
+      else buffer_to_lds_by_register(r, to, off, lane);          // (wait_lds in front of the barrier covers the store)
+    };
 #pragma unroll
-    for (int p = 0; p < Cfg::PA; ++p)
-      buffer_to_lds(ra, st + (wave + NW * p) * kPiece, ok && aoff[p] != kNone ? aoff[p] + kb : kNone);
+    for (int p = 0; p < Cfg::PA; ++p) move(ra, st + (wave + NW * p) * kPiece, aoff[p]);
 #pragma unroll
-    for (int p = 0; p < Cfg::PB; ++p)
-      buffer_to_lds(rb, st + Cfg::kAElems + (wave + NW * p) * kPiece, ok && boff[p] != kNone ? boff[p] + kb : kNone);
+    for (int p = 0; p < Cfg::PB; ++p) move(rb, st + Cfg::kAElems + (wave + NW * p) * kPiece, boff[p]);
   };
 
   f32x16 acc[MB][NB];
@@ -304,12 +308,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_kernel(GemmArgs g) 
   }
 }
 
-template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST>
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int RB, int ST, bool DIRECT = true>
 static hipError_t launch_one(const GemmArgs& a, int m_rows, hipStream_t s) {
   using Cfg = GemmCfg<T, TM, TN, WGM, WGN, WGK, RB, ST>;
   const int TP = a.Bsz * a.Npad;
   dim3 grid((m_rows + TM - 1) / TM, (TP + TN - 1) / TN, a.ksplit > 1 ? a.ksplit : 1);
-  auto kern = gemm_kernel<T, TM, TN, WGM, WGN, WGK, RB, ST>;
+  auto kern = gemm_kernel<T, TM, TN, WGM, WGN, WGK, RB, ST, DIRECT>;
   static LdsOnce lds_once;                                       // one per kernel instantiation
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, Cfg::kBytes); ae != hipSuccess) return ae;
   hipLaunchKernelGGL(kern, grid, dim3(Cfg::kThreads), Cfg::kBytes, s, a);
@@ -339,10 +343,15 @@ template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStrea
   const long tokens = (long)a.Bsz * a.Npad;
   auto tiles = [&](int tm, int tn) { return (long)((m_rows + tm - 1) / tm) * ((tokens + tn - 1) / tn); };
   const bool few = tiles(64, 64) < 192 || a.ksplit > 1;
+  // An operand of the caller's that does not start on 16 bytes (a piece of a larger buffer) is staged through registers,
+  // with one tile for all sizes: rows are whole chunks from there on, so only the start decides.
+  const bool direct = (reinterpret_cast<uintptr_t>(a.A) | reinterpret_cast<uintptr_t>(a.Bsrc)) % 16 == 0;
   if constexpr (sizeof(T) == 4) {
+    if (!direct) return launch_one<T, 32, 32, 1, 1, 4, 128, 4, false>(a, m_rows, s);
     if (few) return launch_one<T, 32, 32, 1, 1, 4, 128, 4>(a, m_rows, s);
     return launch_one<T, 64, 64, 2, 2, 1, 128, 4>(a, m_rows, s);
   } else {
+    if (!direct) return launch_one<T, 32, 32, 1, 1, 8, 256, 4, false>(a, m_rows, s);
     if (few) return launch_one<T, 32, 32, 1, 1, 8, 256, 4>(a, m_rows, s);
     if (a.K >= 1024) {
       if (m_rows % 96 == 0 && tiles(96, 128) >= 256) return launch_one<T, 96, 128, 1, 2, 4, 128, 4>(a, m_rows, s);

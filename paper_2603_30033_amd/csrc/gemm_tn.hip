@@ -108,7 +108,8 @@ __device__ __forceinline__ void tn_store(const TnProduct& p, const f32x16& v, in
   }
 }
 
-template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST>
+// DIRECT: every operand starts on 16 bytes, and stages go straight into LDS.
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST, bool DIRECT>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_tn_kernel(TnArgs a) {
   using Cfg = TnCfg<T, TM, TN, WGM, WGN, WGK, ST>;
   using F = std::conditional_t<sizeof(T) == 2, TnFrag16, TnFrag32>;
@@ -167,10 +168,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_tn_kernel(TnArgs a)
     T* st = smem + (long)slot * Cfg::kStageElems;
     const __amdgpu_buffer_rsrc_t ra = buffer(p.At, p.lda, p.a_padded, m_tile);
     const __amdgpu_buffer_rsrc_t rb = buffer(p.Bt, p.ldb, p.b_padded, n_tile);
+    auto move = [&](__amdgpu_buffer_rsrc_t r, T* to, uint32_t off) {
+      if constexpr (DIRECT) buffer_to_lds(r, to, off);
+      else buffer_to_lds_by_register(r, to, off, lane);          // (wait_lds in front of the barrier covers the store)
+    };
 #pragma unroll
-    for (int k = 0; k < Cfg::PA; ++k) buffer_to_lds(ra, st + (wave + NW * k) * kPiece, aoff[k]);
+    for (int k = 0; k < Cfg::PA; ++k) move(ra, st + (wave + NW * k) * kPiece, aoff[k]);
 #pragma unroll
-    for (int k = 0; k < Cfg::PB; ++k) buffer_to_lds(rb, st + Cfg::kAElems + (wave + NW * k) * kPiece, boff[k]);
+    for (int k = 0; k < Cfg::PB; ++k) move(rb, st + Cfg::kAElems + (wave + NW * k) * kPiece, boff[k]);
     --left;
     sn += kTS;
     if (sn == a.Npad) { sn = 0; ++sb; }
@@ -327,10 +332,10 @@ size_t tn_part_bytes(int dtype, const TnArgs& a) {
   return ks > 1 ? (size_t)ks * tn_blocks(a) * 4096 : 0;
 }
 
-template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST>
+template <typename T, int TM, int TN, int WGM, int WGN, int WGK, int ST, bool DIRECT = true>
 static hipError_t tn_one(const TnArgs& a, hipStream_t s) {
   using Cfg = TnCfg<T, TM, TN, WGM, WGN, WGK, ST>;
-  auto kern = gemm_tn_kernel<T, TM, TN, WGM, WGN, WGK, ST>;
+  auto kern = gemm_tn_kernel<T, TM, TN, WGM, WGN, WGK, ST, DIRECT>;
   static LdsOnce lds_once;
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, Cfg::kBytes); ae != hipSuccess) return ae;
   hipLaunchKernelGGL(kern, dim3(a.tiles * a.ksplit), dim3(Cfg::kThreads), Cfg::kBytes, s, a);
@@ -341,8 +346,12 @@ static hipError_t tn_one(const TnArgs& a, hipStream_t s) {
 
 hipError_t launch_gemm_tn(int dtype, const TnArgs& args, hipStream_t s) {
   TnArgs a = args;
-  const int edge = tn_edge(dtype, a);
-  a.ksplit = tn_ksplit(dtype, a);
+  // operands of the caller's that do not start on 16 bytes: through registers, with 64-wide tiles for all sizes
+  uintptr_t starts = 0;
+  for (int i = 0; i < a.n; ++i) starts |= reinterpret_cast<uintptr_t>(a.p[i].At) | reinterpret_cast<uintptr_t>(a.p[i].Bt);
+  const bool direct = starts % 16 == 0;
+  const int edge = direct ? tn_edge(dtype, a) : 64;
+  a.ksplit = tn_ksplit(dtype, a);                               // (the split that tn_part_bytes has counted with)
   a.tiles = a.blocks = 0;
   for (int i = 0; i < a.n; ++i) {
     a.p[i].first_tile = a.tiles;
@@ -350,6 +359,7 @@ hipError_t launch_gemm_tn(int dtype, const TnArgs& args, hipStream_t s) {
     a.tiles += ((a.p[i].M + edge - 1) / edge) * ((a.p[i].cols + edge - 1) / edge);
     a.blocks += (pad32(a.p[i].M) / 32) * ((a.p[i].cols + 31) / 32);
   }
+  if (!direct) return dtype == 0 ? tn_one<float, 64, 64, 1, 1, 8, 4, false>(a, s) : tn_one<bf16, 64, 64, 1, 1, 4, 4, false>(a, s);
   if (dtype == 0) return tn_one<float, 64, 64, 1, 1, 8, 4>(a, s);
   if (edge == 128) return tn_one<bf16, 128, 128, 1, 2, 4, 4>(a, s);
   return tn_one<bf16, 64, 64, 1, 1, 4, 4>(a, s);

@@ -3,11 +3,13 @@ contraction and the heads, against the CPU oracle.  Bars as in test_gpu_parity.p
 2e-2 in bf16 storage, every row within four times that)."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import tucker_oracle as orc
+from paper_2603_30033_amd import binding as ta
 from paper_2603_30033_amd import workloads as wl
 from paper_2603_30033_amd.device import Layer, to_device, to_host
-from tests.test_gpu_backward import run_backward, run_case, upstream
+from tests.test_gpu_backward import check_all, oracle_backward, run_backward, run_case, upstream
 from tests.test_gpu_parity import check, oracle_forward, run_forward
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +89,37 @@ def test_non_finite_gradients_stay_before_later_tokens(dtype, r3):
     dY[0, 70] = np.inf
     dX = run_backward(w, wl.make_inputs(w), dY)["dX"]
     assert np.all(np.isfinite(dX[0, 96:])) and not np.all(np.isfinite(dX[0, 70]))
+
+
+# caller's arrays that lie one element into a larger buffer: alignment to the element is all that the interface asks for
+@pytest.mark.parametrize("dtype,N,d", [("f32", 70, 136), ("bf16", 70, 136), ("bf16", 1100, 1032)])
+def test_arrays_that_start_on_an_element(dtype, N, d):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=2, N=N, d_model=d, n_heads=3, d_head=32, r1=2, r2=32, r3=32, dtype=dtype,
+                  seed=57)
+    inp = wl.make_inputs(w)
+    dY = upstream(w, 102)
+
+    def shifted(t):
+        flat = torch.zeros(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.flatten()
+        return flat[1:].view(t.shape)
+
+    with Layer(w, inp, max_positions=N + 8) as layer:
+        X, G = to_device(inp["X"], dtype), to_device(dY, dtype)
+        ctx, Y, dX = layer.ctx, shifted(torch.zeros_like(X)), shifted(torch.zeros_like(X))
+        weights = {k: shifted(v) for k, v in layer.weights.items()}
+        nbytes = max(ta.tucker_attn_backward_workspace_bytes(ctx, 2, N), ta.tucker_attn_decode_workspace_bytes(ctx, 2))
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        grads = {"d" + k: torch.empty(v.shape, dtype=torch.float32, device="cuda") for k, v in weights.items()}
+        ta.tucker_attn_forward(ctx, weights, shifted(X), Y, workspace=ws)
+        ta.tucker_attn_backward(ctx, weights, shifted(X), shifted(G), dX, grads, workspace=ws)
+        y = to_host(Y)
+        got = {k: to_host(v) for k, v in grads.items()}
+        got["dX"] = to_host(dX)
+        K, V = (torch.zeros(2, 4, 32, dtype=X.dtype, device="cuda") for _ in range(2))
+        out = shifted(torch.zeros_like(X[:, 0]))                   # one token each: the first row of a causal prefill
+        ta.tucker_attn_decode(ctx, weights, shifted(X[:, 0]), out, K, V, [1, 1], ws)
+        out = to_host(out)
+    assert orc.relative_l2(out, oracle_forward(w, inp)[:, 0]) <= {"f32": 1e-5, "bf16": 2e-2}[dtype]
+    check(y, oracle_forward(w, inp), dtype, repr(w))
+    check_all(got, oracle_backward(w, inp, dY), dtype, repr(w))
