@@ -307,6 +307,12 @@ static int tn_blocks(const TnArgs& a) {
   for (int i = 0; i < a.n; ++i) blocks += (pad32(a.p[i].M) / 32) * ((a.p[i].cols + 31) / 32);
   return blocks;
 }
+// Most parts for these products and this many tokens: four rounds of workgroups over the chip (the choice below never
+// took more: 192 tiles four parts from 184 stages on, 320 in fp32 four), one part per stage, 16.
+static int tn_ksplit_most(const TnArgs& a, int tiles) {
+  const int slices = a.Bsz * (a.Npad / kTS), fill = (1024 + tiles - 1) / tiles, most = fill < 16 ? fill : 16;
+  return most < slices ? most : slices;
+}
 // Parts the tokens are split into: the count with the least estimated time, from what was measured (us): a stage of
 // 64 tokens 0.76 with 128-wide tiles, 0.34 with 64-wide ones, 1.2 in fp32; 9, 5.4 and 7 for a workgroup's start and
 // reduction; 4.5 for the second launch and 0.001 per partial block.  A compute unit holds one workgroup, one and a
@@ -319,7 +325,7 @@ static int tn_ksplit(int dtype, const TnArgs& a) {
   const double stage = dtype == 0 ? 1.2 : edge == 128 ? 0.76 : 0.34, fixed = dtype == 0 ? 7. : edge == 128 ? 9. : 5.4;
   int best = 1;
   double cost = 1e30;
-  for (int ks = 1; ks <= 16 && ks <= slices; ++ks) {
+  for (int ks = 1; ks <= tn_ksplit_most(a, tiles); ++ks) {
     double rounds = dtype == 1 && edge == 64 ? tiles * ks / 384. : (tiles * ks + 255) / 256;
     if (rounds < 1.) rounds = 1.;
     const double c = rounds * ((slices + ks - 1) / ks * stage + fixed) + (ks > 1 ? 4.5 + 0.001 * ks * blocks : 0.);
@@ -327,8 +333,10 @@ static int tn_ksplit(int dtype, const TnArgs& a) {
   }
   return best;
 }
+// Scratch for the most parts, not for the chosen count: that one moves up and down with the tokens, and a workspace made for
+// more tokens is to serve fewer.
 size_t tn_part_bytes(int dtype, const TnArgs& a) {
-  const int ks = tn_ksplit(dtype, a);
+  const int ks = tn_ksplit_most(a, tn_tiles(tn_edge(dtype, a), a));
   return ks > 1 ? (size_t)ks * tn_blocks(a) * 4096 : 0;
 }
 

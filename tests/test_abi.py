@@ -118,6 +118,22 @@ def test_workspace_sizes_and_host_side_argument_checks():
         ta.tucker_attn_destroy(ctx)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [dict(), dict(d_model=136, n_heads=3, r2=48, r3=40), dict(d_model=1024, n_heads=16, r2=64)])
+def test_a_training_workspace_for_more_tokens_serves_fewer(dtype, shape):
+    # up to 1024 blocks of 128 keys all heads have partial gradients of their own, and no part of the workspace shrinks
+    ctx = ta.tucker_attn_create(**_cfg(dtype=dtype, save_for_backward=True, **shape))
+    heads = shape.get("n_heads", 4)
+    try:
+        longest = 128 * (1024 // heads)
+        sizes = [ta.tucker_attn_workspace_bytes(ctx, 1, n) for n in range(64, longest + 1, 64)]
+        assert sizes == sorted(sizes)
+        sizes = [ta.tucker_attn_workspace_bytes(ctx, b, 64) for b in range(1, 1024 // heads + 1)]
+        assert sizes == sorted(sizes)
+    finally:
+        ta.tucker_attn_destroy(ctx)
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
