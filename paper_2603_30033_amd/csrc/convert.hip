@@ -581,13 +581,18 @@ __global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, do
 
 struct HosvdWs {
   double *A, *B, *T, *GA, *GB, *SA, *SB, *M1[2], *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
-  double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~
+  double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~ (one for all where
+                                                        // the problems are solved one by one)
   double *Z[4], *Z2[4], *work[4];                       // eigenvector rows before and behind the polish; scratch
   double* report;                                       // value | resid | err | diagonal | subdiagonal of each problem
   double* S;
   int *idx, *counter;
   size_t bytes;
 };
+
+// The reduction to tridiagonal form takes the sizes whose vectors fit the LDS (whole conversions: d = 768 6.7 ms
+// against 206 ms by the Jacobi iteration, d = 4096 0.36 s against 4.3 s).
+bool by_tridiagonal_form(int d) { return d >= kEigenMinSize && d <= kEigenMaxSize; }
 
 HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   const size_t n = (size_t)nH * dH, D = d;
@@ -612,14 +617,17 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
     w.U2[t] = (double*)take(D * rmax, 8);
     w.U3[t] = (double*)take(D * rmax, 8);
   }
+  const bool batched = by_tridiagonal_form(d);
   for (int e = 0; e < 4; ++e) {
-    w.M[e] = (double*)take(D * D, 8);
+    w.M[e] = batched || e == 0 ? (double*)take(D * D, 8) : w.M[0];
+    w.Z[e] = w.Z2[e] = w.work[e] = nullptr;
+    if (!batched) continue;
     w.Z[e] = (double*)take(D * rmax, 8);
     w.Z2[e] = (double*)take(D * rmax, 8);
     w.work[e] = (double*)take(eigen_work_elems(d), 8);
   }
-  w.report = (double*)take(4 * 5 * D, 8);
-  w.S = (double*)take(rmax * rmax, 8);
+  w.report = batched ? (double*)take(4 * 5 * D, 8) : nullptr;
+  w.S = batched ? (double*)take(rmax * rmax, 8) : nullptr;
   w.P = (double*)take(rmax * n, 8);
   w.Q = (double*)take(rmax * n, 8);
   w.H = (double*)take((size_t)nH * rmax * rmax, 8);
@@ -845,6 +853,7 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
                                    (T*)(t ? (mode == 2 ? o.Ut2 : o.Ut3) : (mode == 2 ? o.U2 : o.U3)), sv ? sv + at : nullptr,
                                    info ? &stats[3 * t + mode - 1] : nullptr};
     }
+  const bool tridiagonal = by_tridiagonal_form(d);
   for (int t = 0; t < 2; ++t) {
     CK(load(t));
     CK(head_products(s, w, d, nH, dH));
@@ -858,24 +867,22 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
       if (st != TUCKER_ATTN_OK) return st;
     }
     for (int j = 0; j < n_jobs; ++j)
-      if (jobs[j].tensor == t) CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
+      if (tridiagonal && jobs[j].tensor == t) CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
   }
-  // The reduction to tridiagonal form takes the sizes whose vectors fit the LDS (whole conversions: d = 768 6.7 ms
-  // against 206 ms by the Jacobi iteration, d = 4096 0.36 s against 4.3 s).  A problem that it cannot certify (on a
-  // Gram matrix formed anew) and every other size go through the Jacobi iteration.
+  // A problem that the reduction to tridiagonal form cannot certify and every other size go through the Jacobi iteration, one
+  // Gram matrix at a time, formed in front of it.
   bool done[4] = {false, false, false, false};
-  const bool tridiagonal = d >= kEigenMinSize && d <= kEigenMaxSize;
   if (tridiagonal)
     if (const int st = tridiagonal_jobs<T>(s, w, d, jobs, n_jobs, done); st != TUCKER_ATTN_OK) return st;
   int loaded = 1;
   for (int j = n_jobs - 1; j >= 0; --j) {
     if (done[j]) continue;
-    if (tridiagonal) {
-      if (loaded != jobs[j].tensor) CK(load(jobs[j].tensor));
-      loaded = jobs[j].tensor;
+    if (loaded != jobs[j].tensor) {
+      CK(load(jobs[j].tensor));
       CK(head_products(s, w, d, nH, dH));
-      CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
     }
+    loaded = jobs[j].tensor;
+    CK(mode_gram(s, w, d, nH, dH, jobs[j].mode, w.M[j]));
     const int st = leading_eigenvectors<T>(s, w.M[j], d, jobs[j].r, w.norms2, w.idx, w.counter, jobs[j].U64, jobs[j].U,
                                            jobs[j].sv, jobs[j].stats);
     if (st != TUCKER_ATTN_OK) return st;

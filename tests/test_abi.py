@@ -52,6 +52,15 @@ def test_conversion_entry_points_reject_bad_arguments_on_the_host():
     assert hosvd(0, 16384, 4, 16, *W, 4, 8, 8, 4, 8, 8, 0, o, None, None, 256, 1 << 40, None) == -2
 
 
+def test_conversion_workspace_holds_one_gram_matrix_where_problems_are_solved_one_by_one():
+    # beyond the sizes of the tridiagonal reduction: the fp64 factors and their products, one d x d matrix, four factors
+    # of 512 columns, the core's intermediates
+    for d, nH, dH in ((8192, 64, 128), (5057, 64, 64)):
+        n, r = nH * dH, 512
+        need = 8 * (3 * d * n + 2 * n * n + 2 * n * dH + d * d + 4 * d * r + 2 * r * n + 2 * nH * r * r)
+        assert need <= ta.tucker_convert_hosvd_workspace_bytes(d, nH, dH) <= need + (1 << 20)
+
+
 def test_status_strings():
     assert ta.tucker_attn_status_string(0) == "ok"
     for s in (-1, -2, -3, -4):
