@@ -233,7 +233,7 @@ def bench_convert_hosvd(w, args):
     jac_ms = sum(i["jacobi_ms"] for i in infos) / K
     jac_bytes = sum(i["jacobi_bytes"] for i in infos) / K
     ach = jac_bytes / (jac_ms * 1e-3) / 1e9 if jac_ms > 0 else 0.0
-    log(f"{w.name}: {dt:.3f} s per conversion; eigen-problems {jac_ms:.1f} ms in {launches:.0f} launches, "
+    log(f"{w.name}: {dt:.3f} s per conversion; eigen-problem steps {jac_ms:.1f} ms in {launches:.0f} launches, "
         f"sweeps {infos[-1]['sweeps']}, {ach:.0f} GB/s")
     out = {
         "metric": "hosvd_conversion_seconds", "value": dt, "unit": "s", "n_gpus": 1, "steps": K, "warmup": W,

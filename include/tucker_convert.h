@@ -65,8 +65,9 @@ typedef struct {
   int32_t sweeps[6];        /* Jacobi sweeps of the eigen-problems of W modes 1, 2, 3 and W~ modes 1, 2, 3    */
                             /* (0: solved by reduction to tridiagonal form, or not solved -- one head, or     */
                             /* mode 3 of W~ with shared_kv)                                                   */
-  int64_t jacobi_launches;  /* step kernels launched for the d x d problems (modes 2 and 3): columns reduced  */
-                            /* (all problems in one launch), Jacobi rounds where that path is taken           */
+  int64_t jacobi_launches;  /* step kernels launched for the d x d problems (modes 2 and 3): one per column   */
+                            /* of the reduction (all problems together) until 192 columns remain, which are   */
+                            /* one launch more and not counted; Jacobi rounds where that path is taken        */
   double  jacobi_ms;        /* time of those launches on the stream, from HIP events around them              */
   double  jacobi_bytes;     /* bytes they read and wrote: the remaining matrix once per column, all rows per  */
                             /* round                                                                          */

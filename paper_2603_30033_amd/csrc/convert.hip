@@ -705,8 +705,7 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     for (hipEvent_t& x : ev.e) CK(hipEventCreate(&x));
     CK(hipEventRecord(ev.e[0], s));
   }
-  CK(launch_tridiag(b, s));
-  if (timed) CK(hipEventRecord(ev.e[1], s));
+  CK(launch_tridiag(b, s, ev.e[1]));
   CK(launch_tridiag_vectors(b, s));
   // rows of close eigenvalues are orthogonal only to rounding / gap: one Newton-Schulz step Z <- (1.5 I - 0.5 Z Z^T) Z,
   // which squares what is missing and moves no vector by more than its own uncertainty
@@ -724,9 +723,11 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
   if (timed) {
     float ms = 0.f;
     CK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
-    jobs[0].stats->ms += ms;                            // one set of launches for all
-    jobs[0].stats->launches += d;
-    jobs[0].stats->bytes += 16.0 * n_jobs * d * (double)d * d / 3;   // every step reads and writes what remains
+    const int steps = tridiag_steps_of(d);
+    if (steps > 0) jobs[0].stats->ms += ms;             // one set of launches for all
+    jobs[0].stats->launches += steps;
+    // step k reads and writes the d - 1 - k rows and columns that remain
+    for (int k = 0; k < steps; ++k) jobs[0].stats->bytes += 16.0 * n_jobs * (d - 1. - k) * (d - 1. - k);
   }
   auto worst_of = [](const double* x, int n) {
     double worst = 0.0;

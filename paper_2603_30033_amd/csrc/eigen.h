@@ -21,8 +21,13 @@ struct EigenBatch {
 };
 inline size_t eigen_work_elems(int m) { return 5ul * m; }
 
-// Enqueues the reduction to tridiagonal form; G, work and tri are written.
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s);
+// columns that the reduction takes by one launch each; the rest goes in one launch
+constexpr int kEigenTail = 192;
+inline int tridiag_steps_of(int m) { return m > kEigenTail ? m - kEigenTail : 0; }
+
+// Enqueues the reduction to tridiagonal form; G, work and tri are written.  steps_done (nullable) is recorded behind the
+// launches of one column each.
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done);
 // Enqueues eigenvalues and eigenvectors of the tridiagonal matrices, vectors carried back to the basis of G.
 // The vectors are unit rows; rows of close eigenvalues are orthogonal only up to (rounding / gap).
 hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s);

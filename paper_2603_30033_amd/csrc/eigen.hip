@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64 * NW) void apply_reflectors_kernel(EigenBatch b)
 // problem: wave w holds the rows k0 + w, k0 + w + 16, ... in registers, and A u is summed over rows (A is symmetric), so
 // that no sum runs across lanes.  Otherwise a step is the one of tridiag_step_kernel.
 // The last 192 steps of four problems: 0.58 ms; as launches of their own 4.8 us each plus the gaps, 1.0 ms.
-constexpr int kTail = 192;                              // 72 of a thread's 128 registers
+constexpr int kTail = kEigenTail;                       // 72 of a thread's 128 registers
 __global__ __launch_bounds__(1024) void tridiag_tail_kernel(EigenBatch b, int k0) {
   constexpr int R = kTail / 16, C = kTail / 64;                 // rows per wave, chunks of 64 columns per row
   __shared__ double red[2][16], v[kTail], w[kTail], u[kTail], part[16][kTail];
@@ -487,11 +487,12 @@ template <int NW, int NC, int PF> void apply_reflectors(const EigenBatch& b, int
 
 }  // namespace
 
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s) {
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done) {
   if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
-  const int steps = b.m > kTail ? b.m - kTail : 0;
+  const int steps = tridiag_steps_of(b.m);
   hipError_t e = hipSuccess;
   if (steps > 0) e = b.m <= 512 ? tridiag_steps<8, 1>(b, steps, s) : (b.m <= 1024 ? tridiag_steps<16, 1>(b, steps, s) : tridiag_steps<0, 4>(b, steps, s));
+  if (e == hipSuccess && steps_done != nullptr) e = hipEventRecord(steps_done, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(tridiag_tail_kernel, dim3(b.n), dim3(1024), 0, s, b, steps);
   return hipGetLastError();

@@ -278,6 +278,16 @@ def test_hosvd_at_the_edges_of_the_eigen_solver(d, nH, dH, r):
         assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
 
 
+@pytest.mark.parametrize("d,shared,steps", [(64, False, 0), (192, False, 0), (256, False, 64), (256, True, 64)])
+def test_hosvd_report_counts_the_launches_of_one_column(d, shared, steps):
+    host = wl.make_classic_weights(d, 4, 16, 98, "f32")
+    devw = {k: to_device(v, "f32") for k, v in host.items()}
+    dev.from_mha_hosvd(devw["WQ"], devw["WK"], devw["WV"], devw["WO"], 4, (2, 8, 8), (2, 8, 8), shared)
+    info = dev.from_mha_hosvd.last_info
+    assert info["jacobi_launches"] == steps and (info["jacobi_ms"] > 0) == (steps > 0)
+    assert info["jacobi_bytes"] == sum(16 * (3 if shared else 4) * (d - 1 - k) ** 2 for k in range(steps))
+
+
 @pytest.mark.parametrize("kind", ["all_equal", "pairs", "blocks"])
 def test_hosvd_with_repeated_singular_values_keeps_the_tensor(kind):
     # vectors of repeated values are not unique: the factors must be orthonormal and, at full ranks, the core
