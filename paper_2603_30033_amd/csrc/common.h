@@ -231,24 +231,7 @@ template <> __device__ __forceinline__ Frag<float> load_frag_swz<float>(const fl
   for (int j = 0; j < 4; ++j) f.v[j] = *reinterpret_cast<const f32x4*>(rowp + ((k0 + j) ^ x) * 4);
   return f;
 }
-// load_frag_tr on a swizzled tile whose rows hold CPR chunks (stride = CPR * elements per chunk)
-template <int CPR>
-__device__ __forceinline__ Frag<bf16> load_frag_tr_swz(const bf16* tile, int row0, int col0, int lane) {
-  const int h = lane / 32, i = lane % 16;
-  const int col = col0 + (lane & 16) + 4 * (i % 4);              // 4 consecutive columns: half a chunk
-  Frag<bf16> f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = row0 + 8 * q + 4 * h + i / 4;
-    const bf16* src = tile + row * (CPR * 8) + (((col / 8) ^ swz_x<CPR>(row)) * 8) + col % 8;
-    auto* lp = (__attribute__((address_space(3))) s16x4*)(src);
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lp);
-    const bf16x4 b = __builtin_bit_cast(bf16x4, v);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) f.v[q / 2][(q % 2) * 4 + r] = b[r];
-  }
-  return f;
-}
+// load_frag_tr on a swizzled tile whose rows hold CPR chunks (stride = CPR * elements per chunk); bf16: load_frags_tr_swz
 template <int CPR>
 __device__ __forceinline__ Frag<float> load_frag_tr_swz(const float* tile, int row0, int col0, int lane) {
   const int h = lane / 32, col = col0 + lane % 32;
@@ -403,9 +386,6 @@ __device__ __forceinline__ float frag_sum(const Frag<bf16>& f, float acc) {
     }
   return acc;
 }
-
-// 16-byte chunk of T elements
-template <typename T> struct Chunk { static constexpr int kElems = 16 / sizeof(T); };
 
 // value held by the partner lane (l ^ 32) combined with ours
 __device__ __forceinline__ float halves_max(float x) {

@@ -1,5 +1,5 @@
-// Epilogues of the token-side products: what becomes of one 32x32 accumulator block.  Shared by the
-// product kernel and the decode kernel that sums the projection's partial tiles itself.
+// Epilogues of the projection and of the head merge: what becomes of one 32x32 accumulator block (Y leaves the product
+// kernel as whole rows).  Shared by the product kernel and the decode kernel that sums the projection's partial tiles itself.
 #pragma once
 #include "common.h"
 #include "params.h"
@@ -121,19 +121,6 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, in
     for (int q = 0; q < 4; ++q) {
       int c = m0 + 8 * q + 4 * h;
       if (c < g.M) store4(row + c, acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-    }
-  } else {                                                      // ---- Y, caller's [B][N][d]
-    if (!valid) return;
-    T* row = static_cast<T*>(g.Out) + ((long)b * g.N + n) * g.ldo;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      int c = m0 + 8 * q + 4 * h;
-      if (c + 3 < g.M)
-        store4(row + c, acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-      else
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e < g.M) store1(row + c + e, acc[4 * q + e]);
     }
   }
 }
