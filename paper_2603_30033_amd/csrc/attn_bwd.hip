@@ -525,7 +525,7 @@ static hipError_t dq_launch(const BwdArgs& a, hipStream_t s) {
 template <typename T, int D, int BC>
 static hipError_t dq_one(const BwdArgs& a, hipStream_t s) {
   const long wgs = (long)((a.nH + 3) / 4) * a.Bsz * (a.Npad / 64);
-  return wgs < 256 ? dq_launch<T, D, BC, 1>(a, s) : dq_launch<T, D, BC, 2>(a, s);
+  return wgs < kComputeUnits ? dq_launch<T, D, BC, 1>(a, s) : dq_launch<T, D, BC, 2>(a, s);
 }
 
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {
@@ -559,7 +559,7 @@ static hipError_t dkv_launch(const BwdArgs& a, hipStream_t s) {
 template <typename T, int D, int TQ>
 static hipError_t dkv_one(const BwdArgs& a, hipStream_t s) {
   const long wgs = (long)a.n_hg * a.Bsz * ((a.Npad + 127) / 128);
-  return wgs < 256 ? dkv_launch<T, D, TQ, 2>(a, s) : dkv_launch<T, D, TQ, 4>(a, s);
+  return wgs < kComputeUnits ? dkv_launch<T, D, TQ, 2>(a, s) : dkv_launch<T, D, TQ, 4>(a, s);
 }
 
 hipError_t launch_bwd_dkv(int dtype, const BwdArgs& a, hipStream_t s) {

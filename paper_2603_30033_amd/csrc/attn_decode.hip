@@ -705,8 +705,7 @@ void decode_attn_shared_kernel(DecodeArgs p) {
 // The workgroup of head i merges the split partials of its head for every sequence (log-sum-exp, loads
 // of 16 splits issued together), keeps the normalised O_i [sequence][c] in LDS in operand order, and multiplies it by the head's
 // post-softmax core: Zpart_i^T[b][sequence] = sum_c G~_i[b][c] O_i[sequence][c].  The per-head
-// contributions are written where a split-K product would put its partial tiles ([head][sequence][RT2],
-// fp32), and the split-K reduction sums them over heads into Z.  This replaces two launches (the merge and
+// contributions ([head][sequence][RT2], fp32) are summed over the heads by the output launch.  This replaces two launches (the merge and
 // a product that streams all heads' cores through a few workgroups) by one in which every head's 32 KB core
 // block is read by its own workgroup.
 template <typename T, int D>

@@ -429,7 +429,7 @@ static hipError_t launch_one(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hi
 template <typename T, int D, int BC>
 static hipError_t launch_sized(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {
   const long wgs = (long)((a.nH + 3) / 4) * a.Bsz * (a.Npad / 64);
-  if (wgs < 256) return launch_one<T, D, 1, BC, 1, 4>(a, s, k0, k1);
+  if (wgs < kComputeUnits) return launch_one<T, D, 1, BC, 1, 4>(a, s, k0, k1);
   return launch_one<T, D, 1, BC, 2, 4>(a, s, k0, k1);
 }
 

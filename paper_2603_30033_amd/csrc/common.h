@@ -28,6 +28,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
+// compute units of the board on which the rules that pick tiles and workgroups by a launch's size were measured; a rule
+// that misses on another count costs time, not correctness
+constexpr int kComputeUnits = 256;
 
 __host__ __device__ constexpr int pad32(int x) { return (x + 31) / 32 * 32; }
 __host__ __device__ constexpr int pad64(int x) { return (x + 63) / 64 * 64; }

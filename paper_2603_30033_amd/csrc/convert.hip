@@ -243,8 +243,8 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
 // norm is at most `tiny` are numerically zero and are left alone.  Rows >= m of the last block
 // read as zero and are never written.  `rotations` counts the rotations applied.
 // One workgroup holds all rows of a matrix of at most 16 (m <= 16, step 0): with LOOP it goes on until a sweep finds
-// nothing to rotate, and `rotations` receives the number of sweeps, 0 if `max_sweeps` were not enough; tol and tiny are
-// then worked out from the rows themselves.
+// nothing to rotate, and `rotations` receives the number of sweeps, 0 if `max_sweeps` were not enough; tiny is then
+// worked out from the rows themselves.
 template <int NW, bool LOOP>   // NW waves per workgroup: they share the columns in steps 1 and 3; the first four run step 2
 __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(double* G, int m, int len, int step, double tol, double tiny,
                                                                int* rotations, int max_sweeps) {
@@ -437,7 +437,7 @@ hipError_t dgemm(hipStream_t s, int batch, int M, int N, int K, const double* A,
   DgemmArgs g{A, a_m, a_k, a_b, B, b_k, b_n, b_b, C, c_m, c_n, c_b, M, N, K};
   // small tiles until the large ones fill every compute unit twice
   const long large = (long)((N + 63) / 64) * ((M + 63) / 64) * batch;
-  if (large >= 512) hipLaunchKernelGGL(dgemm_kernel<2>, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, s, g);
+  if (large >= 2 * kComputeUnits) hipLaunchKernelGGL(dgemm_kernel<2>, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, s, g);
   else hipLaunchKernelGGL(dgemm_kernel<1>, dim3((N + 31) / 32, (M + 31) / 32, batch), dim3(256), 0, s, g);
   return hipGetLastError();
 }
@@ -447,9 +447,6 @@ hipError_t dgemm(hipStream_t s, int batch, int M, int N, int K, const double* A,
     if ((expr) != hipSuccess) return TUCKER_ATTN_HIP_ERROR; \
   } while (0)
 
-// Eigenvectors of the symmetric positive semi-definite G [m, m] (destroyed) with the r largest
-// eigenvalues -> U64 / U [m, r]; sv (host, nullable) receives the square roots of all
-// eigenvalues in decreasing order.  Synchronises the stream.
 constexpr int kJacobiWaves = 16;
 
 struct JacobiStats {
@@ -501,6 +498,9 @@ int finish_small_jacobi(hipStream_t s, const double* G, int m, int r, double* no
   return order_and_extract<T>(s, G, m, r, norms2, idx, U64, U, sv);
 }
 
+// Eigenvectors of the symmetric positive semi-definite G [m, m] (destroyed) with the r largest
+// eigenvalues -> U64 / U [m, r]; sv (host, nullable) receives the square roots of all
+// eigenvalues in decreasing order.  Synchronises the stream.
 template <typename T>
 int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2, int* idx, int* counter,
                          double* U64, T* U, double* sv, JacobiStats* stats) {

@@ -334,7 +334,7 @@ static hipError_t launch_one(const GemmArgs& a, int m_rows, hipStream_t s) {
 // (before, four waves that split the tile only: 48, 63, 39, 14, 25, 36, 7.7, 22.6, 59).  Few tiles: as many
 // workgroups as possible, the eight waves of each dealt over the contraction.  A long contraction with enough
 // tiles for every compute unit is bound by the bytes that the caches deliver, hence the largest tile that still
-// gives 256 workgroups; a short one by the start and the end of a workgroup, hence four waves and 64 KB of LDS,
+// gives each one a workgroup; a short one by the start and the end of a workgroup, hence four waves and 64 KB of LDS,
 // so that two workgroups share a compute unit.  fp32 is bound by its matrix instructions (64 cycles each): only
 // the number of workgroups matters (192 x 768 x 1018 tokens 8.9 us with 32x32 and four waves, 8.0 with eight, 19
 // with 64x64, 21 before; 768 x 192 x 1018 tokens 7.5, 10.0, 8.2, 8.9 before).
@@ -342,7 +342,7 @@ template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStrea
   const int m_rows = (a.epi == 0) ? a.R2 + (a.shared_kv ? 1 : 2) * a.D : a.M;
   const long tokens = (long)a.Bsz * a.Npad;
   auto tiles = [&](int tm, int tn) { return (long)((m_rows + tm - 1) / tm) * ((tokens + tn - 1) / tn); };
-  const bool few = tiles(64, 64) < 192 || a.ksplit > 1;
+  const bool few = tiles(64, 64) < kComputeUnits * 3 / 4 || a.ksplit > 1;
   // An operand of the caller's that does not start on 16 bytes (a piece of a larger buffer) is staged through registers,
   // with one tile for all sizes: rows are whole chunks from there on, so only the start decides.
   const bool direct = (reinterpret_cast<uintptr_t>(a.A) | reinterpret_cast<uintptr_t>(a.Bsrc)) % 16 == 0;
@@ -354,9 +354,9 @@ template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStrea
     if (!direct) return launch_one<T, 32, 32, 1, 1, 8, 256, 4, false>(a, m_rows, s);
     if (few) return launch_one<T, 32, 32, 1, 1, 8, 256, 4>(a, m_rows, s);
     if (a.K >= 1024) {
-      if (m_rows % 96 == 0 && tiles(96, 128) >= 256) return launch_one<T, 96, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
-      if (m_rows > 64 && tiles(128, 128) >= 256) return launch_one<T, 128, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
-    } else if (tiles(96, 128) >= 256) {
+      if (m_rows % 96 == 0 && tiles(96, 128) >= kComputeUnits) return launch_one<T, 96, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
+      if (m_rows > 64 && tiles(128, 128) >= kComputeUnits) return launch_one<T, 128, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
+    } else if (tiles(96, 128) >= kComputeUnits) {
       return launch_one<T, 96, 128, 1, 4, 1, 128, 2>(a, m_rows, s);
     }
     return launch_one<T, 64, 64, 1, 1, 4, 128, 4>(a, m_rows, s);

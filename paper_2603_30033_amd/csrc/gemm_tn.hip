@@ -295,7 +295,7 @@ static int tn_edge(int dtype, const TnArgs& a) {
   if (dtype == 0) return 64;
   int tiles = 0;
   for (int i = 0; i < a.n; ++i) tiles += (a.p[i].M / 128) * (a.p[i].cols / 128);
-  return tiles >= 128 ? 128 : 64;
+  return tiles >= kComputeUnits / 2 ? 128 : 64;
 }
 static int tn_tiles(int edge, const TnArgs& a) {
   int tiles = 0;
@@ -310,7 +310,7 @@ static int tn_blocks(const TnArgs& a) {
 // Most parts for these products and this many tokens: four rounds of workgroups over the chip (the choice below never
 // took more: 192 tiles four parts from 184 stages on, 320 in fp32 four), one part per stage, 16.
 static int tn_ksplit_most(const TnArgs& a, int tiles) {
-  const int slices = a.Bsz * (a.Npad / kTS), fill = (1024 + tiles - 1) / tiles, most = fill < 16 ? fill : 16;
+  const int slices = a.Bsz * (a.Npad / kTS), fill = (4 * kComputeUnits + tiles - 1) / tiles, most = fill < 16 ? fill : 16;
   return most < slices ? most : slices;
 }
 // Parts the tokens are split into: the count with the least estimated time, from what was measured (us): a stage of
@@ -326,7 +326,7 @@ static int tn_ksplit(int dtype, const TnArgs& a) {
   int best = 1;
   double cost = 1e30;
   for (int ks = 1; ks <= tn_ksplit_most(a, tiles); ++ks) {
-    double rounds = dtype == 1 && edge == 64 ? tiles * ks / 384. : (tiles * ks + 255) / 256;
+    double rounds = dtype == 1 && edge == 64 ? tiles * ks / (1.5 * kComputeUnits) : (tiles * ks + kComputeUnits - 1) / kComputeUnits;
     if (rounds < 1.) rounds = 1.;
     const double c = rounds * ((slices + ks - 1) / ks * stage + fixed) + (ks > 1 ? 4.5 + 0.001 * ks * blocks : 0.);
     if (c < cost) { cost = c; best = ks; }

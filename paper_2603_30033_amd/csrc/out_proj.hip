@@ -129,7 +129,7 @@ static hipError_t out_one(const GemmArgs& a, hipStream_t s) {
   const int t_tiles = (TP + 127) / 128, m_tiles = (a.M + TM - 1) / TM;
   // enough workgroups for every compute unit, but as many channel tiles per workgroup as that
   // allows: the Z fragments and the pipeline fill are paid once per workgroup
-  int chunks = (256 + t_tiles - 1) / t_tiles;
+  int chunks = (kComputeUnits + t_tiles - 1) / t_tiles;
   if (chunks > m_tiles) chunks = m_tiles;
   if (chunks < 1) chunks = 1;
   const int per = (m_tiles + chunks - 1) / chunks;

@@ -165,7 +165,7 @@ struct DecodeArgs {
   int Bsz, nH, HB, R2, r3, rt3, D, Lmax, nsplit;
   int shared_kv;       // 1: Kcache holds the unrotated latent, which is also the value; Vcache is null
   const void* Gtil2;   // [RT2][nH*D] post-softmax head-mixed cores, c in acc order (head merge)
-  float* zpart;        // [nH][Bsz][RT2] per-head contributions to Z, summed by the split-K reduction
+  float* zpart;        // [nH][Bsz][RT2] per-head contributions to Z, summed by the output launch
   int RT2;
   const void* Ut2;     // [d_model][ut2_ld] output factor, k = RT2 contiguous (padded copy where rt2 is no multiple of 32)
   long ut2_ld;
