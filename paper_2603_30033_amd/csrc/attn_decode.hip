@@ -593,7 +593,7 @@ void decode_attn_shared_kernel(DecodeArgs p) {
       constexpr int TF = CB < 2 ? 1 : 2;
       Frag<T> vf[CB / TF][TF];
 #pragma unroll
-      for (int k = 0; k < CB / TF; ++k) load_frags_tr_swz<CPR>(vf[k], kt, 0, k * TF * 32, lane);
+      for (int k = 0; k < CB / TF; ++k) load_frags_tr_swz<CPR, false>(vf[k], kt, 0, k * TF * 32, lane);
       wait_lds();
       issue(j + 2, st);
 
