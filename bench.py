@@ -339,6 +339,13 @@ def main():
     if args.seq_len > 0:
         w = wl.scaled(w, name=f"{w.name}_L{args.seq_len}",
                       **({"kv_len": args.seq_len} if w.mode == "decode" else {"N": args.seq_len}))
+    if args.copy_calibration_mib > 0:
+        src = torch.randint(0, 255, (args.copy_calibration_mib << 20,), dtype=torch.uint8, device="cuda")
+        dst = torch.empty_like(src)
+        for _ in range(3):
+            dst.copy_(src)
+        torch.cuda.synchronize()
+        del src, dst
     if args.which == "convert_hosvd":
         print(json.dumps(bench_convert_hosvd(w, args)), flush=True)
         return
@@ -353,14 +360,6 @@ def main():
         sys.exit(2)
     if backward:
         fb = backward_flops(w)
-
-    if args.copy_calibration_mib > 0:
-        src = torch.randint(0, 255, (args.copy_calibration_mib << 20,), dtype=torch.uint8, device="cuda")
-        dst = torch.empty_like(src)
-        for _ in range(3):
-            dst.copy_(src)
-        torch.cuda.synchronize()
-        del src, dst
 
     with Layer(w, inp, save_for_backward=backward and saved) as layer:
         if args.frozen_weights:
