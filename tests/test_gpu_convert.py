@@ -265,7 +265,8 @@ def test_gpt2_sized_layer_converted_on_the_gpu_runs_like_the_oracle_layer_on_ora
 
 @pytest.mark.parametrize("d,nH,dH,r", [
     (7, 2, 3, 3),                                                # below the smallest size of the tridiagonal reduction
-    (8, 2, 4, 5), (17, 3, 5, 15),                                # one workgroup of rows, and one row more
+    (8, 2, 4, 5), (17, 3, 5, 15),                                # the smallest, and one row more than the tail's waves
+    (192, 4, 16, 20), (193, 4, 16, 20),                          # all columns in the tail launch, and one in front of it
     (256, 4, 16, 20), (257, 4, 16, 20),                          # edges of the row lengths held in registers
     (512, 2, 32, 33), (513, 2, 32, 33), (1025, 2, 16, 20),       # and of the rows streamed from memory
 ])
