@@ -67,10 +67,11 @@ typedef struct {
                             /* mode 3 of W~ with shared_kv)                                                   */
   int64_t jacobi_launches;  /* step kernels launched for the d x d problems (modes 2 and 3): one per column   */
                             /* of the reduction (all problems together) until 192 columns remain, which are   */
-                            /* one launch more and not counted; Jacobi rounds where that path is taken        */
+                            /* one launch more and not counted; 1 where all columns are one launch (256 < d   */
+                            /* <= 1024); Jacobi rounds where that path is taken                               */
   double  jacobi_ms;        /* time of those launches on the stream, from HIP events around them              */
-  double  jacobi_bytes;     /* bytes they read and wrote: the remaining matrix once per column, all rows per  */
-                            /* round                                                                          */
+  double  jacobi_bytes;     /* bytes they read and wrote: the remaining matrix once per column (read once,    */
+                            /* its reflectors written, where all columns are one launch), all rows per round  */
 } tucker_convert_hosvd_info;
 
 /* Bytes of device workspace tucker_convert_from_mha_hosvd needs; 0 if an argument is invalid. */

@@ -579,12 +579,14 @@ __global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, do
   }
 }
 
+constexpr int kReportHead = 4;
 struct HosvdWs {
   double *A, *B, *T, *GA, *GB, *SA, *SB, *M1[2], *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
   double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~ (one for all where
                                                         // the problems are solved one by one)
   double *Z[4], *Z2[4], *work[4];                       // eigenvector rows before and behind the polish; scratch
-  double* report;                                       // value | resid | err | diagonal | subdiagonal of each problem
+  double* report;                                       // four marks of failure, then value | resid | err | diagonal |
+                                                        // subdiagonal of each problem
   double* S;
   int *idx, *counter;
   size_t bytes;
@@ -626,7 +628,7 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
     w.Z2[e] = (double*)take(D * rmax, 8);
     w.work[e] = (double*)take(eigen_work_elems(d), 8);
   }
-  w.report = batched ? (double*)take(4 * 5 * D, 8) : nullptr;
+  w.report = batched ? (double*)take(kReportHead + 4 * 5 * D, 8) : nullptr;
   w.S = batched ? (double*)take(rmax * rmax, 8) : nullptr;
   w.P = (double*)take(rmax * n, 8);
   w.Q = (double*)take(rmax * n, 8);
@@ -688,7 +690,8 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     b.G[j] = w.M[j];
     b.Z[j] = w.Z[j];
     b.work[j] = w.work[j];
-    b.value[j] = w.report + 5 * (size_t)d * j;
+    b.failed[j] = w.report + j;
+    b.value[j] = w.report + kReportHead + 5 * (size_t)d * j;
     b.resid[j] = b.value[j] + d;
     b.tri[j] = b.value[j] + 3 * (size_t)d;
   }
@@ -705,7 +708,8 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     for (hipEvent_t& x : ev.e) CK(hipEventCreate(&x));
     CK(hipEventRecord(ev.e[0], s));
   }
-  CK(launch_tridiag(b, s, ev.e[1]));
+  bool resident = false;
+  CK(launch_tridiag(b, s, ev.e[1], &resident));
   CK(launch_tridiag_vectors(b, s));
   // rows of close eigenvalues are orthogonal only to rounding / gap: one Newton-Schulz step Z <- (1.5 I - 0.5 Z Z^T) Z,
   // which squares what is missing and moves no vector by more than its own uncertainty
@@ -717,17 +721,20 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     return dgemm(s, 1, r, d, r, w.S, r, 1, 0, to[j], d, 1, 0, from[j], d, 1, 0);
   };
   for (int j = 0; j < n_jobs; ++j) CK(polish(j));
-  std::vector<double> report(5 * (size_t)d * n_jobs);
+  std::vector<double> report(kReportHead + 5 * (size_t)d * n_jobs);
   CK(hipMemcpyAsync(report.data(), w.report, sizeof(double) * report.size(), hipMemcpyDeviceToHost, s));
   CK(hipStreamSynchronize(s));
   if (timed) {
     float ms = 0.f;
     CK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
-    const int steps = tridiag_steps_of(d);
+    const int steps = resident ? 1 : tridiag_steps_of(d);
     if (steps > 0) jobs[0].stats->ms += ms;             // one set of launches for all
     jobs[0].stats->launches += steps;
-    // step k reads and writes the d - 1 - k rows and columns that remain
-    for (int k = 0; k < steps; ++k) jobs[0].stats->bytes += 16.0 * n_jobs * (d - 1. - k) * (d - 1. - k);
+    // the resident launch reads every matrix and writes its reflectors; step k reads and writes the d - 1 - k rows and
+    // columns that remain
+    if (resident) jobs[0].stats->bytes += 12.0 * n_jobs * d * d;
+    else
+      for (int k = 0; k < steps; ++k) jobs[0].stats->bytes += 16.0 * n_jobs * (d - 1. - k) * (d - 1. - k);
   }
   auto worst_of = [](const double* x, int n) {
     double worst = 0.0;
@@ -736,7 +743,8 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
   };
   for (int j = 0; j < n_jobs; ++j) {
     const int r = b.r[j];
-    const double* rep = report.data() + 5 * (size_t)d * j;
+    const double* rep = report.data() + kReportHead + 5 * (size_t)d * j;
+    if (resident && report[j] != 0.0) continue;
     double fro2 = 0.0;
     for (int k = 0; k < d; ++k) {
       const double on = rep[3 * (size_t)d + k], off = k + 1 < d ? rep[4 * (size_t)d + k] : 0.0;

@@ -18,16 +18,21 @@ struct EigenBatch {
   double* value[kEigenBatch];                           // [m] eigenvalues, largest first (the first n_values written)
   double* resid[kEigenBatch];                           // [m] residual of each vector in the tridiagonal matrix
   int n_values[kEigenBatch];                            // eigenvalues wanted of each, r .. m
+  double* failed[kEigenBatch];                          // 1.0: the resident reduction gave up (see there), nothing else holds
 };
-inline size_t eigen_work_elems(int m) { return 5ul * m; }
+inline size_t eigen_work_elems(int m) { return 13ul * m; }
 
-// columns that the reduction takes by one launch each; the rest goes in one launch
+// Sizes whose whole reduction is one launch with the matrices in registers; its workgroups hold kResidentRows rows each, so that
+// four matrices of 1024 take the 256 compute units once.  Up to 256 most columns are the tail launch's either way.
+constexpr int kResidentRows = 16;
+inline bool tridiag_is_resident(int m) { return m > 256 && m <= 1024; }
+// Otherwise: columns that the reduction takes by one launch each; the rest goes in one launch
 constexpr int kEigenTail = 192;
 inline int tridiag_steps_of(int m) { return m > kEigenTail ? m - kEigenTail : 0; }
 
 // Enqueues the reduction to tridiagonal form; G, work and tri are written.  steps_done (nullable) is recorded behind the
-// launches of one column each.
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done);
+// launches of one column each, or the one launch of all columns; `resident` receives which of the two it was.
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident);
 // Enqueues eigenvalues and eigenvectors of the tridiagonal matrices, vectors carried back to the basis of G.
 // The vectors are unit rows; rows of close eigenvalues are orthogonal only up to (rounding / gap).
 hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s);

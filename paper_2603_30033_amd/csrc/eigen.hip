@@ -15,6 +15,7 @@ namespace {
 
 // layout of a problem's work array, in vectors of m doubles
 constexpr int kTau = 0, kV = 1, kY = 3;                 // kV, kY: two vectors each, used in turn
+constexpr int kExchange = 5;                // slots of m pairs
 
 // x of the lane that the DPP control CTRL names
 template <int CTRL> __device__ __forceinline__ double dpp(double x) {
@@ -470,6 +471,224 @@ __global__ __launch_bounds__(1024) void tridiag_tail_kernel(EigenBatch b, int k0
   }
 }
 
+// All m steps in one launch: the rows stay in registers (workgroup = NW waves of RW rows; lane l holds columns l + 64 c), and
+// what a step needs from the others is exchanged through memory.  At the end of step k the owner of every remaining row i
+// posts the pair (y_i, a_i): the product of step k and the entry of column k+1 that stands in front of its update.  That
+// is all that the next step waits for, so a step costs one such exchange and three barriers.
+//   The exchange goes past the L2 caches (agent scope: those of the XCDs do not see each other's plain stores), through four
+// slots of m pairs, used in turn.  A word of a pair not yet posted holds kUnset, a signalling NaN that no arithmetic
+// returns, and a reader polls until every word it needs differs.  A workgroup that has gathered step k knows that all have
+// gathered step k-1 and sets its pairs of that slot back to kUnset; these stores have arrived when it has gathered step
+// k+1 (the polls wait for every memory operation before them), so in front of its post of that step, without which nobody
+// comes to look at the slot again.
+//   The launch is cooperative (every workgroup is resident, so every wait ends); polls are bounded all the same, and a
+// workgroup that gives up marks the problem as failed, which takes it to the caller's other path.  A workgroup whose
+// rows are done leaves; the last one stores what all work out.
+// Bound by the latency of the exchange: four of 768 x 768 take 3.4 us a step against 7.3 by a launch per column and 3.0
+// in the tail launch (reduction 5.0 -> 2.6 ms); 512: 3.0, 1024: 3.9.  A bare exchange of 16 bytes a row and one barrier take 2.0 us,
+// 32 bytes a row 4.1; eight waves of two rows 2.7 ms, sixteen of one 3.4 (each wave reads the three vectors from LDS).
+constexpr unsigned long kUnset = 0x7ff4a5c3965a3c69ul;
+constexpr int kSlots = 4;
+constexpr int kSpins = 1 << 20;                         // each at least one round trip to memory: 0.5 s and more
+typedef unsigned long u64x2 __attribute__((ext_vector_type(2)));
+// pairs p[at[0]] .. p[at[E-1]], past the L2 of this XCD
+template <int E> __device__ __forceinline__ void peek(u64x2 (&v)[E], const u64x2* p, const int (&at)[E]) {
+  static_assert(E >= 2 && E <= 4, "");
+  if constexpr (E == 2)
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]) : "v"(p + at[0]), "v"(p + at[1]) : "memory");
+  else if constexpr (E == 3)
+    asm volatile("global_load_dwordx4 %0, %3, off sc1\n\tglobal_load_dwordx4 %1, %4, off sc1\n\t"
+                 "global_load_dwordx4 %2, %5, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]) : "v"(p + at[0]), "v"(p + at[1]), "v"(p + at[2]) : "memory");
+  else
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                 "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[E - 1])
+                 : "v"(p + at[0]), "v"(p + at[1]), "v"(p + at[2]), "v"(p + at[E - 1]) : "memory");
+}
+__device__ __forceinline__ void post(unsigned long* p, unsigned long x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// lane l of the wave, as a scalar
+__device__ __forceinline__ double from_lane(double x, int l) {
+  const long b = __builtin_bit_cast(long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, l), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __builtin_bit_cast(double, (long)(((unsigned long)hi << 32) | lo));
+}
+
+__global__ __launch_bounds__(256) void exchange_clear_kernel(EigenBatch b) {
+  const int p = blockIdx.y, n = 2 * kSlots * b.m;
+  unsigned long* x = reinterpret_cast<unsigned long*>(b.work[p] + (long)kExchange * b.m);
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) x[i] = kUnset;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *b.failed[p] = 0.0;
+}
+
+template <int NW, int RW, int NC>
+__global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b) {
+  constexpr int NT = 64 * NW, ROWS = NW * RW, W = 64 * NC, E = W / NT;   // E vector elements per thread
+  static_assert(W % NT == 0 && ROWS == kResidentRows, "");
+  __shared__ double vl[2][W], wl[2][W], ul[2][W], red[2][2][NW], pick[2][2];
+  __shared__ int gave_up;
+  const int m = b.m, p = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double* A = b.G[p];
+  double* work = b.work[p];
+  unsigned long* slots = reinterpret_cast<unsigned long*>(work + (long)kExchange * m);
+  const bool writer = blockIdx.x == gridDim.x - 1;
+  const int row0 = blockIdx.x * ROWS + wave * RW;
+  double x[RW][NC];
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int i = row0 + r, j = lane + 64 * c;
+      x[r][c] = i < m && j < m ? A[(long)i * m + j] : 0.0;
+    }
+  if (tid == 0) gave_up = 0;
+  double v[E], tau = 0.0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = 0.0;
+  __syncthreads();
+  for (int k = 0; k < m; ++k) {
+    const int c0 = k + 1, q = k & 1;
+    if (!writer && (int)(blockIdx.x + 1) * ROWS <= c0) return;
+    // gather: y and column k in front of its update
+    double y[E], a[E];
+    if (k == 0) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        y[e] = 0.0;
+        a[e] = A[min(tid + NT * e, m - 1)];
+      }
+    } else {
+      const u64x2* slot = reinterpret_cast<const u64x2*>(slots + (long)(k % kSlots) * 2 * m);
+      u64x2 got[E];
+      int at[E], spins = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {                             // elements that are not needed look at the last row
+        const int i = tid + NT * e;
+        at[e] = i >= k && i < m ? i : m - 1;
+      }
+      bool all;
+      do {
+        peek(got, slot, at);
+        all = true;
+#pragma unroll
+        for (int e = 0; e < E; ++e) all = all && got[e][0] != kUnset && got[e][1] != kUnset;
+      } while (!all && ++spins < kSpins);
+      if (!all) gave_up = 1;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const unsigned long w0 = got[e][0], w1 = got[e][1];     // (scalars: a cast of a vector's element takes the first)
+        y[e] = __builtin_bit_cast(double, w0);
+        a[e] = __builtin_bit_cast(double, w1);
+      }
+    }
+    double dot = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + NT * e;
+      if (i >= k && i < m) dot += v[e] * y[e];
+      if (i == k) pick[q][0] = y[e];
+    }
+    dot = wave_sum(dot);
+    if (lane == 0) red[q][0][wave] = dot;
+    __syncthreads();
+    if (gave_up) {
+      if (tid == 0) *b.failed[p] = 1.0;
+      return;
+    }
+    dot = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) dot += red[q][0][i];
+    if (k > 0 && lane < 2 * RW && row0 + lane / 2 < m)          // all have gathered step k-1: its pairs are free
+      post(slots + (long)((k - 1) % kSlots) * 2 * m + 2 * row0 + lane, kUnset);
+    const double half = 0.5 * tau * dot, wk = tau * (pick[q][0] - half);
+    double cur[E], tail = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + NT * e;
+      const bool mine = i >= k && i < m;
+      const double w = mine ? tau * (y[e] - half * v[e]) : 0.0;
+      cur[e] = mine ? a[e] - v[e] * wk - w : 0.0;               // column k of the updated matrix (v_k = 1)
+      vl[q][i] = mine ? v[e] : 0.0;
+      wl[q][i] = w;
+      if (i > c0) tail += cur[e] * cur[e];
+      if (i == c0) pick[q][1] = cur[e];
+      if (writer && mine) {
+        if (k > 0) A[(long)(k - 1) * m + i] = v[e];             // row k-1 keeps its reflector for the way back
+        if (i == k) b.tri[p][k] = cur[e];
+      }
+    }
+    tail = wave_sum(tail);
+    if (lane == 0) red[q][1][wave] = tail;
+    __syncthreads();
+    if (c0 >= m) return;                                        // the last diagonal entry
+    tail = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) tail += red[q][1][i];
+    const double x0 = pick[q][1];
+    double beta = x0, tau_k = 0.0, scale = 0.0;
+    if (tail > 0.0) {
+      beta = -copysign(sqrt(x0 * x0 + tail), x0);
+      tau_k = (beta - x0) / beta;
+      scale = 1.0 / (x0 - beta);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + NT * e;
+      v[e] = i < c0 ? 0.0 : (i == c0 ? 1.0 : cur[e] * scale);
+      ul[q][i] = v[e];
+    }
+    tau = tau_k;
+    if (writer && tid == 0) {
+      b.tri[p][m + k] = beta;
+      work[(long)kTau * m + k] = tau_k;
+    }
+    __syncthreads();
+    if (row0 + RW - 1 < c0 || row0 >= m) continue;              // (the same for the whole wave)
+    double vr[RW], wr[RW], sum[RW], next[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      vr[r] = vl[q][row0 + r];
+      wr[r] = wl[q][row0 + r];
+      sum[r] = next[r] = 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (64 * (c + 1) <= c0 || 64 * c >= m) continue;          // columns that are done, or none
+      const int j = lane + 64 * c;
+      const double vj = vl[q][j], wj = wl[q][j], uj = ul[q][j];
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        x[r][c] = x[r][c] - vr[r] * wj - wr[r] * vj;
+        sum[r] += x[r][c] * uj;
+        if (c == c0 >> 6) next[r] = x[r][c];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) sum[r] = wave_sum(sum[r]);
+    // lane 2r (+ 1) posts the first (second) word of row r's pair
+    double mine = 0.0;
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      const double n = from_lane(next[r], c0 & 63);
+      if (lane / 2 == r) mine = lane & 1 ? n : sum[r];
+    }
+    if (lane < 2 * RW && row0 + lane / 2 >= c0 && row0 + lane / 2 < m)
+      post(slots + (long)(c0 % kSlots) * 2 * m + 2 * row0 + lane, __builtin_bit_cast(unsigned long, mine));
+  }
+}
+
+template <int NC> hipError_t tridiag_resident(const EigenBatch& b, hipStream_t s) {
+  const int wgs = (b.m + kResidentRows - 1) / kResidentRows;
+  hipLaunchKernelGGL(exchange_clear_kernel, dim3(8, b.n), dim3(256), 0, s, b);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  EigenBatch args = b;
+  void* list[] = {&args};
+  constexpr int kWaves = 4;
+  auto kern = tridiag_resident_kernel<kWaves, kResidentRows / kWaves, NC>;
+  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kern), dim3(wgs, b.n), dim3(64 * kWaves), list, 0, s);
+}
+
 template <int NC, int RW> hipError_t tridiag_steps(const EigenBatch& b, int steps, hipStream_t s) {
   const size_t lds = 3ul * b.m * sizeof(double);
   auto kern = tridiag_step_kernel<NC, RW>;
@@ -487,10 +706,21 @@ template <int NW, int NC, int PF> void apply_reflectors(const EigenBatch& b, int
 
 }  // namespace
 
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done) {
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident) {
+  *resident = false;
   if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
-  const int steps = tridiag_steps_of(b.m);
   hipError_t e = hipSuccess;
+  if (tridiag_is_resident(b.m)) {
+    e = b.m <= 512 ? tridiag_resident<8>(b, s) : (b.m <= 768 ? tridiag_resident<12>(b, s) : tridiag_resident<16>(b, s));
+    if (e != hipErrorCooperativeLaunchTooLarge) {
+      *resident = true;
+      if (e == hipSuccess && steps_done != nullptr) e = hipEventRecord(steps_done, s);
+      return e;
+    }
+    (void)hipGetLastError();                            // fewer compute units than it takes: by steps
+  }
+  const int steps = tridiag_steps_of(b.m);
+  e = hipSuccess;
   if (steps > 0) e = b.m <= 512 ? tridiag_steps<8, 1>(b, steps, s) : (b.m <= 1024 ? tridiag_steps<16, 1>(b, steps, s) : tridiag_steps<0, 4>(b, steps, s));
   if (e == hipSuccess && steps_done != nullptr) e = hipEventRecord(steps_done, s);
   if (e != hipSuccess) return e;

@@ -289,6 +289,22 @@ def test_hosvd_report_counts_the_launches_of_one_column(d, shared, steps):
     assert info["jacobi_bytes"] == sum(16 * (3 if shared else 4) * (d - 1 - k) ** 2 for k in range(steps))
 
 
+@pytest.mark.parametrize("d,nH,dH,r,shared", [
+    (257, 4, 16, 20, True), (272, 3, 16, 24, False),             # one row in the last workgroup, and whole workgroups
+    (511, 2, 32, 33, False), (512, 2, 32, 33, True),             # edges of the three row lengths
+    (768, 2, 24, 30, False), (769, 2, 24, 30, True),
+    (1024, 2, 16, 20, False),                                    # the largest
+])
+def test_hosvd_with_the_reduction_in_one_launch(d, nH, dH, r, shared):
+    ranks = (min(2, nH), r, r - 1)
+    host, got, sv, _ = hosvd_case(d, nH, dH, ranks, ranks, shared, "f32", 190 + d)
+    assert dev.from_mha_hosvd.last_info["jacobi_launches"] == 1 and not any(dev.from_mha_hosvd.last_info["sweeps"][k] for k in (1, 2, 4, 5))
+    ref = cv.mha_to_tucker_hosvd(host["WQ"], host["WK"], host["WV"], host["WO"], nH, ranks, ranks, shared_kv=shared)
+    check_spectra(sv, host, nH, d, shared)
+    for k in ref:
+        assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
+
+
 @pytest.mark.parametrize("kind", ["all_equal", "pairs", "blocks"])
 def test_hosvd_with_repeated_singular_values_keeps_the_tensor(kind):
     # vectors of repeated values are not unique: the factors must be orthonormal and, at full ranks, the core
