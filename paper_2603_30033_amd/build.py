@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtucker_attn.so")
-SOURCES = ["api.hip", "prep.hip", "gemm.hip", "out_proj.hip", "attn_prefill.hip", "attn_decode.hip",
+SOURCES = ["api.hip", "prep.hip", "gemm.hip", "out_proj.hip", "attn_prefill.hip", "attn_merge.hip", "attn_decode.hip",
            "attn_bwd.hip", "gemm_tn.hip", "bwd_misc.hip", "convert.hip", "eigen.hip", "ceiling.hip", "decode_proj.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed fp32 instructions are kept off: scalar fp32 code must not be fused into them

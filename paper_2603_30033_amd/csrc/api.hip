@@ -337,6 +337,24 @@ int forward_core(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X
   if (launch_gemm(f.dtype, g, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("factor_projection");
 
+  *ut2_out = ut2;
+  *ut2_ld_out = ut2_ld;
+  if (lse == nullptr) {                                           // nobody wants the per-head outputs
+    AttnMergeArgs am;
+    std::memset(&am, 0, sizeof(am));
+    am.Qlat = ws.Qlat; am.Gt = ws.Gt; am.Kr = ws.Kr; am.Vt = ws.Vt; am.Gtil2 = ws.Gtil2; am.Z = ws.Z;
+    am.rope = c->rope; am.rope_ld = f.max_positions;
+    am.Bsz = B; am.N = N; am.Npad = Npad; am.nH = f.n_heads; am.R2 = c->R2; am.RT2 = c->RT2; am.D = c->D;
+    am.causal = f.causal; am.pos0 = pos0; am.nqb = (N + 31) / 32; am.ones = f.rt3 < c->D;
+    if (attn_merge_supported(f.dtype, am)) {
+      if (launch_attn_merge(am, s, rec.on ? c->kev[0] : nullptr, rec.on ? c->kev[1] : nullptr) != hipSuccess)
+        return TUCKER_ATTN_HIP_ERROR;
+      if (rec.on) c->kev_name = "attention_kernel";
+      rec.after("attention_and_merge");
+      return TUCKER_ATTN_OK;
+    }
+  }
+
   AttnArgs a;
   std::memset(&a, 0, sizeof(a));
   a.Qlat = ws.Qlat; a.Gt = ws.Gt; a.Kr = ws.Kr; a.Vt = ws.Vt; a.O = ws.O; a.lse = lse;
@@ -356,8 +374,6 @@ int forward_core(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X
   z.epi = 1; z.Out = ws.Z; z.ldo = c->RT2; z.ksplit = 1; z.R2 = 0; z.D = 0;
   if (launch_gemm(f.dtype, z, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("latent_merge");
-  *ut2_out = ut2;
-  *ut2_ld_out = ut2_ld;
   return TUCKER_ATTN_OK;
 }
 

@@ -107,6 +107,20 @@ struct AttnArgs {
   int causal, pos0;
 };
 
+// The same attention followed by the head merge (attn_merge.hip); no per-head outputs, no log-sum-exp
+struct AttnMergeArgs {
+  const void* Qlat; const void* Gt; const void* Kr; const void* Vt;   // as AttnArgs
+  const void* Gtil2;  // [RT2][nH*D] post-softmax head-mixed cores, c in acc order
+  void* Z;            // [TP][RT2] natural order; rows of padding tokens are zero
+  const float4* rope;
+  int rope_ld;
+  int Bsz, N, Npad, nH, R2, RT2, D;
+  int causal, pos0;
+  int nqb;            // blocks of 32 queries, (N + 31) / 32
+  int ones;           // 1: channel D - 1 of the values is padding
+  int qpw, hs;        // set by the launcher: query blocks of a workgroup, groups that the head pairs are dealt to
+};
+
 // ---- backward pass of prefill attention ---------------------------------------------------------
 struct BwdArgs {
   const void* Qlat;    // [TP][R2] acc order
@@ -210,6 +224,8 @@ hipError_t launch_gemm_tn(int dtype, const TnArgs& a, hipStream_t s);
 size_t tn_part_bytes(int dtype, const TnArgs& a);   // needs the sizes only (n, p[].M, p[].cols, Bsz, Npad)
 // k0, k1 (both or neither): events that take the start and the end of the kernel itself (profiling)
 hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipEvent_t k0 = nullptr, hipEvent_t k1 = nullptr);
+bool attn_merge_supported(int dtype, const AttnMergeArgs& a);
+hipError_t launch_attn_merge(const AttnMergeArgs& a, hipStream_t s, hipEvent_t k0 = nullptr, hipEvent_t k1 = nullptr);
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_dkv(int dtype, const BwdArgs& a, hipStream_t s);
 hipError_t launch_kv_reduce(int dtype, const KvReduceArgs& a, hipStream_t s);

@@ -123,3 +123,30 @@ def test_arrays_that_start_on_an_element(dtype, N, d):
     assert orc.relative_l2(out, oracle_forward(w, inp)[:, 0]) <= {"f32": 1e-5, "bf16": 2e-2}[dtype]
     check(y, oracle_forward(w, inp), dtype, repr(w))
     check_all(got, oracle_backward(w, inp, dY), dtype, repr(w))
+
+
+# attention and head merge in one launch: (sequences, tokens, heads, r2, r3, r~2); query blocks of one workgroup and of several,
+# heads split over waves and not, odd head counts, a key block of one key, every width of the merged latent, values with
+# and without a padding channel.  Values beyond 2^32 take the scores through the online softmax instead of the plain one.
+@pytest.mark.parametrize("values", [1.0, 2.0 ** 40])
+@pytest.mark.parametrize("B,N,heads,r2,r3,rt2,causal,shared", [
+    (512, 1, 2, 32, 32, 32, True, False), (200, 33, 5, 40, 20, 64, True, False), (171, 96, 3, 96, 32, 96, False, False),
+    (52, 290, 2, 32, 24, 40, True, True),                        # D = 32
+    (256, 33, 4, 64, 48, 32, True, False), (512, 64, 3, 96, 64, 64, False, True), (150, 225, 3, 64, 48, 48, False, False),
+    (100, 353, 2, 40, 64, 64, True, False), (512, 32, 8, 160, 40, 128, False, False),   # D = 64
+])
+def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared, values):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=r2, r3=r3, rt1=2, rt2=rt2,
+                  rt3=r3, dtype="bf16", causal=causal, shared_kv=shared, seed=58)
+    inp = wl.make_inputs(w)
+    if shared:
+        inp["U3"] *= np.float32(values)                          # values and keys; the scores stay as they were
+        inp["C"] *= np.float32(1 / values)
+        inp["Ut3"] = inp["U3"]
+    else:
+        inp["Ut3"] *= np.float32(values)
+    with Layer(w, inp) as layer:
+        ta.tucker_attn_profile_enable(layer.ctx, True)
+        y = to_host(layer.forward(to_device(inp["X"], w.dtype)))
+        assert "attention_and_merge" in [n for n, _ in ta.tucker_attn_profile_read(layer.ctx)]
+    check(y, oracle_forward(w, inp), w.dtype, repr(w))
