@@ -142,6 +142,7 @@ struct BackwardWs {
   void *Vr, *Krt, *Ut2T, *Gtil_t, *G2, *Wb, *dZ, *Qr, *dO, *dQ, *dLat;
   int LW;            // width of the latent-gradient rows: R2 + D (shared latent) or R2 + 2 D
   int hpg, n_hg;     // heads per group / number of groups of the key-value gradient kernel
+  int qsplit;        // parts of a group's query blocks
   size_t bytes;
 };
 
@@ -172,6 +173,15 @@ BackwardWs carve_backward(const tucker_attn_ctx* c, void* ws, int B, int N) {
   if (n_hg < 1) n_hg = 1;
   w.hpg = (f.n_heads + n_hg - 1) / n_hg;
   w.n_hg = (f.n_heads + w.hpg - 1) / w.hpg;
+  // Where all heads have partial sums of their own and there are few workgroups of 64 keys, the query blocks of a head are
+  // dealt to two workgroups, or four, so that their chain of query blocks is shorter.  One, two, four parts, without the sum behind
+  // them (us): fp32, D = 64, 12 heads, 2 x 509 tokens 52.4, 37.4, 31.8; bf16, 1024 tokens 28.2, 19.0, 17.4, 2 x 500 17.2, 12.9,
+  // 15.7, 20 x 70 (960 workgroups with two parts) the pass 103, 110; D = 128, 32 heads, 450 tokens 26.0, 19.9, 26.7; D = 32, 4 heads, 512
+  // tokens 13.3, 8.9, 6.7.
+  const int most = c->es == 4 || c->D == 32 ? 4 : 2;
+  const size_t most_wgs = most == 4 ? 768 : 512, key_tiles = TP / 64;
+  auto fits = [&](int parts) { return (size_t)parts * f.n_heads * key_tiles <= most_wgs; };
+  w.qsplit = N <= 64 ? 1 : fits(most) ? most : fits(2) ? 2 : 1;
   w.lse = cv.take<float>((size_t)B * f.n_heads * Npad * 4);
   w.delta = cv.take<float>((size_t)B * f.n_heads * Npad * 4);
   w.Vr = cv.take<char>(TP * c->D * es);
@@ -184,8 +194,15 @@ BackwardWs carve_backward(const tucker_attn_ctx* c, void* ws, int B, int N) {
   w.Qr = cv.take<char>(TP * nHD * es);
   w.dO = cv.take<char>(TP * nHD * es);
   w.dQ = cv.take<char>(TP * nHD * es);
-  w.dKp = cv.take<float>((size_t)w.n_hg * TP * c->D * 4);
-  w.dVp = cv.take<float>((size_t)w.n_hg * TP * c->D * 4);
+  // partial gradients, no fewer rows than a call of fewer tokens with more parts needs
+  size_t rows = (size_t)w.n_hg * w.qsplit * TP;
+  for (int parts = 2; parts <= most; parts *= 2) {
+    const size_t heads = (size_t)parts * f.n_heads, longest = heads * 64 * (most_wgs / heads);
+    const size_t fewer = longest < heads * TP ? longest : heads * TP;
+    if (rows < fewer) rows = fewer;
+  }
+  w.dKp = cv.take<float>(rows * c->D * 4);
+  w.dVp = cv.take<float>(rows * c->D * 4);
   w.dLat = cv.take<char>(TP * w.LW * es);
   w.dG = cv.take<float>((size_t)c->R2 * nHD * 4);
   w.dGt = cv.take<float>((size_t)c->RT2 * nHD * 4);
@@ -723,7 +740,7 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
   a.O = ws.f.O; a.lse = ws.lse; a.delta = ws.delta; a.Qr = ws.Qr; a.dO = ws.dO;
   a.dQ = ws.dQ; a.dKp = ws.dKp; a.dVp = ws.dVp; a.rope = c->rope; a.rope_ld = f.max_positions;
   a.Bsz = B; a.N = N; a.Npad = Npad; a.nH = f.n_heads; a.R2 = c->R2; a.RT2 = c->RT2; a.D = c->D;
-  a.causal = f.causal; a.pos0 = pos0; a.hpg = ws.hpg; a.n_hg = ws.n_hg;
+  a.causal = f.causal; a.pos0 = pos0; a.hpg = ws.hpg; a.n_hg = ws.n_hg; a.qsplit = ws.qsplit;
   if (launch_bwd_dq(f.dtype, a, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
   rec.after("attention_bwd_dq");
   if (launch_bwd_dkv(f.dtype, a, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
@@ -733,7 +750,7 @@ int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const
     std::memset(&k, 0, sizeof(k));
     k.dKp = ws.dKp; k.dVp = ws.dVp; k.dLat = ws.dLat; k.ld = LW; k.colK = c->R2; k.colV = c->R2 + c->D;
     k.rope = c->rope; k.rope_ld = f.max_positions;
-    k.Bsz = B; k.N = N; k.Npad = Npad; k.D = c->D; k.n_hg = ws.n_hg; k.pos0 = pos0; k.shared_kv = f.shared_kv;
+    k.Bsz = B; k.N = N; k.Npad = Npad; k.D = c->D; k.n_hg = ws.n_hg * ws.qsplit; k.pos0 = pos0; k.shared_kv = f.shared_kv;
     if (launch_kv_reduce(f.dtype, k, s) != hipSuccess) return TUCKER_ATTN_HIP_ERROR;
     rec.after("grad_kv_latent");
   }

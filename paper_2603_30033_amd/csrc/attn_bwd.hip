@@ -86,19 +86,20 @@ template <typename T, int D, int BC> struct DqLds {
   static constexpr size_t kBytes = 2ul * kStage * sizeof(T);
 };
 
-// Workgroup = 4 heads x QW blocks of 32 queries (two: waves w and w+4 share a SIMD; one for calls with few
-// workgroups); key tiles
-// of BC keys are staged once per workgroup and walked in 32-key halves, so that only one half's
+// Workgroup = HW heads x QW blocks of 32 queries (two: waves w and w+4 share a SIMD; one for calls with few
+// workgroups), whose keys KS waves share (those with few workgroups: each takes every KS-th tile, the sums meet in LDS); key
+// tiles of BC keys, one for each part, are staged once per workgroup and walked in 32-key halves, so that only one half's
 // scores live in registers at a time.
-template <typename T, int D, int BC, int QW>
-__global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
-  constexpr int CB = D / 32, NB = BC / 32, HW = 4, TQ = 32 * QW, NT = 64 * HW * QW;
+template <typename T, int D, int BC, int QW, int HW, int KS>
+__global__ __launch_bounds__(64 * QW * HW * KS) void bwd_dq_kernel(BwdArgs p) {
+  constexpr int CB = D / 32, NB = BC / 32, TQ = 32 * QW, NT = 64 * HW * QW * KS;
   constexpr int CE = 16 / sizeof(T);
   using L = DqLds<T, D, BC>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* smem = reinterpret_cast<T*>(smem_raw);
 
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int ks = wave / (QW * HW), wq = wave % (QW * HW);       // part of the keys; wave within the part
   const int h = lane / 32, lr = lane % 32;
   const int n_qtiles = p.Npad / TQ;
   const int qt = n_qtiles - 1 - blockIdx.y;                     // heavy (late causal) tiles first
@@ -108,29 +109,32 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
   int item = blockIdx.x;
   if (gridDim.x % 8 == 0) item = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
   const int b = item / n_hg;
-  const int head_raw = (item % n_hg) * HW + wave % HW;
+  const int head_raw = (item % n_hg) * HW + wq % HW;
   const bool head_ok = head_raw < p.nH;
   const int head = head_ok ? head_raw : p.nH - 1;
   const int t0 = qt * TQ;
-  const int tw = t0 + (wave / HW) * 32;                         // first query of this wave
+  const int tw = t0 + (wq / HW) * 32;                           // first query of this wave
   const int m = tw + lr;                                        // this lane's query, < Npad
   const long tok_base = (long)b * p.Npad;
   const long TP = (long)p.Bsz * p.Npad;
 
-  // staging of one key tile: K rows, V rows, K^T columns
+  // staging of the key tiles t KS .. t KS + KS - 1: K rows, V rows, K^T columns
+  const int kv_end = p.causal ? min(p.N, t0 + TQ) : p.N;
+  const int last = (kv_end + BC - 1) / BC - 1;                  // last key tile
   constexpr int RCH = BC * D / CE;                              // chunks of a row tile (and of the transposed one)
-  constexpr int PT = (RCH + NT - 1) / NT;
-  constexpr bool FULL = RCH % NT == 0;
+  constexpr int PT = (KS * RCH + NT - 1) / NT;
+  constexpr bool FULL = KS * RCH % NT == 0;
   constexpr int RCPR = D / CE, TCPR = BC / CE;
   const T* Kg = static_cast<const T*>(p.Kr) + tok_base * D;
   const T* Vg = static_cast<const T*>(p.Vr) + tok_base * D;
   const T* Tg = static_cast<const T*>(p.Krt) + (long)b * D * p.Npad;
   u32x4 kreg[PT], vreg[PT], treg[PT];
-  auto g_load = [&](int tile) {
+  auto g_load = [&](int t) {
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      const int ci = threadIdx.x + i * NT;
-      if (!FULL && ci >= RCH) break;
+      const int at = threadIdx.x + i * NT, ci = at % RCH;
+      if (!FULL && at >= KS * RCH) break;
+      const int tile = min(t * KS + at / RCH, last);
       const int row = ci / RCPR, cc = ci % RCPR;
       kreg[i] = *reinterpret_cast<const u32x4*>(Kg + (long)(tile * BC + row) * D + cc * CE);
       vreg[i] = *reinterpret_cast<const u32x4*>(Vg + (long)(tile * BC + row) * D + cc * CE);
@@ -139,15 +143,15 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
     }
   };
   auto s_store = [&](int stage) {
-    T* ks = smem + (long)stage * L::kStage;
-    T* vs = ks + L::kKElems;
-    T* ts = vs + L::kKElems;
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      const int ci = threadIdx.x + i * NT;
-      if (!FULL && ci >= RCH) break;
+      const int at = threadIdx.x + i * NT, ci = at % RCH;
+      if (!FULL && at >= KS * RCH) break;
+      T* rows = smem + (long)(stage * KS + at / RCH) * L::kStage;
+      T* vs = rows + L::kKElems;
+      T* ts = vs + L::kKElems;
       const int row = ci / RCPR, cc = ci % RCPR;
-      *reinterpret_cast<u32x4*>(ks + row * L::kRow + cc * CE) = kreg[i];
+      *reinterpret_cast<u32x4*>(rows + row * L::kRow + cc * CE) = kreg[i];
       *reinterpret_cast<u32x4*>(vs + row * L::kRow + cc * CE) = vreg[i];
       const int trow = ci / TCPR, tc = ci % TCPR;
       *reinterpret_cast<u32x4*>(ts + trow * L::kTRow + tc * CE) = treg[i];
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
     const float nlse = p.lse[((long)b * p.nH + head) * p.Npad + m];   // -inf for padding tokens
 #pragma unroll
     for (int e = 0; e < 16; ++e) { negl[e] = nlse; negd[e] = -delta; }
-    if (head_ok) {
+    if (head_ok && ks == 0) {
       if (h == 0) p.delta[((long)b * p.nH + head) * p.Npad + m] = -delta;
       T* Qr = static_cast<T*>(p.Qr) + ((tok_base + m) * p.nH + head) * D + 16 * h;
       T* dOr = static_cast<T*>(p.dO) + ((tok_base + m) * p.nH + head) * D + 16 * h;
@@ -200,22 +204,21 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int e = 0; e < 16; ++e) dq[cb][e] = 0.f;
-  const int kv_end = p.causal ? min(p.N, t0 + TQ) : p.N;
-  const int n_tiles = (kv_end + BC - 1) / BC;
-  const int last = n_tiles - 1;
+  const int n_int = last / KS + 1;                              // intervals: tiles of part 0
   const int lim = p.causal ? min(m, p.N - 1) : p.N - 1;         // last key visible to this lane's query
   s_store(0);
   __syncthreads();
-  for (int t = 0; t < n_tiles; ++t) {
-    g_load(min(t + 1, last));
-    const T* st = smem + (long)(t & 1) * L::kStage;
+  for (int t = 0; t < n_int; ++t) {
+    g_load(min(t + 1, n_int - 1));
+    const T* st = smem + (long)((t & 1) * KS + ks) * L::kStage;
     const T* kbase = st + lr * L::kRow + 16 * h;
     const T* vbase = kbase + L::kKElems;
     const T* tbase = st + 2 * L::kKElems + lr * L::kTRow + 16 * h;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int n0 = t * BC + nb * 32;
+      const int n0 = (t * KS + ks) * BC + nb * 32;
       if (p.causal && n0 > tw + 31) continue;                   // every key of the half follows every query
+      if (KS > 1 && n0 >= p.N) continue;                        // a tile past the last one
       // scores start from -log-sum-exp and dP from -delta, so the products form S - lse and dP - delta
       f32x16 s, dp;
       mma32_from(s, negl, load_frag<T>(kbase + nb * 32 * L::kRow), qf[0]);
@@ -237,6 +240,26 @@ __global__ __launch_bounds__(256 * QW) void bwd_dq_kernel(BwdArgs p) {
     }
     s_store((t + 1) & 1);
     __syncthreads();
+  }
+
+  // ---- the other parts' sums, in their order ------------------------------------------------------------
+  if constexpr (KS > 1) {
+    float* sums = reinterpret_cast<float*>(smem_raw);           // [KS - 1][QW * HW][16 CB][64]
+    auto at = [&](int part) { return sums + (long)((part - 1) * QW * HW + wq) * (16 * CB * 64) + lane; };
+    if (ks > 0) {                                               // (behind the loop's last barrier: the tiles are done with)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) at(ks)[(16 * cb + e) * 64] = dq[cb][e];
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int part = 1; part < KS; ++part)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dq[cb][e] += at(part)[(16 * cb + e) * 64];
   }
 
   // ---- epilogue: remove the rotation, store -----------------------------------------------------------
@@ -288,7 +311,8 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
   const int h = lane / 32, lr = lane % 32;
   const bool k_role = wave >= KB;                               // dK^T wave (else dV^T wave)
   const int kb = wave % KB;                                     // key block of this wave
-  const int b = blockIdx.x / p.n_hg, hg = blockIdx.x % p.n_hg;
+  const int n_parts = p.n_hg * p.qsplit;                        // partial sums: head groups, their queries in qsplit parts
+  const int b = blockIdx.x / n_parts, part = blockIdx.x % n_parts, hg = part / p.qsplit;
   const int key0 = blockIdx.y * KT + 32 * kb;                   // first key of this wave
   const int nk = key0 + lr;                                     // this lane's key
   const bool key_ok = nk < p.Npad;
@@ -315,7 +339,8 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
   const int n_heads = min(p.hpg, p.nH - head0);
   const int qb_first = p.causal ? (blockIdx.y * KT) / TQ : 0;
   const int n_qb = p.Npad / TQ - qb_first;                      // >= 1: the grid covers Npad
-  const int n_it = n_heads * n_qb;
+  const int it0 = n_heads * n_qb * (part % p.qsplit) / p.qsplit;        // the pairs of this part
+  const int n_it = n_heads * n_qb * (part % p.qsplit + 1) / p.qsplit;
   // Query blocks are walked from the last one down: the workgroups of one (sequence, head group),
   // which run on the same XCD at the same time, then all read the same block at the same moment
   // (with causal masking their ranges start at different blocks but all end at the last).
@@ -360,15 +385,14 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
     asm volatile("" ::: "memory");
   };
 
-  issue(0, 0);
+  if (it0 < n_it) issue(it0, it0 % NS);
   meet();
-  if (1 < n_it) issue(1, 1);
+  if (it0 + 1 < n_it) issue(it0 + 1, (it0 + 1) % NS);
   // one interval: the dV^T waves work on pair t (stage t % 3), the dK^T waves on pair t-1; behind the meeting pair t+2
   // is fetched into stage (t+2) % 3, which held pair t-1.
-  const int n_int = n_it + 1;
-  for (int t = 0; t < n_int; ++t) {
+  for (int t = it0; t < n_it + 1; ++t) {
     const int it = k_role ? t - 1 : t;                          // pair this wave works on in this interval
-    if (it >= 0 && it < n_it) {
+    if (it >= it0 && it < n_it) {
       const unsigned char* sb = smem_raw + (size_t)(it % NS) * L::kStageBytes;
       const T* qs = reinterpret_cast<const T*>(sb);
       const T* os = qs + L::kRElems;
@@ -457,7 +481,7 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
 
   // rows of the accumulators are stored channel positions: position 16h'+4q'+r of a 32-block
   if (key_ok) {
-    float* dst = (k_role ? p.dKp : p.dVp) + ((long)hg * TP + tok_base + nk) * D + 4 * h;
+    float* dst = (k_role ? p.dKp : p.dVp) + ((long)part * TP + tok_base + nk) * D + 4 * h;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -469,25 +493,64 @@ __global__ __launch_bounds__(128 * KB) void bwd_dkv_kernel(BwdArgs p) {
 // ---- sum of the head-group partials, rotation removed from the key part -----------------------------
 // The scores carry a factor log2(e) (the per-head query is pre-scaled so that the softmax runs on
 // exp2), so the key gradient formed from those queries is multiplied by ln 2 here.
-template <typename T>
+// SP threads share the partials of a channel quad (every SP-th each, four loads of either kind in flight): with few tokens one
+// thread's chain of loads is what the launch takes (D = 64, 2 x 509 tokens, 48 partials 7.1 us, 17.3 with one thread, 8.9 with
+// eight loads of it in flight; 32 partials of 150 tokens, D = 128: 12.1 -> 64 of them 6.9).  With many tokens the launch reads at 5.8
+// TB/s as it is.
+template <typename T, int SP>
 __global__ __launch_bounds__(256) void kv_reduce_kernel(KvReduceArgs a) {
+  constexpr int QT = 256 / SP;                                  // quads of a workgroup
   const long TP = (long)a.Bsz * a.Npad;
   const int quads = a.D / 4;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= TP * quads) return;
-  const long tp = idx / quads;
+  const long idx = (long)blockIdx.x * QT + threadIdx.x % QT;
+  const bool live = idx < TP * quads;
+  if (SP == 1 && !live) return;
+  const long tp = live ? idx / quads : 0;
   const int k = (int)(idx % quads);
   const int n = (int)(tp % a.Npad);
   f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
   // the partials hold channel quad k at its stored (acc-order) position inside its 32-block
   const int c32 = (4 * k) % 32;
   const int spos = (4 * k) / 32 * 32 + 16 * ((c32 / 4) % 2) + 4 * (c32 / 8);
-  for (int g = 0; g < a.n_hg; ++g) {
-    const long off = ((long)g * TP + tp) * a.D + spos;
-    const f32x4 x = *reinterpret_cast<const f32x4*>(a.dKp + off);
-    const f32x4 y = *reinterpret_cast<const f32x4*>(a.dVp + off);
+  if constexpr (SP == 1) {
+    for (int g = 0; g < a.n_hg; ++g) {
+      const long off = ((long)g * TP + tp) * a.D + spos;
+      const f32x4 x = *reinterpret_cast<const f32x4*>(a.dKp + off);
+      const f32x4 y = *reinterpret_cast<const f32x4*>(a.dVp + off);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { sk[e] += x[e]; sv[e] += y[e]; }
+      for (int e = 0; e < 4; ++e) { sk[e] += x[e]; sv[e] += y[e]; }
+    }
+  } else {
+    constexpr int RD = 4;
+    const int part = threadIdx.x / QT;
+    for (int g0 = part; g0 < a.n_hg; g0 += RD * SP) {
+      f32x4 x[RD], y[RD];
+#pragma unroll
+      for (int r = 0; r < RD; ++r) {
+        const long off = ((long)min(g0 + r * SP, a.n_hg - 1) * TP + tp) * a.D + spos;
+        x[r] = *reinterpret_cast<const f32x4*>(a.dKp + off);
+        y[r] = *reinterpret_cast<const f32x4*>(a.dVp + off);
+      }
+#pragma unroll
+      for (int r = 0; r < RD; ++r)
+        if (g0 + r * SP < a.n_hg)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { sk[e] += x[r][e]; sv[e] += y[r][e]; }
+    }
+    __shared__ f32x4 sums[SP - 1][2][QT];
+    if (part > 0) {
+      sums[part - 1][0][threadIdx.x % QT] = sk;
+      sums[part - 1][1][threadIdx.x % QT] = sv;
+    }
+    __syncthreads();
+    if (part > 0 || !live) return;
+#pragma unroll
+    for (int q = 0; q < SP - 1; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sk[e] += sums[q][0][threadIdx.x][e];
+        sv[e] += sums[q][1][threadIdx.x][e];
+      }
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) sk[e] *= kLn2;
@@ -510,22 +573,30 @@ __global__ __launch_bounds__(256) void kv_reduce_kernel(KvReduceArgs a) {
 }
 
 // ---- launchers ---------------------------------------------------------------------------------------
-template <typename T, int D, int BC, int QW>
+template <typename T, int D, int BC, int QW, int HW, int KS>
 static hipError_t dq_launch(const BwdArgs& a, hipStream_t s) {
-  dim3 grid(((a.nH + 3) / 4) * a.Bsz, a.Npad / (32 * QW));
-  const size_t smem = DqLds<T, D, BC>::kBytes;
-  auto kern = bwd_dq_kernel<T, D, BC, QW>;
+  dim3 grid(((a.nH + HW - 1) / HW) * a.Bsz, a.Npad / (32 * QW));
+  const size_t smem = KS * DqLds<T, D, BC>::kBytes;
+  auto kern = bwd_dq_kernel<T, D, BC, QW, HW, KS>;
   static LdsOnce lds_once;
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  hipLaunchKernelGGL(kern, grid, dim3(256 * QW), smem, s, a);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * QW * HW * KS), smem, s, a);
   return hipGetLastError();
 }
-// Fewer workgroups than compute units: one block of queries each, so that a wave has a SIMD to itself (two sequences
-// of 509 tokens, 12 heads, D = 64 in fp32: 112 -> 70 us).  The same below with the keys (81 -> 54 us).
+// Fewer workgroups than compute units: one block of queries each, so that a wave has a SIMD to itself, and its keys dealt
+// to two waves, or four.  One block of queries and one, two, four waves (us): fp32, D = 64, 12 heads, 2 x 509 tokens 70.1,
+// 44.5; 5 x 100 28.0, 21.4; bf16, D = 64, 1024 tokens 29.6, 22.2; D = 128 (tiles of 32 keys when they are shared), 32 heads, 450
+// tokens 31.1, 25.5, 900 tokens (464 workgroups) 46.6, 48.7; D = 32, 4 heads, 512 tokens 12.1, 9.1, 7.8.
 template <typename T, int D, int BC>
 static hipError_t dq_one(const BwdArgs& a, hipStream_t s) {
-  const long wgs = (long)((a.nH + 3) / 4) * a.Bsz * (a.Npad / 64);
-  return wgs < kComputeUnits ? dq_launch<T, D, BC, 1>(a, s) : dq_launch<T, D, BC, 2>(a, s);
+  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
+  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return dq_launch<T, D, BC, 2, 4, 1>(a, s);
+  if constexpr (D == 32)
+    if (tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return dq_launch<T, D, BC, 1, 1, 4>(a, s);
+  constexpr int SC = 2 * DqLds<T, D, BC>::kBytes <= 160 * 1024 ? BC : 32;   // keys of a tile that is shared
+  if constexpr (2 * DqLds<T, D, SC>::kBytes <= 160 * 1024)
+    if (tiles >= 2 && (a.nH + 1) / 2 * blocks <= kComputeUnits) return dq_launch<T, D, SC, 1, 2, 2>(a, s);
+  return dq_launch<T, D, BC, 1, 4, 1>(a, s);
 }
 
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {
@@ -545,11 +616,12 @@ hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// Few workgroups: 64 keys each instead of 128 (fp32, D = 64, 12 heads, 2 x 509 tokens: 81 -> 54 us).
 template <typename T, int D, int TQ, int KB>
 static hipError_t dkv_launch(const BwdArgs& a, hipStream_t s) {
   using L = DkvLds<T, D, TQ, KB>;
   static_assert(L::kBytes <= 160 * 1024, "fits the LDS of a compute unit");
-  dim3 grid(a.n_hg * a.Bsz, (a.Npad + 32 * KB - 1) / (32 * KB));
+  dim3 grid(a.n_hg * a.qsplit * a.Bsz, (a.Npad + 32 * KB - 1) / (32 * KB));
   auto kern = bwd_dkv_kernel<T, D, TQ, KB>;
   static LdsOnce lds_once;
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, L::kBytes); ae != hipSuccess) return ae;
@@ -558,7 +630,7 @@ static hipError_t dkv_launch(const BwdArgs& a, hipStream_t s) {
 }
 template <typename T, int D, int TQ>
 static hipError_t dkv_one(const BwdArgs& a, hipStream_t s) {
-  const long wgs = (long)a.n_hg * a.Bsz * ((a.Npad + 127) / 128);
+  const long wgs = (long)a.n_hg * a.qsplit * a.Bsz * ((a.Npad + 127) / 128);
   return wgs < kComputeUnits ? dkv_launch<T, D, TQ, 2>(a, s) : dkv_launch<T, D, TQ, 4>(a, s);
 }
 
@@ -579,13 +651,14 @@ hipError_t launch_bwd_dkv(int dtype, const BwdArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_kv_reduce(int dtype, const KvReduceArgs& a, hipStream_t s) {
+template <typename T> static void kv_reduce(const KvReduceArgs& a, hipStream_t s) {
   const long total = (long)a.Bsz * a.Npad * (a.D / 4);
-  const int blocks = (int)((total + 255) / 256);
-  if (dtype == 0)
-    hipLaunchKernelGGL(kv_reduce_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(kv_reduce_kernel<bf16>, dim3(blocks), dim3(256), 0, s, a);
+  if (total <= 256l * kComputeUnits) hipLaunchKernelGGL((kv_reduce_kernel<T, 4>), dim3((total + 63) / 64), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((kv_reduce_kernel<T, 1>), dim3((total + 255) / 256), dim3(256), 0, s, a);
+}
+hipError_t launch_kv_reduce(int dtype, const KvReduceArgs& a, hipStream_t s) {
+  if (dtype == 0) kv_reduce<float>(a, s);
+  else kv_reduce<bf16>(a, s);
   return hipGetLastError();
 }
 

@@ -13,9 +13,9 @@
 // partner lane, and accumulators turn into the next product's operand without any
 // cross-lane movement (see the fragment model in common.h).
 //
-// Workgroup = QW x HW waves = HW heads x (32*QB*QW) queries; K/V tile = BC keys, double buffered.
-// Built as 8 waves (4 heads x 2 query blocks of 32; waves w and w+4 share a SIMD), and as 4 waves (one query
-// block) for calls with few workgroups: see the launcher.
+// Workgroup = QW x HW x KS waves = HW heads x (32*QB*QW) queries, whose keys KS waves share; K/V tile = BC keys, one for
+// each of the KS parts, double buffered.  Built as 8 waves (4 heads x 2 query blocks of 32; waves w and w+4 share a
+// SIMD), and as 4 waves (one query block; keys in one, two or four parts) for calls with few workgroups: see the launcher.
 #include <type_traits>
 
 #include "common.h"
@@ -32,17 +32,18 @@ template <typename T, int D, int BC> struct AttnLds {
   static constexpr size_t kBytes = 2ul * kStageElems * sizeof(T);
 };
 
-template <typename T, int D, int QB, int BC, int QW, int HW>
-__global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) {
+template <typename T, int D, int QB, int BC, int QW, int HW, int KS>
+__global__ __launch_bounds__(64 * QW * HW * KS) void attn_prefill_kernel(AttnArgs p) {
   // QW x HW waves: wave (qw, hw) owns 32*QB queries of one head; the workgroup covers
   // TQ = 32*QB*QW consecutive tokens of HW heads
-  constexpr int CB = D / 32, NB = BC / 32, TQ = 32 * QB * QW, NT = 64 * QW * HW;
+  constexpr int CB = D / 32, NB = BC / 32, TQ = 32 * QB * QW, NT = 64 * QW * HW * KS;
   constexpr int CE = 16 / sizeof(T);                            // elements per 16-byte chunk
   using L = AttnLds<T, D, BC>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   T* smem = reinterpret_cast<T*>(smem_raw);
 
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int ks = wave / (QW * HW), wq = wave % (QW * HW);       // part of the keys; wave within the part
   const int h = lane / 32, lr = lane % 32;
   const int n_qtiles = p.Npad / TQ;
   // blockIdx.x = (head group, sequence) varies fastest, blockIdx.y = query tile: workgroups are
@@ -55,14 +56,14 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   int item = blockIdx.x;
   if (gridDim.x % 8 == 0) item = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
   const int b = item / n_hg;
-  const int head_raw = (item % n_hg) * HW + wave / QW;
+  const int head_raw = (item % n_hg) * HW + wq / QW;
   const bool head_ok = head_raw < p.nH;
   const int head = head_ok ? head_raw : p.nH - 1;
   const int t0 = qt * TQ;                                       // first token of the workgroup
-  const int tw = t0 + (wave % QW) * 32 * QB;                    // first token of this wave
+  const int tw = t0 + (wq % QW) * 32 * QB;                      // first token of this wave
   const long tok_base = (long)b * p.Npad;
   if (TQ < 64 && t0 >= p.N) {                                   // nothing but padding tokens: see the epilogue
-    if (head_ok) {
+    if (head_ok && ks == 0) {
       const int m = tw + lr;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
@@ -86,29 +87,33 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   constexpr int WK = KCPR >= 16 ? 1 : 16 / KCPR, MK = (KCPR >= 16 ? 16 : KCPR) - 1;
   constexpr int WV = VCPR >= 16 ? 1 : 16 / VCPR, MV = (VCPR >= 16 ? 16 : VCPR) - 1;
   static_assert(KCH % 64 == 0 && VCH % 64 == 0, "whole 1 KB pieces");
-  auto dma_load = [&](int ktile, int vtile, int stage) {
-    T* ks = smem + (long)stage * L::kStageElems;
-    T* vs = ks + L::kKElems;
+  // key tiles of interval t: the KS parts take tiles t KS, t KS + 1, ...; those past the last one are masked where they are used
+  const int kv_end = p.causal ? min(p.N, t0 + TQ) : p.N;        // keys needed: causal -> 0 .. t0+TQ-1 (clipped to N), else 0 .. N-1
+  const int last_tile = (kv_end + BC - 1) / BC - 1;
+  constexpr int KP = KCH / 64, VP = VCH / 64;                    // 1 KB pieces of a K, of a V^T tile
+  auto dma_load = [&](int kt, int vt, int stage) {
+    T* base = smem + (long)stage * KS * L::kStageElems;
 #pragma unroll
-    for (int i = 0; i < (KCH / 64 + NWV - 1) / NWV; ++i) {
-      const int q = i * NWV + wave;                              // 1 KB piece of the K tile
-      if (q < KCH / 64) {
-        const int ci = q * 64 + lane, row = ci / KCPR, pos = ci % KCPR;
+    for (int i = 0; i < (KS * KP + NWV - 1) / NWV; ++i) {
+      const int q = i * NWV + wave, g = q / KP;
+      if (q < KS * KP) {
+        const int ci = (q % KP) * 64 + lane, row = ci / KCPR, pos = ci % KCPR;
         const int c = pos ^ ((row / WK) & MK);
-        const T* g = Kg + (long)(ktile * BC + row) * D + c * CE;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                         (__attribute__((address_space(3))) void*)(ks + q * 64 * CE), 16, 0, 0);
+        const T* src = Kg + (long)(min(kt * KS + g, last_tile) * BC + row) * D + c * CE;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(base + g * L::kStageElems + (q % KP) * 64 * CE), 16, 0, 0);
       }
     }
 #pragma unroll
-    for (int i = 0; i < (VCH / 64 + NWV - 1) / NWV; ++i) {
-      const int q = i * NWV + wave;
-      if (q < VCH / 64) {
-        const int ci = q * 64 + lane, row = ci / VCPR, pos = ci % VCPR;
+    for (int i = 0; i < (KS * VP + NWV - 1) / NWV; ++i) {
+      const int q = i * NWV + wave, g = q / VP;
+      if (q < KS * VP) {
+        const int ci = (q % VP) * 64 + lane, row = ci / VCPR, pos = ci % VCPR;
         const int c = pos ^ ((row / WV) & MV);
-        const T* g = Vg + (long)row * p.Npad + vtile * BC + c * CE;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                         (__attribute__((address_space(3))) void*)(vs + q * 64 * CE), 16, 0, 0);
+        const T* src = Vg + (long)row * p.Npad + min(vt * KS + g, last_tile) * BC + c * CE;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(base + g * L::kStageElems + L::kKElems + (q % VP) * 64 * CE),
+                                         16, 0, 0);
       }
     }
   };
@@ -231,9 +236,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
       for (int e = 0; e < 16; ++e) oacc[qb][cb][e] = 0.f;
   }
 
-  // keys needed: causal -> 0 .. t0+TQ-1 (clipped to N), else 0 .. N-1
-  const int kv_end = p.causal ? min(p.N, t0 + TQ) : p.N;
-  const int n_tiles = (kv_end + BC - 1) / BC;
+  const int n_tiles = last_tile / KS + 1;                       // intervals: tiles of part 0
 
   // The two waves that share a SIMD (waves w and w+4) go through a key tile in opposite order, so
   // that one is in its MFMA phase while the other is in its softmax (VALU) phase:
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   auto mfma_phase = [&](auto pv_c, auto ss_c, int tile) {
     constexpr bool PV = decltype(pv_c)::value, SS = decltype(ss_c)::value;
     constexpr int NPV = PV ? CB * NB : 0, NSS = SS ? NB * CB : 0, TOT = NPV + NSS;
-    const T* st = smem + (long)(tile & 1) * L::kStageElems;    // K(tile) and V(tile-1) share a stage
+    const T* st = smem + (long)((tile & 1) * KS + ks) * L::kStageElems;   // K(tile) and V(tile-1) share a stage
     const T* kbase = st + lr * L::kKRowElems;
     const T* vbase = st + L::kKElems + lr * L::kVRowElems;
     constexpr int FC = 16 / CE;                                   // 16-byte chunks per fragment half-slice
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   constexpr std::true_type kYes{};
   constexpr std::false_type kNo{};
   auto do_softmax = [&](int tile) {                             // s of `tile` -> pf, running sums
-    const int n0 = tile * BC;
+    const int n0 = (tile * KS + ks) * BC;
     // mask: keys beyond the sequence, and (causal) keys after the query
     const bool need_mask = (n0 + BC > p.N) || (p.causal && n0 + BC - 1 > t0);
     if (need_mask) {
@@ -385,6 +388,40 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
     mfma_phase(kYes, kNo, n_tiles);
   }
 
+  // ---- the other parts' sums, scaled to a common reference (a part without a visible key has l = 0 and O = 0) ------------
+  if constexpr (KS > 1) {
+    static_assert(QB == 1, "one query block");
+    __syncthreads();                                            // K and V are done with
+    float* sums = reinterpret_cast<float*>(smem_raw);           // [KS - 1][QW * HW][16 CB + 2][64]
+    auto at = [&](int part) { return sums + (long)((part - 1) * QW * HW + wq) * ((16 * CB + 2) * 64) + lane; };
+    if (ks > 0) {
+      float* to = at(ks);
+      to[0] = m_ref[0];
+      to[64] = l_run[0];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) to[(2 + 16 * cb + e) * 64] = oacc[0][cb][e];
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int part = 1; part < KS; ++part) {
+      const float* from = at(part);
+      const float mp = from[0], lp = from[64];
+      // (either half of a row may hold no probability of its own: the reference is that of the row)
+      const bool has = halves_sum(lp) != 0.f;
+      const float top = has ? fmaxf(m_ref[0], mp) : m_ref[0];
+      const float mine = fast_exp2(m_ref[0] - top), theirs = has ? fast_exp2(mp - top) : 0.f;
+      m_ref[0] = top;
+      l_run[0] = l_run[0] * mine + lp * theirs;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[0][cb][e] = oacc[0][cb][e] * mine + from[(2 + 16 * cb + e) * 64] * theirs;
+    }
+  }
+
   // ---- epilogue: normalise, store O[tok][head][c] (acc order in c) -------------------------
   // Rows of padding tokens (N <= m < Npad) are written as zeros, and their negated log-sum-exp as -inf,
   // so that a pass over all padded rows (the backward kernels) sees no undefined values.
@@ -408,29 +445,36 @@ __global__ __launch_bounds__(64 * QW * HW) void attn_prefill_kernel(AttnArgs p) 
   }
 }
 
-template <typename T, int D, int QB, int BC, int QW, int HW>
+template <typename T, int D, int QB, int BC, int QW, int HW, int KS>
 static hipError_t launch_one(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {
   constexpr int TQ = 32 * QB * QW;
   static_assert(64 % TQ == 0, "whole tiles of the padded tokens");
   dim3 grid(((a.nH + HW - 1) / HW) * a.Bsz, a.Npad / TQ);
-  size_t smem = AttnLds<T, D, BC>::kBytes;
-  auto kern = attn_prefill_kernel<T, D, QB, BC, QW, HW>;
+  size_t smem = KS * AttnLds<T, D, BC>::kBytes;
+  auto kern = attn_prefill_kernel<T, D, QB, BC, QW, HW, KS>;
   static LdsOnce lds_once;                                       // one per kernel instantiation
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
-  if (k0 != nullptr && k1 != nullptr) hipExtLaunchKernelGGL(kern, grid, dim3(64 * QW * HW), (uint32_t)smem, s, k0, k1, 0, a);
-  else hipLaunchKernelGGL(kern, grid, dim3(64 * QW * HW), smem, s, a);
+  if (k0 != nullptr && k1 != nullptr) hipExtLaunchKernelGGL(kern, grid, dim3(64 * QW * HW * KS), (uint32_t)smem, s, k0, k1, 0, a);
+  else hipLaunchKernelGGL(kern, grid, dim3(64 * QW * HW * KS), smem, s, a);
   return hipGetLastError();
 }
 
 // Two waves of a SIMD that take turns on the matrix pipe use it best (D = 128, bf16: 64 queries x 4 heads in
 // 8 waves), but only where there is a workgroup for every compute unit.  With fewer, the waves of a query block get a
-// SIMD each: two sequences of 509 tokens, 12 heads, D = 64 in fp32 78 -> 48 us; 333 tokens, 32 heads, D = 128 in bf16
-// 19.8 -> 18.4 us.
+// SIMD each, and its keys are dealt to two waves, or four, whose sums meet in LDS: a launch is then as long as its longest
+// chain of key tiles.  One wave, two, four (us): fp32, D = 64, 12 heads, 2 x 509 tokens 46.5, 30.5, 29.4; 1 x 1024 86.4, 53.7,
+// 43.2; 3 x 197 25.0, 19.8, 15.9; bf16, D = 128, 32 heads, 333 tokens 18.6, 15.4; D = 64, 12 heads, 1000 tokens 24.2, 17.3, 19.4;
+// 4 x 300 12.7, 11.9, 17.9; 8 x 197 (384 workgroups of two heads) 11.4, 12.8; 2 x 1000 (384, 16 tiles) the pass 40.2, 35.0, 6 x 577
+// (720) 45.5, 47.4; D = 32, 4 heads, 512 tokens 12.0, 9.5, 8.0; two tiles only: 11.5, 12.2.
 template <typename T, int D, int BC>
 static hipError_t launch_sized(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {
-  const long wgs = (long)((a.nH + 3) / 4) * a.Bsz * (a.Npad / 64);
-  if (wgs < kComputeUnits) return launch_one<T, D, 1, BC, 1, 4>(a, s, k0, k1);
-  return launch_one<T, D, 1, BC, 2, 4>(a, s, k0, k1);
+  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
+  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return launch_one<T, D, 1, BC, 2, 4, 1>(a, s, k0, k1);
+  if constexpr (4 * AttnLds<T, D, BC>::kBytes <= 160 * 1024 && (sizeof(T) == 4 || D == 32))
+    if (tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return launch_one<T, D, 1, BC, 1, 1, 4>(a, s, k0, k1);
+  const long halves = (a.nH + 1) / 2 * blocks;
+  if ((tiles >= 3 && halves <= kComputeUnits) || (tiles >= 8 && halves <= kComputeUnits * 3 / 2)) return launch_one<T, D, 1, BC, 1, 2, 2>(a, s, k0, k1);
+  return launch_one<T, D, 1, BC, 1, 4, 1>(a, s, k0, k1);
 }
 
 hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {

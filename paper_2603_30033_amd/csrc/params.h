@@ -144,6 +144,7 @@ struct BwdArgs {
   int Bsz, N, Npad, nH, R2, RT2, D;
   int causal, pos0;
   int hpg, n_hg;       // heads per group and number of groups of the key/value gradient kernel
+  int qsplit;          // parts of a group's (head, query block) pairs; [n_hg * qsplit] partial gradients
 };
 
 // dLat[tp][col0 + c] from the partial key/value gradients: keys un-rotated; with a shared latent

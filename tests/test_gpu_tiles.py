@@ -150,3 +150,15 @@ def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared,
         y = to_host(layer.forward(to_device(inp["X"], w.dtype)))
         assert "attention_and_merge" in [n for n, _ in ta.tucker_attn_profile_read(layer.ctx)]
     check(y, oracle_forward(w, inp), w.dtype, repr(w))
+
+
+# few workgroups: the keys of a query block dealt to two and to four waves, with a remainder and with parts that hold no visible
+# key; the query blocks of a head dealt to two and to four workgroups (all gradients, no RoPE offset and an odd head count)
+@pytest.mark.parametrize("dtype,B,N,heads,r3,causal", [
+    ("bf16", 1, 129, 3, 128, True), ("bf16", 1, 513, 5, 64, True), ("bf16", 2, 321, 4, 64, False), ("bf16", 1, 450, 3, 32, True),
+    ("bf16", 2, 65, 3, 32, False), ("f32", 1, 65, 3, 64, True), ("f32", 1, 225, 5, 64, False), ("f32", 1, 97, 3, 32, True),
+    ("f32", 3, 160, 3, 128, True), ("f32", 1, 96, 2, 128, False),
+])
+def test_attention_with_shared_keys(dtype, B, N, heads, r3, causal):
+    run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
+                       dtype=dtype, causal=causal, seed=59))
