@@ -162,3 +162,26 @@ def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared,
 def test_attention_with_shared_keys(dtype, B, N, heads, r3, causal):
     run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
                        dtype=dtype, causal=causal, seed=59))
+
+
+# head-mixed cores: slices in batches of 4, 8 and 16 with remainders, head counts off the four of a tile, rows of a core that are no
+# whole quads (prefill through the preparation launch, the last row as a decode step with the tiles in the projection's)
+@pytest.mark.parametrize("dtype,heads,r1,r2,r3", [
+    ("f32", 1, 1, 32, 32), ("bf16", 5, 3, 40, 30), ("f32", 7, 5, 33, 22), ("bf16", 9, 9, 48, 64), ("f32", 18, 17, 96, 32),
+    ("bf16", 34, 33, 72, 40), ("bf16", 64, 64, 32, 32),
+])
+def test_mixed_cores(dtype, heads, r1, r2, r3):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=2, N=40, d_model=64, n_heads=heads, d_head=32, r1=r1, r2=r2, r3=r3, dtype=dtype,
+                  seed=60)
+    inp = wl.make_inputs(w)
+    ref = oracle_forward(w, inp)
+    check(run_forward(w, inp), ref, dtype, repr(w))
+    if r3 % 8 == 0:                                              # whole 16-byte chunks: what a decode step takes
+        with Layer(w, inp) as layer:
+            X = to_device(inp["X"], dtype)
+            K, V = (torch.zeros(2, 40, r3, dtype=X.dtype, device="cuda") for _ in range(2))
+            ws = torch.empty(ta.tucker_attn_workspace_bytes(layer.ctx, 2, 39), dtype=torch.uint8, device="cuda")
+            head = X[:, :39].contiguous()
+            ta.tucker_attn_forward(layer.ctx, layer.weights, head, torch.empty_like(head), 0, K, V, ws)
+            y = to_host(layer.decode(X[:, 39].contiguous(), K, V, [40, 40]))
+        check(y, ref[:, 39], dtype, repr(w))
