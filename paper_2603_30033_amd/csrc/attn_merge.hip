@@ -232,7 +232,8 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnMergeArgs p) {
             for (int e = 0; e < 16; ++e) s[i][e] = fast_exp2(s[i][e]);
           }
           const Frag<T> pf = to_frag<T>(s[i]);
-          if (!p.ones) l_run[i] = block_sum(s[i], l_run[i]);
+          // the rounded probabilities, as they are multiplied: a row of one key then has the value itself as its result
+          if (!p.ones) l_run[i] = frag_sum(pf, l_run[i]);
 #pragma unroll
           for (int c = 0; c < CB; ++c) mma32(o[i][c], v[c], pf);
         }
