@@ -456,7 +456,6 @@ int decode_impl(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* x,
     g.Qlat = ws.Qlat; g.R2 = c->R2; g.Kr = nullptr; g.D = c->D; g.Vt = nullptr;
     g.Kcache = Kb; g.Vcache = Vb; g.Lmax = Lmax; g.r3 = f.r3; g.rt3 = f.rt3;
     g.rope = c->rope; g.rope_ld = f.max_positions; g.pos0 = 0; g.decode = 1;
-    for (int b = 0; b < Bc; ++b) g.kv_pos[b] = len[b] - 1;
     g.ksplit = decode_ksplit(g.K); g.part = ws.part;              // the query launch sums the partial tiles
     if (direct) {
       if (g.ksplit < 2) g.ksplit = 2;                             // always partial tiles on this path

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
               for (int r = 0; r < 4; ++r) acc[4 * q + r] += v[u][q][r];
       }
     }
-    epilogue_block<T>(g, acc, m0, tok);
+    epilogue_block<T>(g, acc, m0, tok, p.kv_len[min(tok, p.Bsz - 1)] - 1);
     return;
   }
 

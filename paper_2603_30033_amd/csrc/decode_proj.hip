@@ -15,8 +15,8 @@
 
 namespace ta {
 
-template <typename T>
-__global__ __launch_bounds__(256) void decode_proj_kernel(DecodeProjArgs a, PrepArgs prep) {
+template <typename T, bool PREP>
+__device__ __forceinline__ void decode_proj(const DecodeProjArgs& a, const PrepArgs& prep) {
   constexpr int CE = 16 / (int)sizeof(T);
   constexpr int TS = 32 + CE;                                     // padded tile row, elements
   constexpr int CPRW = 32 / CE;                                   // 16-byte chunks per tile row
@@ -27,11 +27,11 @@ __global__ __launch_bounds__(256) void decode_proj_kernel(DecodeProjArgs a, Prep
                                                     : (kPrepBytes > kRedBytes ? kPrepBytes : kRedBytes);
   __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
 
-  if ((int)blockIdx.x < prep.total_blocks) {                      // ---- a weight-preparation tile
+  if (PREP && (int)blockIdx.x < prep.total_blocks) {              // ---- a weight-preparation tile
     prep_tile<T>(prep, blockIdx.x, reinterpret_cast<float(*)[kPrepTile + 1]>(smem));
     return;
   }
-  const int wg = blockIdx.x - prep.total_blocks;
+  const int wg = blockIdx.x - (PREP ? prep.total_blocks : 0);
   const int Mp = a.R2 + (a.shared_kv ? 1 : 2) * a.D;
   const int nmb = Mp / 32;
   const int mb = wg % nmb, z = wg / nmb;
@@ -108,13 +108,21 @@ __global__ __launch_bounds__(256) void decode_proj_kernel(DecodeProjArgs a, Prep
   }
 }
 
+template <typename T> __global__ __launch_bounds__(256) void decode_proj_prep_kernel(DecodeProjArgs a, PrepArgs prep) {
+  decode_proj<T, true>(a, prep);
+}
+// with weights prepared before: without the preparation's 712 bytes of arguments
+template <typename T> __global__ __launch_bounds__(256) void decode_proj_kernel(DecodeProjArgs a) { decode_proj<T, false>(a, PrepArgs{}); }
+
+template <typename T> static void decode_proj_one(const DecodeProjArgs& a, const PrepArgs& prep, int blocks, hipStream_t s) {
+  if (prep.total_blocks > 0) hipLaunchKernelGGL(decode_proj_prep_kernel<T>, dim3(prep.total_blocks + blocks), dim3(256), 0, s, a, prep);
+  else hipLaunchKernelGGL(decode_proj_kernel<T>, dim3(blocks), dim3(256), 0, s, a);
+}
 hipError_t launch_decode_proj(int dtype, const DecodeProjArgs& a, const PrepArgs& prep, hipStream_t s) {
   const int Mp = a.R2 + (a.shared_kv ? 1 : 2) * a.D;
-  const int blocks = prep.total_blocks + (Mp / 32) * a.ksplit;
-  if (dtype == 0)
-    hipLaunchKernelGGL(decode_proj_kernel<float>, dim3(blocks), dim3(256), 0, s, a, prep);
-  else
-    hipLaunchKernelGGL(decode_proj_kernel<bf16>, dim3(blocks), dim3(256), 0, s, a, prep);
+  const int blocks = (Mp / 32) * a.ksplit;
+  if (dtype == 0) decode_proj_one<float>(a, prep, blocks, s);
+  else decode_proj_one<bf16>(a, prep, blocks, s);
   return hipGetLastError();
 }
 

@@ -8,7 +8,8 @@ namespace ta {
 
 // ---- epilogues: one 32x32 accumulator block = 32 weight rows (m0..) x 32 tokens ----------
 template <typename T>
-__device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, int m0, int tp) {
+// decode_pos: position (and cache row) of the sequence's one token in a decode step
+__device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, int m0, int tp, int decode_pos = 0) {
   const int lane = threadIdx.x % kWave;
   const int h = lane / 32;
   const int TP = g.Bsz * g.Npad;
@@ -17,7 +18,7 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, in
   const bool valid = n < g.N;
 
   if (g.epi == 0) {
-    const int pos = g.decode ? g.kv_pos[b] : g.pos0 + n;
+    const int pos = g.decode ? decode_pos : g.pos0 + n;
     if (m0 < g.R2) {                                            // ---- Qlat, acc order
       T* dst = static_cast<T*>(g.Qlat) + (long)tp * g.R2 + m0 + 16 * h;
       store_frag<T>(dst, to_frag<T>(acc));

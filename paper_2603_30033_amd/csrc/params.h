@@ -35,6 +35,7 @@ struct PrepArgs {
   int total_blocks;
 };
 
+// (Launch arguments are kept short: on the host a launch takes 2.9 us with 16 bytes of them, 3.6 with 512, 4.9 with 1024.)
 // ---- generic product  acc[m][tok] = sum_k A[m][k] * Btok[tok][k]  with three epilogues ---
 struct GemmArgs {
   const void* A;        // [M][lda] weights side (rows beyond M read as zero)
@@ -63,8 +64,7 @@ struct GemmArgs {
   int rope_ld;
   int pos0;
   int shared_kv;                // 1: no V rows in A; the K block also yields Vt, and the cache row, UNROTATED
-  int decode;                   // 1: one token per sequence, position/cache row from kv_pos[b]
-  int kv_pos[32];
+  int decode;                   // 1: one token per sequence, at the position its caller names
   // Z / Y
   void* Out; long ldo;          // Z: [TP][ldo] natural order;  Y: [B][N][ldo] natural order
   // split-K (decode-sized token counts): ksplit > 1 writes fp32 partial tiles to part
