@@ -422,7 +422,8 @@ __global__ __launch_bounds__(256) void extract_factor_kernel(const double* G, in
     }
     __syncthreads();
   }
-  const double scale = (g[best_j[0]] < 0.0 ? -1.0 : 1.0) / sqrt(norms2[src]);
+  const int at = best_j[0] < len ? best_j[0] : 0;       // (a row without a number has no largest entry; the caller refuses it)
+  const double scale = (g[at] < 0.0 ? -1.0 : 1.0) / sqrt(norms2[src]);
   for (int j = threadIdx.x; j < len; j += 256) {
     const double v = scale * g[j];
     U64[(long)j * r + k] = v;
@@ -487,15 +488,34 @@ hipError_t enqueue_small_jacobi(hipStream_t s, double* G, int m, int* counter) {
   hipLaunchKernelGGL((jacobi_block_kernel<4, true>), dim3(1), dim3(256), 0, s, G, m, m, 0, tol, 0.0, counter, 60);
   return hipGetLastError();
 }
+// idx: rows in the order of their norms, largest first (the first of equal ones first); any order where they are no numbers
+__global__ __launch_bounds__(64) void small_order_kernel(const double* norms2, int m, int* idx) {
+  const int i = threadIdx.x;
+  if (i < m) idx[i] = i;
+  __syncthreads();
+  if (i >= m) return;
+  int rank = 0;
+  for (int j = 0; j < m; ++j) rank += norms2[j] > norms2[i] || (norms2[j] == norms2[i] && j < i);
+  idx[rank] = i;
+}
+// Enqueues the second half: norms, order, factor.  The host looks at norms2 and counter later (check_small_jacobi).
 template <typename T>
-int finish_small_jacobi(hipStream_t s, const double* G, int m, int r, double* norms2, int* idx, const int* counter, double* U64,
-                        T* U, double* sv, JacobiStats* stats) {
-  int sweeps = 0;
-  CK(hipMemcpyAsync(&sweeps, counter, sizeof(int), hipMemcpyDeviceToHost, s));
-  CK(hipStreamSynchronize(s));
+hipError_t finish_small_jacobi(hipStream_t s, const double* G, int m, int r, double* norms2, int* idx, double* U64, T* U) {
+  hipLaunchKernelGGL(row_norms_kernel, dim3(m), dim3(256), 0, s, G, m, norms2);
+  hipLaunchKernelGGL(small_order_kernel, dim3(1), dim3(64), 0, s, norms2, m, idx);
+  hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, G, m, idx, norms2, r, U64, U);
+  return hipGetLastError();
+}
+// what the iteration has to have given, by its norms on the host: as order_and_extract
+int check_small_jacobi(const double* norms2, int m, int r, int sweeps, double* sv, JacobiStats* stats) {
   if (stats) stats->sweeps += m > 1 ? sweeps : 0;
   if (sweeps == 0) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
-  return order_and_extract<T>(s, G, m, r, norms2, idx, U64, U, sv);
+  std::vector<double> h(norms2, norms2 + m);
+  const double tiny = 1e-28 * m * std::accumulate(h.begin(), h.end(), 0.0);
+  std::stable_sort(h.begin(), h.end(), [](double x, double y) { return x > y; });
+  if (sv)
+    for (int k = 0; k < m; ++k) sv[k] = std::sqrt(std::sqrt(h[k]));   // row norm = eigenvalue = sigma^2
+  return !(h[r - 1] > 1e8 * tiny) || !(h[r - 1] > 0.0) ? TUCKER_ATTN_UNSUPPORTED_SHAPE : TUCKER_ATTN_OK;
 }
 
 // Eigenvectors of the symmetric positive semi-definite G [m, m] (destroyed) with the r largest
@@ -557,8 +577,11 @@ int leading_eigenvectors(hipStream_t s, double* G, int m, int r, double* norms2,
 }
 
 // Polish of nearly orthonormal rows, S = Z Z^T: S <- 1.5 I - 0.5 S in place, err[blockIdx.x] = largest |S - I| of a row
-__global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, double* err) {
+// blockIdx.y: problems, their S r^2 and their err err_stride apart
+__global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, double* err, long err_stride) {
   __shared__ double red[4];
+  S += (long)blockIdx.y * r * r;
+  err += blockIdx.y * err_stride;
   double* row = S + (long)blockIdx.x * r;
   double worst = 0.0;
   for (int j = threadIdx.x; j < r; j += 256) {
@@ -579,16 +602,52 @@ __global__ __launch_bounds__(256) void newton_schulz_kernel(double* S, int r, do
   }
 }
 
-constexpr int kReportHead = 4;
+// the report of the eigen-problems: a summary of each, then value | resid | err | diagonal | subdiagonal of each
+constexpr int kSummary = 8, kReportHead = 4 * kSummary;
+constexpr int kFailed = 0, kFro2 = 1, kLeast = 2, kResid = 3, kMissing = 4;   // (kFailed: by the reduction)
+// squared Frobenius norm, least of the r eigenvalues, largest residual and largest deviation from orthogonality (a NaN stays)
+__global__ __launch_bounds__(256) void eigen_summary_kernel(EigenBatch b, double* report) {
+  __shared__ double red[256][4];
+  const int p = blockIdx.x, m = b.m, r = b.r[p];
+  double fro2 = 0.0, least = INFINITY, resid = 0.0, missing = 0.0;
+  auto more = [](double x, double y) { return y > x || y != y ? y : x; };
+  auto less = [](double x, double y) { return y < x || y != y ? y : x; };
+  for (int k = threadIdx.x; k < m; k += 256) {
+    const double on = b.tri[p][k], off = k + 1 < m ? b.tri[p][m + k] : 0.0;
+    fro2 += on * on + 2.0 * off * off;
+    if (k < r) {
+      least = less(least, b.value[p][k]);
+      resid = more(resid, b.resid[p][k]);
+      missing = more(missing, b.value[p][2l * m + k]);
+    }
+  }
+  double* mine = red[threadIdx.x];
+  mine[0] = fro2; mine[1] = least; mine[2] = resid; mine[3] = missing;
+  for (int n = 128; n > 0; n >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+      const double* other = red[threadIdx.x + n];
+      mine[0] += other[0];
+      mine[1] = less(mine[1], other[1]);
+      mine[2] = more(mine[2], other[2]);
+      mine[3] = more(mine[3], other[3]);
+    }
+  }
+  if (threadIdx.x == 0) {
+    double* to = report + kSummary * p;
+    to[kFro2] = mine[0]; to[kLeast] = mine[1]; to[kResid] = mine[2]; to[kMissing] = mine[3];
+  }
+}
 struct HosvdWs {
   double *A, *B, *T, *GA, *GB, *SA, *SB, *M1[2], *U1[2], *U2[2], *U3[2], *P, *Q, *H, *C, *norms2;
   double *M[4];                                         // Gram matrices: modes 2 and 3 of W, then of W~ (one for all where
                                                         // the problems are solved one by one)
   double *Z[4], *Z2[4], *work[4];                       // eigenvector rows before and behind the polish; scratch
-  double* report;                                       // four marks of failure, then value | resid | err | diagonal |
-                                                        // subdiagonal of each problem
+  double* report;                                       // see kReportHead
   double* S;
   int *idx, *counter;
+  double* small_norms;                                  // the head mode of both tensors, where it is small
+  int* small_idx;
   size_t bytes;
 };
 
@@ -629,7 +688,7 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
     w.work[e] = (double*)take(eigen_work_elems(d), 8);
   }
   w.report = batched ? (double*)take(kReportHead + 4 * 5 * D, 8) : nullptr;
-  w.S = batched ? (double*)take(rmax * rmax, 8) : nullptr;
+  w.S = batched ? (double*)take(4 * rmax * rmax, 8) : nullptr;
   w.P = (double*)take(rmax * n, 8);
   w.Q = (double*)take(rmax * n, 8);
   w.H = (double*)take((size_t)nH * rmax * rmax, 8);
@@ -637,6 +696,8 @@ HosvdWs carve_hosvd(void* base, int d, int nH, int dH) {
   w.norms2 = (double*)take(D + nH, 8);
   w.idx = (int*)take(D + nH, 4);
   w.counter = (int*)take(64, 4);
+  w.small_norms = (double*)take(2 * kSmallJacobi, 8);
+  w.small_idx = (int*)take(2 * kSmallJacobi, 4);
   w.bytes = off;
   return w;
 }
@@ -651,8 +712,8 @@ hipError_t head_products(hipStream_t s, const HosvdWs& w, int d, int nH, int dH)
 // mode 1: <W_i, W_j> from the full Gram matrices of the factors
 hipError_t head_mode_gram(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, double* M1) {
   const long n = (long)nH * dH;
-  if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.A, 1, n, 0, w.A, n, 1, 0, w.GA, n, 1, 0)) return e;
-  if (hipError_t e = dgemm(s, 1, (int)n, (int)n, d, w.B, 1, n, 0, w.B, n, 1, 0, w.GB, n, 1, 0)) return e;
+  const long ab = w.B - w.A;                            // both factors in one launch
+  if (hipError_t e = dgemm(s, 2, (int)n, (int)n, d, w.A, 1, n, ab, w.A, n, 1, ab, w.GA, n, 1, w.GB - w.GA)) return e;
   hipLaunchKernelGGL(head_gram_kernel, dim3(nH, nH), dim3(256), 0, s, w.GA, w.GB, M1, nH, dH);
   return hipGetLastError();
 }
@@ -690,7 +751,7 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     b.G[j] = w.M[j];
     b.Z[j] = w.Z[j];
     b.work[j] = w.work[j];
-    b.failed[j] = w.report + j;
+    b.failed[j] = w.report + kSummary * j + kFailed;
     b.value[j] = w.report + kReportHead + 5 * (size_t)d * j;
     b.resid[j] = b.value[j] + d;
     b.tri[j] = b.value[j] + 3 * (size_t)d;
@@ -713,15 +774,25 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
   CK(launch_tridiag_vectors(b, s));
   // rows of close eigenvalues are orthogonal only to rounding / gap: one Newton-Schulz step Z <- (1.5 I - 0.5 Z Z^T) Z,
   // which squares what is missing and moves no vector by more than its own uncertainty
-  auto polish = [&](int j) -> hipError_t {
+  // (problems j .. j + n - 1 of one rank together, their rows lie `apart`: a product of 64 rows alone leaves most of the chip idle;
+  // four of 64 x 768: 122 us one by one, 31 together)
+  const long apart = w.Z[1] - w.Z[0];
+  auto polish = [&](int j, int n) -> hipError_t {
     const int r = b.r[j];
-    if (hipError_t e = dgemm(s, 1, r, r, d, from[j], d, 1, 0, from[j], 1, d, 0, w.S, r, 1, 0)) return e;
-    hipLaunchKernelGGL(newton_schulz_kernel, dim3(r), dim3(256), 0, s, w.S, r, b.value[j] + 2 * (size_t)d);
-    std::swap(from[j], to[j]);
-    return dgemm(s, 1, r, d, r, w.S, r, 1, 0, to[j], d, 1, 0, from[j], d, 1, 0);
+    if (hipError_t e = dgemm(s, n, r, r, d, from[j], d, 1, apart, from[j], 1, d, apart, w.S, r, 1, (long)r * r)) return e;
+    hipLaunchKernelGGL(newton_schulz_kernel, dim3(r, n), dim3(256), 0, s, w.S, r, b.value[j] + 2 * (size_t)d, 5l * d);
+    for (int i = j; i < j + n; ++i) std::swap(from[i], to[i]);
+    return dgemm(s, n, r, d, r, w.S, r, 1, (long)r * r, to[j], d, 1, apart, from[j], d, 1, apart);
   };
-  for (int j = 0; j < n_jobs; ++j) CK(polish(j));
-  std::vector<double> report(kReportHead + 5 * (size_t)d * n_jobs);
+  for (int j = 0, n; j < n_jobs; j += n) {
+    for (n = 1; j + n < n_jobs && b.r[j + n] == b.r[j]; ++n) {}
+    CK(polish(j, n));
+  }
+  hipLaunchKernelGGL(eigen_summary_kernel, dim3(n_jobs), dim3(256), 0, s, b, w.report);
+  CK(hipGetLastError());
+  bool want_values = false;
+  for (int j = 0; j < n_jobs; ++j) want_values = want_values || jobs[j].sv;
+  std::vector<double> report(kReportHead + (want_values ? 5 * (size_t)d * n_jobs : 0));
   CK(hipMemcpyAsync(report.data(), w.report, sizeof(double) * report.size(), hipMemcpyDeviceToHost, s));
   CK(hipStreamSynchronize(s));
   if (timed) {
@@ -736,33 +807,26 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     else
       for (int k = 0; k < steps; ++k) jobs[0].stats->bytes += 16.0 * n_jobs * (d - 1. - k) * (d - 1. - k);
   }
-  auto worst_of = [](const double* x, int n) {
-    double worst = 0.0;
-    for (int k = 0; k < n; ++k) worst = x[k] > worst || x[k] != x[k] ? x[k] : worst;
-    return worst;
-  };
   for (int j = 0; j < n_jobs; ++j) {
     const int r = b.r[j];
-    const double* rep = report.data() + kReportHead + 5 * (size_t)d * j;
-    if (resident && report[j] != 0.0) continue;
-    double fro2 = 0.0;
-    for (int k = 0; k < d; ++k) {
-      const double on = rep[3 * (size_t)d + k], off = k + 1 < d ? rep[4 * (size_t)d + k] : 0.0;
-      fro2 += on * on + 2.0 * off * off;
-    }
-    std::vector<double> value(rep, rep + b.n_values[j]);
-    std::sort(value.begin(), value.end(), [](double x, double y) { return x > y; });
+    const double* sum = report.data() + kSummary * j;
+    if (resident && sum[kFailed] != 0.0) continue;
+    const double fro2 = sum[kFro2], least = sum[kLeast];
     const double top = std::sqrt(fro2);
     // the rank test of the Jacobi path, on the squared eigenvalue
-    if (!(value[r - 1] > 0.0) || !(value[r - 1] * value[r - 1] > 1e8 * 1e-28 * d * fro2)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
-    double missing = worst_of(rep + 2 * (size_t)d, r);
-    const double resid = worst_of(rep + d, r);
+    if (!(least > 0.0) || !(least * least > 1e8 * 1e-28 * d * fro2)) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
+    double missing = sum[kMissing];
+    const double resid = sum[kResid];
     // residuals of 2.1e-16 of the norm at most were seen (d = 8 .. 5056, repeated and graded spectra among them), whatever
     // the size: a vector that is further off than the rounding of G explains is no answer
     if (!(resid <= 4e-15 * top) || !(missing <= 1e-3 / r)) continue;
-    for (; missing > 1e-8 / r; missing = r * missing * missing) CK(polish(j));   // rare: very close eigenvalues
-    if (jobs[j].sv)
+    for (; missing > 1e-8 / r; missing = r * missing * missing) CK(polish(j, 1));   // rare: very close eigenvalues
+    if (jobs[j].sv) {
+      const double* rep = report.data() + kReportHead + 5 * (size_t)d * j;
+      std::vector<double> value(rep, rep + d);
+      std::sort(value.begin(), value.end(), [](double x, double y) { return x > y; });
       for (int k = 0; k < d; ++k) jobs[j].sv[k] = std::sqrt(std::max(value[k], 0.0));
+    }
     hipLaunchKernelGGL(row_norms_kernel, dim3(r), dim3(256), 0, s, from[j], d, w.norms2);
     hipLaunchKernelGGL((extract_factor_kernel<T>), dim3(r), dim3(256), 0, s, from[j], d, nullptr, w.norms2, r, jobs[j].U64, jobs[j].U);
     CK(hipGetLastError());
@@ -776,8 +840,12 @@ template <typename T>
 int core_of(hipStream_t s, const HosvdWs& w, int d, int nH, int dH, int r1, int r2, int r3, const double* U1, const double* U2,
             const double* U3, T* C) {
   const long n = (long)nH * dH;
-  CK(dgemm(s, 1, r2, (int)n, d, U2, 1, r2, 0, w.A, n, 1, 0, w.P, n, 1, 0));
-  CK(dgemm(s, 1, r3, (int)n, d, U3, 1, r3, 0, w.B, n, 1, 0, w.Q, n, 1, 0));
+  if (r2 == r3) {                                       // both in one launch
+    CK(dgemm(s, 2, r2, (int)n, d, U2, 1, r2, U3 - U2, w.A, n, 1, w.B - w.A, w.P, n, 1, w.Q - w.P));
+  } else {
+    CK(dgemm(s, 1, r2, (int)n, d, U2, 1, r2, 0, w.A, n, 1, 0, w.P, n, 1, 0));
+    CK(dgemm(s, 1, r3, (int)n, d, U3, 1, r3, 0, w.B, n, 1, 0, w.Q, n, 1, 0));
+  }
   CK(dgemm(s, nH, r2, r3, dH, w.P, n, 1, dH, w.Q, 1, n, dH, w.H, r3, 1, (long)r2 * r3));
   CK(dgemm(s, 1, r1, r2 * r3, nH, U1, 1, r1, 0, w.H, (long)r2 * r3, 1, 0, w.C, (long)r2 * r3, 1, 0));
   const long total = (long)r1 * r2 * r3;
@@ -898,12 +966,9 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
                                            jobs[j].sv, jobs[j].stats);
     if (st != TUCKER_ATTN_OK) return st;
   }
-  for (int t = 0; t < 2 && nH <= kSmallJacobi; ++t) {
-    const int st = finish_small_jacobi<T>(s, w.M1[t], nH, t ? rt1 : r1, w.norms2, w.idx, w.counter + 1 + t, w.U1[t],
-                                          (T*)(t ? o.Ut1 : o.U1), sv ? sv + t * (nH + 2l * d) : nullptr,
-                                          info ? &stats[3 * t] : nullptr);
-    if (st != TUCKER_ATTN_OK) return st;
-  }
+  for (int t = 0; t < 2 && nH <= kSmallJacobi; ++t)
+    CK(finish_small_jacobi<T>(s, w.M1[t], nH, t ? rt1 : r1, w.small_norms + t * kSmallJacobi, w.small_idx + t * kSmallJacobi, w.U1[t],
+                              (T*)(t ? o.Ut1 : o.U1)));
   for (int t = 1; t >= 0; --t) {
     if (loaded != t) CK(load(t));
     loaded = t;
@@ -911,7 +976,20 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
                               t && !shared ? w.U3[1] : w.U3[0], (T*)(t ? o.Ct : o.C));
     if (st != TUCKER_ATTN_OK) return st;
   }
+  if (nH > kSmallJacobi) {
+    CK(hipStreamSynchronize(s));
+    return TUCKER_ATTN_OK;
+  }
+  double small[2 * kSmallJacobi];                       // the head mode's norms, sweeps behind them
+  int sweeps[2];
+  CK(hipMemcpyAsync(small, w.small_norms, sizeof(small), hipMemcpyDeviceToHost, s));
+  CK(hipMemcpyAsync(sweeps, w.counter + 1, sizeof(sweeps), hipMemcpyDeviceToHost, s));
   CK(hipStreamSynchronize(s));
+  for (int t = 0; t < 2; ++t)
+    if (const int st = check_small_jacobi(small + t * kSmallJacobi, nH, t ? rt1 : r1, sweeps[t], sv ? sv + t * (nH + 2l * d) : nullptr,
+                                          info ? &stats[3 * t] : nullptr);
+        st != TUCKER_ATTN_OK)
+      return st;
   return TUCKER_ATTN_OK;
 }
 

@@ -204,41 +204,53 @@ constexpr double kPivot = 1e-290;                       // smallest pivot magnit
 
 // Eigenvalue number 4 blockIdx.x + wave of a problem, counted from the largest: the 64 lanes of a wave count the
 // eigenvalues below 64 points of the current interval, which shrinks 65-fold per round (10 rounds: below the
-// rounding of the largest eigenvalue).  A serial chain of m pivots per round: 30 us a round at m = 768.
+// rounding of the largest eigenvalue).  The count is that of the sign changes in the sequence of leading minors
+// p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: a serial chain of one fused multiply-add a row, where the pivots p_i / p_{i-1} would take
+// a reciprocal (four problems of 768, 128 values each: 312 us by pivots, 165 so).  With the matrix scaled to a norm of 1 to 2 and
+// an off-diagonal of less than 1e-20 taken as 1e-20 (far below the rounding of the diagonal), eight rows change the larger of two
+// neighbouring minors by less than 2^20 upwards and 1e-205 downwards: a common power of two is taken out of both every eight rows,
+// and what underflows next to the other is a zero minor, whose sign does not matter.
 __global__ __launch_bounds__(256) void tridiag_values_kernel(EigenBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int m = b.m, p = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double* d = b.tri[p];
   const double* e = b.tri[p] + m;
-  double* pd = reinterpret_cast<double*>(smem_raw);     // (d_i, e_{i-1}^2) pairs
-  double e2max = 0.0;
+  double* pd = reinterpret_cast<double*>(smem_raw);     // (d_i, e_{i-1}^2) pairs, scaled
+  double lo, hi;
+  spectrum_bounds(d, e, m, lane, lo, hi);
+  const int shift = -ilogb(fmax(fabs(lo), fabs(hi)));   // (the bounds are never zero)
   for (int i = threadIdx.x; i < m; i += 256) {
-    const double o = i > 0 ? e[i - 1] : 0.0;
-    pd[2 * i] = d[i];
-    pd[2 * i + 1] = o * o;
+    const double o = i > 0 ? ldexp(e[i - 1], shift) : 0.0;
+    pd[2 * i] = ldexp(d[i], shift);
+    pd[2 * i + 1] = fmax(o * o, 1e-40);
   }
-  for (int i = lane; i + 1 < m; i += 64) e2max = fmax(e2max, e[i] * e[i]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) e2max = fmax(e2max, __shfl_xor(e2max, o));
   __syncthreads();
   const int idx = blockIdx.x * 4 + wave;
   if (idx >= b.n_values[p]) return;
-  const double pivot = kPivot * fmax(1.0, e2max);
-  double lo, hi;
-  spectrum_bounds(d, e, m, lane, lo, hi);
+  lo = ldexp(lo, shift);
+  hi = ldexp(hi, shift);
   const int below = m - idx;                            // count at and above the eigenvalue wanted
   for (int round = 0; round < 10; ++round) {
     const double x = lo + (hi - lo) * ((lane + 1) / 65.0);
-    double q = pd[0] - x;
-    int cnt = 0;
-    if (fabs(q) < pivot) q = -pivot;
-    cnt += q < 0.0;
-#pragma unroll 8
-    for (int i = 1; i < m; ++i) {
-      q = (pd[2 * i] - x) - pd[2 * i + 1] * recip(q);
-      if (fabs(q) < pivot) q = -pivot;
-      cnt += q < 0.0;
+    // p1, p0: minors i and i-1.  A zero minor has either sign: the next one is -e^2 times the one before, so that the two
+    // steps count one change together.
+    double p1 = 1.0, p0 = 0.0;
+    int cnt = 0, i = 0;
+    auto high = [](double v) { return (unsigned)(__builtin_bit_cast(unsigned long, v) >> 32); };
+    auto row = [&](int at) {
+      const double q = fma(pd[2 * at] - x, p1, -(pd[2 * at + 1] * p0));
+      cnt += (int)((high(q) ^ high(p1)) >> 31);
+      p0 = p1;
+      p1 = q;
+    };
+    for (; i + 8 <= m; i += 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) row(i + u);
+      const int e2 = -ilogb(fmax(fabs(p0), fabs(p1)));  // (not both are zero)
+      p0 = ldexp(p0, e2);
+      p1 = ldexp(p1, e2);
     }
+    for (; i < m; ++i) row(i);
     const unsigned long long up = __builtin_amdgcn_ballot_w64(cnt >= below);
     const int f = up == 0ull ? 64 : __builtin_ctzll(up);
     const double nhi = f < 64 ? __shfl(x, f & 63) : hi;
@@ -246,7 +258,7 @@ __global__ __launch_bounds__(256) void tridiag_values_kernel(EigenBatch b) {
     lo = nlo;
     hi = nhi;
   }
-  if (lane == 0) b.value[p][idx] = 0.5 * (lo + hi);
+  if (lane == 0) b.value[p][idx] = ldexp(0.5 * (lo + hi), -shift);
 }
 
 // Unit eigenvector of the tridiagonal matrix for its eigenvalue blockIdx.x: pivots of the factorisations from the top

@@ -305,6 +305,19 @@ def test_hosvd_with_the_reduction_in_one_launch(d, nH, dH, r, shared):
         assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
 
 
+@pytest.mark.parametrize("d,nH,dH,ranks,ranks_t,shared", [
+    (64, 1, 16, (1, 5, 5), (1, 5, 5), False),                    # four problems of one rank; one head
+    (64, 16, 4, (9, 7, 7), (3, 6, 7), False),                    # ranks that differ, then two alike; the most heads of one workgroup
+    (72, 17, 4, (9, 6, 8), (3, 8, 8), True),                     # three problems; one head more
+])
+def test_hosvd_with_problems_of_equal_and_of_other_ranks(d, nH, dH, ranks, ranks_t, shared):
+    host, got, sv, _ = hosvd_case(d, nH, dH, ranks, ranks_t, shared, "f32", 230 + nH)
+    ref = cv.mha_to_tucker_hosvd(host["WQ"], host["WK"], host["WV"], host["WO"], nH, ranks, ranks_t, shared_kv=shared)
+    check_spectra(sv, host, nH, d, shared)
+    for k in ref:
+        assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
+
+
 @pytest.mark.parametrize("kind", ["all_equal", "pairs", "blocks"])
 def test_hosvd_with_repeated_singular_values_keeps_the_tensor(kind):
     # vectors of repeated values are not unique: the factors must be orthonormal and, at full ranks, the core
