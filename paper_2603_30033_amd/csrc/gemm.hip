@@ -19,6 +19,7 @@
 // that a wave's piece of the tile stays large (few LDS bytes per matrix instruction) even where the tile is
 // small, and the groups' accumulators are added through LDS at the end, in a fixed order.  Split-K over
 // workgroups (ksplit > 1, decode) leaves partial tiles for the caller's next kernel to sum.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -334,8 +335,20 @@ static hipError_t launch_one(const GemmArgs& a, int m_rows, hipStream_t s) {
 // (before, four waves that split the tile only: 48, 63, 39, 14, 25, 36, 7.7, 22.6, 59).  Few tiles: as many
 // workgroups as possible, the eight waves of each dealt over the contraction.  A long contraction with enough
 // tiles for every compute unit is bound by the bytes that the caches deliver, hence the largest tile that still
-// gives each one a workgroup; a short one by the start and the end of a workgroup, hence four waves and 64 KB of LDS,
-// so that two workgroups share a compute unit.  fp32 is bound by its matrix instructions (64 cycles each): only
+// gives each one a workgroup; a short one by the start and the end of a workgroup, hence 56 to 80 KB of LDS,
+// so that two workgroups share a compute unit, and by the number of rounds that 512 workgroups at a time make:
+//                                    96x128/4  128x128/8  192x128/8
+//   192 x  768 x 24576                   15.8      17.8       17.8      1, 1, 1 rounds
+//   192 x  768 x 65536 (50432 exist)     30.2      32.6       26.4      2, 2, 1
+//   128 x  768 x 34816                   25.4      18.4       23.2      2, 1, 1
+//   128 x  768 x 65536                   31.6      23.0       27.1      2, 1, 1
+//   256 x  768 x 36864                   29.0      29.3       34.8      2, 2, 2
+//   256 x  768 x 65536                   51.8      45.1       52.9      3, 2, 2
+//   320 x  768 x 36864                   46.8      37.1       41.7      3, 2, 2
+//   320 x  768 x 65536                   75.2      60.2       59.8      4, 3, 2
+// A round takes about as long as 30 rows more than a tile has (96x128 alone before; a forward pass over 256 x 197 tokens of 768
+// channels 126.9 us then, 120.3 now).  That is for the projection; outputs as whole rows gain nothing (training of 64 x 1024 tokens
+// 1183 us with the one tile, 1227 with all three).  fp32 is bound by its matrix instructions (64 cycles each): only
 // the number of workgroups matters (192 x 768 x 1018 tokens 8.9 us with 32x32 and four waves, 8.0 with eight, 19
 // with 64x64, 21 before; 768 x 192 x 1018 tokens 7.5, 10.0, 8.2, 8.9 before).
 template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
@@ -357,7 +370,11 @@ template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStrea
       if (m_rows % 96 == 0 && tiles(96, 128) >= kComputeUnits) return launch_one<T, 96, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
       if (m_rows > 64 && tiles(128, 128) >= kComputeUnits) return launch_one<T, 128, 128, 1, 2, 4, 128, 4>(a, m_rows, s);
     } else if (tiles(96, 128) >= kComputeUnits) {
-      return launch_one<T, 96, 128, 1, 4, 1, 128, 2>(a, m_rows, s);
+      auto cost = [&](int tm) { return ((tiles(tm, 128) + 2 * kComputeUnits - 1) / (2 * kComputeUnits)) * (tm + 30); };
+      const long least = std::min(cost(96), std::min(cost(128), cost(192)));
+      if (a.epi != 0 || cost(96) == least) return launch_one<T, 96, 128, 1, 4, 1, 128, 2>(a, m_rows, s);
+      if (cost(128) == least) return launch_one<T, 128, 128, 2, 4, 1, 128, 2>(a, m_rows, s);
+      return launch_one<T, 192, 128, 2, 4, 1, 128, 2>(a, m_rows, s);
     }
     return launch_one<T, 64, 64, 1, 1, 4, 128, 4>(a, m_rows, s);
   }

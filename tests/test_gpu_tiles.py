@@ -152,6 +152,22 @@ def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared,
     check(y, oracle_forward(w, inp), w.dtype, repr(w))
 
 
+# projections of many tokens, one and two weight tiles of 128 and of 192 rows: whole tiles and rows past the weights, a contraction that is
+# no whole stage, a last token tile that is not full
+@pytest.mark.parametrize("B,N,d,r2,r3,shared", [
+    (600, 33, 72, 64, 64, True), (577, 17, 136, 96, 32, False),  # 128 of 128 rows, 160 of 192
+    (600, 33, 200, 64, 64, False), (519, 64, 64, 64, 64, False),  # 192 of 192
+    (400, 64, 72, 128, 64, False), (512, 33, 72, 64, 128, False),  # 256 of 2 x 128, 320 of 2 x 192
+])
+def test_projection_of_many_tokens(B, N, d, r2, r3, shared):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=d, n_heads=2, d_head=32, r1=2, r2=r2, r3=r3, rt1=2, rt2=32, rt3=r3,
+                  dtype="bf16", causal=True, shared_kv=shared, seed=60)
+    inp = wl.make_inputs(w)
+    with Layer(w, inp) as layer:
+        y = to_host(layer.forward(to_device(inp["X"], w.dtype)))
+    check(y, oracle_forward(w, inp), w.dtype, repr(w))
+
+
 # few workgroups: the keys of a query block dealt to two and to four waves, with a remainder and with parts that hold no visible
 # key; the query blocks of a head dealt to two and to four workgroups (all gradients, no RoPE offset and an odd head count)
 @pytest.mark.parametrize("dtype,B,N,heads,r3,causal", [
