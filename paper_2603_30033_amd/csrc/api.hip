@@ -88,7 +88,7 @@ struct PrefillWs {
   size_t bytes;
 };
 struct DecodeWs {
-  void *Gt, *Gtil2, *Wcat, *Ut2p, *Qlat, *Qh;
+  void *Gt, *Gtil2, *Wcat, *Ut2p, *Qh;
   float *pm, *pl, *po, *part;
   size_t bytes;
 };
@@ -229,9 +229,11 @@ int decode_nsplit(const tucker_attn_ctx* c, int B, int longest) {
   if (n > tiles) n = (int)tiles;
   return n < 1 ? 1 : n;
 }
+// parts of the projection's contraction: at least two (the second may be empty), so that its product always leaves partial
+// tiles and the new cache rows come from the query launch, which knows the sequences' positions
 int decode_ksplit(int K) {
-  int nk = (K + 63) / 64;
-  return nk < 16 ? (nk < 1 ? 1 : nk) : 16;
+  const int nk = (K + 63) / 64;
+  return nk < 2 ? 2 : (nk < 16 ? nk : 16);
 }
 // the decode projection can read the factor matrices as they lie in memory when every row of them is a whole
 // number of aligned 16-byte chunks
@@ -248,13 +250,11 @@ DecodeWs carve_decode(const tucker_attn_ctx* c, void* ws, int B) {
   Carver cv{static_cast<char*>(ws), 0};
   DecodeWs w;
   carve_weights(c, cv, w.Gt, w.Gtil2, w.Wcat, w.Ut2p);
-  w.Qlat = cv.take<char>((size_t)32 * c->R2 * c->es);
   w.Qh = cv.take<char>((size_t)B * HB32 * c->D * c->es);
   w.pm = cv.take<float>((size_t)B * ns * HB32 * 4);
   w.pl = cv.take<float>((size_t)B * ns * HB32 * 4);
   w.po = cv.take<float>((size_t)B * ns * HB32 * c->D * 4);
-  const int ks1 = decode_ksplit(f.d_model) < 2 ? 2 : decode_ksplit(f.d_model);
-  const size_t p1 = (size_t)ks1 * B * (c->R2 + 2 * c->D) * 4;
+  const size_t p1 = (size_t)decode_ksplit(f.d_model) * B * (c->R2 + 2 * c->D) * 4;
   const size_t p2 = (size_t)f.n_heads * B * c->RT2 * 4;            // one contribution to Z per head
   w.part = cv.take<float>(p1 > p2 ? p1 : p2);
   w.bytes = cv.off;
@@ -453,12 +453,11 @@ int decode_impl(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* x,
     g.Bsrc = xb; g.ldb = f.d_model; g.K = f.d_model;
     g.Bsz = Bc; g.N = 1; g.Npad = 1; g.src_padded = 0;
     g.epi = 0;
-    g.Qlat = ws.Qlat; g.R2 = c->R2; g.Kr = nullptr; g.D = c->D; g.Vt = nullptr;
+    g.Qlat = nullptr; g.R2 = c->R2; g.Kr = nullptr; g.D = c->D; g.Vt = nullptr;
     g.Kcache = Kb; g.Vcache = Vb; g.Lmax = Lmax; g.r3 = f.r3; g.rt3 = f.rt3;
     g.rope = c->rope; g.rope_ld = f.max_positions; g.pos0 = 0; g.decode = 1;
     g.ksplit = decode_ksplit(g.K); g.part = ws.part;              // the query launch sums the partial tiles
     if (direct) {
-      if (g.ksplit < 2) g.ksplit = 2;                             // always partial tiles on this path
       DecodeProjArgs dp;
       std::memset(&dp, 0, sizeof(dp));
       dp.X = xb; dp.U2 = w->U2; dp.U3 = w->U3; dp.Ut3 = w->Ut3;
@@ -474,7 +473,7 @@ int decode_impl(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* x,
 
     DecodeArgs d;
     std::memset(&d, 0, sizeof(d));
-    d.Qlat = ws.Qlat; d.Gt = ws.Gt; d.Qh = ws.Qh; d.Kcache = Kb; d.Vcache = Vb;
+    d.Gt = ws.Gt; d.Qh = ws.Qh; d.Kcache = Kb; d.Vcache = Vb;
     d.part_m = ws.pm; d.part_l = ws.pl; d.part_o = ws.po; d.rope = c->rope; d.rope_ld = f.max_positions;
     d.Bsz = Bc; d.nH = f.n_heads; d.HB = pad32(f.n_heads) / 32; d.R2 = c->R2; d.r3 = f.r3; d.rt3 = f.rt3;
     d.D = c->D; d.Lmax = Lmax; d.nsplit = decode_nsplit(c, Bc, longest); d.shared_kv = f.shared_kv;

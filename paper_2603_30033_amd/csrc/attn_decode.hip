@@ -29,8 +29,7 @@ static int seq_groups(const DecodeArgs& a) { return (a.Bsz + kSeqGroup - 1) / kS
 // ([split][sequence][R2 + D (+ D)] fp32): every head's workgroup sums the Qlat columns of all sequences into
 // LDS itself (a few hundred KB that stay in L2; all loads of a thread issued together), and the workgroups
 // behind the heads' sum one 32-column block of the key or value part each and run the projection's epilogue
-// on it (rotation, cache rows).  With one split the product has run its epilogue already and Qlat is read
-// from where it put it.
+// on it (rotation, cache rows).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs g) {
   constexpr int CB = D / 32;
@@ -86,25 +85,19 @@ __global__ __launch_bounds__(256) void decode_qhat_kernel(DecodeArgs p, GemmArgs
   for (int ci = threadIdx.x; ci < kSeqGroup * (p.R2 / 4); ci += 256) {
     const int t = ci / (p.R2 / 4), k = (ci % (p.R2 / 4)) * 4;     // four natural indices k..k+3 keep their order
     const int pos = (k & ~31) + acc_pos(k & 31);
-    if (g.ksplit > 1) {
-      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-      if (t < nt) {
-        for (int z0 = 0; z0 < g.ksplit; z0 += 2 * U) {
-          f32x4 v[2 * U];
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    if (t < nt) {
+      for (int z0 = 0; z0 < g.ksplit; z0 += 2 * U) {
+        f32x4 v[2 * U];
 #pragma unroll
-          for (int u = 0; u < 2 * U; ++u)
-            v[u] = *reinterpret_cast<const f32x4*>(g.part + ((long)min(z0 + u, g.ksplit - 1) * p.Bsz + t0 + t) * Mp + k);
+        for (int u = 0; u < 2 * U; ++u)
+          v[u] = *reinterpret_cast<const f32x4*>(g.part + ((long)min(z0 + u, g.ksplit - 1) * p.Bsz + t0 + t) * Mp + k);
 #pragma unroll
-          for (int u = 0; u < 2 * U; ++u)
-            if (z0 + u < g.ksplit) sum += v[u];
-        }
+        for (int u = 0; u < 2 * U; ++u)
+          if (z0 + u < g.ksplit) sum += v[u];
       }
-      store4(Ql + t * RE + pos, sum[0], sum[1], sum[2], sum[3]);
-    } else {
-      const T* src = static_cast<const T*>(p.Qlat) + (long)(t0 + t) * p.R2 + pos;   // already in acc order
-      if (t < nt) store4(Ql + t * RE + pos, to_f32(src[0]), to_f32(src[1]), to_f32(src[2]), to_f32(src[3]));
-      else store4(Ql + t * RE + pos, 0.f, 0.f, 0.f, 0.f);
     }
+    store4(Ql + t * RE + pos, sum[0], sum[1], sum[2], sum[3]);
   }
   __syncthreads();
 
@@ -912,7 +905,7 @@ static hipError_t qhat_one(const DecodeArgs& a, const GemmArgs& proj, hipStream_
   static LdsOnce lds_once;                                       // one per kernel instantiation
   if (hipError_t ae = allow_dynamic_lds(lds_once, kern, smem); ae != hipSuccess) return ae;
   // behind the heads' workgroups: one per 32-column block of the projection's key (and value) part
-  const int kv_blocks = proj.ksplit > 1 ? (proj.shared_kv ? 1 : 2) * proj.D / 32 : 0;
+  const int kv_blocks = (proj.shared_kv ? 1 : 2) * proj.D / 32;
   hipLaunchKernelGGL(kern, dim3(a.HB * 32 + kv_blocks, seq_groups(a)), dim3(256), smem, s, a, proj);
   return hipGetLastError();
 }

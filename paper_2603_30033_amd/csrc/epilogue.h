@@ -7,9 +7,9 @@
 namespace ta {
 
 // ---- epilogues: one 32x32 accumulator block = 32 weight rows (m0..) x 32 tokens ----------
+// decode_pos: position (and cache row) of the sequence's one token in a decode step, not looked at otherwise
 template <typename T>
-// decode_pos: position (and cache row) of the sequence's one token in a decode step
-__device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, int m0, int tp, int decode_pos = 0) {
+__device__ __forceinline__ void epilogue_block(const GemmArgs& g, f32x16 acc, int m0, int tp, int decode_pos) {
   const int lane = threadIdx.x % kWave;
   const int h = lane / 32;
   const int TP = g.Bsz * g.Npad;

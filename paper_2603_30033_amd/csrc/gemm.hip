@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_kernel(GemmArgs g) 
       const f32x16 one[1][1] = {{v}};
       store_rows_y<T, 1, 1>(g, one, patch, m0, t0);
     } else {
-      epilogue_block<T>(g, v, m0, tp);
+      epilogue_block<T>(g, v, m0, tp, 0);                       // (not a decode step: see launch_gemm)
     }
   };
   constexpr int NBLK = MB * NB;
@@ -380,6 +380,7 @@ template <typename T> static hipError_t launch_tiles(const GemmArgs& a, hipStrea
   }
 }
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
+  if (a.decode && a.ksplit < 2) return hipErrorInvalidValue;      // the positions are its caller's next kernel's
   return dtype == 0 ? launch_tiles<float>(a, s) : launch_tiles<bf16>(a, s);
 }
 

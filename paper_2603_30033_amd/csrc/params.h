@@ -64,7 +64,7 @@ struct GemmArgs {
   int rope_ld;
   int pos0;
   int shared_kv;                // 1: no V rows in A; the K block also yields Vt, and the cache row, UNROTATED
-  int decode;                   // 1: one token per sequence, at the position its caller names
+  int decode;                   // 1: one token per sequence, at the position its caller names (ksplit > 1 only)
   // Z / Y
   void* Out; long ldo;          // Z: [TP][ldo] natural order;  Y: [B][N][ldo] natural order
   // split-K (decode-sized token counts): ksplit > 1 writes fp32 partial tiles to part
@@ -167,7 +167,6 @@ struct CoreGradArgs {
 
 // ---- decode ------------------------------------------------------------------------------
 struct DecodeArgs {
-  const void* Qlat;    // [32][R2] acc order (rows >= B are zero)
   const void* Gt;      // as above
   void* Qh;            // [B][HB*32][D] natural order, rotated, scaled (rows >= nH zero)
   const void* Kcache;  // [B][Lmax][r3]

@@ -176,6 +176,44 @@ def check_decode_shared(w, inp, what):
         assert np.array_equal(Lc[b, : L - 1], inp["Lcache"][b, : L - 1])      # old rows untouched
 
 
+# factor matrices that the projection cannot read as they lie in memory (rows or starts off 16 bytes) and a contraction that
+# is one part: the new cache rows of every sequence, at its own position, and the output
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("dtype,d,r2,r3,off", [
+    ("bf16", 64, 20, 32, 0), ("bf16", 8, 6, 8, 0), ("bf16", 64, 32, 24, 1), ("f32", 64, 18, 32, 0), ("f32", 8, 8, 4, 1),
+    ("f32", 40, 32, 20, 1),
+])
+def test_decode_of_a_narrow_model_writes_rows_at_their_positions(dtype, d, r2, r3, off, shared):
+    base = wl.WORKLOADS["decode_32k_shared_kv" if shared else "decode_32k"]
+    w = wl.scaled(base, d_model=d, n_heads=4, d_head=16, r1=2, r2=r2, r3=r3, rt1=2, rt2=r2, rt3=r3, B=3, kv_len=77, dtype=dtype,
+                  recipe="fan_in", seed=27)
+    inp = wl.make_inputs(w)
+    inp["kv_len"] = np.array([77, 1, 40], dtype=np.int32)
+
+    def moved(t):                                              # `off` elements into a larger buffer
+        flat = torch.zeros(t.numel() + off, dtype=t.dtype, device="cuda")
+        flat[off:] = t.flatten()
+        return flat[off:].view(t.shape)
+
+    lens = [int(n) for n in inp["kv_len"]]
+    with Layer(w, inp, max_positions=78) as layer:
+        layer.weights = {k: moved(v) for k, v in layer.weights.items()}
+        K = to_device(inp["Lcache" if shared else "Kcache"], dtype)
+        V = None if shared else to_device(inp["Vcache"], dtype)
+        y = to_host(layer.decode(to_device(inp["X"][:, 0], dtype), K, V, lens))
+        K, V = to_host(K), None if shared else to_host(V)
+    args = (lens, wl.weights_of(inp), w.d_head, w.rope_base)
+    if shared:
+        y_ref, K_ref = orc.decode_step_shared_kv(inp["X"][:, 0], inp["Lcache"], *args)
+    else:
+        y_ref, K_ref, V_ref = orc.decode_step(inp["X"][:, 0], inp["Kcache"], inp["Vcache"], *args)
+    check(y, y_ref, dtype, repr(w))
+    for got, ref, old in [(K, K_ref, "Lcache")] if shared else [(K, K_ref, "Kcache"), (V, V_ref, "Vcache")]:
+        for b, n in enumerate(lens):
+            check(got[b, n - 1], ref[b, n - 1], dtype, f"new row of sequence {b}")
+            assert np.array_equal(got[b, :n - 1], inp[old][b, :n - 1]) and np.array_equal(got[b, n:], inp[old][b, n:])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("rope", [1e4, None])
 def test_shared_kv_prefill_and_its_cache(dtype, rope):
