@@ -15,8 +15,11 @@
 
 namespace ta {
 
+// (a by value: through a reference the choice of factor matrix below becomes a choice of address, and the compiler keeps the
+// arguments in scratch memory: two more round trips before a wave's first load.  Launch with the preparation of 32 heads x 8
+// slices 7.4 -> 6.9 us, the decode step of 16 x 32768 tokens around it 76.7 -> 74.7)
 template <typename T, bool PREP>
-__device__ __forceinline__ void decode_proj(const DecodeProjArgs& a, const PrepArgs& prep) {
+__device__ __forceinline__ void decode_proj(const DecodeProjArgs a, const PrepArgs& prep) {
   constexpr int CE = 16 / (int)sizeof(T);
   constexpr int TS = 32 + CE;                                     // padded tile row, elements
   constexpr int CPRW = 32 / CE;                                   // 16-byte chunks per tile row
