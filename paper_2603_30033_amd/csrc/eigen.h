@@ -20,7 +20,10 @@ struct EigenBatch {
   int n_values[kEigenBatch];                            // eigenvalues wanted of each, r .. m
   double* failed[kEigenBatch];                          // 1.0: the resident reduction gave up (see there), nothing else holds
 };
-inline size_t eigen_work_elems(int m) { return 13ul * m; }
+// vectors of m doubles in a work array: those of the steps, one place left free, and behind them the exchange of the resident
+// reduction, whose 16-byte words start on 16 bytes for every m because an even number of vectors stands in front of them
+constexpr int kEigenExchange = 6, kEigenSlots = 4;
+inline size_t eigen_work_elems(int m) { return (kEigenExchange + 2ul * kEigenSlots) * m; }
 
 // Sizes whose whole reduction is one launch with the matrices in registers; its workgroups hold kResidentRows rows each, so that
 // four matrices of 1024 take the 256 compute units once.  Up to 256 most columns are the tail launch's either way.

@@ -15,7 +15,6 @@ namespace {
 
 // layout of a problem's work array, in vectors of m doubles
 constexpr int kTau = 0, kV = 1, kY = 3;                 // kV, kY: two vectors each, used in turn
-constexpr int kExchange = 5;                // slots of m pairs
 
 // x of the lane that the DPP control CTRL names
 template <int CTRL> __device__ __forceinline__ double dpp(double x) {
@@ -500,7 +499,8 @@ __global__ __launch_bounds__(1024) void tridiag_tail_kernel(EigenBatch b, int k0
 // in the tail launch (reduction 5.0 -> 2.6 ms); 512: 3.0, 1024: 3.9.  A bare exchange of 16 bytes a row and one barrier take 2.0 us,
 // 32 bytes a row 4.1; eight waves of two rows 2.7 ms, sixteen of one 3.4 (each wave reads the three vectors from LDS).
 constexpr unsigned long kUnset = 0x7ff4a5c3965a3c69ul;
-constexpr int kSlots = 4;
+constexpr int kSlots = kEigenSlots;
+static_assert(kY + 2 <= kEigenExchange && kEigenExchange % 2 == 0, "16-byte words on 16 bytes, also where m is odd");
 constexpr int kSpins = 1 << 20;                         // each at least one round trip to memory: 0.5 s and more
 typedef unsigned long u64x2 __attribute__((ext_vector_type(2)));
 // pairs p[at[0]] .. p[at[E-1]], past the L2 of this XCD
@@ -529,7 +529,7 @@ __device__ __forceinline__ double from_lane(double x, int l) {
 
 __global__ __launch_bounds__(256) void exchange_clear_kernel(EigenBatch b) {
   const int p = blockIdx.y, n = 2 * kSlots * b.m;
-  unsigned long* x = reinterpret_cast<unsigned long*>(b.work[p] + (long)kExchange * b.m);
+  unsigned long* x = reinterpret_cast<unsigned long*>(b.work[p] + (long)kEigenExchange * b.m);
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) x[i] = kUnset;
   if (blockIdx.x == 0 && threadIdx.x == 0) *b.failed[p] = 0.0;
 }
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b)
   const int m = b.m, p = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double* A = b.G[p];
   double* work = b.work[p];
-  unsigned long* slots = reinterpret_cast<unsigned long*>(work + (long)kExchange * m);
+  unsigned long* slots = reinterpret_cast<unsigned long*>(work + (long)kEigenExchange * m);
   const bool writer = blockIdx.x == gridDim.x - 1;
   const int row0 = blockIdx.x * ROWS + wave * RW;
   double x[RW][NC];
