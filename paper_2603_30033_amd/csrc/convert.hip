@@ -739,7 +739,7 @@ template <typename T> struct EigenJob {
 // where the vectors are no certified answer (eigenvalues too close for the twisted factorisation); w.M[j] is lost
 // either way.  Synchronises the stream.
 template <typename T>
-int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* jobs, int n_jobs, bool* done) {
+int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* jobs, int n_jobs, const TridiagWay& way, bool* done) {
   EigenBatch b;
   b.n = n_jobs;
   b.m = d;
@@ -770,7 +770,7 @@ int tridiagonal_jobs(hipStream_t s, const HosvdWs& w, int d, const EigenJob<T>* 
     CK(hipEventRecord(ev.e[0], s));
   }
   bool resident = false;
-  CK(launch_tridiag(b, s, ev.e[1], &resident));
+  CK(launch_tridiag(b, s, ev.e[1], &resident, way));
   CK(launch_tridiag_vectors(b, s));
   // rows of close eigenvalues are orthogonal only to rounding / gap: one Newton-Schulz step Z <- (1.5 I - 0.5 Z Z^T) Z,
   // which squares what is missing and moves no vector by more than its own uncertainty
@@ -890,7 +890,7 @@ int from_mla(int d, int nH, int dH, int dcQ, int dcK, const T* WDQ, const T* WUQ
 template <typename T>
 int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV, const T* WO, int r1, int r2, int r3,
                    int rt1, int rt2, int rt3, bool shared, const tucker_convert_weights_out& o, double* sv,
-                   tucker_convert_hosvd_info* info, void* workspace, hipStream_t s) {
+                   tucker_convert_hosvd_info* info, void* workspace, hipStream_t s, const TridiagWay& way) {
   JacobiStats stats[6];
   struct Report {                                       // filled on every return path
     tucker_convert_hosvd_info* info;
@@ -952,7 +952,7 @@ int from_mha_hosvd(int d, int nH, int dH, const T* WQ, const T* WK, const T* WV,
   // Gram matrix at a time, formed in front of it.
   bool done[4] = {false, false, false, false};
   if (tridiagonal)
-    if (const int st = tridiagonal_jobs<T>(s, w, d, jobs, n_jobs, done); st != TUCKER_ATTN_OK) return st;
+    if (const int st = tridiagonal_jobs<T>(s, w, d, jobs, n_jobs, way, done); st != TUCKER_ATTN_OK) return st;
   int loaded = 1;
   for (int j = n_jobs - 1; j >= 0; --j) {
     if (done[j]) continue;
@@ -1033,11 +1033,13 @@ size_t tucker_convert_hosvd_workspace_bytes(int32_t d, int32_t nH, int32_t dH) {
   return ta::carve_hosvd(nullptr, d, nH, dH).bytes;
 }
 
-int tucker_convert_from_mha_hosvd(int32_t dtype, int32_t d, int32_t nH, int32_t dH, const void* WQ, const void* WK,
-                                  const void* WV, const void* WO, int32_t r1, int32_t r2, int32_t r3, int32_t rt1,
-                                  int32_t rt2, int32_t rt3, int32_t shared_kv, const tucker_convert_weights_out* out,
-                                  double* singular_values, tucker_convert_hosvd_info* info, void* workspace,
-                                  size_t workspace_bytes, void* hip_stream) {
+// tucker_convert_from_mha_hosvd with the way of its reduction stated (TridiagWay), so that tests reach the ways out of it
+int tucker_test_from_mha_hosvd(int32_t dtype, int32_t d, int32_t nH, int32_t dH, const void* WQ, const void* WK, const void* WV,
+                               const void* WO, int32_t r1, int32_t r2, int32_t r3, int32_t rt1, int32_t rt2, int32_t rt3,
+                               int32_t shared_kv, const tucker_convert_weights_out* out, double* singular_values,
+                               tucker_convert_hosvd_info* info, void* workspace, size_t workspace_bytes, void* hip_stream,
+                               int32_t one_launch, int32_t looks) {
+  const ta::TridiagWay way{one_launch != 0, looks};
   if (dtype != TUCKER_ATTN_F32 && dtype != TUCKER_ATTN_BF16) return TUCKER_ATTN_INVALID_ARG;
   if (d < 1 || nH < 1 || dH < 1) return TUCKER_ATTN_INVALID_ARG;
   if (d > 8192 || nH > 256 || (long)nH * dH > 8192) return TUCKER_ATTN_UNSUPPORTED_SHAPE;
@@ -1054,10 +1056,20 @@ int tucker_convert_from_mha_hosvd(int32_t dtype, int32_t d, int32_t nH, int32_t 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (dtype == TUCKER_ATTN_F32)
     return ta::from_mha_hosvd<float>(d, nH, dH, (const float*)WQ, (const float*)WK, (const float*)WV, (const float*)WO, r1,
-                                     r2, r3, rt1, rt2, rt3, shared_kv != 0, *out, singular_values, info, workspace, s);
+                                     r2, r3, rt1, rt2, rt3, shared_kv != 0, *out, singular_values, info, workspace, s, way);
   return ta::from_mha_hosvd<ta::bf16>(d, nH, dH, (const ta::bf16*)WQ, (const ta::bf16*)WK, (const ta::bf16*)WV,
                                       (const ta::bf16*)WO, r1, r2, r3, rt1, rt2, rt3, shared_kv != 0, *out, singular_values,
-                                      info, workspace, s);
+                                      info, workspace, s, way);
+}
+
+int tucker_convert_from_mha_hosvd(int32_t dtype, int32_t d, int32_t nH, int32_t dH, const void* WQ, const void* WK,
+                                  const void* WV, const void* WO, int32_t r1, int32_t r2, int32_t r3, int32_t rt1,
+                                  int32_t rt2, int32_t rt3, int32_t shared_kv, const tucker_convert_weights_out* out,
+                                  double* singular_values, tucker_convert_hosvd_info* info, void* workspace,
+                                  size_t workspace_bytes, void* hip_stream) {
+  const ta::TridiagWay way;
+  return tucker_test_from_mha_hosvd(dtype, d, nH, dH, WQ, WK, WV, WO, r1, r2, r3, rt1, rt2, rt3, shared_kv, out, singular_values,
+                                    info, workspace, workspace_bytes, hip_stream, way.one_launch, way.looks);
 }
 
 }  // extern "C"

@@ -33,9 +33,15 @@ inline bool tridiag_is_resident(int m) { return m > 256 && m <= 1024; }
 constexpr int kEigenTail = 192;
 inline int tridiag_steps_of(int m) { return m > kEigenTail ? m - kEigenTail : 0; }
 
+// The ways a reduction may take; other values than these are for tests of the ways out.
+struct TridiagWay {
+  bool one_launch = true;                               // where tridiag_is_resident
+  int looks = 1 << 20;                                  // of a workgroup of that launch at words not yet posted, before it gives up:
+                                                        // each at least one round trip to memory, 0.5 s and more.  0: at once
+};
 // Enqueues the reduction to tridiagonal form; G, work and tri are written.  steps_done (nullable) is recorded behind the
 // launches of one column each, or the one launch of all columns; `resident` receives which of the two it was.
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident);
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident, const TridiagWay& way);
 // Enqueues eigenvalues and eigenvectors of the tridiagonal matrices, vectors carried back to the basis of G.
 // The vectors are unit rows; rows of close eigenvalues are orthogonal only up to (rounding / gap).
 hipError_t launch_tridiag_vectors(const EigenBatch& b, hipStream_t s);

@@ -501,7 +501,6 @@ __global__ __launch_bounds__(1024) void tridiag_tail_kernel(EigenBatch b, int k0
 constexpr unsigned long kUnset = 0x7ff4a5c3965a3c69ul;
 constexpr int kSlots = kEigenSlots;
 static_assert(kY + 2 <= kEigenExchange && kEigenExchange % 2 == 0, "16-byte words on 16 bytes, also where m is odd");
-constexpr int kSpins = 1 << 20;                         // each at least one round trip to memory: 0.5 s and more
 typedef unsigned long u64x2 __attribute__((ext_vector_type(2)));
 // pairs p[at[0]] .. p[at[E-1]], past the L2 of this XCD
 template <int E> __device__ __forceinline__ void peek(u64x2 (&v)[E], const u64x2* p, const int (&at)[E]) {
@@ -535,7 +534,7 @@ __global__ __launch_bounds__(256) void exchange_clear_kernel(EigenBatch b) {
 }
 
 template <int NW, int RW, int NC>
-__global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b) {
+__global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b, int looks) {
   constexpr int NT = 64 * NW, ROWS = NW * RW, W = 64 * NC, E = W / NT;   // E vector elements per thread
   static_assert(W % NT == 0 && ROWS == kResidentRows, "");
   __shared__ double vl[2][W], wl[2][W], ul[2][W], red[2][2][NW], pick[2][2];
@@ -585,8 +584,8 @@ __global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b)
         all = true;
 #pragma unroll
         for (int e = 0; e < E; ++e) all = all && got[e][0] != kUnset && got[e][1] != kUnset;
-      } while (!all && ++spins < kSpins);
-      if (!all) gave_up = 1;
+      } while (!all && ++spins < looks);
+      if (spins >= looks) gave_up = 1;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const unsigned long w0 = got[e][0], w1 = got[e][1];     // (scalars: a cast of a vector's element takes the first)
@@ -690,12 +689,12 @@ __global__ __launch_bounds__(64 * NW) void tridiag_resident_kernel(EigenBatch b)
   }
 }
 
-template <int NC> hipError_t tridiag_resident(const EigenBatch& b, hipStream_t s) {
+template <int NC> hipError_t tridiag_resident(const EigenBatch& b, int looks, hipStream_t s) {
   const int wgs = (b.m + kResidentRows - 1) / kResidentRows;
   hipLaunchKernelGGL(exchange_clear_kernel, dim3(8, b.n), dim3(256), 0, s, b);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   EigenBatch args = b;
-  void* list[] = {&args};
+  void* list[] = {&args, &looks};
   constexpr int kWaves = 4;
   auto kern = tridiag_resident_kernel<kWaves, kResidentRows / kWaves, NC>;
   return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kern), dim3(wgs, b.n), dim3(64 * kWaves), list, 0, s);
@@ -718,18 +717,19 @@ template <int NW, int NC, int PF> void apply_reflectors(const EigenBatch& b, int
 
 }  // namespace
 
-hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident) {
+hipError_t launch_tridiag(const EigenBatch& b, hipStream_t s, hipEvent_t steps_done, bool* resident, const TridiagWay& way) {
   *resident = false;
   if (b.n < 1 || b.n > kEigenBatch || b.m < kEigenMinSize || b.m > kEigenMaxSize) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
-  if (tridiag_is_resident(b.m)) {
-    e = b.m <= 512 ? tridiag_resident<8>(b, s) : (b.m <= 768 ? tridiag_resident<12>(b, s) : tridiag_resident<16>(b, s));
-    if (e != hipErrorCooperativeLaunchTooLarge) {
+  if (way.one_launch && tridiag_is_resident(b.m)) {
+    e = b.m <= 512 ? tridiag_resident<8>(b, way.looks, s)
+                   : (b.m <= 768 ? tridiag_resident<12>(b, way.looks, s) : tridiag_resident<16>(b, way.looks, s));
+    if (e == hipSuccess) {
       *resident = true;
-      if (e == hipSuccess && steps_done != nullptr) e = hipEventRecord(steps_done, s);
-      return e;
+      return steps_done != nullptr ? hipEventRecord(steps_done, s) : e;
     }
-    (void)hipGetLastError();                            // fewer compute units than it takes: by steps
+    // fewer compute units than it takes, or no cooperative launch at all: by steps, which say what else is wrong
+    (void)hipGetLastError();
   }
   const int steps = tridiag_steps_of(b.m);
   e = hipSuccess;

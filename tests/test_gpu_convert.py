@@ -6,6 +6,8 @@ Bars: copies, transposes and selector cores are bit-exact.  Products and the hig
 floating point: fp32 storage within 1e-5 relative (the SVD itself runs in fp64 and is compared at
 1e-9 before rounding matters: singular values), bf16 storage within one rounding step of the oracle's
 rounded value."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +15,7 @@ import torch
 from oracle import classic_attention as ca
 from oracle import conversions as cv
 from oracle import tucker_oracle as orc
+from paper_2603_30033_amd import binding as ta
 from paper_2603_30033_amd import device as dev
 from paper_2603_30033_amd import workloads as wl
 from paper_2603_30033_amd.device import Layer, to_device, to_host
@@ -299,6 +302,30 @@ def test_hosvd_with_the_reduction_in_one_launch(d, nH, dH, r, shared):
     ranks = (min(2, nH), r, r - 1)
     host, got, sv, _ = hosvd_case(d, nH, dH, ranks, ranks, shared, "f32", 190 + d)
     assert dev.from_mha_hosvd.last_info["jacobi_launches"] == 1 and not any(dev.from_mha_hosvd.last_info["sweeps"][k] for k in (1, 2, 4, 5))
+    ref = cv.mha_to_tucker_hosvd(host["WQ"], host["WK"], host["WV"], host["WO"], nH, ranks, ranks, shared_kv=shared)
+    check_spectra(sv, host, nH, d, shared)
+    for k in ref:
+        assert np.max(np.abs(got[k] - ref[k])) <= 1e-5 * float(np.max(np.abs(ref[k]))), k
+
+
+# the ways out of the reduction in one launch: refused by the device (one launch a column), and given up by its workgroups (every
+# problem by the Jacobi iteration, whatever the launches behind the unfinished reduction made of it)
+@pytest.mark.parametrize("one_launch,looks", [(0, 1 << 20), (1, 0)])
+@pytest.mark.parametrize("d,nH,dH,r,shared", [(257, 4, 16, 20, True), (320, 3, 16, 24, False)])
+def test_hosvd_without_the_reduction_in_one_launch(monkeypatch, d, nH, dH, r, shared, one_launch, looks):
+    lib = ta.load_library()
+    way = lib.tucker_test_from_mha_hosvd
+    way.restype = lib.tucker_convert_from_mha_hosvd.restype
+    way.argtypes = list(lib.tucker_convert_from_mha_hosvd.argtypes) + [C.c_int32, C.c_int32]
+    monkeypatch.setattr(lib, "tucker_convert_from_mha_hosvd", lambda *args: way(*args, one_launch, looks))
+    ranks = (min(2, nH), r, r - 1)
+    host, got, sv, _ = hosvd_case(d, nH, dH, ranks, ranks, shared, "f32", 210 + d)
+    info = dev.from_mha_hosvd.last_info
+    solved = [1, 2, 4] if shared else [1, 2, 4, 5]
+    if one_launch:
+        assert all(info["sweeps"][k] > 0 for k in solved) and info["jacobi_launches"] > 1
+    else:
+        assert not any(info["sweeps"][k] for k in solved) and info["jacobi_launches"] == d - 192
     ref = cv.mha_to_tucker_hosvd(host["WQ"], host["WK"], host["WV"], host["WO"], nH, ranks, ranks, shared_kv=shared)
     check_spectra(sv, host, nH, d, shared)
     for k in ref:
