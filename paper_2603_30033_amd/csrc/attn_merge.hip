@@ -18,9 +18,11 @@
 
 namespace ta {
 
-// Scores of at most kPlainScore in magnitude and values of at most kPlainValue need no reference exponent: probabilities up to
-// 2^64 of 1280 keys times values up to 2^32 stay below 2^107.
-constexpr float kPlainScore = 64.f, kPlainValue = 4294967296.f;
+// Scores of at most kPlainScore in magnitude need no reference exponent over values between 2^-40 and 2^32 (or zero):
+// probabilities up to 2^64 of 1280 keys times values up to 2^32 stay below 2^107, and one of 2^-64 times 2^-40 is 2^22 times the
+// smallest normal number, so that what a sum of 1280 such products loses below it is less than the rounding to bf16.
+constexpr float kPlainScore = 64.f;
+constexpr unsigned kPlainMost = (127 + 32) << 7, kPlainLeast = (127 - 40) << 7;   // magnitudes as bf16 bits
 template <int CB, int ZB>
 __global__ __launch_bounds__(512) void attn_merge_kernel(AttnMergeArgs p) {
   typedef bf16 T;
@@ -62,12 +64,12 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnMergeArgs p) {
   const Frag<T> x0 = load_frag<T>(Ql), x1 = load_frag<T>(Ql + 32 * min(1, nbb - 1));
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // largest |k|^2 (infinite where a value is too large for plain probabilities); the last channel of the values, where it is
+  // largest |k|^2 (infinite where a value is too large or too small for plain probabilities); the last channel of the values, where it is
   // padding, becomes ones, so that the products with the probabilities sum them along the way
   __shared__ float most[8];
   float k2 = 0.f;
   {
-    float v_abs = 0.f;
+    unsigned v_most = 0u, v_least = ~0u;                        // least: less one, so that zero does not count
     for (int r = threadIdx.x; r < 32 * nkb; r += blockDim.x) {
       const T* row = smem + (long)(2 * (r / 32)) * kTile + (r % 32) * D;
       float n2 = 0.f;
@@ -81,12 +83,16 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnMergeArgs p) {
       const T* val = smem + (long)(2 * (r / 32) + 1) * kTile + (r % 32) * D;
 #pragma unroll
       for (int u = 0; u < KCPR; ++u) {
-        const bf16x8 x8 = *reinterpret_cast<const bf16x8*>(val + 8 * u);
+        const u32x4 x8 = *reinterpret_cast<const u32x4*>(val + 8 * u);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v_abs = fmaxf(v_abs, fabsf((float)x8[e]));
+        for (int e = 0; e < 8; ++e) {
+          const unsigned size = (e % 2 ? x8[e / 2] >> 16 : x8[e / 2]) & 0x7fffu;
+          v_most = max(v_most, size);
+          v_least = min(v_least, size - 1u);
+        }
       }
     }
-    if (!(v_abs <= kPlainValue)) k2 = INFINITY;
+    if (v_most > kPlainMost || v_least < kPlainLeast - 1u) k2 = INFINITY;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
       const float y = __shfl_xor(k2, d);

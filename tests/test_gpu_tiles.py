@@ -152,6 +152,26 @@ def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared,
     check(y, oracle_forward(w, inp), w.dtype, repr(w))
 
 
+# queries that point away from every token's own key (scores of about -45 in powers of two, the only ones that a first token
+# has) over values of 2^-100: their products lie below the smallest normal number unless the largest score is taken out first
+@pytest.mark.parametrize("B,N,heads,r3,rt3", [(512, 1, 2, 32, 32), (512, 40, 3, 32, 24), (256, 33, 4, 64, 48)])
+def test_attention_with_the_head_merge_of_tiny_values(B, N, heads, r3, rt3):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=r3, r3=r3, rt1=2, rt2=32,
+                  rt3=rt3, dtype="bf16", causal=True, seed=61)
+    inp = wl.make_inputs(w)
+    inp["U2"] = inp["U3"].copy()
+    inp["U1"] = np.zeros_like(inp["U1"])
+    inp["U1"][:, 0] = 1
+    inp["C"] = np.zeros_like(inp["C"])
+    inp["C"][0] = wl.round_to_storage(np.eye(r3) * (-45 * np.sqrt(32) / (1.4427 * r3)), "bf16")
+    inp["Ut3"] *= np.float32(2.0 ** -100)
+    with Layer(w, inp) as layer:
+        ta.tucker_attn_profile_enable(layer.ctx, True)
+        y = to_host(layer.forward(to_device(inp["X"], w.dtype)))
+        assert "attention_and_merge" in [n for n, _ in ta.tucker_attn_profile_read(layer.ctx)]
+    check(y, oracle_forward(w, inp), w.dtype, repr(w))
+
+
 # projections of many tokens, one and two weight tiles of 128 and of 192 rows: whole tiles and rows past the weights, a contraction that is
 # no whole stage, a last token tile that is not full
 @pytest.mark.parametrize("B,N,d,r2,r3,shared", [
