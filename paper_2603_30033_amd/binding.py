@@ -10,8 +10,6 @@ import ctypes as C
 import os
 from typing import Dict, List, Optional, Tuple
 
-import torch
-
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # TUCKER_ATTN_LIB names another build of the same library (comparing two builds in one session)
 LIB_PATH = os.environ.get("TUCKER_ATTN_LIB") or os.path.join(_HERE, "libtucker_attn.so")
@@ -158,6 +156,7 @@ def _ptr(t) -> Optional[int]:
 def _stream_ptr(stream) -> Optional[int]:
     if stream is not None:
         return stream.cuda_stream or None
+    import torch
     # the handle alone: torch.cuda.current_stream() makes a Stream object first (3.0 us of a decode call's 23, this 0.4)
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
 
@@ -314,6 +313,7 @@ def tucker_attn_measure_mfma_ceiling(from_lds: bool, iters: int = 20000) -> floa
 # ---- weight front-ends (include/tucker_convert.h) ------------------------------------------------
 
 def _dtype_code(t) -> int:
+    import torch
     if t.dtype == torch.float32:
         return TUCKER_ATTN_F32
     if t.dtype == torch.bfloat16:

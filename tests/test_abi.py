@@ -61,6 +61,17 @@ def test_conversion_workspace_holds_one_gram_matrix_where_problems_are_solved_on
         assert need <= ta.tucker_convert_hosvd_workspace_bytes(d, nH, dH) <= need + (1 << 20)
 
 
+def test_the_binding_loads_without_torch():
+    # a caller with buffers and a stream of its own needs nothing else of this process
+    import subprocess
+    import sys
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "from paper_2603_30033_amd import binding as ta\n"
+            "assert ta.tucker_attn_status_string(0) == 'ok' and ta.tucker_convert_hosvd_workspace_bytes(64, 4, 16) > 0\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+
 def test_status_strings():
     assert ta.tucker_attn_status_string(0) == "ok"
     for s in (-1, -2, -3, -4):
