@@ -174,13 +174,6 @@ __global__ __launch_bounds__(1024) void tridiag_step_kernel(EigenBatch b, int k)
   }
 }
 
-// 1/x to about two units in the last place: hardware estimate and two Newton steps
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-
 // interval that holds every eigenvalue, from Gershgorin's circles of the tridiagonal matrix (all lanes alike)
 __device__ __forceinline__ void spectrum_bounds(const double* d, const double* e, int m, int lane, double& lo, double& hi) {
   lo = INFINITY;

@@ -152,6 +152,51 @@ def test_attention_with_the_head_merge(B, N, heads, r2, r3, rt2, causal, shared,
     check(y, oracle_forward(w, inp), w.dtype, repr(w))
 
 
+# the same with a position offset, caches written and weights prepared before, one cache and two
+@pytest.mark.parametrize("B,N,heads,r3,rt3,shared", [(200, 33, 5, 32, 20, False), (256, 40, 4, 64, 64, True), (150, 225, 3, 48, 40, False)])
+def test_attention_with_the_head_merge_at_an_offset_with_caches(B, N, heads, r3, rt3, shared):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=40, r3=r3, rt1=2, rt2=64,
+                  rt3=rt3, dtype="bf16", causal=True, shared_kv=shared, pos0=7, seed=62)
+    inp = wl.make_inputs(w)
+    with Layer(w, inp, max_positions=N + 20) as layer:
+        layer.freeze_weights()
+        ta.tucker_attn_profile_enable(layer.ctx, True)
+        K = torch.zeros(B, N + 9, r3, dtype=torch.bfloat16, device="cuda")
+        V = None if shared else torch.zeros(B, N + 9, rt3, dtype=torch.bfloat16, device="cuda")
+        y = to_host(layer.forward(to_device(inp["X"], w.dtype), pos0=7, Kc=K, Vc=V))
+        names = [n for n, _ in ta.tucker_attn_profile_read(layer.ctx)]
+        assert "attention_and_merge" in names and "prep_weights" not in names
+        K, V = to_host(K), None if shared else to_host(V)
+    check(y, oracle_forward(w, inp), w.dtype, repr(w))
+    x = inp["X"].astype(np.float64)
+    k = x @ inp["U3"].astype(np.float64)
+    if not shared:
+        k = np.stack([orc.rope_rotate(s, np.arange(7, 7 + N), w.rope_base) for s in k])
+        check(V[:, 7:7 + N], x @ inp["Ut3"].astype(np.float64), w.dtype, "value rows")
+        assert not V[:, :7].any() and not V[:, 7 + N:].any()
+    check(K[:, 7:7 + N], k, w.dtype, "key rows")
+    assert not K[:, :7].any() and not K[:, 7 + N:].any()
+
+
+# a token without a finite value reaches the queries from its own block of 32 on, and no other sequence
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("B,N,heads,r3,rt3", [(200, 100, 5, 32, 20), (256, 70, 4, 64, 64)])
+def test_attention_with_the_head_merge_of_non_finite_tokens(B, N, heads, r3, rt3, bad):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=40, r3=r3, rt1=2, rt2=64,
+                  rt3=rt3, dtype="bf16", causal=True, seed=63)
+    inp = wl.make_inputs(w)
+    ref = oracle_forward(w, inp)
+    inp["X"][3, 40] = bad
+    with Layer(w, inp) as layer:
+        ta.tucker_attn_profile_enable(layer.ctx, True)
+        y = to_host(layer.forward(to_device(inp["X"], w.dtype)))
+        assert "attention_and_merge" in [n for n, _ in ta.tucker_attn_profile_read(layer.ctx)]
+    assert not np.all(np.isfinite(y[3, 40]))
+    check(y[3, :32], ref[3, :32], w.dtype, "queries of the block before")
+    other = np.arange(B) != 3
+    check(y[other], ref[other], w.dtype, "other sequences")
+
+
 # queries that point away from every token's own key (scores of about -45 in powers of two, the only ones that a first token
 # has) over values of 2^-100: their products lie below the smallest normal number unless the largest score is taken out first
 @pytest.mark.parametrize("B,N,heads,r3,rt3", [(512, 1, 2, 32, 32), (512, 40, 3, 32, 24), (256, 33, 4, 64, 48)])
