@@ -664,6 +664,20 @@ size_t tucker_attn_backward_workspace_bytes(const tucker_attn_ctx* c, int32_t B,
   return carve_backward(c, nullptr, B, N).bytes;
 }
 
+// for tests: the parts that a call of B x N tokens deals the keys of a query block to in the forward and in the query gradient
+// (0: the large forms), and the query blocks of a head in the key-value gradient
+void tucker_test_attention_parts(const tucker_attn_ctx* c, int32_t B, int32_t N, int32_t* parts) {
+  AttnArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.Bsz = B; a.N = N; a.Npad = pad64(N); a.nH = c->cfg.n_heads; a.D = c->D;
+  BwdArgs b;
+  std::memset(&b, 0, sizeof(b));
+  b.Bsz = B; b.N = N; b.Npad = a.Npad; b.nH = a.nH; b.D = a.D;
+  parts[0] = attn_prefill_key_parts(c->cfg.dtype, a);
+  parts[1] = bwd_dq_key_parts(c->cfg.dtype, b);
+  parts[2] = carve_backward(c, nullptr, B, N).qsplit;
+}
+
 int tucker_attn_backward(tucker_attn_ctx* c, const tucker_attn_weights* w, const void* X, const void* dY, void* dX,
                          const tucker_attn_grads* gr, int32_t B, int32_t N, int32_t pos0, int32_t forward_state,
                          void* workspace, size_t workspace_bytes, void* hip_stream) {

@@ -587,16 +587,37 @@ static hipError_t dq_launch(const BwdArgs& a, hipStream_t s) {
 // to two waves, or four.  One block of queries and one, two, four waves (us): fp32, D = 64, 12 heads, 2 x 509 tokens 70.1,
 // 44.5; 5 x 100 28.0, 21.4; bf16, D = 64, 1024 tokens 29.6, 22.2; D = 128 (tiles of 32 keys when they are shared), 32 heads, 450
 // tokens 31.1, 25.5, 900 tokens (464 workgroups) 46.6, 48.7; D = 32, 4 heads, 512 tokens 12.1, 9.1, 7.8.
+template <typename T, int D, int BC> static constexpr int shared_tile() {   // keys of a tile that is shared
+  return 2 * DqLds<T, D, BC>::kBytes <= 160 * 1024 ? BC : 32;
+}
+template <typename T, int D, int BC> static constexpr bool by_two() {
+  return 2 * DqLds<T, D, shared_tile<T, D, BC>()>::kBytes <= 160 * 1024;
+}
+// waves that share a query block's keys; 0: two query blocks a workgroup
+template <typename T, int D, int BC> static int dq_key_parts(const BwdArgs& a) {
+  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
+  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return 0;
+  if (D == 32 && tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return 4;
+  return by_two<T, D, BC>() && tiles >= 2 && (a.nH + 1) / 2 * blocks <= kComputeUnits ? 2 : 1;
+}
 template <typename T, int D, int BC>
 static hipError_t dq_one(const BwdArgs& a, hipStream_t s) {
-  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
-  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return dq_launch<T, D, BC, 2, 4, 1>(a, s);
-  if constexpr (D == 32)
-    if (tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return dq_launch<T, D, BC, 1, 1, 4>(a, s);
-  constexpr int SC = 2 * DqLds<T, D, BC>::kBytes <= 160 * 1024 ? BC : 32;   // keys of a tile that is shared
-  if constexpr (2 * DqLds<T, D, SC>::kBytes <= 160 * 1024)
-    if (tiles >= 2 && (a.nH + 1) / 2 * blocks <= kComputeUnits) return dq_launch<T, D, SC, 1, 2, 2>(a, s);
-  return dq_launch<T, D, BC, 1, 4, 1>(a, s);
+  switch (dq_key_parts<T, D, BC>(a)) {
+    case 0: return dq_launch<T, D, BC, 2, 4, 1>(a, s);
+    case 4:
+      if constexpr (D == 32) return dq_launch<T, D, BC, 1, 1, 4>(a, s);
+      break;
+    case 2:
+      if constexpr (by_two<T, D, BC>()) return dq_launch<T, D, shared_tile<T, D, BC>(), 1, 2, 2>(a, s);
+      break;
+    case 1: return dq_launch<T, D, BC, 1, 4, 1>(a, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+int bwd_dq_key_parts(int dtype, const BwdArgs& a) {
+  if (dtype == 0) return a.D == 32 ? dq_key_parts<float, 32, 32>(a) : a.D == 64 ? dq_key_parts<float, 64, 32>(a) : dq_key_parts<float, 128, 32>(a);
+  return a.D == 32 ? dq_key_parts<bf16, 32, 64>(a) : a.D == 64 ? dq_key_parts<bf16, 64, 64>(a) : dq_key_parts<bf16, 128, 64>(a);
 }
 
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s) {

@@ -466,15 +466,33 @@ static hipError_t launch_one(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hi
 // 43.2; 3 x 197 25.0, 19.8, 15.9; bf16, D = 128, 32 heads, 333 tokens 18.6, 15.4; D = 64, 12 heads, 1000 tokens 24.2, 17.3, 19.4;
 // 4 x 300 12.7, 11.9, 17.9; 8 x 197 (384 workgroups of two heads) 11.4, 12.8; 2 x 1000 (384, 16 tiles) the pass 40.2, 35.0, 6 x 577
 // (720) 45.5, 47.4; D = 32, 4 heads, 512 tokens 12.0, 9.5, 8.0; two tiles only: 11.5, 12.2.
+template <typename T, int D, int BC> static constexpr bool by_four() {
+  return 4 * AttnLds<T, D, BC>::kBytes <= 160 * 1024 && (sizeof(T) == 4 || D == 32);
+}
+// waves that share a query block's keys; 0: the eight waves of the large form
+template <typename T, int D, int BC> static int key_parts(const AttnArgs& a) {
+  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
+  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return 0;
+  if (by_four<T, D, BC>() && tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return 4;
+  const long halves = (a.nH + 1) / 2 * blocks;
+  return (tiles >= 3 && halves <= kComputeUnits) || (tiles >= 8 && halves <= kComputeUnits * 3 / 2) ? 2 : 1;
+}
 template <typename T, int D, int BC>
 static hipError_t launch_sized(const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {
-  const long blocks = (long)a.Bsz * (a.Npad / 32), tiles = (a.N + BC - 1) / BC;
-  if ((a.nH + 3) / 4 * (blocks / 2) >= kComputeUnits) return launch_one<T, D, 1, BC, 2, 4, 1>(a, s, k0, k1);
-  if constexpr (4 * AttnLds<T, D, BC>::kBytes <= 160 * 1024 && (sizeof(T) == 4 || D == 32))
-    if (tiles >= 4 && a.nH * blocks <= kComputeUnits * 3 / 2) return launch_one<T, D, 1, BC, 1, 1, 4>(a, s, k0, k1);
-  const long halves = (a.nH + 1) / 2 * blocks;
-  if ((tiles >= 3 && halves <= kComputeUnits) || (tiles >= 8 && halves <= kComputeUnits * 3 / 2)) return launch_one<T, D, 1, BC, 1, 2, 2>(a, s, k0, k1);
-  return launch_one<T, D, 1, BC, 1, 4, 1>(a, s, k0, k1);
+  switch (key_parts<T, D, BC>(a)) {
+    case 0: return launch_one<T, D, 1, BC, 2, 4, 1>(a, s, k0, k1);
+    case 4:
+      if constexpr (by_four<T, D, BC>()) return launch_one<T, D, 1, BC, 1, 1, 4>(a, s, k0, k1);
+      break;
+    case 2: return launch_one<T, D, 1, BC, 1, 2, 2>(a, s, k0, k1);
+    case 1: return launch_one<T, D, 1, BC, 1, 4, 1>(a, s, k0, k1);
+  }
+  return hipErrorInvalidValue;
+}
+
+int attn_prefill_key_parts(int dtype, const AttnArgs& a) {
+  if (dtype == 0) return a.D == 32 ? key_parts<float, 32, 32>(a) : a.D == 64 ? key_parts<float, 64, 32>(a) : key_parts<float, 128, 32>(a);
+  return a.D == 32 ? key_parts<bf16, 32, 64>(a) : a.D == 64 ? key_parts<bf16, 64, 64>(a) : key_parts<bf16, 128, 64>(a);
 }
 
 hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipEvent_t k0, hipEvent_t k1) {

@@ -224,6 +224,8 @@ hipError_t launch_gemm_tn(int dtype, const TnArgs& a, hipStream_t s);
 size_t tn_part_bytes(int dtype, const TnArgs& a);   // needs the sizes only (n, p[].M, p[].cols, Bsz, Npad)
 // k0, k1 (both or neither): events that take the start and the end of the kernel itself (profiling)
 hipError_t launch_attn_prefill(int dtype, const AttnArgs& a, hipStream_t s, hipEvent_t k0 = nullptr, hipEvent_t k1 = nullptr);
+int attn_prefill_key_parts(int dtype, const AttnArgs& a);   // by its sizes: waves that share a query block's keys, 0 for the large form
+int bwd_dq_key_parts(int dtype, const BwdArgs& a);
 bool attn_merge_supported(int dtype, const AttnMergeArgs& a);
 hipError_t launch_attn_merge(const AttnMergeArgs& a, hipStream_t s, hipEvent_t k0 = nullptr, hipEvent_t k1 = nullptr);
 hipError_t launch_bwd_dq(int dtype, const BwdArgs& a, hipStream_t s);

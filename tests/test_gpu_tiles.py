@@ -1,6 +1,8 @@
 """Sizes at which the kernels' tilings change: every tile of a dispatch rule, with remainders in the tokens, the
 contraction and the heads, against the CPU oracle.  Bars as in test_gpu_parity.py (relative L2 at most 1e-5 in fp32 and
 2e-2 in bf16 storage, every row within four times that)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -234,15 +236,22 @@ def test_projection_of_many_tokens(B, N, d, r2, r3, shared):
 
 
 # few workgroups: the keys of a query block dealt to two and to four waves, with a remainder and with parts that hold no visible
-# key; the query blocks of a head dealt to two and to four workgroups (all gradients, no RoPE offset and an odd head count)
-@pytest.mark.parametrize("dtype,B,N,heads,r3,causal", [
-    ("bf16", 1, 129, 3, 128, True), ("bf16", 1, 513, 5, 64, True), ("bf16", 2, 321, 4, 64, False), ("bf16", 1, 450, 3, 32, True),
-    ("bf16", 2, 65, 3, 32, False), ("f32", 1, 65, 3, 64, True), ("f32", 1, 225, 5, 64, False), ("f32", 1, 97, 3, 32, True),
-    ("f32", 3, 160, 3, 128, True), ("f32", 1, 96, 2, 128, False),
+# key; the query blocks of a head dealt to two and to four workgroups (all gradients, no RoPE offset and an odd head count);
+# parts: of the forward's keys, the query gradient's keys, the key-value gradient's queries
+@pytest.mark.parametrize("dtype,B,N,heads,r3,causal,parts", [
+    ("bf16", 1, 129, 3, 128, True, (2, 2, 2)), ("bf16", 1, 513, 5, 64, True, (2, 2, 2)), ("bf16", 2, 321, 4, 64, False, (2, 2, 2)),
+    ("bf16", 1, 450, 3, 32, True, (4, 4, 4)), ("bf16", 2, 65, 3, 32, False, (1, 2, 4)), ("f32", 1, 65, 3, 64, True, (2, 2, 4)),
+    ("f32", 1, 225, 5, 64, False, (4, 2, 4)), ("f32", 1, 97, 3, 32, True, (4, 4, 4)), ("f32", 3, 160, 3, 128, True, (2, 1, 4)),
+    ("f32", 1, 96, 2, 128, False, (2, 1, 4)),
 ])
-def test_attention_with_shared_keys(dtype, B, N, heads, r3, causal):
-    run_case(wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
-                       dtype=dtype, causal=causal, seed=59))
+def test_attention_with_shared_keys(dtype, B, N, heads, r3, causal, parts):
+    w = wl.scaled(wl.WORKLOADS["tiny_f32"], B=B, N=N, d_model=64, n_heads=heads, d_head=32, r1=2, r2=32, r3=r3,
+                  dtype=dtype, causal=causal, seed=59)
+    with Layer(w, wl.make_inputs(w)) as layer:
+        got = (C.c_int32 * 3)()
+        ta.load_library().tucker_test_attention_parts(C.c_void_p(layer.ctx), C.c_int32(B), C.c_int32(N), got)
+        assert tuple(got) == parts
+    run_case(w)
 
 
 # head-mixed cores: slices in batches of 4, 8 and 16 with remainders, head counts off the four of a tile, rows of a core that are no
