@@ -11,6 +11,11 @@
 // latency of a pair's start and end with two waves on a SIMD.  Tried: four waves of one head on 128 registers with the outputs
 // stored 66 + 21; two heads in turn, probabilities of one under the products of the other, outputs stored 71 + 21; the
 // cores of a pair staged in LDS 74 (a barrier per pair); the online softmax for all scores 75.
+//   With latents of 64 channels and merged ones of 64, 96 and 128, 7, 24 and 38 registers go through scratch memory, at the start and
+// the end of a pair; the loops over the keys touch none.
+//   Without a reference exponent the largest probability of a row is rounded to bf16 like the others, where with one it is exactly
+// 1: the error of those 256 sequences against fp64 is 4.916e-3, 4.896e-3 in the prefill kernel, whose first 64 keys give the
+// reference.  With that reference here the whole pass takes 5 % more, with the one of the first 32 keys (4.900e-3) 2 to 5 %.
 #include <type_traits>
 
 #include "common.h"
@@ -314,8 +319,9 @@ constexpr size_t kLdsMost = 160 * 1024 - 256;                   // beside the fe
 
 // Waves below which the chip is better filled by the prefill kernel, whose workgroups split the heads (the time here is then that
 // of one wave).  D = 64: 12 heads, ranks up to 64, 1024 waves 54.8 -> 51.4 us (128 x 128 tokens) and 94.4 -> 92.9 (128 x
-// 250), 896 waves 93.2 -> 83.7 (128 x 197), 560 waves 67.3 -> 70.1; 1600 waves 143 -> 99.  Ranks of 128 have twice the products
-// outside the key loop: 1280 waves 169 -> 180, 2048 116 -> 103.  D = 32 has half of them: 512 waves 19.8 -> 19.1.
+// 250), 896 waves 93.2 -> 83.7 (128 x 197), 560 waves 67.3 -> 70.1; 1600 waves 143 -> 99.  So the two meet between 560 and 896, and
+// the line stands above, where every SIMD has a wave.  Ranks of 128 have twice the products outside the key loop: 1280 waves
+// 169 -> 180, 2048 116 -> 103.  D = 32 has half of them: 512 waves 19.8 -> 19.1.
 long fewest_waves(const AttnMergeArgs& a) {
   return (a.R2 > 64 || a.RT2 > 64 ? 2048 : 1024) / (a.D == 32 ? 2 : 1);
 }

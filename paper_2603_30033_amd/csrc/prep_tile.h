@@ -35,9 +35,9 @@ template <> __device__ __forceinline__ void store_chunk<float>(float* out, const
 
 // A 32 x 32 tile of kMixHeads head-mixed cores, sum_a coef[z][a] src[a]: every element of the core is fetched once for four heads
 // (one head a workgroup read the core through the L2 once per head, 64 MB for 32 heads x 32 slices of 128 x 128, in batches of
-// eight slices).  Thread = four neighbouring elements; 16 slices in flight.  Projection launch of a decode step with these tiles, 32 heads x
-// 32 slices of 128 x 128: 11.6 -> 7.9 us, 8 slices: 6.7 -> 6.0; preparation alone, 32 heads x 8 slices and three factors of 4096 rows: 12.3
-// -> 9.0; 12 heads x 4 of 64 x 64: 5.7 -> 4.7.
+// eight slices).  Thread = four neighbouring elements; 16 slices in flight.  Under the profiler, projection launch of a decode step
+// with these tiles, 32 heads x 32 slices of 128 x 128, 24 sequences: 11.0 -> 8.7 us; 8 slices, 16 sequences: 7.5 -> 6.9; preparation
+// alone, 32 heads x 8 slices and three factors of 4096 rows: 9.2 -> 6.3; 12 heads x 4 of 64 x 64: 5.7 -> 4.9.
 template <typename T>
 __device__ __forceinline__ void mix_tile(const PrepJob& jb, int local, float* lds) {
   constexpr int TS = kMixTile, NH = kMixHeads, CE = 16 / (int)sizeof(T);
